@@ -49,19 +49,18 @@ typedef enum {
  * for a zero vector), clamped to [0, 2]; SILH_CANB takes a 0/0 coordinate as 0. */
 typedef enum { SILH_EUCL = 0, SILH_COS = 1, SILH_MANH = 2, SILH_CANB = 3 } silh_metric;
 
-/* Arithmetic of the Phase-2 distance tiles.  Accumulation is float32 inside
+/* Arithmetic of the Phase-2 distances.  Accumulation is float32 inside
  * a tile and float64 across tiles; Phase 1 always runs in float64.
- *  SILH_FP32       float32.  Euclidean and cosine run on the matrix cores
- *                  (v_mfma_f32_32x32x2_f32), Manhattan and Canberra on the
- *                  vector ALUs.
- *  SILH_BF16       bf16 operands, float32 accumulation (v_mfma_f32_32x32x16_bf16);
- *                  Euclidean and cosine only.
- *  SILH_FP8        OCP e4m3 operands, float32 accumulation
- *                  (v_mfma_f32_32x32x64_f8f6f4); cosine with d >= 64 only
- *                  (the K step is 64 wide, and at smaller d the 3-bit
+ *  SILH_FP32       float32.  Euclidean runs on the matrix cores
+ *                  (v_mfma_f32_32x32x2_f32, d <= 128), Manhattan and Canberra on
+ *                  the vector ALUs; cosine sums in float64.
+ *  SILH_BF16       bf16 operands, float32 accumulation (Euclidean:
+ *                  v_mfma_f32_32x32x16_bf16); Euclidean and cosine only.
+ *  SILH_FP8        OCP e4m3 operands, float32 accumulation; cosine with
+ *                  d >= 64 only (at smaller d the 3-bit
  *                  mantissa's error per coordinate no longer averages out).
  *                  Operands are the centred unit vectors times 64.
- *  SILH_FP32_VALU  float32 on the vector ALUs for every metric. */
+ *  SILH_FP32_VALU  float32 on the vector ALUs (cosine: as SILH_FP32). */
 typedef enum { SILH_FP32 = 0, SILH_BF16 = 1, SILH_FP8 = 2, SILH_FP32_VALU = 3 } silh_prec;
 
 /* SILH_PPS: Algorithm 1, Phase 1.  SILH_UNI: uniform Poisson sampling with
@@ -263,13 +262,14 @@ silh_status silh_exact_rows(const silh_params* prm, const float* X, const int32_
 silh_status silh_coh_sep(silh_ctx* ctx, const float* W_hat, double* coh_host, double* sep_host);
 
 /*
- * Autotuning of the matrix-core Phase-2 kernel's block shape, process-wide.
- * Shapes: 1 one 32-element block per wave; 2 two blocks per wave (d <= 64,
- * not fp8); 3 one block per wave with the other number of tiles per stage
+ * Autotuning of the matrix-core (Euclidean) Phase-2 kernel's block shape,
+ * process-wide.  Cosine has one shape, recorded as 1 under its key.
+ * Shapes: 1 one 32-element block per wave; 2 two blocks per wave (d <= 64);
+ * 3 one block per wave with the other number of tiles per stage
  * (one or two 32-row sample tiles between block barriers) on the shapes that
- * stage sample tiles in LDS (bf16 / float32 with d >= 64, fp8 with d >= 128).
+ * stage sample tiles in LDS (d >= 64).
  *  mode 0  the built-in choice (two blocks for float32 operands with
- *          d <= 32 and for cosine bf16 at d = 32, else one);
+ *          d <= 32, else one);
  *  mode 1  (default) on the first launch for a key (metric, operand type, d
  *          rounded up as in the kernels, floor(log2) of the padded sample
  *          size) time every valid shape twice, keep the fastest; setting

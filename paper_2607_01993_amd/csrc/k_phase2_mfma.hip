@@ -1,24 +1,21 @@
 // Phase 2 of Algorithm 1 on the matrix cores (gfx950 MFMA), for the
-// Euclidean and cosine distances:
+// Euclidean distance:
 //   W_hat_{C_j}(e) = sum_{e' in F_j} w_{e'} d(e, e'),  w = 1/p,
 // then a_hat, b_hat, s_hat (Eq. 5) and per-block float64 partials of the sum
 // of s_hat (for Eq. 9).
 //
-// Both distances are evaluated as a squared difference of centred points,
+// The distance is evaluated as a squared difference of centred points,
 //   |x~ - y~|^2 = |x~|^2 + |y~|^2 - 2 x~.y~ ,   x~ = x - mu_j,  y~ = y - mu_j,
-// where mu_j is a centre of cluster j's sample (the mean of its first samples)
-// and x, y are the raw rows (Euclidean) or the rows scaled to unit length
-// (cosine, where 1 - x^.y^ = |x^ - y^|^2 / 2).  The translation leaves every
+// where mu_j is a centre of cluster j's sample (the mean of its first samples).
+// The translation leaves every
 // distance unchanged but keeps the operands small near cluster j, so the
 // expansion does not cancel for near pairs, in float32 or in bf16.  The dot
 // product runs on the MFMA units; the two squared norms ride along as extra
 // contraction columns (split into three bf16 pieces in the bf16 path), so the
-// accumulator leaves the MFMA holding the squared distance itself:
-//   Euclidean:  d = sqrt(|c|)
-//   cosine:     d = med3(c, 0, 2) with c = |x~ - y~|^2 / 2 + u_x + u_y
-//               (u = 0.5 for a zero vector, else 0, which makes d = 1 there).
+// accumulator leaves the MFMA holding the squared distance c itself and
+// d = sqrt(|c|).
 //
-// Tile mapping (v_mfma_f32_32x32x{2f32,16_bf16}, 32x32x64 f8f6f4): a wave
+// Tile mapping (v_mfma_f32_32x32x{2f32,16_bf16}): a wave
 // owns 32 elements (the B operand columns); each tile is 32 samples of one
 // cluster (the A operand rows, cluster blocks padded to 32 with zero-weight
 // rows).  Lane l holds element column l%32 of the accumulator and the 16
@@ -27,7 +24,7 @@
 // term's weight taken from a neighbouring lane by a DPP broadcast inside the
 // FMA, and one exchange between the two halves when the cluster ends or
 // every kFold tiles, then added in float64.  The pipelined LDS path (long
-// rows, bf16 / fp8) keeps the other orientation, elements as the rows (see
+// rows, bf16) keeps the other orientation, elements as the rows (see
 // kT in p2_mfma_block).  The contraction order is free,
 // so each lane feeds the MFMA a contiguous half of the (augmented) row: half
 // h of the row holds logical coordinates [h*HALF, (h+1)*HALF).
@@ -42,22 +39,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-// fp8 (OCP e4m3) path, cosine only: operands are 64 (x~ - y~ components of
-// unit vectors lie in [-2, 2], so |64 v| <= 128 < 448) times the centred
-// coordinates; the squared norms enter through the accumulator input (with
-// elements as rows the sample's through the clamp bounds instead, kF8R).  The
-// norms are those of the unrounded float32 coordinates, not of the e4m3
-// operands: with c = |x~|^2/2 + |y~|^2/2 - x~_q.y~_q the rounding error of
-// each pair is first order in the operand errors (x~.dy + dx.y~), whose sum
-// over a cluster's samples averages out, while the exact distance of the
-// rounded points |x~_q - y~_q|^2 adds |dx|^2 + |dy|^2 - 2 x~.dx to every pair:
-// a bias of one sign that is the same for all samples of the cluster (about
-// 0.3 % of W_hat at d = 128, against under 0.02 % this way).
-constexpr float kFp8Scale = 64.0f;
 
 // tiles summed in float32 before the float64 add: with samples as the rows
 // each of a lane's four sums takes four terms per tile; with elements as the
@@ -95,25 +78,24 @@ constexpr int kCenterRows = 256;
 
 __host__ __device__ constexpr int round_up_c(int a, int b) { return (a + b - 1) / b * b; }
 
-// P = 0: float32 operands (32x32x2), P = 1: bf16 (32x32x16), P = 2: fp8 (32x32x64)
+// P = 0: float32 operands (32x32x2), P = 1: bf16 (32x32x16)
 template <int P, int DM>
 struct MCfg {
-  static constexpr int AUG = P == 0 ? 2 : (P == 1 ? 6 : 0);
-  static constexpr int KP = P == 0 ? round_up_c(DM + AUG, 4)
-                                   : (P == 1 ? round_up_c(DM + AUG, 16) : round_up_c(DM, 64));
+  static constexpr int AUG = P == 0 ? 2 : 6;
+  static constexpr int KP = P == 0 ? round_up_c(DM + AUG, 4) : round_up_c(DM + AUG, 16);
   static constexpr int HALF = KP / 2;
-  static constexpr int NSTEP = P == 0 ? HALF : (P == 1 ? HALF / 8 : HALF / 32);
-  static constexpr int ELEM = P == 0 ? 4 : (P == 1 ? 2 : 1);  // operand bytes
+  static constexpr int NSTEP = P == 0 ? HALF : HALF / 8;
+  static constexpr int ELEM = P == 0 ? 4 : 2;  // operand bytes
   // long rows go through LDS (the block's waves share each tile)
-  static constexpr bool LDS = P == 2 ? HALF > 40 : HALF > 30;
+  static constexpr bool LDS = HALF > 30;
   // bytes per packed row: the operands, and on the LDS path a 16-byte tail
   // with the sample's weight and per-sample value (so that one contiguous
   // copy brings a whole tile into LDS)
   static constexpr int ROWB = KP * ELEM + (LDS ? 16 : 0);
   // bf16: lane half h feeds elements [16 s + 8 h, 16 s + 8 h + 8) of each
   // 16-wide MFMA step s, so both halves hold DM / 2 coordinates and the
-  // augmentation sits in step DM / 16 (elements 8 s + e of a lane); the other
-  // operand types give each half a contiguous half row [h HALF, (h+1) HALF)
+  // augmentation sits in step DM / 16 (elements 8 s + e of a lane); float32
+  // gives each half a contiguous half row [h HALF, (h+1) HALF)
   static constexpr bool IL = P == 1;
   static constexpr int FOFF = IL ? 8 : HALF;   // first element of half h: FOFF h
   static constexpr int FSTEP = IL ? 16 : 8;    // bf16 elements between steps
@@ -122,27 +104,17 @@ struct MCfg {
 };
 
 int mfma_kp(int prec, int DM) {
-  if (prec == 0) return round_up_c(DM + 2, 4);
-  if (prec == 1) return round_up_c(DM + 6, 16);
-  return round_up_c(DM, 64);
+  return prec == 0 ? round_up_c(DM + 2, 4) : round_up_c(DM + 6, 16);
 }
 
 bool mfma_lds_path(int prec, int DM) {
-  return prec == 2 ? round_up_c(DM, 64) / 2 > 40 : mfma_kp(prec, DM) / 2 > 30;
+  return mfma_kp(prec, DM) / 2 > 30;
 }
 
 size_t mfma_mu_floats(int prec, int DM, int k) { return (size_t)k * mfma_kp(prec, DM) + k; }
 
 int mfma_row_bytes(int prec, int DM) {
-  return mfma_kp(prec, DM) * (prec == 0 ? 4 : (prec == 1 ? 2 : 1)) + (mfma_lds_path(prec, DM) ? 16 : 0);
-}
-
-__device__ __forceinline__ int fp8_pack4(float a, float b, float c, float d) {
-  int v = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-  return __builtin_amdgcn_cvt_pk_fp8_f32(c, d, v, true);
-}
-__device__ __forceinline__ float q_fp8(float v) {
-  return __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_pk_fp8_f32(v, 0.0f, 0, false), 0);
+  return mfma_kp(prec, DM) * (prec == 0 ? 4 : 2) + (mfma_lds_path(prec, DM) ? 16 : 0);
 }
 
 __device__ __forceinline__ float q_bf16(float v) { return (float)(__bf16)v; }
@@ -196,32 +168,26 @@ void launch_center(hipStream_t st, const float* Y32, int DM, int KP, const int32
 }
 
 // ----------------------------------------------------------------------------
-// Sample operand rows: [ -2 alpha y~_q (DM) | augmentation | 0 ... ] with
-// alpha = 1 (Euclidean) or 1/2 (cosine); y~_q = y~ rounded to the input
-// precision; the augmentation carries alpha |y~_q|^2 + u_y and the ones that
-// take in the element's norm term.  Padding rows keep only those ones, so an
-// element meets them at c = its own norm term (never below its recompute
-// threshold) with weight 0.  bnorm and, on the LDS path, each row's 16-byte
-// tail carry the per-sample value (fp8: the norm term; cosine: the element
-// id; Euclidean: the sample's recompute threshold, which the element-row
-// layout tests against); the tail also holds the weight w and two zero
-// words.
+// Sample operand rows: [ -2 y~_q (DM) | augmentation | 0 ... ]; y~_q = y~
+// rounded to the input precision; the augmentation carries |y~_q|^2 and the
+// ones that take in the element's norm term.  Padding rows keep only those
+// ones, so an element meets them at c = its own norm term (never below its
+// recompute threshold) with weight 0.  On the LDS path each row's 16-byte
+// tail carries the weight w, the sample's recompute threshold (which the
+// element-row layout tests against) and two zero words.
 // ----------------------------------------------------------------------------
-template <int M, int P, int DM>
+template <int P, int DM>
 __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32,
-                                                   const float* __restrict__ aux,
                                                    const float* __restrict__ w,
-                                                   const int32_t* __restrict__ gid_pk,
                                                    const int32_t* __restrict__ sp_off,
                                                    const int32_t* __restrict__ cnt, int k,
                                                    float* __restrict__ mu, int S_pad,
-                                                   void* __restrict__ Ym, float* __restrict__ bnorm) {
+                                                   void* __restrict__ Ym) {
   using C = MCfg<P, DM>;
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  // sp_off[k]: packed rows in use (the Euclidean kernels keep every lane to
-  // the end, for the wave-wide radius below)
+  // sp_off[k]: packed rows in use (every lane stays to the end, for the
+  // wave-wide radius below)
   const bool valid = s < S_pad && s < sp_off[k];
-  if (M != kEucl && !valid) return;
   // cluster of padded row s (binary search over sp_off)
   int lo = 0, hi = k;
   while (valid && hi - lo > 1) {
@@ -230,37 +196,10 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
   }
   const int j = lo;
   const bool real = valid && s - sp_off[j] < cnt[j];
-  float ny_r = 0.0f;  // Euclidean: the row's squared norm, 0 for padding
-  const float alpha = M == kCos ? 0.5f : 1.0f;
+  float ny_r = 0.0f;  // the row's squared norm, 0 for padding
   float row[C::KP];
 #pragma unroll
   for (int c = 0; c < C::KP; ++c) row[c] = 0.f;
-  if (P == 2) {
-    // fp8: B = e4m3(-64 y~), the norm term alpha |y~_q|^2 + u_y goes to bnorm
-    float bn = 0.0f;
-    if (real) {
-      const float* y = Y32 + (size_t)s * DM;
-      const float* m = mu + (size_t)j * C::KP;
-      float ny = 0.f;
-#pragma unroll
-      for (int c = 0; c < DM; ++c) {
-        const float v = y[c] - m[c];
-        const float q = q_fp8(kFp8Scale * v);
-        ny = fmaf(v, v, ny);  // the norm of the unrounded coordinates
-        row[c] = -q;
-      }
-      bn = fmaf(alpha, ny, M == kCos ? aux[s] : 0.0f);
-    }
-    bnorm[s] = bn;
-    int* out = (int*)((unsigned char*)Ym + (size_t)s * C::ROWB);
-#pragma unroll
-    for (int c = 0; c < C::KP; c += 4) out[c / 4] = fp8_pack4(row[c], row[c + 1], row[c + 2], row[c + 3]);
-    if constexpr (C::LDS)
-      *(u32x4*)(out + C::KP / 4) = u32x4{__float_as_uint(w[s]), __float_as_uint(bn), 0u, 0u};
-    return;
-  }
-  // Euclidean, element-row layout: the sample's recompute threshold
-  float thr = 0.0f;
   if (real) {
     const float* y = Y32 + (size_t)s * DM;
     const float* m = mu + (size_t)j * C::KP;
@@ -270,15 +209,13 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
       float v = y[c] - m[c];
       if (P == 1) v = q_bf16(v);
       ny = fmaf(v, v, ny);
-      row[c] = -2.0f * alpha * v;
+      row[c] = -2.0f * v;
     }
-    const float bn = fmaf(alpha, ny, M == kCos ? aux[s] : 0.0f);
-    thr = M == kEucl ? kRecomputeThr<P> * ny : 0.0f;
     ny_r = ny;
     if (P == 0) {
-      row[DM + 1] = bn;
+      row[DM + 1] = ny;
     } else {
-      split3(bn, row[DM + 3], row[DM + 4], row[DM + 5]);
+      split3(ny, row[DM + 3], row[DM + 4], row[DM + 5]);
     }
   }
   if (P == 0) {
@@ -287,7 +224,6 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
     row[DM] = row[DM + 1] = row[DM + 2] = 1.0f;
   }
   if (valid) {
-    bnorm[s] = thr;
     unsigned char* rowp = (unsigned char*)Ym + (size_t)s * C::ROWB;
     if constexpr (P == 0) {
       float* out = (float*)rowp;
@@ -298,26 +234,23 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
 #pragma unroll
       for (int c = 0; c < C::KP; ++c) out[c] = (__bf16)row[c];
     }
-    if constexpr (C::LDS) {
-      const unsigned g = M == kCos ? (unsigned)gid_pk[s] : __float_as_uint(thr);
-      *(u32x4*)(rowp + C::KP * C::ELEM) = u32x4{__float_as_uint(w[s]), g, 0u, 0u};
-    }
+    if constexpr (C::LDS)
+      *(u32x4*)(rowp + C::KP * C::ELEM) =
+          u32x4{__float_as_uint(w[s]), __float_as_uint(kRecomputeThr<P> * ny_r), 0u, 0u};
   }
-  if constexpr (M == kEucl) {
-    // the cluster's squared radius, the largest ny (>= 0, so its bits order
-    // like the values): one atomic per wave where all its rows belong to one
-    // cluster (rows of a cluster are contiguous), else one per row
-    int* rad = (int*)(mu + (size_t)k * C::KP);
-    const int jv = valid ? j : -1;
-    const int j0 = __builtin_amdgcn_readfirstlane(jv);
-    if (__builtin_amdgcn_ballot_w64(jv != j0) == 0 && j0 >= 0) {
-      int m = __float_as_int(ny_r);
+  // the cluster's squared radius, the largest ny (>= 0, so its bits order
+  // like the values): one atomic per wave where all its rows belong to one
+  // cluster (rows of a cluster are contiguous), else one per row
+  int* rad = (int*)(mu + (size_t)k * C::KP);
+  const int jv = valid ? j : -1;
+  const int j0 = __builtin_amdgcn_readfirstlane(jv);
+  if (__builtin_amdgcn_ballot_w64(jv != j0) == 0 && j0 >= 0) {
+    int m = __float_as_int(ny_r);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
-      if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(rad + j0, m);
-    } else if (real) {
-      atomicMax(rad + j, __float_as_int(ny_r));
-    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(rad + j0, m);
+  } else if (real) {
+    atomicMax(rad + j, __float_as_int(ny_r));
   }
 }
 
@@ -362,13 +295,6 @@ __device__ __forceinline__ void wsum16(float (&acc)[4], float w0, float w1, cons
         "v"(dv[7]), "v"(dv[8]), "v"(dv[9]), "v"(dv[10]), "v"(dv[11]), "v"(dv[12]), "v"(dv[13]), "v"(dv[14]),
         "v"(dv[15]));
 #undef SILH_FMAC
-}
-
-// per-row value v of row r (the same broadcast, for the compiler's own
-// DPP-combined adds)
-template <int R>
-__device__ __forceinline__ float row_val(float v0, float v1) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(R < 8 ? v0 : v1), 0x150 + wsrc_lane(R), 0xF, 0xF, true));
 }
 
 // the sum of a lane's four running sums and its partner's in the other half
@@ -446,10 +372,6 @@ template <int DM>
 struct AFrag<1, DM> {
   bf16x8 v[MCfg<1, DM>::NSTEP];
 };
-template <int DM>
-struct AFrag<2, DM> {
-  i32x8 v[MCfg<2, DM>::NSTEP];
-};
 
 template <int P, int DM>
 struct BFrag;
@@ -460,10 +382,6 @@ struct BFrag<0, DM> {
 template <int DM>
 struct BFrag<1, DM> {
   bf16x8 v[MCfg<1, DM>::NSTEP];
-};
-template <int DM>
-struct BFrag<2, DM> {
-  i32x8 v[MCfg<2, DM>::NSTEP];
 };
 
 // A raw buffer resource over `bytes` bytes at p (gfx9 descriptor: stride 0,
@@ -527,15 +445,11 @@ __device__ __forceinline__ void load_chunk(const float* __restrict__ xp, int c, 
   }
 }
 
-// one tile's sample operand (this lane's half row), the weights of rows
-// wrow(lane) and 16 + wrow(lane), and per-row values: fp8 the norm terms of
-// those two rows (bnorm), cosine the element id of row lane % 32 (gid_pk)
-template <int M, int P, int DM>
-__device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const float* __restrict__ w,
-                                          const int32_t* __restrict__ gid_pk,
-                                          const float* __restrict__ bnorm, int row0, uint32_t lane_off,
-                                          uint32_t col, uint32_t wr, BFrag<P, DM>& b, float (&wv)[2],
-                                          int (&gv)[2]) {
+// one tile's sample operand (this lane's half row) and the weights of rows
+// wrow(lane) and 16 + wrow(lane)
+template <int P, int DM>
+__device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const float* __restrict__ w, int row0,
+                                          uint32_t lane_off, uint32_t wr, BFrag<P, DM>& b, float (&wv)[2]) {
   using C = MCfg<P, DM>;
   // row0 is wave-uniform: each 32-row tile gets buffer descriptors built on
   // the scalar unit, and a lane reads at a fixed byte offset (no per-tile
@@ -543,15 +457,7 @@ __device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const flo
   const auto rb = rsrc_at((const unsigned char*)Ym + (size_t)row0 * (size_t)(C::KP * C::ELEM),
                           32 * C::KP * C::ELEM);
   const auto rw = rsrc_at(w + row0, 32 * 4);
-  const auto rg = rsrc_at(P != 2 ? (const void*)(gid_pk + row0) : (const void*)(bnorm + row0), 32 * 4);
-  if constexpr (P == 2) {
-#pragma unroll
-    for (int s = 0; s < C::NSTEP; ++s) {
-      const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rb, lane_off + 32u * s, 0, 0);
-      const u32x4 hi = __builtin_amdgcn_raw_buffer_load_b128(rb, lane_off + 32u * s + 16u, 0, 0);
-      b.v[s] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-    }
-  } else if constexpr (P == 0) {
+  if constexpr (P == 0) {
 #pragma unroll
     for (int s2 = 0; s2 < C::NSTEP / 2; ++s2)
       b.v[s2] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rb, lane_off + 8u * s2, 0, 0));
@@ -562,20 +468,13 @@ __device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const flo
   }
   wv[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, 4u * wr, 0, 0));
   wv[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, 4u * (wr + 16u), 0, 0));
-  if constexpr (P == 2) {
-    gv[0] = (int)__builtin_amdgcn_raw_buffer_load_b32(rg, 4u * wr, 0, 0);
-    gv[1] = (int)__builtin_amdgcn_raw_buffer_load_b32(rg, 4u * (wr + 16u), 0, 0);
-  } else if constexpr (M == kCos) {
-    gv[0] = (int)__builtin_amdgcn_raw_buffer_load_b32(rg, 4u * col, 0, 0);
-  }
 }
 
 // waves per SIMD the one-block shapes from d = 32 on keep (their occupancy
 // without the recompute path, which must not lower it)
 // (two tiles per LDS stage hold enough LDS to set the occupancy themselves)
-template <int M, int P, int DM, int PB, int TBX>
-constexpr int kMinWaves = (P == 2 && DM == 128) ? 2
-                          : (M != kEucl || P == 2 || PB == 2 || DM < 32 || (TBX == 2 && MCfg<P, DM>::LDS)) ? 1
+template <int P, int DM, int PB, int TBX>
+constexpr int kMinWaves = (PB == 2 || DM < 32 || (TBX == 2 && MCfg<P, DM>::LDS)) ? 1
                           : DM == 32 ? (P == 1 ? 4 : 1) : DM == 64 ? 3 : DM == 128 ? 2 : 1;
 
 // One block of the Phase-2 launch: 4 waves x PB x 32 elements, from element
@@ -583,27 +482,25 @@ constexpr int kMinWaves = (P == 2 && DM == 128) ? 2
 // or for the (request, block) work items of a multi-request launch.
 
 // tiles per LDS stage of the one-block shape by default: two where measured
-// faster (bf16 from d = 64 on, fp8), else one; the autotuner may try the other
+// faster (bf16 from d = 64 on), else one; the autotuner may try the other
 template <int P, int DM>
-constexpr int kTBDefault = (P == 2 || (P == 1 && DM >= 64)) ? 2 : 1;
+constexpr int kTBDefault = (P == 1 && DM >= 64) ? 2 : 1;
 
-template <int M, int P, int DM, int PB, int TBX>
+template <int P, int DM, int PB, int TBX>
 __device__ __forceinline__ void p2_mfma_block(
     const int blk, const float* __restrict__ X, int n, int d, const int32_t* __restrict__ labels,
-    const void* __restrict__ Ym, const float* __restrict__ w, const int32_t* __restrict__ gid_pk,
+    const void* __restrict__ Ym, const float* __restrict__ w,
     const int32_t* __restrict__ sp_off, const int32_t* __restrict__ cnt,
     const int32_t* __restrict__ csize, int k, const float* __restrict__ mu,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
-    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ bnorm,
-    const float* __restrict__ Y32, int DMY, const float* __restrict__ aux, const float* __restrict__ rn) {
+    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32) {
   using C = MCfg<P, DM>;
   // contiguous halves: the augmentation columns always fall in the upper half
   // of the row
   constexpr int AUG0 = DM - C::HALF;
-  static_assert(C::IL || C::AUG == 0 || (AUG0 >= 0 && AUG0 + C::AUG <= C::HALF), "augmentation placement");
-  constexpr float S2 = kFp8Scale * kFp8Scale;
+  static_assert(C::IL || (AUG0 >= 0 && AUG0 + C::AUG <= C::HALF), "augmentation placement");
   __shared__ double sh32[4 * PB];  // 32-element partials of the block, in element order
-  // Long rows (bf16 / float32 with d >= 64, fp8 with d >= 128): the block's
+  // Long rows (bf16 / float32 with d >= 64): the block's
   // four waves sweep the same tiles, so each is loaded once per block into
   // LDS and every wave reads its sample fragment from there.  Tiles go in stages
   // of kTB; a stage's slot holds its tiles (32 packed rows each, whose
@@ -626,7 +523,7 @@ __device__ __forceinline__ void p2_mfma_block(
   static_assert(!kLds || (kTileI >= 4 && kMuI <= 4), "every wave loads part of each tile; mu takes at most four loads");
   constexpr int kDw = (kTileI + 3) / 4;             // loads per wave per tile
   constexpr int kNIw = kTB * kDw;                   // per wave per stage, without mu
-  // LDS path with bf16 / fp8 operands: one tile's epilogue runs beside the
+  // LDS path with bf16 operands: one tile's epilogue runs beside the
   // next tile's MFMAs (float32 operands are bound by the MFMA rate)
   constexpr bool kPipe = kLds && P != 0 && DM >= 128;
   // Accumulator layout.  kT (every path but the pipelined one): samples are
@@ -646,7 +543,6 @@ __device__ __forceinline__ void p2_mfma_block(
   const int col = lane & 31;
   // PB blocks of 32 elements per wave share every sample tile
   const int P0 = __builtin_amdgcn_readfirstlane((blk * 4 + (threadIdx.x >> 6)) * 32 * PB);
-  const float alpha = M == kCos ? 0.5f : 1.0f;
   const uint32_t lane_off = (uint32_t)((col * C::KP + h * C::FOFF) * C::ELEM);  // bytes
   // kT: this lane's rows of a tile's per-row values (weights)
   const int wr = wrow(lane);
@@ -655,7 +551,7 @@ __device__ __forceinline__ void p2_mfma_block(
   const int rr = (lane >> 1) & 15;
   const int prow = 8 * (rr >> 2) + 4 * h + (rr & 3);
 
-  // this lane's half of its A rows (raw or unit-scaled), zero outside [0, d),
+  // this lane's half of its A rows, zero outside [0, d),
   // resident for the whole cluster loop (at d = 256 partly in AGPRs, which
   // the one wave per SIMD that the tile registers allow leaves free);
   // re-reading it per cluster would stream X k times through L2.
@@ -676,7 +572,6 @@ __device__ __forceinline__ void p2_mfma_block(
       return xr[b][i];
     }
   };
-  float ux[PB];
   int pout[PB], own[PB];
   // b_hat as the fraction bnum / bden of the smallest W_hat_j / |C_j| so far
   // (candidates compared by cross-multiplication, one division at the end;
@@ -695,15 +590,6 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
       for (int e = 0; e < V; ++e) xr[b][i0 + e] = xc[e];
     }
-    ux[b] = 0.f;
-    if (M == kCos) {
-      // unit vector: the row times its float32 reciprocal norm, the product
-      // the packing forms for the sample rows (u = 0.5 for a zero row)
-      const float rx = rn[pa];
-      ux[b] = rx > 0.f ? 0.f : 0.5f;
-#pragma unroll
-      for (int i = 0; i < C::XR; ++i) xr[b][i] *= rx;
-    }
     if constexpr (kXA) {
       // kept in accumulation registers (AGPRs) until the A operands of each
       // cluster read them back
@@ -719,20 +605,8 @@ __device__ __forceinline__ void p2_mfma_block(
   }
 
   AFrag<P, DM> A[PB];
-  // fp8: 64^2 (alpha |x~_q|^2 + u_x) of this lane's element (kT), of its
-  // 16 accumulator rows (element-row layout)
-  float nxc[PB][kT ? 1 : 16];
-  // fp8 with element rows (the pipelined path): the element terms as the
-  // MFMA's accumulator input (the same every tile of a cluster); the sample
-  // term 64^2 |y~|^2 / 2 of column col shifts the clamp instead,
-  //   med3(c + v, 0, 2 S2) = med3(c, -v, 2 S2 - v) + v,
-  // and its weighted sum, the same for every element, goes into tcol (per
-  // lane column, added to every element's sum at the fold)
-  constexpr bool kF8R = P == 2 && !kT;
-  f32x16 nxv[PB];
-  float tcol[PB];
-  int thrx[PB];   // Euclidean: the element's recompute threshold (float bits, >= 0)
-  int chk[PB];    // Euclidean: some element of the block may meet the threshold (wave-uniform, 0 / 1)
+  int thrx[PB];   // the element's recompute threshold (float bits, >= 0)
+  int chk[PB];    // some element of the block may meet the threshold (wave-uniform, 0 / 1)
   // The packed cluster blocks are contiguous, so the tile after a cluster's
   // last one is the first tile of the next cluster with samples: it is
   // prefetched there, and a cluster normally starts with its first tile
@@ -744,7 +618,6 @@ __device__ __forceinline__ void p2_mfma_block(
   int pre = -1;
   BFrag<P, DM> b0, b1;
   float w0[2] = {0.f, 0.f}, w1[2] = {0.f, 0.f};
-  int g0[2] = {-1, -1}, g1[2] = {-1, -1};
 
   // ---- LDS path: the stage ring.  (cj, cm) is the next stage to load
   // (cluster, stage within it; cj = k past the end, where the last tile is
@@ -816,8 +689,8 @@ __device__ __forceinline__ void p2_mfma_block(
     // rounded to the input precision, plus the augmentation; m is this
     // lane's half of mu_j (in memory, or in the LDS slot of the cluster's
     // first stage)
-    // Euclidean: the squared radius of the cluster's packed sample
-    const float R2 = (M == kEucl && P != 2) ? mu[(size_t)k * C::KP + j] : 0.0f;
+    // the squared radius of the cluster's packed sample
+    const float R2 = mu[(size_t)k * C::KP + j];
     auto buildA = [&](const float* m) {
     float mv[C::HALF];
 #pragma unroll
@@ -830,29 +703,6 @@ __device__ __forceinline__ void p2_mfma_block(
     for (int b = 0; b < PB; ++b) {
       float xq[C::HALF];
       float part = 0.f;
-      if constexpr (P == 2) {
-#pragma unroll
-        for (int i = 0; i < C::HALF; ++i) {
-          const float v = xget(b, i) - mv[i];
-          xq[i] = q_fp8(kFp8Scale * v);
-          part = fmaf(v, v, part);  // the norm of the unrounded coordinates
-        }
-        const float rowv = S2 * fmaf(alpha, part + __shfl_xor(part, 32, kWave), ux[b]);
-        if constexpr (kT) {
-          nxc[b][0] = rowv;  // the lane's element is its accumulator column
-        } else {
-          // the C rows of this lane are elements 8(r/4) + 4h + r%4 of the block
-#pragma unroll
-          for (int r = 0; r < 16; ++r) nxv[b][r] = __shfl(rowv, 8 * (r >> 2) + 4 * h + (r & 3), kWave);
-        }
-#pragma unroll
-        for (int s = 0; s < C::NSTEP; ++s)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            A[b].v[s][e] = fp8_pack4(xq[32 * s + 4 * e], xq[32 * s + 4 * e + 1], xq[32 * s + 4 * e + 2],
-                                     xq[32 * s + 4 * e + 3]);
-        continue;
-      }
       if constexpr (P == 1) {
         // bf16: each pair of centred coordinates is rounded into one packed
         // register (the fragment's layout) and its squares are added to the
@@ -872,7 +722,7 @@ __device__ __forceinline__ void p2_mfma_block(
             pk[i2] = bf16x2{};
           }
         }
-        const float an = fmaf(alpha, part + __shfl_xor(part, 32, kWave), ux[b]);
+        const float an = part + __shfl_xor(part, 32, kWave);
         thrx[b] = __float_as_int(kRecomputeThr<P> * an);
         chk[b] = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(an < kSkipFactor<P> * R2) != 0 ? 1 : 0);
         float aug[6];
@@ -896,8 +746,7 @@ __device__ __forceinline__ void p2_mfma_block(
         part = fmaf(v, v, part);
       }
       // float32: the norm and a 1 ride along as two extra columns
-      const float nx = part + __shfl_xor(part, 32, kWave);
-      const float an = fmaf(alpha, nx, ux[b]);
+      const float an = part + __shfl_xor(part, 32, kWave);
       thrx[b] = __float_as_int(kRecomputeThr<P> * an);
       chk[b] = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(an < kSkipFactor<P> * R2) != 0 ? 1 : 0);
       xq[AUG0] = h ? an : xq[AUG0];
@@ -918,7 +767,6 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
       wsum[b] = 0.0;
-      tcol[b] = 0.f;
 #pragma unroll
       for (int r = 0; r < kNA; ++r) acc[b][r] = 0.f;
     }
@@ -926,31 +774,13 @@ __device__ __forceinline__ void p2_mfma_block(
     // One tile, in four parts: chain (the MFMAs; getB(q) gives step q of
     // this lane's sample fragment, a float2 of two steps for float32, from
     // registers or read from LDS just in time), fixup (pairs prone to
-    // cancellation, the cosine self pair), wsum_add (distances and the
+    // cancellation), wsum_add (distances and the
     // weighted sums) and fold (the float64 add every kFold tiles and at the
     // cluster's end).  The LDS path overlaps the wsum_add of one tile with
-    // the chain of the next; the arithmetic per pair is the same.  wv, gv:
-    // the tile's weights and per-row values as load_tile gives them.
-    auto dist = [&](float c) {
-      if constexpr (M == kEucl)
-        return __builtin_amdgcn_sqrtf(fabsf(c));
-      else
-        return __builtin_amdgcn_fmed3f(c, 0.0f, P == 2 ? 2.0f * S2 : 2.0f);
-    };
-    // fp8: the accumulator starts at 64^2 (element term + sample term), the
-    // MFMA adds -64^2 x~_q . y~_q (unscaled f8f6f4 form, e4m3 operands)
-    auto fp8_init = [&](f32x16& c, int b, const int (&gv)[2]) {
-      if constexpr (kT) {
-        const float v0 = S2 * __int_as_float(gv[0]), v1 = S2 * __int_as_float(gv[1]);
-        static_for<16>([&](auto RC) {
-          constexpr int r = decltype(RC)::value;
-          c[r] = nxc[b][0] + row_val<r>(v0, v1);
-        });
-      } else {
-        c = nxv[b];  // the sample term is in the clamp bounds (kF8R)
-      }
-    };
-    auto chain = [&](auto&& getB, const int (&gv)[2], f32x16 (&cc)[PB]) {
+    // the chain of the next; the arithmetic per pair is the same.  wv: the
+    // tile's weights as load_tile gives them.
+    auto dist = [&](float c) { return __builtin_amdgcn_sqrtf(fabsf(c)); };
+    auto chain = [&](auto&& getB, f32x16 (&cc)[PB]) {
 #pragma unroll
       for (int b = 0; b < PB; ++b) {
         f32x16 c;
@@ -964,25 +794,21 @@ __device__ __forceinline__ void p2_mfma_block(
             c = __builtin_amdgcn_mfma_f32_32x32x2f32(bq.x, A[b].v[2 * s2], c, 0, 0, 0);
             c = __builtin_amdgcn_mfma_f32_32x32x2f32(bq.y, A[b].v[2 * s2 + 1], c, 0, 0, 0);
           }
-        } else if constexpr (P == 1) {
+        } else {
           c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(getB(0), A[b].v[0], f32x16{}, 0, 0, 0);
 #pragma unroll
           for (int s = 1; s < C::NSTEP; ++s)
             c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(getB(s), A[b].v[s], c, 0, 0, 0);
-        } else {
-          fp8_init(c, b, gv);
-#pragma unroll
-          for (int s = 0; s < C::NSTEP; ++s)
-            c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(getB(s), A[b].v[s], c, 0, 0, 0, 0, 0, 0);
         }
         cc[b] = c;
       }
     };
-    auto fixup = [&](f32x16 (&cc)[PB], const int (&gv)[2], int srow) {
+    // thr: element rows, the sample's recompute threshold (the lane's column)
+    auto fixup = [&](f32x16 (&cc)[PB], int thr, int srow) {
 #pragma unroll
       for (int b = 0; b < PB; ++b) {
         f32x16& c = cc[b];
-        if constexpr (P != 2 && M == kEucl) {
+        {
           // pairs prone to cancellation (kRecomputeThr) get their squared
           // distance again from the float32 rows; rare outside the self pair.
           // The threshold is >= 0, so comparing bit patterns as signed
@@ -994,7 +820,7 @@ __device__ __forceinline__ void p2_mfma_block(
           if constexpr (kT) {
             if (__builtin_amdgcn_readfirstlane(chk[b]) == 0) continue;  // wave-uniform: no pair of the block can be flagged
           }
-          const int tx = kT ? thrx[b] : gv[0];
+          const int tx = kT ? thrx[b] : thr;
           int mn = __float_as_int(c[0]);
 #pragma unroll
           for (int r = 1; r < 16; ++r) mn = min(mn, __float_as_int(c[r]));
@@ -1005,7 +831,7 @@ __device__ __forceinline__ void p2_mfma_block(
             for (int r = 0; r < 16; ++r) flagged |= (__float_as_int(c[r]) < tx ? 1u : 0u) << r;
             const int e0 = P0 + 32 * b + col;
             const float* xc = X + (size_t)(e0 < n ? e0 : n - 1) * d;
-            const float* yc = Y32 + (size_t)(srow + col) * DMY;
+            const float* yc = Y32 + (size_t)(srow + col) * DM;
             while (flagged) {
               const int r = __builtin_ctz(flagged);
               flagged &= flagged - 1;
@@ -1013,7 +839,7 @@ __device__ __forceinline__ void p2_mfma_block(
               const int rw = 8 * (r >> 2) + 4 * h + (r & 3);
               const int er = P0 + 32 * b + rw;
               const float* xp = kT ? xc : X + (size_t)(er < n ? er : n - 1) * d;
-              const float* yr = kT ? Y32 + (size_t)(srow + rw) * DMY : yc;
+              const float* yr = kT ? Y32 + (size_t)(srow + rw) * DM : yc;
               float acc2 = 0.0f;
               for (int q = 0; q < d; ++q) {
                 const float t = xp[q] - yr[q];
@@ -1022,36 +848,6 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
               for (int q = 0; q < 16; ++q) c[q] = q == r ? acc2 : c[q];
             }
-          }
-        } else if constexpr (P != 2 && !kT) {
-          // cosine, element rows: a column holding one of this block's own
-          // 32 elements (in this lane's half of the rows) zeroes that row
-          // (the self pair, as below)
-          const int self = gv[0] - (P0 + 32 * b);
-          if ((unsigned)self < 32u && ((self >> 2) & 1) == h) {
-            const int rh = ((self >> 3) << 2) | (self & 3);
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (r == rh) c[r] = 0.0f;
-          }
-        } else if constexpr (P != 2) {
-          // cosine: no square root amplifies the expansion's absolute error
-          // (of order 2^-22 here), so only the self pair d(e, e) = 0 is
-          // forced: a sample row holding one of this block's own 32 elements
-          // (lane l reads the id of row l % 32) zeroes that row in the
-          // element's column.  The unit rows of both sides are the same
-          // product x * rn, so the pair's operands are identical; zero rows
-          // carry id -1 and keep their d = 1.
-          const int self = gv[0] - (P0 + 32 * b);
-          unsigned hit = (unsigned)__builtin_amdgcn_ballot_w64((unsigned)self < 32u);  // rows 0..31
-          while (__builtin_expect(hit != 0u, 0)) {  // wave-uniform
-            const int sr = __builtin_ctz(hit);
-            hit &= hit - 1u;
-            const int e = __builtin_amdgcn_readlane(self, sr);
-            const int rs = 4 * (sr >> 3) + (sr & 3);
-            const bool mine = col == e && h == ((sr >> 2) & 1);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) c[q] = (mine && q == rs) ? 0.0f : c[q];
           }
         }
       }
@@ -1065,11 +861,6 @@ __device__ __forceinline__ void p2_mfma_block(
         for (int r = 0; r < 16; ++r) dv[r] = dist(cc[b][r]);
         if constexpr (kT) {
           wsum16(acc[b], wv[0], wv[1], dv);
-        } else if constexpr (kF8R) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            acc[b][r] = fmaf(wv[0], __builtin_amdgcn_fmed3f(cc[b][r], -wv[1], 2.0f * S2 - wv[1]), acc[b][r]);
-          tcol[b] = fmaf(wv[0], wv[1], tcol[b]);
         } else {
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[b][r] = fmaf(wv[0], dv[r], acc[b][r]);
@@ -1086,17 +877,7 @@ __device__ __forceinline__ void p2_mfma_block(
             v = lane_sum(acc[b]);
           else
             v = transpose_reduce16(acc[b], lane);
-          if constexpr (kF8R) {
-            // the sample terms' sum over the 32 columns (the same in both halves)
-            float t = tcol[b];
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
-            wsum[b] += ((double)v + (double)t) * (1.0 / S2);
-            tcol[b] = 0.f;
-          } else {
-            // fp8: the distances came scaled by 64^2 (a power of two)
-            wsum[b] += P == 2 ? (double)v * (1.0 / S2) : (double)v;
-          }
+          wsum[b] += (double)v;
 #pragma unroll
           for (int r = 0; r < kNA; ++r) acc[b][r] = 0.f;
         }
@@ -1112,7 +893,7 @@ __device__ __forceinline__ void p2_mfma_block(
     // order (left to itself the compiler reads each step's operand right
     // before its MFMA, which then waits for the whole LDS latency).  Same
     // arithmetic per accumulator as chain + wsum_add.
-    auto chain_pipe = [&](auto&& getB, const int (&gv)[2], f32x16 (&cn)[PB], const f32x16 (&cp)[PB],
+    auto chain_pipe = [&](auto&& getB, f32x16 (&cn)[PB], const f32x16 (&cp)[PB],
                           const float (&wp)[2], int tt) {
       static_assert(PB == 1 && !kT, "the pipelined LDS path runs one block of 32 elements per wave, element rows");
       constexpr int NS = C::NSTEP;
@@ -1122,23 +903,13 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
       for (int q = 0; q < kAhead; ++q) bq[q] = getB(q);
       f32x16 c;
-      if constexpr (P == 2) {
-        fp8_init(c, 0, gv);
-      } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) c[r] = 0.0f;
-      }
-      // fp8: the pending tile's clamp bounds and its sample-term sum
-      const float plo = -wp[1], phi = 2.0f * S2 - wp[1];
-      if constexpr (kF8R) tcol[0] = fmaf(wp[0], wp[1], tcol[0]);
+      for (int r = 0; r < 16; ++r) c[r] = 0.0f;
       __builtin_amdgcn_sched_barrier(0);
       static_for<NS>([&](auto QC) {
         constexpr int q = decltype(QC)::value;
         const BT cur = bq[q % kAhead];
-        if constexpr (P == 1)
-          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[0].v[q], cur, c, 0, 0, 0);
-        else
-          c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A[0].v[q], cur, c, 0, 0, 0, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[0].v[q], cur, c, 0, 0, 0);
         if constexpr (q + kAhead < NS) bq[q % kAhead] = getB(q + kAhead);
         // the next-but-one stage's loads of tile tt, spread over the steps
 #pragma unroll
@@ -1146,15 +917,15 @@ __device__ __forceinline__ void p2_mfma_block(
           if (q == (2 * mi + 1) * NS / (2 * kDw)) tile_load(tt, mi);
 #pragma unroll
         for (int r = 16 * q / NS; r < 16 * (q + 1) / NS; ++r)
-          acc[0][r] = fmaf(wp[0], kF8R ? __builtin_amdgcn_fmed3f(cp[0][r], plo, phi) : dist(cp[0][r]), acc[0][r]);
+          acc[0][r] = fmaf(wp[0], dist(cp[0][r]), acc[0][r]);
         __builtin_amdgcn_sched_barrier(0);
       });
       cn[0] = c;
     };
-    auto tile = [&](auto&& getB, const float (&wv)[2], const int (&gv)[2], int srow, bool last) {
+    auto tile = [&](auto&& getB, const float (&wv)[2], int srow, bool last) {
       f32x16 cc[PB];
-      chain(getB, gv, cc);
-      fixup(cc, gv, srow);
+      chain(getB, cc);
+      fixup(cc, 0, srow);
       wsum_add(cc, wv);
       fold(last);
     };
@@ -1189,16 +960,13 @@ __device__ __forceinline__ void p2_mfma_block(
           return [tl](int q) {
             if constexpr (P == 0) {
               return *(const float2*)(tl + 8 * q);
-            } else if constexpr (P == 1) {
-              return *(const bf16x8*)(tl + 2 * C::FSTEP * q);
             } else {
-              const u32x4 lo = *(const u32x4*)(tl + 32 * q), hi = *(const u32x4*)(tl + 32 * q + 16);
-              return i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+              return *(const bf16x8*)(tl + 2 * C::FSTEP * q);
             }
           };
         };
-        // the row tails: weights of rows wr and 16 + wr, per-row values
-        // (element rows: the weight and value of the lane's sample column)
+        // the row tails: weights of rows wr and 16 + wr (element rows: the
+        // weight and the recompute threshold of the lane's sample column)
         auto wval = [&](int tt, float (&wv)[2]) {
           const unsigned char* tb = sb + tt * kTileCh * 16 + kRowB;
           if constexpr (kT) {
@@ -1206,38 +974,24 @@ __device__ __forceinline__ void p2_mfma_block(
             wv[1] = *(const float*)(tb + (wr + 16) * kLRow);
           } else {
             wv[0] = *(const float*)(tb + col * kLRow);
-            // fp8: the sample term 64^2 |y~|^2 / 2 of the lane's column
-            if constexpr (kF8R) wv[1] = S2 * *(const float*)(tb + 4 + col * kLRow);
           }
         };
-        auto gval = [&](int tt, int (&gv)[2]) {
-          const unsigned char* tb = sb + tt * kTileCh * 16 + kRowB + 4;
-          if constexpr (!kT) {
-            gv[0] = *(const int*)(tb + col * kLRow);
-          } else if constexpr (P == 2) {
-            gv[0] = *(const int*)(tb + wr * kLRow);
-            gv[1] = *(const int*)(tb + (wr + 16) * kLRow);
-          } else if constexpr (M == kCos) {
-            gv[0] = *(const int*)(tb + col * kLRow);
-          }
-        };
+        auto thr_of = [&](int tt) { return *(const int*)(sb + tt * kTileCh * 16 + kRowB + 4 + col * kLRow); };
         if constexpr (kPipe) {
           // a tile's MFMAs and the pending tile's square roots and sums in one
           // stretch of code, so the vector ALU works while the matrix core runs
           {
-            int gv[2];
-            gval(0, gv);
-            chain_pipe(fromLds(0), gv, cb, ca, wa, 0);
+            const int thr = thr_of(0);
+            chain_pipe(fromLds(0), cb, ca, wa, 0);
             if (t > 0) fold(false);
-            fixup(cb, gv, base + t * 32);
+            fixup(cb, thr, base + t * 32);
             wval(0, wb);
           }
           if (kTB == 2 && t + 1 < ntile) {  // block-uniform
-            int gv[2];
-            gval(1, gv);
-            chain_pipe(fromLds(1), gv, ca, cb, wb, 1);
+            const int thr = thr_of(1);
+            chain_pipe(fromLds(1), ca, cb, wb, 1);
             fold(false);
-            fixup(ca, gv, base + (t + 1) * 32);
+            fixup(ca, thr, base + (t + 1) * 32);
             wval(1, wa);
           } else {
             // one tile in the stage: the pending tile is in cb (and the
@@ -1256,10 +1010,8 @@ __device__ __forceinline__ void p2_mfma_block(
           for (int tt = 0; tt < kTB; ++tt)
             if (t + tt < ntile) {  // block-uniform
               float wv[2];
-              int gv[2];
               wval(tt, wv);
-              gval(tt, gv);
-              tile(fromLds(tt), wv, gv, base + (t + tt) * 32, t + tt + 1 == ntile);
+              tile(fromLds(tt), wv, base + (t + tt) * 32, t + tt + 1 == ntile);
             }
         }
         rs = rs == 2 ? 0 : rs + 1;
@@ -1275,19 +1027,19 @@ __device__ __forceinline__ void p2_mfma_block(
       // each tile covers only that tile's loads; an odd last tile runs after
       // the loop from the buffer already loaded, and its successor is loaded
       // into the same buffer once its MFMAs are issued.
-      if (ntile > 0 && pre != base) load_tile<M, P, DM>(Ym, w, gid_pk, bnorm, base, lane_off, col, wr, b0, w0, g0);
+      if (ntile > 0 && pre != base) load_tile<P, DM>(Ym, w, base, lane_off, wr, b0, w0);
       int t = 0;
       for (; t + 2 <= ntile; t += 2) {
-        load_tile<M, P, DM>(Ym, w, gid_pk, bnorm, base + (t + 1) * 32, lane_off, col, wr, b1, w1, g1);
-        tile([&](int q) { return b0.v[q]; }, w0, g0, base + t * 32, false);
+        load_tile<P, DM>(Ym, w, base + (t + 1) * 32, lane_off, wr, b1, w1);
+        tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, false);
         pre = clamp_row(base + (t + 2) * 32);
-        load_tile<M, P, DM>(Ym, w, gid_pk, bnorm, pre, lane_off, col, wr, b0, w0, g0);
-        tile([&](int q) { return b1.v[q]; }, w1, g1, base + (t + 1) * 32, t + 2 == ntile);
+        load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
+        tile([&](int q) { return b1.v[q]; }, w1, base + (t + 1) * 32, t + 2 == ntile);
       }
       if (t < ntile) {
-        tile([&](int q) { return b0.v[q]; }, w0, g0, base + t * 32, true);
+        tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, true);
         pre = clamp_row(base + ntile * 32);
-        load_tile<M, P, DM>(Ym, w, gid_pk, bnorm, pre, lane_off, col, wr, b0, w0, g0);
+        load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
       }
     }
     const int sz = csize[j];
@@ -1334,17 +1086,16 @@ __device__ __forceinline__ void p2_mfma_block(
   }
 }
 
-template <int M, int P, int DM, int PB, int TBX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<M, P, DM, PB, TBX>))) void k_p2_mfma(
+template <int P, int DM, int PB, int TBX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P, DM, PB, TBX>))) void k_p2_mfma(
     const float* __restrict__ X, int n, int d, const int32_t* __restrict__ labels,
-    const void* __restrict__ Ym, const float* __restrict__ w, const int32_t* __restrict__ gid_pk,
+    const void* __restrict__ Ym, const float* __restrict__ w,
     const int32_t* __restrict__ sp_off, const int32_t* __restrict__ cnt,
     const int32_t* __restrict__ csize, int k, const float* __restrict__ mu,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
-    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ bnorm,
-    const float* __restrict__ Y32, int DMY, const float* __restrict__ aux, const float* __restrict__ rn) {
-  p2_mfma_block<M, P, DM, PB, TBX>(blockIdx.x, X, n, d, labels, Ym, w, gid_pk, sp_off, cnt, csize, k, mu, a_out, b_out,
-                              s_out, What, bpart, bnorm, Y32, DMY, aux, rn);
+    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32) {
+  p2_mfma_block<P, DM, PB, TBX>(blockIdx.x, X, n, d, labels, Ym, w, sp_off, cnt, csize, k, mu, a_out, b_out,
+                              s_out, What, bpart, Y32);
 }
 
 // Several requests in one launch: workgroup i runs work item i = (request,
@@ -1356,16 +1107,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<M
 // registers in the shapes from d = 32 on.  The job table and the items are
 // read through the constant address space, so their values sit in scalar
 // registers like kernel arguments.
-template <int M, int P, int DM, int PB, int TBX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<M, P, DM, PB, TBX>))) void k_p2_mfma_jobs(
+template <int P, int DM, int PB, int TBX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P, DM, PB, TBX>))) void k_p2_mfma_jobs(
     const P2Job* __restrict__ jobs, const int2* __restrict__ items) {
   typedef const __attribute__((address_space(4))) P2Job* cjob_ptr;
   typedef const __attribute__((address_space(4))) int* citem_ptr;
   const int jx = ((citem_ptr)items)[2 * blockIdx.x];
   const int blk = ((citem_ptr)items)[2 * blockIdx.x + 1];
   const auto& J = ((cjob_ptr)jobs)[jx];
-  p2_mfma_block<M, P, DM, PB, TBX>(blk, J.X, J.n, J.d, J.labels, J.Ym, J.w, J.gid_pk, J.sp_off, J.cnt, J.csize, J.k, J.mu,
-                              J.a, J.b, J.s, J.What, J.bpart, J.bnorm, J.Y32, DM, J.aux, J.rn);
+  p2_mfma_block<P, DM, PB, TBX>(blk, J.X, J.n, J.d, J.labels, J.Ym, J.w, J.sp_off, J.cnt, J.csize, J.k, J.mu,
+                              J.a, J.b, J.s, J.What, J.bpart, J.Y32);
 }
 
 // Block shapes of the matrix-core kernel (ids used by the autotuner):
@@ -1373,13 +1124,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<M
 //     per stage);
 //  2  two blocks per wave: half the B-operand loads per pair (the float32
 //     path is bound by the MFMA rate and gains) but twice the accumulator
-//     and A-operand registers (fewer waves per SIMD); d <= 64, not fp8;
+//     and A-operand registers (fewer waves per SIMD); d <= 64;
 //  3  one block per wave with the other number of tiles per LDS stage (the
 //     LDS path only).
 // The arithmetic of every element, and the 128-element partials of the
 // mean, are the same in every shape.
 int mfma_pb_default(int prec, int DM) { return (prec == 0 && DM <= 32) ? 2 : 1; }
-int mfma_pb_max(int prec, int DM) { return (prec == 2 || DM > 64) ? 1 : 2; }
+int mfma_pb_max(int, int DM) { return DM > 64 ? 1 : 2; }
 int mfma_shapes(int prec, int DM, int* ids) {
   int m = 0;
   ids[m++] = 1;
@@ -1388,118 +1139,87 @@ int mfma_shapes(int prec, int DM, int* ids) {
   return m;
 }
 
-template <int M, int P, int DM, int PB, int TBX>
-static void launch_mfma_pb(hipStream_t st, const P2Args& A, const float* mu, const void* Ym,
-                           const float* bnorm) {
+template <int P, int DM, int PB, int TBX>
+static void launch_mfma_pb(hipStream_t st, const P2Args& A, const float* mu, const void* Ym) {
   const int blocks = (int)ceil_div(A.n, 128 * PB);
-  hipLaunchKernelGGL((k_p2_mfma<M, P, DM, PB, TBX>), dim3(blocks), dim3(256), 0, st, A.X, A.n, A.d, A.labels, Ym,
-                     A.w, A.gid_pk, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart,
-                     bnorm, A.Y, DM, A.aux, A.rn);
+  hipLaunchKernelGGL((k_p2_mfma<P, DM, PB, TBX>), dim3(blocks), dim3(256), 0, st, A.X, A.n, A.d, A.labels, Ym,
+                     A.w, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart, A.Y);
 }
 
-template <int M, int P, int DM>
-static void launch_mfma_one(hipStream_t st, const P2Args& A, const float* mu, const void* Ym,
-                            const float* bnorm, int shape) {
+template <int P, int DM>
+static void launch_mfma_one(hipStream_t st, const P2Args& A, const float* mu, const void* Ym, int shape) {
   constexpr int TB0 = kTBDefault<P, DM>;
-  if constexpr (P != 2 && DM <= 64) {  // two blocks per wave would not fit the registers beyond
+  if constexpr (DM <= 64) {  // two blocks per wave would not fit the registers beyond
     if (shape == 2) {
-      launch_mfma_pb<M, P, DM, 2, 1>(st, A, mu, Ym, bnorm);
+      launch_mfma_pb<P, DM, 2, 1>(st, A, mu, Ym);
       return;
     }
   }
   if (shape == 3 && mfma_lds_path(P, DM)) {
-    launch_mfma_pb<M, P, DM, 1, 3 - TB0>(st, A, mu, Ym, bnorm);
+    launch_mfma_pb<P, DM, 1, 3 - TB0>(st, A, mu, Ym);
     return;
   }
-  launch_mfma_pb<M, P, DM, 1, TB0>(st, A, mu, Ym, bnorm);
+  launch_mfma_pb<P, DM, 1, TB0>(st, A, mu, Ym);
 }
 
-template <int M, int P, int DM>
+template <int P, int DM>
 static void launch_jobs_one(hipStream_t st, const P2Job* jobs, const int2* items, int nitems, int shape) {
   constexpr int TB0 = kTBDefault<P, DM>;
-  if constexpr (P != 2 && DM <= 64) {
+  if constexpr (DM <= 64) {
     if (shape == 2) {
-      hipLaunchKernelGGL((k_p2_mfma_jobs<M, P, DM, 2, 1>), dim3(nitems), dim3(256), 0, st, jobs, items);
+      hipLaunchKernelGGL((k_p2_mfma_jobs<P, DM, 2, 1>), dim3(nitems), dim3(256), 0, st, jobs, items);
       return;
     }
   }
   if (shape == 3 && mfma_lds_path(P, DM)) {
-    hipLaunchKernelGGL((k_p2_mfma_jobs<M, P, DM, 1, 3 - TB0>), dim3(nitems), dim3(256), 0, st, jobs, items);
+    hipLaunchKernelGGL((k_p2_mfma_jobs<P, DM, 1, 3 - TB0>), dim3(nitems), dim3(256), 0, st, jobs, items);
     return;
   }
-  hipLaunchKernelGGL((k_p2_mfma_jobs<M, P, DM, 1, TB0>), dim3(nitems), dim3(256), 0, st, jobs, items);
+  hipLaunchKernelGGL((k_p2_mfma_jobs<P, DM, 1, TB0>), dim3(nitems), dim3(256), 0, st, jobs, items);
 }
 
-template <int M, int P, int DM>
-static void launch_pack_one(hipStream_t st, const float* Y32, const float* aux, const float* w,
-                            const int32_t* gid_pk, const int32_t* sp_off, const int32_t* cnt, int k,
-                            float* mu, int S_pad, void* Ym, float* bnorm) {
-  hipLaunchKernelGGL((k_pack_mfma<M, P, DM>), dim3((int)ceil_div(S_pad, 256)), dim3(256), 0, st, Y32,
-                     aux, w, gid_pk, sp_off, cnt, k, mu, S_pad, Ym, bnorm);
+template <int P, int DM>
+static void launch_pack_one(hipStream_t st, const float* Y32, const float* w, const int32_t* sp_off,
+                            const int32_t* cnt, int k, float* mu, int S_pad, void* Ym) {
+  hipLaunchKernelGGL((k_pack_mfma<P, DM>), dim3((int)ceil_div(S_pad, 256)), dim3(256), 0, st, Y32, w, sp_off, cnt, k,
+                     mu, S_pad, Ym);
 }
 
-#define SILH_MFMA_DISPATCH(FN, ...)                                     \
-  do {                                                                  \
-    if (metric == kEucl && prec == 0) {                                 \
-      switch (DM) {                                                     \
-        case 8: FN<kEucl, 0, 8>(__VA_ARGS__); return true;              \
-        case 16: FN<kEucl, 0, 16>(__VA_ARGS__); return true;            \
-        case 32: FN<kEucl, 0, 32>(__VA_ARGS__); return true;            \
-        case 64: FN<kEucl, 0, 64>(__VA_ARGS__); return true;            \
-        case 128: FN<kEucl, 0, 128>(__VA_ARGS__); return true;          \
-      }                                                                 \
-    } else if (metric == kEucl && prec == 1) {                          \
-      switch (DM) {                                                     \
-        case 8: FN<kEucl, 1, 8>(__VA_ARGS__); return true;              \
-        case 16: FN<kEucl, 1, 16>(__VA_ARGS__); return true;            \
-        case 32: FN<kEucl, 1, 32>(__VA_ARGS__); return true;            \
-        case 64: FN<kEucl, 1, 64>(__VA_ARGS__); return true;            \
-        case 128: FN<kEucl, 1, 128>(__VA_ARGS__); return true;          \
-        case 256: FN<kEucl, 1, 256>(__VA_ARGS__); return true;          \
-      }                                                                 \
-    } else if (metric == kCos && prec == 0) {                           \
-      switch (DM) {                                                     \
-        case 8: FN<kCos, 0, 8>(__VA_ARGS__); return true;               \
-        case 16: FN<kCos, 0, 16>(__VA_ARGS__); return true;             \
-        case 32: FN<kCos, 0, 32>(__VA_ARGS__); return true;             \
-        case 64: FN<kCos, 0, 64>(__VA_ARGS__); return true;             \
-        case 128: FN<kCos, 0, 128>(__VA_ARGS__); return true;           \
-      }                                                                 \
-    } else if (metric == kCos && prec == 1) {                           \
-      switch (DM) {                                                     \
-        case 8: FN<kCos, 1, 8>(__VA_ARGS__); return true;               \
-        case 16: FN<kCos, 1, 16>(__VA_ARGS__); return true;             \
-        case 32: FN<kCos, 1, 32>(__VA_ARGS__); return true;             \
-        case 64: FN<kCos, 1, 64>(__VA_ARGS__); return true;             \
-        case 128: FN<kCos, 1, 128>(__VA_ARGS__); return true;           \
-        case 256: FN<kCos, 1, 256>(__VA_ARGS__); return true;           \
-      }                                                                 \
-    } else if (metric == kCos && prec == 2) {                           \
-      switch (DM) {                                                     \
-        case 8: FN<kCos, 2, 8>(__VA_ARGS__); return true;               \
-        case 16: FN<kCos, 2, 16>(__VA_ARGS__); return true;             \
-        case 32: FN<kCos, 2, 32>(__VA_ARGS__); return true;             \
-        case 64: FN<kCos, 2, 64>(__VA_ARGS__); return true;             \
-        case 128: FN<kCos, 2, 128>(__VA_ARGS__); return true;           \
-        case 256: FN<kCos, 2, 256>(__VA_ARGS__); return true;           \
-      }                                                                 \
-    }                                                                   \
-    return false;                                                       \
+#define SILH_MFMA_DISPATCH(FN, ...)                 \
+  do {                                              \
+    if (prec == 0) {                                \
+      switch (DM) {                                 \
+        case 8: FN<0, 8>(__VA_ARGS__); return true;     \
+        case 16: FN<0, 16>(__VA_ARGS__); return true;   \
+        case 32: FN<0, 32>(__VA_ARGS__); return true;   \
+        case 64: FN<0, 64>(__VA_ARGS__); return true;   \
+        case 128: FN<0, 128>(__VA_ARGS__); return true; \
+      }                                             \
+    } else if (prec == 1) {                         \
+      switch (DM) {                                 \
+        case 8: FN<1, 8>(__VA_ARGS__); return true;     \
+        case 16: FN<1, 16>(__VA_ARGS__); return true;   \
+        case 32: FN<1, 32>(__VA_ARGS__); return true;   \
+        case 64: FN<1, 64>(__VA_ARGS__); return true;   \
+        case 128: FN<1, 128>(__VA_ARGS__); return true; \
+        case 256: FN<1, 256>(__VA_ARGS__); return true; \
+      }                                             \
+    }                                               \
+    return false;                                   \
   } while (0)
 
-bool launch_pack_mfma(hipStream_t st, int metric, int prec, int DM, const float* Y32, const float* aux,
-                      const float* w, const int32_t* gid_pk, const int32_t* sp_off, const int32_t* cnt, int k,
-                      float* mu, int S_pad, void* Ym, float* bnorm) {
-  SILH_MFMA_DISPATCH(launch_pack_one, st, Y32, aux, w, gid_pk, sp_off, cnt, k, mu, S_pad, Ym, bnorm);
+bool launch_pack_mfma(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
+                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym) {
+  SILH_MFMA_DISPATCH(launch_pack_one, st, Y32, w, sp_off, cnt, k, mu, S_pad, Ym);
 }
 
-bool launch_phase2_mfma(hipStream_t st, int metric, int prec, int DM, const P2Args& A, const float* mu,
-                        const void* Ym, const float* bnorm, int shape) {
-  SILH_MFMA_DISPATCH(launch_mfma_one, st, A, mu, Ym, bnorm, shape);
+bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const float* mu, const void* Ym,
+                        int shape) {
+  SILH_MFMA_DISPATCH(launch_mfma_one, st, A, mu, Ym, shape);
 }
 
-bool launch_phase2_mfma_jobs(hipStream_t st, int metric, int prec, int DM, int shape, const P2Job* jobs,
-                             const int2* items, int nitems) {
+bool launch_phase2_mfma_jobs(hipStream_t st, int prec, int DM, int shape, const P2Job* jobs, const int2* items,
+                             int nitems) {
   if (nitems <= 0) return true;
   SILH_MFMA_DISPATCH(launch_jobs_one, st, jobs, items, nitems, shape);
 }

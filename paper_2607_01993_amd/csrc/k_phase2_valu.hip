@@ -1,5 +1,5 @@
-// Phase 2 of Algorithm 1 on the vector ALUs (float32 distances; float64 sums
-// across tiles): for each element e and cluster C_j,
+// Phase 2 of Algorithm 1 on the vector ALUs (Euclidean, Manhattan, Canberra;
+// float32 distances, float64 sums across tiles): for each element e and cluster C_j,
 //   W_hat_{C_j}(e) = sum_{e' in F_j} w_{e'} d(e, e'),  w = 1/p,
 // then a_hat, b_hat, s_hat (Eq. 5) and a per-block float64 partial of the sum
 // of s_hat (for Eq. 9).
@@ -20,11 +20,8 @@ namespace silh {
 
 constexpr int kGroup = 32;  // samples summed in float32 before the float64 add
 
-// One coordinate of a float32 distance, and the final step.  Cosine runs as
-// half the squared distance of the unit vectors plus u (0.5 for a zero vector,
-// else 0): for unit x_hat, y_hat, 1 - x_hat.y_hat = |x_hat - y_hat|^2 / 2, and
-// the u terms give 1 whenever either vector is zero; this form does not
-// cancel for near-parallel pairs.
+// One coordinate of a float32 distance, and the final step (cosine has a
+// kernel of its own, k_phase2_cos.hip).
 // Canberra's guard (G) keeps a 0/0 coordinate at 0 (den >= FLT_MIN).  The
 // unguarded form (dist32 with G = false) takes the coordinates in pairs with
 // one reciprocal per pair,
@@ -42,21 +39,18 @@ __device__ __forceinline__ float dist32_step(float s, float xc, float yc) {
     const float den = G ? fmaxf(fabsf(xc) + fabsf(yc), FLT_MIN) : fabsf(xc) + fabsf(yc);
     return fmaf(fabsf(xc - yc), __builtin_amdgcn_rcpf(den), s);
   }
-  const float df = xc - yc;  // Euclidean, cosine
+  const float df = xc - yc;  // Euclidean
   return fmaf(df, df, s);
 }
 
 template <int M>
-__device__ __forceinline__ float dist32_final(float s, float ux, float uy) {
-  if (M == kEucl) return __builtin_amdgcn_sqrtf(s);
-  if (M == kCos) return __builtin_amdgcn_fmed3f(fmaf(0.5f, s, ux + uy), 0.0f, 2.0f);
-  return s;
+__device__ __forceinline__ float dist32_final(float s) {
+  return M == kEucl ? __builtin_amdgcn_sqrtf(s) : s;
 }
 
 // the element's row in registers
 template <int M, int DM, bool G = true>
-__device__ __forceinline__ float dist32(const float (&x)[DM], const float* __restrict__ y, float ux,
-                                      float uy) {
+__device__ __forceinline__ float dist32(const float (&x)[DM], const float* __restrict__ y) {
   float s = 0.f;
   if constexpr (M == kCanb && !G) {
     static_assert(DM % 2 == 0, "coordinate pairs");
@@ -70,17 +64,16 @@ __device__ __forceinline__ float dist32(const float (&x)[DM], const float* __res
   }
 #pragma unroll
   for (int c = 0; c < DM; ++c) s = dist32_step<M, G>(s, x[c], y[c]);
-  return dist32_final<M>(s, ux, uy);
+  return dist32_final<M>(s);
 }
 
 // the element's row in LDS, one column per lane (x[c * 64])
 template <int M, int DM>
-__device__ __forceinline__ float dist32_col(const float* __restrict__ x, const float* __restrict__ y, float ux,
-                                          float uy) {
+__device__ __forceinline__ float dist32_col(const float* __restrict__ x, const float* __restrict__ y) {
   float s = 0.f;
 #pragma unroll 32
   for (int c = 0; c < DM; ++c) s = dist32_step<M>(s, x[c * kWave], y[c]);
-  return dist32_final<M>(s, ux, uy);
+  return dist32_final<M>(s);
 }
 
 // PASS 0: the whole row.  Manhattan and Canberra are sums over coordinates,
@@ -97,7 +90,7 @@ __device__ __forceinline__ void p2_valu_block(
     const int32_t* __restrict__ cnt, const int32_t* __restrict__ csize, int k,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
     float* __restrict__ What, double* __restrict__ bpart, int c0, int ystride,
-    double* __restrict__ Wpart, const float* __restrict__ rn) {
+    double* __restrict__ Wpart) {
   static_assert(PASS == 0 || M == kManh || M == kCanb, "only sums over coordinates split");
   __shared__ double sh[kP2Rows / kWave];
   const int e = blk * kP2Rows + threadIdx.x;
@@ -108,13 +101,6 @@ __device__ __forceinline__ void p2_valu_block(
   const float* xr = X + (size_t)er * d + c0;
 #pragma unroll
   for (int c = 0; c < DM; ++c) x[c] = c0 + c < d ? xr[c] : 0.0f;
-  float ux = 0.f;
-  if (M == kCos) {  // unit vector: the row times its reciprocal norm (zero stays zero, u = 0.5)
-    const float rx = rn[er];
-    ux = rx > 0.f ? 0.f : 0.5f;
-#pragma unroll
-    for (int c = 0; c < DM; ++c) x[c] *= rx;
-  }
   const int own = (unsigned)labels[er] < (unsigned)k ? labels[er] : 0;  // labels are checked before; stay in bounds
 
   // Canberra: the pair form (dist32, G = false) when every element row of the
@@ -142,11 +128,10 @@ __device__ __forceinline__ void p2_valu_block(
         float acc = 0.f;
         for (int q = g0; q < g1; ++q) {
           const float* y = Y + (size_t)(s0 + q) * ystride + c0;
-          const float uy = M == kCos ? aux[s0 + q] : 0.f;
           if (M == kCanb && !G && aux[s0 + q] != 0.f)  // wave-uniform
-            acc = fmaf(w[s0 + q], dist32<M, DM, true>(x, y, ux, uy), acc);
+            acc = fmaf(w[s0 + q], dist32<M, DM, true>(x, y), acc);
           else
-            acc = fmaf(w[s0 + q], dist32<M, DM, G>(x, y, ux, uy), acc);
+            acc = fmaf(w[s0 + q], dist32<M, DM, G>(x, y), acc);
         }
         accd += (double)acc;
       }
@@ -192,9 +177,9 @@ __global__ __launch_bounds__(kP2Rows) void k_p2_valu(
     const int32_t* __restrict__ cnt, const int32_t* __restrict__ csize, int k,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
     float* __restrict__ What, double* __restrict__ bpart, int c0, int ystride,
-    double* __restrict__ Wpart, const float* __restrict__ rn) {
+    double* __restrict__ Wpart) {
   p2_valu_block<M, DM, PASS>(blockIdx.x, X, n, d, labels, Y, w, aux, sp_off, cnt, csize, k, a_out, b_out, s_out,
-                             What, bpart, c0, ystride, Wpart, rn);
+                             What, bpart, c0, ystride, Wpart);
 }
 
 // Several requests in one launch (one-pass shapes): workgroup i runs work
@@ -209,7 +194,7 @@ __global__ __launch_bounds__(kP2Rows) void k_p2_valu_jobs(const P2Job* __restric
   const int blk = ((citem_ptr)items)[2 * blockIdx.x + 1];
   const auto& J = ((cjob_ptr)jobs)[jx];
   p2_valu_block<M, DM, 0>(blk, J.X, J.n, J.d, J.labels, J.Y32, J.w, J.aux, J.sp_off, J.cnt, J.csize, J.k, J.a, J.b,
-                          J.s, J.What, J.bpart, 0, DM, nullptr, J.rn);
+                          J.s, J.What, J.bpart, 0, DM, nullptr);
 }
 
 // d > 128: one wave per block, each lane's row in LDS (column-major, 64 KB);
@@ -218,10 +203,10 @@ constexpr int kWideDM = 256;
 template <int M>
 __global__ __launch_bounds__(kWave) void k_p2_valu_wide(
     const float* __restrict__ X, int n, int d, const int32_t* __restrict__ labels,
-    const float* __restrict__ Y, const float* __restrict__ w, const float* __restrict__ aux,
+    const float* __restrict__ Y, const float* __restrict__ w,
     const int32_t* __restrict__ sp_off, const int32_t* __restrict__ cnt, const int32_t* __restrict__ csize, int k,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
-    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ rn) {
+    float* __restrict__ What, double* __restrict__ bpart) {
   __shared__ float xs[kWideDM * kWave];
   __shared__ double sh[1];
   const int e = blockIdx.x * kWave + threadIdx.x;
@@ -229,10 +214,7 @@ __global__ __launch_bounds__(kWave) void k_p2_valu_wide(
   const int er = valid ? e : n - 1;
   float* xl = xs + threadIdx.x;
   const float* xr = X + (size_t)er * d;
-  // cosine: the row times its reciprocal norm (zero stays zero, u = 0.5)
-  const float rx = M == kCos ? rn[er] : 1.0f;
-  for (int c = 0; c < kWideDM; ++c) xl[c * kWave] = c < d ? xr[c] * rx : 0.0f;
-  const float ux = (M == kCos && !(rx > 0.f)) ? 0.5f : 0.f;
+  for (int c = 0; c < kWideDM; ++c) xl[c * kWave] = c < d ? xr[c] : 0.0f;
   const int own = (unsigned)labels[er] < (unsigned)k ? labels[er] : 0;  // labels are checked before; stay in bounds
   double w_own = 0.0;
   double bmin = __builtin_inf();
@@ -245,8 +227,7 @@ __global__ __launch_bounds__(kWave) void k_p2_valu_wide(
       float acc = 0.f;
       for (int q = g0; q < g1; ++q) {
         const float* y = Y + (size_t)(s0 + q) * kWideDM;
-        const float uy = M == kCos ? aux[s0 + q] : 0.f;
-        acc = fmaf(w[s0 + q], dist32_col<M, kWideDM>(xl, y, ux, uy), acc);
+        acc = fmaf(w[s0 + q], dist32_col<M, kWideDM>(xl, y), acc);
       }
       accd += (double)acc;
     }
@@ -293,7 +274,7 @@ static void launch_one(hipStream_t st, const P2Args& A, int c0 = 0, int ystride 
   const int blocks = (int)ceil_div(A.n, kP2Rows);
   hipLaunchKernelGGL((k_p2_valu<M, DM, PASS>), dim3(blocks), dim3(kP2Rows), 0, st, A.X, A.n, A.d, A.labels,
                      A.Y, A.w, A.aux, A.sp_off, A.cnt, A.csize, A.k, A.a, A.b, A.s, A.What, A.bpart, c0,
-                     ystride, A.Wpart, A.rn);
+                     ystride, A.Wpart);
 }
 
 template <int M>
@@ -313,8 +294,7 @@ static bool launch_metric(hipStream_t st, int DM, const P2Args& A) {
         }
       }
       hipLaunchKernelGGL(k_p2_valu_wide<M>, dim3((int)ceil_div(A.n, kWave)), dim3(kWave), 0, st, A.X, A.n, A.d,
-                         A.labels, A.Y, A.w, A.aux, A.sp_off, A.cnt, A.csize, A.k, A.a, A.b, A.s, A.What,
-                         A.bpart, A.rn);
+                         A.labels, A.Y, A.w, A.sp_off, A.cnt, A.csize, A.k, A.a, A.b, A.s, A.What, A.bpart);
       return true;
     default: return false;
   }
@@ -334,13 +314,12 @@ static bool launch_jobs_metric(hipStream_t st, int DM, const P2Job* jobs, const 
   }
 }
 
-bool phase2_valu_jobs_ok(int metric, int DM) { return metric >= 0 && metric <= 3 && DM >= 8 && DM <= 128; }
+bool phase2_valu_jobs_ok(int metric, int DM) { return metric != kCos && DM >= 8 && DM <= 128; }
 
 bool launch_phase2_valu_jobs(hipStream_t st, int metric, int DM, const P2Job* jobs, const int2* items, int nitems) {
   if (nitems <= 0) return true;
   switch (metric) {
     case kEucl: return launch_jobs_metric<kEucl>(st, DM, jobs, items, nitems);
-    case kCos: return launch_jobs_metric<kCos>(st, DM, jobs, items, nitems);
     case kManh: return launch_jobs_metric<kManh>(st, DM, jobs, items, nitems);
     case kCanb: return launch_jobs_metric<kCanb>(st, DM, jobs, items, nitems);
     default: return false;
@@ -350,7 +329,6 @@ bool launch_phase2_valu_jobs(hipStream_t st, int metric, int DM, const P2Job* jo
 bool launch_phase2_valu(hipStream_t st, int metric, int DM, const P2Args& A) {
   switch (metric) {
     case kEucl: return launch_metric<kEucl>(st, DM, A);
-    case kCos: return launch_metric<kCos>(st, DM, A);
     case kManh: return launch_metric<kManh>(st, DM, A);
     case kCanb: return launch_metric<kCanb>(st, DM, A);
     default: return false;

@@ -84,22 +84,6 @@ __device__ __forceinline__ int find_sorted(const int32_t* __restrict__ a, int le
   return (lo < len && a[lo] == v) ? lo : -1;
 }
 
-__global__ __launch_bounds__(256) void k_rows_remap(const int32_t* __restrict__ gid_pk, int64_t S_pad,
-                                                    const int32_t* __restrict__ urows, int mu,
-                                                    int32_t* __restrict__ gid_sub) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S_pad) return;
-  const int g = gid_pk[s];
-  gid_sub[s] = g < 0 ? -1 : find_sorted(urows, mu, g);
-}
-
-void launch_rows_remap(hipStream_t st, const int32_t* gid_pk, int64_t S_pad, const int32_t* urows, int mu,
-                       int32_t* gid_sub) {
-  if (S_pad <= 0) return;
-  hipLaunchKernelGGL(k_rows_remap, dim3((unsigned)ceil_div(S_pad, 256)), dim3(256), 0, st, gid_pk, S_pad,
-                     urows, mu, gid_sub);
-}
-
 __global__ __launch_bounds__(kRowsBlock) void k_rows_expand(const int32_t* __restrict__ rows, int64_t m,
                                                             const int32_t* __restrict__ urows, int mu,
                                                             const float* __restrict__ au,

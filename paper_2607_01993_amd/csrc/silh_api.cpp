@@ -84,7 +84,8 @@ struct silh_ctx {
   const int32_t* labels = nullptr;
   int n = 0, d = 0, k = 0, DM = 0;
   bool mfma = false;  // Phase 2 on the matrix cores
-  int mprec = 0;      // MFMA operand type: 0 float32, 1 bf16, 2 fp8
+  bool cos = false;   // Phase 2 by the collapsed cosine sums
+  int mprec = 0;      // operand type: 0 float32, 1 bf16, 2 fp8
   int p2_rows = kP2Rows;
   int state = 0;  // 0 = indexed, 1 = sampled
 
@@ -120,8 +121,10 @@ struct silh_ctx {
   int64_t *f0_gid = nullptr, *gid_view = nullptr;
   double *f0X = nullptr, *W0 = nullptr, *partial = nullptr, *p_gid = nullptr;
   int32_t *s_off = nullptr, *sp_off = nullptr, *cnt = nullptr, *gid_pk = nullptr;
-  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr, *bnorm = nullptr;
+  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr;
   void* Ym = nullptr;
+  unsigned char* cstat = nullptr;  // cosine: the clusters' records
+  float* cself = nullptr;          // cosine, fp8: the clamp's share of the self pairs
   double *bpart = nullptr, *mean_d = nullptr;
 
   // pinned staging for the small host <-> device transfers (from a
@@ -587,12 +590,11 @@ silh_status create(const silh_params* prm, const float* X, const int32_t* labels
   c->d = prm->d;
   c->k = prm->k;
   c->DM = phase2_valu_dm(prm->d);
-  // float32 operands of d > 128 do not fit the MFMA kernel's registers: the
-  // vector-ALU kernel takes them
-  c->mfma = (prm->metric == SILH_EUCL || prm->metric == SILH_COS) &&
-            (prm->prec == SILH_BF16 || prm->prec == SILH_FP8 || (prm->prec == SILH_FP32 && c->DM <= 128));
-  c->mprec = prm->prec == SILH_BF16 ? 1 : (prm->prec == SILH_FP8 ? 2 : 0);
-  c->p2_rows = c->mfma ? phase2_mfma_rows(c->mprec, c->DM) : phase2_valu_rows(prm->metric, c->DM);
+  const int path = phase2_path(prm->metric, prm->prec, c->DM);
+  c->mfma = path == kPathMfma;
+  c->cos = path == kPathCos;
+  c->mprec = operand_type(prm->prec);
+  c->p2_rows = phase2_rows(path, prm->metric, c->mprec, c->DM);
   silh_status s = build_index(c);
   if (s != SILH_OK) {
     std::string msg = g_err;
@@ -650,9 +652,11 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     cv.add(&c->aux32, (size_t)c->S_pad).add(&c->Y32, (size_t)c->S_pad * c->DM);
     unsigned char* ym = nullptr;
     if (mfma_pack) {
-      cv.add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k)).add(&c->bnorm, (size_t)c->S_pad);
+      cv.add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k));
       cv.add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
     }
+    if (c->cos) cv.add(&c->cstat, (size_t)k * cos_stat_bytes(c->DM));
+    if (c->cos && prec == 2) cv.add(&c->cself, (size_t)n);
     CHK(cv.commit(c, c->alloc_sample));
     c->Ym = ym;
   }
@@ -665,6 +669,13 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
                 c->w32, c->aux32, c->Y32);
     CHK(L.done());
   }
+  if (c->cos) {
+    Launch L(c, K_CENTER);
+    launch_cos_stats(c->st, prec, c->DM, c->Y32, c->w32, c->aux32, c->sp_off, c->cnt, k, c->cstat);
+    if (c->cself)
+      launch_cos_self(c->st, c->DM, c->Y32, c->w32, c->gid_pk, c->sp_off, k, (int)c->S_pad, c->cstat, n, c->cself);
+    CHK(L.done());
+  }
   if (mfma_pack) {
     {
       Launch L(c, K_CENTER);
@@ -673,8 +684,7 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     }
     {
       Launch L(c, K_PACK_MFMA);
-      if (!launch_pack_mfma(c->st, c->prm.metric, prec, c->DM, c->Y32, c->aux32, c->w32, c->gid_pk, c->sp_off,
-                            c->cnt, k, c->mu, (int)c->S_pad, c->Ym, c->bnorm))
+      if (!launch_pack_mfma(c->st, prec, c->DM, c->Y32, c->w32, c->sp_off, c->cnt, k, c->mu, (int)c->S_pad, c->Ym))
         return fail(SILH_E_UNSUPPORTED, "no MFMA packing for metric %d, d=%d", c->prm.metric, c->d);
       CHK(L.done());
     }
@@ -691,8 +701,10 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   c->ibase = c->dbase = nullptr;
   c->dkeep = nullptr;
   c->f0X = c->W0 = c->partial = nullptr;
-  c->w32 = c->aux32 = c->Y32 = c->mu = c->bnorm = nullptr;
+  c->w32 = c->aux32 = c->Y32 = c->mu = nullptr;
   c->Ym = nullptr;
+  c->cstat = nullptr;
+  c->cself = nullptr;
   const int n = c->n, k = c->k;
   const int nb = (int)ceil_div(n, c->p2_rows);
   Carve cv;
@@ -860,15 +872,24 @@ int size_bucket(int64_t S_pad) {
   return b;
 }
 
+// cosine has one shape: it is recorded under the same key, nothing is timed
+void note_cos_shape(const silh_ctx* c) {
+  if (g_tune_mode.load() != 1 || c->prm.prec == SILH_FP32_VALU || (c->mprec == 0 && c->DM > 128)) return;
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  g_tune.emplace(std::array<int, 4>{SILH_COS, c->mprec, c->DM, size_bucket(c->S_pad)}, 1);
+}
+
 int pick_pb(silh_ctx* c, const P2Args& A) {
+  if (c->cos) note_cos_shape(c);
+  if (!c->mfma) return 1;
   int ids[3];
   const int m = mfma_shapes(c->mprec, c->DM, ids);
   const int mode = g_tune_mode.load();
-  if (mode == 0 || m == 1) return m == 1 ? 1 : pb_builtin(c->prm.metric, c->mprec, c->DM);
+  if (mode == 0 || m == 1) return m == 1 ? 1 : mfma_pb_default(c->mprec, c->DM);
   if (mode >= 2) {  // a fixed shape where valid, else the built-in one
     for (int i = 0; i < m; ++i)
       if (ids[i] == mode - 1) return ids[i];
-    return pb_builtin(c->prm.metric, c->mprec, c->DM);
+    return mfma_pb_default(c->mprec, c->DM);
   }
   const std::array<int, 4> key{c->prm.metric, c->mprec, c->DM, size_bucket(c->S_pad)};
   {
@@ -886,7 +907,7 @@ int pick_pb(silh_ctx* c, const P2Args& A) {
   if (ok) {
     ok = hipEventRecord(e[0], c->st) == hipSuccess;
     for (int r = 0; r < 2 * m && ok; ++r)
-      ok = launch_phase2_mfma(c->st, c->prm.metric, c->mprec, c->DM, A, c->mu, c->Ym, c->bnorm, ids[r % m]) &&
+      ok = launch_phase2_mfma(c->st, c->mprec, c->DM, A, c->mu, c->Ym, ids[r % m]) &&
            hipEventRecord(e[r + 1], c->st) == hipSuccess;
     ok = ok && hipEventSynchronize(e[2 * m]) == hipSuccess;
     for (int r = 0; r < 2 * m && ok; ++r) {
@@ -899,7 +920,7 @@ int pick_pb(silh_ctx* c, const P2Args& A) {
     if (ev) (void)hipEventDestroy(ev);
   if (!ok) {
     (void)hipGetLastError();
-    return pb_builtin(c->prm.metric, c->mprec, c->DM);
+    return mfma_pb_default(c->mprec, c->DM);
   }
   int choice = ids[0];
   float tb = best_t[0];
@@ -914,8 +935,9 @@ int pick_pb(silh_ctx* c, const P2Args& A) {
 }
 
 bool launch_p2(silh_ctx* c, const P2Args& A, int pb) {
+  if (c->cos) return launch_phase2_cos(c->st, c->mprec, c->DM, A);
   if (!c->mfma) return launch_phase2_valu(c->st, c->prm.metric, c->DM, A);
-  return launch_phase2_mfma(c->st, c->prm.metric, c->mprec, c->DM, A, c->mu, c->Ym, c->bnorm, pb);
+  return launch_phase2_mfma(c->st, c->mprec, c->DM, A, c->mu, c->Ym, pb);
 }
 
 silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, double* mean_host) {
@@ -927,7 +949,6 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   A.Y = c->Y32;
   A.w = c->w32;
   A.aux = c->aux32;
-  A.gid_pk = c->gid_pk;
   A.sp_off = c->sp_off;
   A.cnt = c->cnt;
   A.csize = c->csize;
@@ -938,6 +959,8 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   A.What = What;
   A.bpart = c->bpart;
   A.rn = c->rn;
+  A.cstat = c->cstat;
+  A.cself = c->cself;
   free_list(c, c->alloc_p2);
   if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
@@ -945,7 +968,7 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
     CHK(cv.commit(c, c->alloc_p2));
   }
   {
-    const int pb = c->mfma ? pick_pb(c, A) : 0;  // (tuning runs stay outside the timed launch)
+    const int pb = pick_pb(c, A);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
     const bool ok = launch_p2(c, A, pb);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
@@ -965,8 +988,7 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
 
 // Phase 2 for the entries of rows[0..m) (duplicates allowed): the distinct
 // rows are gathered into a contiguous block and run through the same Phase-2
-// kernels, with the sample's ids renumbered into that block so that the
-// self-pair test still finds each element's own column.
+// kernels.
 silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, float* b, float* s,
                         double* mean_host) {
   if (!rows) return fail(SILH_E_ARG, "rows is NULL");
@@ -974,7 +996,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   free_list(c, c->alloc_rows);
   const int n = c->n, d = c->d;
   const int64_t cap = m < n ? m : n;  // distinct rows
-  int32_t *mark = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr, *gsub = nullptr;
+  int32_t *mark = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr;
   int* bad = nullptr;
   float *Xs = nullptr, *au = nullptr, *bu = nullptr, *su = nullptr, *rnu = nullptr;
   double *bpu = nullptr, *bpm = nullptr, *mean_d = nullptr;
@@ -983,7 +1005,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     Carve cv;
     cv.add(&mark, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
     cv.add(&urows, (size_t)cap).add(&bad, 1).add(&Xs, (size_t)cap * d).add(&ls, (size_t)cap);
-    cv.add(&gsub, (size_t)c->S_pad).add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
+    cv.add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
     cv.add(&bpu, (size_t)ceil_div(cap, c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
     if (c->rn) cv.add(&rnu, (size_t)cap);
     CHK(cv.commit(c, c->alloc_rows));
@@ -1001,7 +1023,6 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   const int mu = mu_h;
   launch_rows_compact(c->st, mark, pos, n, urows);
   launch_rows_gather(c->st, c->X, c->labels, d, urows, mu, Xs, ls);
-  launch_rows_remap(c->st, c->gid_pk, c->S_pad, urows, mu, gsub);
   if (rnu) launch_rnorm(c->st, Xs, mu, d, rnu);  // the same factors as for the rows of X
   HIPCHK(hipGetLastError());
   P2Args A;
@@ -1012,7 +1033,6 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   A.Y = c->Y32;
   A.w = c->w32;
   A.aux = c->aux32;
-  A.gid_pk = gsub;
   A.sp_off = c->sp_off;
   A.cnt = c->cnt;
   A.csize = c->csize;
@@ -1023,13 +1043,16 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   A.What = nullptr;
   A.bpart = bpu;
   A.rn = rnu;
+  A.cstat = c->cstat;
+  A.cself = c->cself;
+  A.egid = urows;
   if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
     cv.add(&A.Wpart, (size_t)(mu > 0 ? mu : 1) * c->k);
     CHK(cv.commit(c, c->alloc_rows));
   }
   {
-    const int pb = c->mfma ? pick_pb(c, A) : 0;  // (tuning runs stay outside the timed launch)
+    const int pb = pick_pb(c, A);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
     const bool ok = launch_p2(c, A, pb);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
@@ -1057,11 +1080,21 @@ silh_status validate_exact_params(const silh_params* prm, const float* X, const 
   return check_params(prm, X, labels, true, &t);
 }
 int dm_for(int d) { return phase2_valu_dm(d); }
+int phase2_path(int metric, int prec, int DM) {
+  if (metric == SILH_COS) return kPathCos;
+  if (metric == SILH_EUCL && (prec == SILH_BF16 || (prec == SILH_FP32 && DM <= 128))) return kPathMfma;
+  return kPathValu;
+}
+int operand_type(int prec) { return prec == SILH_BF16 ? 1 : (prec == SILH_FP8 ? 2 : 0); }
+int phase2_rows(int path, int metric, int mprec, int DM) {
+  if (path == kPathCos) return kCosRows;
+  return path == kPathMfma ? phase2_mfma_rows(mprec, DM) : phase2_valu_rows(metric, DM);
+}
 silh_status set_error(silh_status st, const char* msg) { return fail(st, "%s", msg); }
 int64_t sample_rows(const silh_ctx* c) { return c && c->state == 1 ? c->S_pad : 0; }
 
 int tuned_shape(silh_ctx* c) {
-  if (!c || c->state != 1 || !c->mfma) return 1;
+  if (!c || c->state != 1) return 1;
   P2Args A;
   A.X = c->X;
   A.n = c->n;
@@ -1070,7 +1103,6 @@ int tuned_shape(silh_ctx* c) {
   A.Y = c->Y32;
   A.w = c->w32;
   A.aux = c->aux32;
-  A.gid_pk = c->gid_pk;
   A.sp_off = c->sp_off;
   A.cnt = c->cnt;
   A.csize = c->csize;
@@ -1078,29 +1110,28 @@ int tuned_shape(silh_ctx* c) {
   A.a = A.b = A.s = A.What = nullptr;
   A.bpart = c->bpart;
   A.rn = c->rn;
+  A.cstat = c->cstat;
+  A.cself = c->cself;
   return pick_pb(c, A);
 }
 
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   if (!c || c->state != 1) return false;
   const bool batch = c->mfma || phase2_valu_jobs_ok(c->prm.metric, c->DM);
-  if (!batch) return false;
+  if (!batch || c->cos) return false;
   P2Job J{};
   J.X = c->X;
   J.labels = c->labels;
   J.Ym = c->Ym;
   J.w = c->w32;
-  J.gid_pk = c->gid_pk;
   J.sp_off = c->sp_off;
   J.cnt = c->cnt;
   J.csize = c->csize;
   J.mu = c->mu;
   J.a = J.b = J.s = J.What = nullptr;
   J.bpart = c->bpart;
-  J.bnorm = c->bnorm;
   J.Y32 = c->Y32;
   J.aux = c->aux32;
-  J.rn = c->rn;
   J.n = c->n;
   J.d = c->d;
   J.k = c->k;
@@ -1119,7 +1150,7 @@ bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
 }
 
 bool launch_phase2_class(hipStream_t st, const P2Class& cls, const P2Job* jobs, const int2* items, int nitems) {
-  if (cls.mfma) return launch_phase2_mfma_jobs(st, cls.metric, cls.prec, cls.DM, cls.pb, jobs, items, nitems);
+  if (cls.mfma) return launch_phase2_mfma_jobs(st, cls.prec, cls.DM, cls.pb, jobs, items, nitems);
   return launch_phase2_valu_jobs(st, cls.metric, cls.DM, jobs, items, nitems);
 }
 
@@ -1133,11 +1164,6 @@ silh_status phase2_job_mean(silh_ctx* c, double* mean) {
   CHK(fetch(c, {{&c->mean_h, c->mean_d, sizeof(double)}}));
   *mean = c->mean_h;
   return SILH_OK;
-}
-
-int pb_builtin(int metric, int prec, int DM) {
-  if (metric == SILH_COS && prec == 1 && DM == 32) return 2;
-  return mfma_pb_default(prec, DM);
 }
 
 }  // namespace silh

@@ -44,8 +44,10 @@ struct Branch {
   double* dkeep = nullptr;
   int64_t* gid_view = nullptr;
   int32_t* gid_pk = nullptr;
-  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr, *bnorm = nullptr;
+  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr;
   void* Ym = nullptr;
+  unsigned char* cstat = nullptr;  // cosine: the clusters' records
+  float* cself = nullptr;          // cosine, fp8: the clamp's share of the self pairs
   double *bpart = nullptr, *Wpart = nullptr;
 };
 
@@ -62,7 +64,7 @@ struct silh_graph {
   std::vector<int32_t> shape;    // Phase-2 block shape captured for each clustering
   std::vector<int64_t> probe_S;  // padded sample size of the request the shape was tuned on
   int K = 0, n = 0, d = 0, DM = 0, KP = 0, mprec = 0, p2_rows = 0, chunk = 0, kmax = 0;
-  bool mfma = false;
+  bool mfma = false, cos = false;
   int64_t S_cap = 0, F0_cap = 0, items_cap = 0, part_cap = 0, dist_cap = 0;
   std::vector<Branch> br;
   std::vector<void*> allocs;
@@ -144,9 +146,11 @@ bool alloc_branch(silh_graph* g, Branch& b) {
             take(g, b.bpart, ceil_div(n, g->p2_rows));
   if (ok && g->mfma) {
     unsigned char* ym = nullptr;
-    ok = take(g, b.mu, mfma_mu_floats(g->mprec, g->DM, k)) && take(g, b.bnorm, S) && take(g, ym, S * (size_t)mfma_row_bytes(g->mprec, g->DM));
+    ok = take(g, b.mu, mfma_mu_floats(g->mprec, g->DM, k)) && take(g, ym, S * (size_t)mfma_row_bytes(g->mprec, g->DM));
     b.Ym = ym;
   }
+  if (ok && g->cos) ok = take(g, b.cstat, k * (int64_t)cos_stat_bytes(g->DM));
+  if (ok && g->cos && g->mprec == 2) ok = take(g, b.cself, n);
   if (ok && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
   if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
   return ok;
@@ -210,7 +214,6 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
   A.Y = b.Y32;
   A.w = b.w32;
   A.aux = b.aux32;
-  A.gid_pk = b.gid_pk;
   A.sp_off = b.sp_off;
   A.cnt = b.cnt;
   A.csize = b.csize;
@@ -220,13 +223,16 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
   A.bpart = b.bpart;
   A.Wpart = b.Wpart;
   A.rn = g->rn;
-  if (g->mfma) {
+  A.cstat = b.cstat;
+  A.cself = b.cself;
+  if (g->cos) {
+    launch_cos_stats(st, g->mprec, DM, b.Y32, b.w32, b.aux32, b.sp_off, b.cnt, k, b.cstat);
+    if (b.cself) launch_cos_self(st, DM, b.Y32, b.w32, b.gid_pk, b.sp_off, k, (int)g->S_cap, b.cstat, n, b.cself);
+    if (!launch_phase2_cos(st, g->mprec, DM, A)) return false;
+  } else if (g->mfma) {
     launch_center(st, b.Y32, DM, g->KP, b.sp_off, b.cnt, k, b.mu);
-    if (!launch_pack_mfma(st, metric, g->mprec, DM, b.Y32, b.aux32, b.w32, b.gid_pk, b.sp_off, b.cnt, k, b.mu,
-                          (int)g->S_cap, b.Ym, b.bnorm))
-      return false;
-    if (!launch_phase2_mfma(st, metric, g->mprec, DM, A, b.mu, b.Ym, b.bnorm, g->shape[(size_t)i]))
-      return false;
+    if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym)) return false;
+    if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
     return false;
   }
@@ -278,11 +284,12 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
   g->n = (int)base->n;
   g->d = base->d;
   g->DM = dm_for(base->d);
-  g->mfma = (base->metric == SILH_EUCL || base->metric == SILH_COS) &&
-            (base->prec == SILH_BF16 || base->prec == SILH_FP8 || (base->prec == SILH_FP32 && g->DM <= 128));
-  g->mprec = base->prec == SILH_BF16 ? 1 : (base->prec == SILH_FP8 ? 2 : 0);
+  const int path = phase2_path(base->metric, base->prec, g->DM);
+  g->mfma = path == kPathMfma;
+  g->cos = path == kPathCos;
+  g->mprec = operand_type(base->prec);
   g->KP = g->mfma ? mfma_kp(g->mprec, g->DM) : 0;
-  g->p2_rows = g->mfma ? phase2_mfma_rows(g->mprec, g->DM) : phase2_valu_rows(base->metric, g->DM);
+  g->p2_rows = phase2_rows(path, base->metric, g->mprec, g->DM);
   g->chunk = g->DM > 128 ? kWChunkWide : kWChunk;
   double kt = 0.0;
   for (int32_t i = 0; i < K; ++i) {
@@ -328,7 +335,7 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
   // labels, ...) leaves the built-in shape
   g->shape.assign((size_t)K, 1);
   g->probe_S.assign((size_t)K, 0);
-  if (g->mfma) {
+  if (g->mfma || g->cos) {
     std::map<int, std::pair<int32_t, int64_t>> group;
     for (int32_t i = 0; i < K; ++i) {
       const double kt = (double)ks[i] * (double)ts[(size_t)i];
@@ -338,7 +345,7 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
         silh_params prm = *base;
         prm.k = ks[i];
         silh_ctx* c = nullptr;
-        std::pair<int32_t, int64_t> pick{pb_builtin(base->metric, g->mprec, g->DM), 0};
+        std::pair<int32_t, int64_t> pick{g->mfma ? mfma_pb_default(g->mprec, g->DM) : 1, 0};
         if (silh_sample_init(&prm, X, labels + (size_t)i * (size_t)g->n, stream, &c) == SILH_OK &&
             silh_pps_sample(c, nullptr, nullptr) == SILH_OK) {
           pick = {tuned_shape(c), sample_rows(c)};

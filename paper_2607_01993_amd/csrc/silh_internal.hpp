@@ -97,8 +97,7 @@ struct P2Args {
   const int32_t* labels;
   const float* Y;      // [S_pad][DM]
   const float* w;      // [S_pad]
-  const float* aux;    // [S_pad] cosine: 0.5 for a zero sample vector, else 0
-  const int32_t* gid_pk;  // [S_pad] element id of each packed sample row, -1 for padding
+  const float* aux;    // [S_pad] Canberra: the row's form flag (launch_pack)
   const int32_t* sp_off;  // [k+1] padded sample offsets
   const int32_t* cnt;     // [k] |F_j|
   const int32_t* csize;   // [k] |C_j|
@@ -110,6 +109,9 @@ struct P2Args {
   double* bpart;        // [ceil(n / rows per partial)]
   double* Wpart = nullptr;  // [n][k] float64, for the split vector-ALU pass (d > 128)
   const float* rn = nullptr;  // [n] cosine: reciprocal row norms (launch_rnorm) of X's rows
+  const unsigned char* cstat = nullptr;  // cosine: the clusters' records (launch_cos_stats)
+  const float* cself = nullptr;    // cosine, fp8: launch_cos_self's values by element id
+  const int32_t* egid = nullptr;   // element ids of the rows of X (null: row i is element i)
 };
 // One request's Phase-2 launch as a work source of a multi-request launch
 // (the arguments of P2Args and of the matrix-core operands, in device memory).
@@ -118,7 +120,6 @@ struct P2Job {
   const int32_t* labels;
   const void* Ym;        // matrix-core operands (null on the vector-ALU path)
   const float* w;
-  const int32_t* gid_pk;
   const int32_t* sp_off;
   const int32_t* cnt;
   const int32_t* csize;
@@ -128,10 +129,8 @@ struct P2Job {
   float* s;
   float* What;
   double* bpart;
-  const float* bnorm;
   const float* Y32;
   const float* aux;
-  const float* rn;
   int n, d, k, pad0;
 };
 // returns false if (metric, d) has no VALU kernel
@@ -142,8 +141,8 @@ bool launch_phase2_valu(hipStream_t st, int metric, int DM, const P2Args& a);
 // are phase2_valu_rows / phase2_mfma_rows * pb elements.
 bool launch_phase2_valu_jobs(hipStream_t st, int metric, int DM, const P2Job* jobs, const int2* items, int nitems);
 bool phase2_valu_jobs_ok(int metric, int DM);
-bool launch_phase2_mfma_jobs(hipStream_t st, int metric, int prec, int DM, int shape, const P2Job* jobs,
-                             const int2* items, int nitems);
+bool launch_phase2_mfma_jobs(hipStream_t st, int prec, int DM, int shape, const P2Job* jobs, const int2* items,
+                             int nitems);
 int phase2_valu_dm(int d);   // padded dimension used by the VALU kernel, 0 if unsupported
 // elements per block (and per partial of the mean) of the VALU kernel
 int phase2_valu_rows(int metric, int DM);
@@ -151,37 +150,55 @@ int phase2_valu_rows(int metric, int DM);
 // P2Args::Wpart ([n][k] float64 scratch)
 bool phase2_valu_split(int metric, int DM);
 
-// MFMA path (Euclidean and cosine with float32 or bf16 operands; cosine with
-// fp8 operands).  prec: 0 float32, 1 bf16, 2 fp8.
+// MFMA path (Euclidean).  prec: 0 float32, 1 bf16 operands.
 int mfma_kp(int prec, int DM);   // contraction length of a packed row
 int mfma_row_bytes(int prec, int DM);  // bytes per packed row (operands, LDS-path tail)
 // mu: [k][KP] centres, zero beyond DM, then [k] squared radii of the
-// clusters' packed samples (Euclidean; the largest |y~_q|^2), mfma_mu_floats
+// clusters' packed samples (the largest |y~_q|^2), mfma_mu_floats
 // floats in all
 size_t mfma_mu_floats(int prec, int DM, int k);
 void launch_center(hipStream_t st, const float* Y32, int DM, int KP, const int32_t* sp_off,
                    const int32_t* cnt, int k, float* mu);
-// packs rows [0, min(S_pad, sp_off[k])) (w: weights, gid_pk: element ids of
-// the packed rows, copied into the rows' tails on the LDS path)
-bool launch_pack_mfma(hipStream_t st, int metric, int prec, int DM, const float* Y32, const float* aux,
-                      const float* w, const int32_t* gid_pk, const int32_t* sp_off, const int32_t* cnt, int k,
-                      float* mu, int S_pad, void* Ym, float* bnorm);
+// packs rows [0, min(S_pad, sp_off[k])) (w: weights of the packed rows,
+// copied into the rows' tails on the LDS path)
+bool launch_pack_mfma(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
+                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym);
 // elements per float64 partial of the sum of s_hat written by the MFMA
 // Phase-2 kernel (independent of its block shape)
 int phase2_mfma_rows(int prec, int DM);
 // Block shapes (ids): 1 one 32-element block per wave, 2 two blocks per wave
-// (d <= 64, not fp8), 3 one block with the other number of tiles per LDS
+// (d <= 64), 3 one block with the other number of tiles per LDS
 // stage (the LDS-staged shapes only).  The default choice of blocks per wave:
 int mfma_pb_default(int prec, int DM);
-// the built-in shape with the metric taken into account (cosine bf16 at
-// d = 32 measures faster with two blocks per wave, Euclidean with one)
-int pb_builtin(int metric, int prec, int DM);
 int mfma_pb_max(int prec, int DM);
 bool mfma_lds_path(int prec, int DM);
 // the shape ids valid for (prec, DM) into ids[0..2]; returns their count
 int mfma_shapes(int prec, int DM, int* ids);
-bool launch_phase2_mfma(hipStream_t st, int metric, int prec, int DM, const P2Args& A, const float* mu,
-                        const void* Ym, const float* bnorm, int shape);
+bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const float* mu, const void* Ym,
+                        int shape);
+
+// Cosine (every operand type; prec as above, float32 arithmetic for the
+// vector-ALU precision too): the clusters' samples collapsed into one record
+// each (k records of cos_stat_bytes), then one pass over the elements.
+constexpr int kCosRows = 64;  // elements per block (and per partial of the mean)
+size_t cos_stat_bytes(int DM);
+void launch_cos_stats(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const float* aux,
+                      const int32_t* sp_off, const int32_t* cnt, int k, unsigned char* stat);
+// fp8 only: self [n] (zeros, then the sampled elements' values); rows at or
+// past `cap` of the packed sample are not read
+void launch_cos_self(hipStream_t st, int DM, const float* Y32, const float* w, const int32_t* gid_pk,
+                     const int32_t* sp_off, int k, int cap, const unsigned char* stat, int n, float* self);
+bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A);
+
+// ---- Phase-2 path of a request ------------------------------------------------
+// cosine: the collapsed sums; Euclidean with matrix-core operands: the MFMA
+// kernel (float32 operands of d > 128 do not fit its registers); else the
+// vector ALUs
+enum P2Path { kPathValu = 0, kPathMfma = 1, kPathCos = 2 };
+int phase2_path(int metric, int prec, int DM);
+// operand type of the matrix-core and cosine kernels: 0 float32, 1 bf16, 2 fp8
+int operand_type(int prec);
+int phase2_rows(int path, int metric, int mprec, int DM);
 
 // ---- global mean -------------------------------------------------------------
 void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out);
@@ -271,9 +288,6 @@ void launch_rows_compact(hipStream_t st, const int32_t* mark, const int32_t* pos
 // Xs[i] = X[urows[i]], ls[i] = labels[urows[i]]
 void launch_rows_gather(hipStream_t st, const float* X, const int32_t* labels, int d,
                         const int32_t* urows, int mu, float* Xs, int32_t* ls);
-// gid_sub[s] = index of gid_pk[s] in urows, or -1 when it is not there
-void launch_rows_remap(hipStream_t st, const int32_t* gid_pk, int64_t S_pad, const int32_t* urows,
-                       int mu, int32_t* gid_sub);
 // a/b/s[i] = a/b/s_u[index of rows[i] in urows]; bpart[block] = float64 sum
 // of the block's s (blocks of kRowsBlock entries)
 constexpr int kRowsBlock = 256;

@@ -35,22 +35,30 @@ constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
+// the cosine path's cluster records, at their largest (k = 4096, d = 256);
+// an array of their own, so that they take nothing from the capacity above
+constexpr size_t kRecordBytes = (size_t)4096 * (64 + 256 * 12);
+static __device__ __align__(256) unsigned char records[kRecordBytes];
+
 std::mutex g_mu[kMaxDevices];
 void* g_ptr[kMaxDevices] = {};
+void* g_rec[kMaxDevices] = {};
 
 // The device address of this device's copy of `scratch`, looked up once per
 // device (with that device current) and kept.
-silh_status scratch_for(int dev, unsigned char** out) {
+silh_status scratch_for(int dev, unsigned char** out, unsigned char** rec) {
   if (!g_ptr[dev]) {
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || p == nullptr) {
+    void *p = nullptr, *r = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || p == nullptr ||
+        hipGetSymbolAddress(&r, HIP_SYMBOL(records)) != hipSuccess || r == nullptr) {
       (void)hipGetLastError();
       return set_error(SILH_E_HIP, "hipGetSymbolAddress of the static scratch array failed");
     }
     g_ptr[dev] = p;
+    g_rec[dev] = r;
   }
   *out = (unsigned char*)g_ptr[dev];
+  *rec = (unsigned char*)g_rec[dev];
   return SILH_OK;
 }
 
@@ -77,10 +85,12 @@ struct Bufs {
   double* p_gid = nullptr;
   int64_t* gid_view = nullptr;
   int32_t* gid_pk = nullptr;
-  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr, *bnorm = nullptr;
+  float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr;
   unsigned char* Ym = nullptr;
   double *bpart = nullptr, *Wpart = nullptr, *mean = nullptr;
   float* rn = nullptr;
+  unsigned char* cstat = nullptr;
+  float* cself = nullptr;
 };
 
 struct Shape {
@@ -97,10 +107,11 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
   sl.add(&b.p_gid, n).add(&b.gid_view, s.S_cap).add(&b.gid_pk, s.S_cap).add(&b.w32, s.S_cap);
   sl.add(&b.aux32, s.S_cap).add(&b.Y32, s.S_cap * s.DM).add(&b.bpart, ceil_div(n, s.p2_rows));
   if (s.mfma) {
-    sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.bnorm, s.S_cap).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
+    sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
   }
   if (s.split) sl.add(&b.Wpart, n * k);
   if (s.cos) sl.add(&b.rn, n);
+  if (s.cos && s.mprec == 2) sl.add(&b.cself, n);
 }
 
 }  // namespace
@@ -117,13 +128,13 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   sh.d = prm->d;
   sh.k = prm->k;
   sh.DM = dm_for(prm->d);
-  sh.mfma = (prm->metric == SILH_EUCL || prm->metric == SILH_COS) &&
-            (prm->prec == SILH_BF16 || prm->prec == SILH_FP8 || (prm->prec == SILH_FP32 && sh.DM <= 128));
-  sh.mprec = prm->prec == SILH_BF16 ? 1 : (prm->prec == SILH_FP8 ? 2 : 0);
+  const int path = phase2_path(prm->metric, prm->prec, sh.DM);
+  sh.mfma = path == kPathMfma;
+  sh.mprec = operand_type(prm->prec);
   sh.KP = sh.mfma ? mfma_kp(sh.mprec, sh.DM) : 0;
-  sh.p2_rows = sh.mfma ? phase2_mfma_rows(sh.mprec, sh.DM) : phase2_valu_rows(prm->metric, sh.DM);
+  sh.p2_rows = phase2_rows(path, prm->metric, sh.mprec, sh.DM);
   sh.split = !sh.mfma && phase2_valu_split(prm->metric, sh.DM);
-  sh.cos = prm->metric == SILH_COS;
+  sh.cos = path == kPathCos;
   sh.seg = sort_seg(sh.n, sh.k);
   sh.units = (int)ceil_div(sh.n, sh.seg);
   sh.S_cap = (int64_t)sh.n + (int64_t)kSamplePad * sh.k;  // every element, each cluster padded
@@ -145,15 +156,18 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
     return set_error(SILH_E_HIP, "no current HIP device");
   }
   std::lock_guard<std::mutex> lk(g_mu[dev]);
-  unsigned char* base = nullptr;
+  unsigned char *base = nullptr, *rec = nullptr;
   {
-    const silh_status v = scratch_for(dev, &base);
+    const silh_status v = scratch_for(dev, &base, &rec);
     if (v != SILH_OK) return v;
   }
   Slices sl;
   sl.base = base;
   Bufs B;
   layout(sh, sl, B);
+  if (sh.cos) B.cstat = rec;
+  if (sh.cos && (size_t)sh.k * cos_stat_bytes(sh.DM) > kRecordBytes)
+    return set_error(SILH_E_ARG, "too many clusters for the static record array");
 
   const hipStream_t st = (hipStream_t)stream;
   const int n = sh.n, k = sh.k, d = sh.d, DM = sh.DM;
@@ -183,7 +197,6 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   A.Y = B.Y32;
   A.w = B.w32;
   A.aux = B.aux32;
-  A.gid_pk = B.gid_pk;
   A.sp_off = B.sp_off;
   A.cnt = B.cnt;
   A.csize = B.csize;
@@ -195,12 +208,17 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   A.bpart = B.bpart;
   A.Wpart = B.Wpart;
   A.rn = B.rn;
+  A.cstat = B.cstat;
+  A.cself = B.cself;
   bool ok = true;
-  if (sh.mfma) {
+  if (sh.cos) {
+    launch_cos_stats(st, sh.mprec, DM, B.Y32, B.w32, B.aux32, B.sp_off, B.cnt, k, B.cstat);
+    if (B.cself) launch_cos_self(st, DM, B.Y32, B.w32, B.gid_pk, B.sp_off, k, (int)sh.S_cap, B.cstat, n, B.cself);
+    ok = launch_phase2_cos(st, sh.mprec, DM, A);
+  } else if (sh.mfma) {
     launch_center(st, B.Y32, DM, sh.KP, B.sp_off, B.cnt, k, B.mu);
-    ok = launch_pack_mfma(st, metric, sh.mprec, DM, B.Y32, B.aux32, B.w32, B.gid_pk, B.sp_off, B.cnt, k, B.mu,
-                          (int)sh.S_cap, B.Ym, B.bnorm) &&
-         launch_phase2_mfma(st, metric, sh.mprec, DM, A, B.mu, B.Ym, B.bnorm, pb_builtin(metric, sh.mprec, DM));
+    ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym) &&
+         launch_phase2_mfma(st, sh.mprec, DM, A, B.mu, B.Ym, mfma_pb_default(sh.mprec, DM));
   } else {
     ok = launch_phase2_valu(st, metric, DM, A);
   }

@@ -223,9 +223,8 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
   const uint64_t n = (uint64_t)ds.n;
   uint64_t S = 2ull * (uint64_t)r.k * (uint64_t)r.t + 32ull * (uint64_t)r.k;
   if (S > n + 32ull * (uint64_t)r.k) S = n + 32ull * (uint64_t)r.k;
-  const bool mfma = (r.metric == SILH_EUCL || r.metric == SILH_COS) && r.prec != SILH_FP32_VALU;
-  const int mprec = r.prec == SILH_BF16 ? 1 : (r.prec == SILH_FP8 ? 2 : 0);
-  const uint64_t kp = mfma ? (uint64_t)silh::mfma_row_bytes(mprec, DM) : 0;
+  const bool mfma = silh::phase2_path(r.metric, r.prec, DM) == silh::kPathMfma;
+  const uint64_t kp = mfma ? (uint64_t)silh::mfma_row_bytes(silh::operand_type(r.prec), DM) : 0;
   const uint64_t row = (uint64_t)DM * 4 + kp + 24;
   const uint64_t m = r.m > 0 ? (uint64_t)r.m : 0;  // row draws: ids, gathered rows, outputs
   // d > 128 Manhattan / Canberra: float64 partial sums per element and cluster
@@ -235,8 +234,11 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
   const uint64_t kept = r.sampler == SILH_PPS
                             ? 8 * (uint64_t)silh::dist_capacity((int64_t)n, std::log(5.0 * r.k / r.delta))
                             : 0;
-  // cosine: one float32 reciprocal norm per element
-  const uint64_t rn = r.metric == SILH_COS ? 4 * n : 0;
+  // cosine: one float32 reciprocal norm per element (fp8: one more value) and
+  // a record per cluster
+  const uint64_t rn = r.metric == SILH_COS
+                          ? (r.prec == SILH_FP8 ? 8 : 4) * n + (uint64_t)r.k * silh::cos_stat_bytes(DM)
+                          : 0;
   return 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
 }
 
