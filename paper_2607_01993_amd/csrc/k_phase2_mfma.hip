@@ -74,8 +74,6 @@ constexpr float kRecomputeThr = P == 0 ? 6.0f / 32.0f : 6.0f / 256.0f;
 template <int P>
 constexpr float kSkipFactor = P == 0 ? 4.0f : 2.25f;
 
-constexpr int kCenterRows = 256;
-
 __host__ __device__ constexpr int round_up_c(int a, int b) { return (a + b - 1) / b * b; }
 
 // P = 0: float32 operands (32x32x2), P = 1: bf16 (32x32x16)
@@ -125,46 +123,6 @@ __device__ __forceinline__ void split3(float v, float& h, float& m, float& l) {
   const float r1 = v - h;
   m = q_bf16(r1);
   l = q_bf16(r1 - m);
-}
-
-// ----------------------------------------------------------------------------
-// centre of each cluster's sample: mean of its first kCenterRows rows of Y32
-// (float64 sums; any point of the cluster would do, the mean keeps the
-// centred operands smallest); one block per cluster (grid = k)
-// ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_center(const float* __restrict__ Y32, int DM, int KP,
-                                                const int32_t* __restrict__ sp_off,
-                                                const int32_t* __restrict__ cnt,
-                                                float* __restrict__ mu) {
-  __shared__ double part[256];
-  const int j = blockIdx.x;
-  // the cluster's squared radius, the packing takes its maximum
-  if (threadIdx.x == 0) mu[(size_t)gridDim.x * KP + j] = 0.0f;
-  const int m = cnt[j] < kCenterRows ? cnt[j] : kCenterRows;
-  const int base = sp_off[j];
-  // coordinate chunks of up to 32 columns; 8 row groups per chunk
-  const int cc = threadIdx.x & 31, rg = threadIdx.x >> 5;
-  for (int c0 = 0; c0 < KP; c0 += 32) {
-    const int c = c0 + cc;
-    double s = 0.0;
-    if (c < DM) {
-#pragma unroll 8
-      for (int r = rg; r < m; r += 8) s += (double)Y32[(size_t)(base + r) * DM + c];  // loads issued ahead
-    }
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (rg == 0 && c < KP) {
-      double t = 0.0;
-      for (int g = 0; g < 8; ++g) t += part[g * 32 + cc];
-      mu[(size_t)j * KP + c] = (m > 0 && c < DM) ? (float)(t / m) : 0.0f;
-    }
-    __syncthreads();
-  }
-}
-
-void launch_center(hipStream_t st, const float* Y32, int DM, int KP, const int32_t* sp_off,
-                   const int32_t* cnt, int k, float* mu) {
-  hipLaunchKernelGGL(k_center, dim3(k), dim3(256), 0, st, Y32, DM, KP, sp_off, cnt, mu);
 }
 
 // ----------------------------------------------------------------------------
@@ -493,7 +451,8 @@ __device__ __forceinline__ void p2_mfma_block(
     const int32_t* __restrict__ sp_off, const int32_t* __restrict__ cnt,
     const int32_t* __restrict__ csize, int k, const float* __restrict__ mu,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
-    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32) {
+    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32,
+    const int32_t* __restrict__ perm, const uint32_t* __restrict__ mask) {
   using C = MCfg<P, DM>;
   // contiguous halves: the augmentation columns always fall in the upper half
   // of the row
@@ -559,6 +518,8 @@ __device__ __forceinline__ void p2_mfma_block(
   constexpr int V = C::HALF % 4 == 0 ? 4 : 2;
   typedef float fvec __attribute__((ext_vector_type(V)));
   const bool vec = d % V == 0 && ((uintptr_t)X & (4 * V - 1)) == 0;
+  // position i of the launch is row perm[i] of X (null: row i)
+  auto row_of = [&](int i) { return perm != nullptr ? perm[i] : i; };
   float xr[PB][C::HALF];
   // d = 256: the rows wait in the AGPRs, so the vector registers serve the
   // tile pipeline (deeper B-operand reads ahead of the MFMAs)
@@ -580,7 +541,7 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
   for (int b = 0; b < PB; ++b) {
     const int pb = P0 + 32 * b + col;
-    const int pa = pb < n ? pb : n - 1;
+    const int pa = row_of(pb < n ? pb : n - 1);
     const float* xp = X + (size_t)pa * d;
 #pragma unroll
     for (int i0 = 0; i0 < C::XR; i0 += V) {
@@ -596,9 +557,12 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
       for (int i = 0; i < C::XR; ++i) asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(xr[b][i]) : "v"(xr[b][i]));
     }
-    pout[b] = P0 + 32 * b + (kT ? col : prow);
-    own[b] = labels[pout[b] < n ? pout[b] : n - 1];
+    // the row this lane writes (kT: the one it holds), -1 past the end
+    const int po = P0 + 32 * b + (kT ? col : prow);
+    pout[b] = kT ? pa : row_of(po < n ? po : n - 1);
+    own[b] = labels[pout[b]];
     own[b] = (unsigned)own[b] < (unsigned)k ? own[b] : 0;  // labels are checked before; stay in bounds
+    pout[b] = po < n ? pout[b] : -1;
     w_own[b] = 0.0;
     bnum[b] = 1.0;
     bden[b] = 0.0;
@@ -607,9 +571,8 @@ __device__ __forceinline__ void p2_mfma_block(
   AFrag<P, DM> A[PB];
   int thrx[PB];   // the element's recompute threshold (float bits, >= 0)
   int chk[PB];    // some element of the block may meet the threshold (wave-uniform, 0 / 1)
-  // The packed cluster blocks are contiguous, so the tile after a cluster's
-  // last one is the first tile of the next cluster with samples: it is
-  // prefetched there, and a cluster normally starts with its first tile
+  // The first tile of the next cluster to evaluate is prefetched behind a
+  // cluster's last one, so a cluster normally starts with its first tile
   // already loaded while its A operands are built.  Past the sample's end the
   // last tile is re-read.  `pre` is the first row of the tile held in b0 (the
   // register path) or in LDS buffer `cb` (the LDS path).
@@ -623,10 +586,31 @@ __device__ __forceinline__ void p2_mfma_block(
   // (cluster, stage within it; cj = k past the end, where the last tile is
   // loaded again and never read); rs the slot of the next stage to compute.
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // The clusters to evaluate: every one, or those with a bit set in the masks
+  // of the 32-element groups that share the sample tiles (the wave's PB
+  // groups; on the LDS path the block's four waves).  next_cluster(j): the
+  // first one from j on, k past the last.
+  const int kw = (k + 31) >> 5;
+  const int grp0 = kLds ? blk * 4 * PB : P0 >> 5;
+  constexpr int kGrp = kLds ? 4 * PB : PB;
+  auto next_cluster = [&](int j) {
+    if (mask == nullptr) return j;
+    for (int wd = j >> 5; wd < kw; ++wd) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int q = 0; q < kGrp; ++q)
+        if ((grp0 + q) * 32 < n) bits |= mask[(size_t)(grp0 + q) * kw + wd];
+      bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)bits);
+      if (wd == j >> 5) bits &= ~0u << (j & 31);
+      if (bits != 0) return wd * 32 + __builtin_ctz(bits);
+    }
+    return k;
+  };
   int cj = 0, cm = 0, rs = 0;
   int cnt_c = 0, row_c = 0;  // samples and first packed row of cluster cj
-  auto seek = [&](int j0) {  // cj: the first cluster from j0 on with samples
-    while (j0 < k && cnt[j0] <= 0) ++j0;
+  auto seek = [&](int j0) {  // cj: the first cluster to evaluate from j0 on with samples
+    j0 = next_cluster(j0);
+    while (j0 < k && cnt[j0] <= 0) j0 = next_cluster(j0 + 1);
     cj = j0;
     if (j0 < k) {
       cnt_c = cnt[j0];
@@ -684,7 +668,8 @@ __device__ __forceinline__ void p2_mfma_block(
     }
   }
 
-  for (int j = 0; j < k; ++j) {
+  for (int j = next_cluster(0), jn; j < k; j = jn) {
+    jn = next_cluster(j + 1);
     // ---- A operands for cluster j: x~ = x - mu_j (mu zero-padded to KP),
     // rounded to the input precision, plus the augmentation; m is this
     // lane's half of mu_j (in memory, or in the LDS slot of the cluster's
@@ -761,6 +746,7 @@ __device__ __forceinline__ void p2_mfma_block(
     // the next tile's loads are issued before this tile's MFMAs)
     const int base = sp_off[j];
     const int ntile = (cnt[j] + 31) >> 5;
+    const int next_base = sp_off[jn];  // (jn = k: past the last tile)
     double wsum[PB];
     constexpr int kNA = kT ? 4 : 16;  // running float32 sums per lane and block
     float acc[PB][kNA];
@@ -830,7 +816,7 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
             for (int r = 0; r < 16; ++r) flagged |= (__float_as_int(c[r]) < tx ? 1u : 0u) << r;
             const int e0 = P0 + 32 * b + col;
-            const float* xc = X + (size_t)(e0 < n ? e0 : n - 1) * d;
+            const float* xc = X + (size_t)row_of(e0 < n ? e0 : n - 1) * d;
             const float* yc = Y32 + (size_t)(srow + col) * DM;
             while (flagged) {
               const int r = __builtin_ctz(flagged);
@@ -838,7 +824,7 @@ __device__ __forceinline__ void p2_mfma_block(
               // the row's partner: a sample (kT) or an element
               const int rw = 8 * (r >> 2) + 4 * h + (r & 3);
               const int er = P0 + 32 * b + rw;
-              const float* xp = kT ? xc : X + (size_t)(er < n ? er : n - 1) * d;
+              const float* xp = kT ? xc : X + (size_t)row_of(er < n ? er : n - 1) * d;
               const float* yr = kT ? Y32 + (size_t)(srow + rw) * DM : yc;
               float acc2 = 0.0f;
               for (int q = 0; q < d; ++q) {
@@ -1032,13 +1018,13 @@ __device__ __forceinline__ void p2_mfma_block(
       for (; t + 2 <= ntile; t += 2) {
         load_tile<P, DM>(Ym, w, base + (t + 1) * 32, lane_off, wr, b1, w1);
         tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, false);
-        pre = clamp_row(base + (t + 2) * 32);
+        pre = clamp_row(t + 2 < ntile ? base + (t + 2) * 32 : next_base);
         load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
         tile([&](int q) { return b1.v[q]; }, w1, base + (t + 1) * 32, t + 2 == ntile);
       }
       if (t < ntile) {
         tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, true);
-        pre = clamp_row(base + ntile * 32);
+        pre = clamp_row(next_base);
         load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
       }
     }
@@ -1046,7 +1032,7 @@ __device__ __forceinline__ void p2_mfma_block(
     const double dsz = (double)sz;
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
-      if (What != nullptr && pout[b] < n && (kT ? h == 0 : (lane & 1) == 0)) What[(size_t)pout[b] * k + j] = (float)wsum[b];
+      if (What != nullptr && pout[b] >= 0 && (kT ? h == 0 : (lane & 1) == 0)) What[(size_t)pout[b] * k + j] = (float)wsum[b];
       if (j == own[b]) {
         w_own[b] = wsum[b];
       } else if (sz > 0 && wsum[b] * bden[b] < bnum[b] * dsz) {
@@ -1065,7 +1051,7 @@ __device__ __forceinline__ void p2_mfma_block(
     const double bb = bden[b] > 0.0 ? bnum[b] / bden[b] : __builtin_inf();
     const double mx = a > bb ? a : bb;
     const double s = (szo > 1 && mx > 0.0) ? (bb - a) / mx : 0.0;
-    const bool writer = pout[b] < n && (kT ? h == 0 : (lane & 1) == 0);
+    const bool writer = pout[b] >= 0 && (kT ? h == 0 : (lane & 1) == 0);
     if (writer) {
       if (a_out) a_out[pout[b]] = (float)a;
       if (b_out) b_out[pout[b]] = (float)bb;
@@ -1093,9 +1079,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
     const int32_t* __restrict__ sp_off, const int32_t* __restrict__ cnt,
     const int32_t* __restrict__ csize, int k, const float* __restrict__ mu,
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
-    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32) {
+    float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32,
+    const int32_t* __restrict__ perm, const uint32_t* __restrict__ mask) {
   p2_mfma_block<P, DM, PB, TBX>(blockIdx.x, X, n, d, labels, Ym, w, sp_off, cnt, csize, k, mu, a_out, b_out,
-                              s_out, What, bpart, Y32);
+                              s_out, What, bpart, Y32, perm, mask);
 }
 
 // Several requests in one launch: workgroup i runs work item i = (request,
@@ -1116,7 +1103,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
   const int blk = ((citem_ptr)items)[2 * blockIdx.x + 1];
   const auto& J = ((cjob_ptr)jobs)[jx];
   p2_mfma_block<P, DM, PB, TBX>(blk, J.X, J.n, J.d, J.labels, J.Ym, J.w, J.sp_off, J.cnt, J.csize, J.k, J.mu,
-                              J.a, J.b, J.s, J.What, J.bpart, J.Y32);
+                              J.a, J.b, J.s, J.What, J.bpart, J.Y32, J.perm, J.mask);
 }
 
 // Block shapes of the matrix-core kernel (ids used by the autotuner):
@@ -1143,7 +1130,8 @@ template <int P, int DM, int PB, int TBX>
 static void launch_mfma_pb(hipStream_t st, const P2Args& A, const float* mu, const void* Ym) {
   const int blocks = (int)ceil_div(A.n, 128 * PB);
   hipLaunchKernelGGL((k_p2_mfma<P, DM, PB, TBX>), dim3(blocks), dim3(256), 0, st, A.X, A.n, A.d, A.labels, Ym,
-                     A.w, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart, A.Y);
+                     A.w, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart, A.Y, A.perm,
+                     A.mask);
 }
 
 template <int P, int DM>

@@ -38,15 +38,33 @@ void launch_rows_mark(hipStream_t st, const int32_t* rows, int64_t m, int n, int
   hipLaunchKernelGGL(k_rows_mark, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, rows, m, n, mark, bad);
 }
 
-__global__ __launch_bounds__(256) void k_rows_compact(const int32_t* __restrict__ mark,
-                                                      const int32_t* __restrict__ pos, int n,
-                                                      int32_t* __restrict__ urows) {
+__global__ __launch_bounds__(256) void k_rows_flag(const int32_t* __restrict__ mark,
+                                                   const int32_t* __restrict__ perm, int n,
+                                                   int32_t* __restrict__ flag) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && mark[i]) urows[pos[i]] = i;
+  if (i < n) flag[i] = mark[perm[i]];
 }
 
-void launch_rows_compact(hipStream_t st, const int32_t* mark, const int32_t* pos, int n, int32_t* urows) {
-  hipLaunchKernelGGL(k_rows_compact, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, mark, pos, n, urows);
+void launch_rows_flag(hipStream_t st, const int32_t* mark, const int32_t* perm, int n, int32_t* flag) {
+  hipLaunchKernelGGL(k_rows_flag, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, mark, perm, n, flag);
+}
+
+__global__ __launch_bounds__(256) void k_rows_compact(const int32_t* __restrict__ flag,
+                                                      const int32_t* __restrict__ pos,
+                                                      const int32_t* __restrict__ perm, int n,
+                                                      int32_t* __restrict__ urows, int32_t* __restrict__ slot) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n && flag[i]) {
+    const int g = perm[i], p = pos[i];
+    urows[p] = g;
+    slot[g] = p;
+  }
+}
+
+void launch_rows_compact(hipStream_t st, const int32_t* flag, const int32_t* pos, const int32_t* perm, int n,
+                         int32_t* urows, int32_t* slot) {
+  hipLaunchKernelGGL(k_rows_compact, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, flag, pos, perm, n, urows,
+                     slot);
 }
 
 // one wave per gathered row
@@ -71,21 +89,8 @@ void launch_rows_gather(hipStream_t st, const float* X, const int32_t* labels, i
                      mu, Xs, ls);
 }
 
-// index of v in the ascending array a[0..len), or -1
-__device__ __forceinline__ int find_sorted(const int32_t* __restrict__ a, int len, int v) {
-  int lo = 0, hi = len;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < v)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return (lo < len && a[lo] == v) ? lo : -1;
-}
-
 __global__ __launch_bounds__(kRowsBlock) void k_rows_expand(const int32_t* __restrict__ rows, int64_t m,
-                                                            const int32_t* __restrict__ urows, int mu,
+                                                            const int32_t* __restrict__ slot,
                                                             const float* __restrict__ au,
                                                             const float* __restrict__ bu,
                                                             const float* __restrict__ su, float* __restrict__ a,
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows_expand(const int32_t* __res
   const int64_t i = (int64_t)blockIdx.x * kRowsBlock + threadIdx.x;
   double v = 0.0;
   if (i < m) {
-    const int u = find_sorted(urows, mu, rows[i]);  // every entry is there
+    const int u = slot[rows[i]];  // every entry is there
     const float sv = su[u];
     if (a) a[i] = au[u];
     if (b) b[i] = bu[u];
@@ -106,12 +111,12 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows_expand(const int32_t* __res
   if (threadIdx.x == 0) bpart[blockIdx.x] = tot;
 }
 
-void launch_rows_expand(hipStream_t st, const int32_t* rows, int64_t m, const int32_t* urows, int mu,
-                        const float* au, const float* bu, const float* su, float* a, float* b, float* s,
+void launch_rows_expand(hipStream_t st, const int32_t* rows, int64_t m, const int32_t* slot, const float* au,
+                        const float* bu, const float* su, float* a, float* b, float* s,
                         double* bpart) {
   if (m <= 0) return;
   hipLaunchKernelGGL(k_rows_expand, dim3((unsigned)ceil_div(m, kRowsBlock)), dim3(kRowsBlock), 0, st, rows, m,
-                     urows, mu, au, bu, su, a, b, s, bpart);
+                     slot, au, bu, su, a, b, s, bpart);
 }
 
 }  // namespace silh

@@ -122,6 +122,8 @@ struct silh_ctx {
   double *f0X = nullptr, *W0 = nullptr, *partial = nullptr, *p_gid = nullptr;
   int32_t *s_off = nullptr, *sp_off = nullptr, *cnt = nullptr, *gid_pk = nullptr;
   float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr;
+  float* brec = nullptr;      // Euclidean on the matrix cores: the clusters' bound records
+  uint32_t* bmask = nullptr;  // and the masks of the element groups
   void* Ym = nullptr;
   unsigned char* cstat = nullptr;  // cosine: the clusters' records
   float* cself = nullptr;          // cosine, fp8: the clamp's share of the self pairs
@@ -644,7 +646,6 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   c->S = c->s_off_h[k];
   c->S_pad = c->sp_off_h[k];
   const int prec = c->mprec;
-  const int KP = c->mfma ? mfma_kp(prec, c->DM) : 0;
   const bool mfma_pack = c->mfma && c->S_pad > 0;
   {
     Carve cv;
@@ -654,6 +655,8 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     if (mfma_pack) {
       cv.add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k));
       cv.add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
+      if (bounds_pay(n, k, c->S_pad))
+        cv.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
     }
     if (c->cos) cv.add(&c->cstat, (size_t)k * cos_stat_bytes(c->DM));
     if (c->cos && prec == 2) cv.add(&c->cself, (size_t)n);
@@ -679,7 +682,7 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   if (mfma_pack) {
     {
       Launch L(c, K_CENTER);
-      launch_center(c->st, c->Y32, c->DM, KP, c->sp_off, c->cnt, k, c->mu);
+      launch_center(c->st, prec, c->DM, c->Y32, c->w32, c->sp_off, c->cnt, c->csize, k, c->mu, c->brec);
       CHK(L.done());
     }
     {
@@ -705,6 +708,8 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   c->Ym = nullptr;
   c->cstat = nullptr;
   c->cself = nullptr;
+  c->brec = nullptr;
+  c->bmask = nullptr;
   const int n = c->n, k = c->k;
   const int nb = (int)ceil_div(n, c->p2_rows);
   Carve cv;
@@ -872,6 +877,14 @@ int size_bucket(int64_t S_pad) {
   return b;
 }
 
+// The masks of the scores' clusters for the rows of A (part of Phase 2);
+// mask holds bound_mask_words words.
+void mask_clusters(silh_ctx* c, P2Args& A, uint32_t* mask) {
+  if (!c->brec || !mask || A.What != nullptr || A.n <= 0) return;
+  launch_bounds(c->st, c->DM, A.X, A.n, A.d, A.labels, A.perm, c->brec, A.k, mask);
+  A.mask = mask;
+}
+
 // cosine has one shape: it is recorded under the same key, nothing is timed
 void note_cos_shape(const silh_ctx* c) {
   if (g_tune_mode.load() != 1 || c->prm.prec == SILH_FP32_VALU || (c->mprec == 0 && c->DM > 128)) return;
@@ -879,7 +892,7 @@ void note_cos_shape(const silh_ctx* c) {
   g_tune.emplace(std::array<int, 4>{SILH_COS, c->mprec, c->DM, size_bucket(c->S_pad)}, 1);
 }
 
-int pick_pb(silh_ctx* c, const P2Args& A) {
+int pick_pb(silh_ctx* c, P2Args A, uint32_t* mask = nullptr) {
   if (c->cos) note_cos_shape(c);
   if (!c->mfma) return 1;
   int ids[3];
@@ -897,6 +910,7 @@ int pick_pb(silh_ctx* c, const P2Args& A) {
     auto it = g_tune.find(key);
     if (it != g_tune.end()) return it->second;
   }
+  mask_clusters(c, A, mask);
   // each shape launched twice, in two rounds over the shapes, and the faster
   // launch of each compared (one launch of each mis-picks when they are
   // ~10 % apart)
@@ -961,6 +975,7 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   A.rn = c->rn;
   A.cstat = c->cstat;
   A.cself = c->cself;
+  A.perm = c->perm;
   free_list(c, c->alloc_p2);
   if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
@@ -968,8 +983,9 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
     CHK(cv.commit(c, c->alloc_p2));
   }
   {
-    const int pb = pick_pb(c, A);  // (tuning runs stay outside the timed launch)
+    const int pb = pick_pb(c, A, c->bmask);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
+    mask_clusters(c, A, c->bmask);
     const bool ok = launch_p2(c, A, pb);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
     CHK(L.done());
@@ -996,32 +1012,36 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   free_list(c, c->alloc_rows);
   const int n = c->n, d = c->d;
   const int64_t cap = m < n ? m : n;  // distinct rows
-  int32_t *mark = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr;
+  int32_t *mark = nullptr, *flag = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr;
+  uint32_t* mask = nullptr;
   int* bad = nullptr;
   float *Xs = nullptr, *au = nullptr, *bu = nullptr, *su = nullptr, *rnu = nullptr;
   double *bpu = nullptr, *bpm = nullptr, *mean_d = nullptr;
   const int64_t nbm = ceil_div(m, kRowsBlock);
   {
     Carve cv;
-    cv.add(&mark, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
+    cv.add(&mark, (size_t)n).add(&flag, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
     cv.add(&urows, (size_t)cap).add(&bad, 1).add(&Xs, (size_t)cap * d).add(&ls, (size_t)cap);
     cv.add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
     cv.add(&bpu, (size_t)ceil_div(cap, c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
     if (c->rn) cv.add(&rnu, (size_t)cap);
+    if (c->brec) cv.add(&mask, bound_mask_words(cap, c->k));
     CHK(cv.commit(c, c->alloc_rows));
   }
   HIPCHK(hipMemsetAsync(mark, 0, (size_t)n * sizeof(int32_t), c->st));
   HIPCHK(hipMemsetAsync(bad, 0, sizeof(int), c->st));
   launch_rows_mark(c->st, rows, m, n, mark, bad);
   HIPCHK(hipGetLastError());
-  launch_scan(c->st, mark, n, pos, tmp);
+  launch_rows_flag(c->st, mark, c->perm, n, flag);  // in cluster order, so that neighbours share clusters
+  HIPCHK(hipGetLastError());
+  launch_scan(c->st, flag, n, pos, tmp);
   HIPCHK(hipGetLastError());
   int32_t mu_h = 0;
   int bad_h = 0;
   CHK(fetch(c, {{&mu_h, pos + n, sizeof(int32_t)}, {&bad_h, bad, sizeof(int)}}));
   if (bad_h) return fail(SILH_E_ARG, "a row index lies outside [0, %d)", n);
   const int mu = mu_h;
-  launch_rows_compact(c->st, mark, pos, n, urows);
+  launch_rows_compact(c->st, flag, pos, c->perm, n, urows, mark);  // mark: each row's place in urows
   launch_rows_gather(c->st, c->X, c->labels, d, urows, mu, Xs, ls);
   if (rnu) launch_rnorm(c->st, Xs, mu, d, rnu);  // the same factors as for the rows of X
   HIPCHK(hipGetLastError());
@@ -1052,13 +1072,15 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     CHK(cv.commit(c, c->alloc_rows));
   }
   {
-    const int pb = pick_pb(c, A);  // (tuning runs stay outside the timed launch)
+    if (!bounds_pay(mu, c->k, c->S_pad)) mask = nullptr;
+    const int pb = pick_pb(c, A, mask);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
+    mask_clusters(c, A, mask);
     const bool ok = launch_p2(c, A, pb);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
     CHK(L.done());
   }
-  launch_rows_expand(c->st, rows, m, urows, mu, au, bu, su, a, b, s, bpm);
+  launch_rows_expand(c->st, rows, m, mark, au, bu, su, a, b, s, bpm);
   HIPCHK(hipGetLastError());
   if (mean_host) {
     launch_mean(c->st, bpm, (int)nbm, m, mean_d);
@@ -1112,7 +1134,8 @@ int tuned_shape(silh_ctx* c) {
   A.rn = c->rn;
   A.cstat = c->cstat;
   A.cself = c->cself;
-  return pick_pb(c, A);
+  A.perm = c->perm;
+  return pick_pb(c, A, c->bmask);
 }
 
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
@@ -1132,6 +1155,12 @@ bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   J.bpart = c->bpart;
   J.Y32 = c->Y32;
   J.aux = c->aux32;
+  J.perm = c->perm;
+  J.mask = nullptr;
+  if (c->brec) {  // on the context's stream, which the caller synchronises
+    launch_bounds(c->st, c->DM, c->X, c->n, c->d, c->labels, c->perm, c->brec, c->k, c->bmask);
+    J.mask = c->bmask;
+  }
   J.n = c->n;
   J.d = c->d;
   J.k = c->k;

@@ -48,6 +48,8 @@ struct Branch {
   void* Ym = nullptr;
   unsigned char* cstat = nullptr;  // cosine: the clusters' records
   float* cself = nullptr;          // cosine, fp8: the clamp's share of the self pairs
+  float* brec = nullptr;           // Euclidean bounds: cluster records, group masks
+  uint32_t* bmask = nullptr;
   double *bpart = nullptr, *Wpart = nullptr;
 };
 
@@ -63,7 +65,7 @@ struct silh_graph {
   std::vector<int64_t> ts;  // Algorithm 1's t of each clustering (k enters it when derived from eps)
   std::vector<int32_t> shape;    // Phase-2 block shape captured for each clustering
   std::vector<int64_t> probe_S;  // padded sample size of the request the shape was tuned on
-  int K = 0, n = 0, d = 0, DM = 0, KP = 0, mprec = 0, p2_rows = 0, chunk = 0, kmax = 0;
+  int K = 0, n = 0, d = 0, DM = 0, mprec = 0, p2_rows = 0, chunk = 0, kmax = 0;
   bool mfma = false, cos = false;
   int64_t S_cap = 0, F0_cap = 0, items_cap = 0, part_cap = 0, dist_cap = 0;
   std::vector<Branch> br;
@@ -148,6 +150,7 @@ bool alloc_branch(silh_graph* g, Branch& b) {
     unsigned char* ym = nullptr;
     ok = take(g, b.mu, mfma_mu_floats(g->mprec, g->DM, k)) && take(g, ym, S * (size_t)mfma_row_bytes(g->mprec, g->DM));
     b.Ym = ym;
+    ok = ok && take(g, b.brec, k * (int64_t)bound_rec_floats(g->DM)) && take(g, b.bmask, (int64_t)bound_mask_words(n, (int)k));
   }
   if (ok && g->cos) ok = take(g, b.cstat, k * (int64_t)cos_stat_bytes(g->DM));
   if (ok && g->cos && g->mprec == 2) ok = take(g, b.cself, n);
@@ -230,8 +233,14 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     if (b.cself) launch_cos_self(st, DM, b.Y32, b.w32, b.gid_pk, b.sp_off, k, (int)g->S_cap, b.cstat, n, b.cself);
     if (!launch_phase2_cos(st, g->mprec, DM, A)) return false;
   } else if (g->mfma) {
-    launch_center(st, b.Y32, DM, g->KP, b.sp_off, b.cnt, k, b.mu);
+    const bool bounds = bounds_pay(n, k, (int64_t)std::min((double)n, (double)k * (double)t));
+    launch_center(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, b.csize, k, b.mu, bounds ? b.brec : nullptr);
     if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym)) return false;
+    A.perm = b.perm;
+    if (bounds) {
+      launch_bounds(st, DM, A.X, n, d, lab, b.perm, b.brec, k, b.bmask);
+      A.mask = b.bmask;
+    }
     if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
     return false;
@@ -288,7 +297,6 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
   g->mfma = path == kPathMfma;
   g->cos = path == kPathCos;
   g->mprec = operand_type(base->prec);
-  g->KP = g->mfma ? mfma_kp(g->mprec, g->DM) : 0;
   g->p2_rows = phase2_rows(path, base->metric, g->mprec, g->DM);
   g->chunk = g->DM > 128 ? kWChunkWide : kWChunk;
   double kt = 0.0;

@@ -112,6 +112,11 @@ struct P2Args {
   const unsigned char* cstat = nullptr;  // cosine: the clusters' records (launch_cos_stats)
   const float* cself = nullptr;    // cosine, fp8: launch_cos_self's values by element id
   const int32_t* egid = nullptr;   // element ids of the rows of X (null: row i is element i)
+  // matrix-core path: the order in which the rows are taken (a permutation of
+  // [0, n), null: as they lie) and the clusters each group of 32 of them
+  // needs (launch_bounds; null: every cluster)
+  const int32_t* perm = nullptr;
+  const uint32_t* mask = nullptr;
 };
 // One request's Phase-2 launch as a work source of a multi-request launch
 // (the arguments of P2Args and of the matrix-core operands, in device memory).
@@ -131,6 +136,8 @@ struct P2Job {
   double* bpart;
   const float* Y32;
   const float* aux;
+  const int32_t* perm;
+  const uint32_t* mask;
   int n, d, k, pad0;
 };
 // returns false if (metric, d) has no VALU kernel
@@ -157,8 +164,9 @@ int mfma_row_bytes(int prec, int DM);  // bytes per packed row (operands, LDS-pa
 // clusters' packed samples (the largest |y~_q|^2), mfma_mu_floats
 // floats in all
 size_t mfma_mu_floats(int prec, int DM, int k);
-void launch_center(hipStream_t st, const float* Y32, int DM, int KP, const int32_t* sp_off,
-                   const int32_t* cnt, int k, float* mu);
+// With rec non-null also the bound records (below).
+void launch_center(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
+                   const int32_t* cnt, const int32_t* csize, int k, float* mu, float* rec);
 // packs rows [0, min(S_pad, sp_off[k])) (w: weights of the packed rows,
 // copied into the rows' tails on the LDS path)
 bool launch_pack_mfma(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
@@ -176,6 +184,19 @@ bool mfma_lds_path(int prec, int DM);
 int mfma_shapes(int prec, int DM, int* ids);
 bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const float* mu, const void* Ym,
                         int shape);
+
+// Bounds on the Euclidean sums (k_phase2_bounds.hip): a record per cluster
+// (bound_rec_floats floats each, by launch_center), then for every
+// group of 32 elements (in perm order, null: as they lie) a mask of the
+// clusters its scores need, bit j of word [group][j / 32]
+size_t bound_rec_floats(int DM);
+size_t bound_mask_words(int64_t n, int k);
+void launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels, const int32_t* perm,
+                   const float* rec, int k, uint32_t* mask);
+// whether scores of n elements against a sample of S rows (or so) go through
+// the bounds: two clusters are both needed, and below 2^24 pairs the two
+// launches cost more than they save
+inline bool bounds_pay(int64_t n, int k, int64_t S) { return k > 2 && n * S >= ((int64_t)1 << 24); }
 
 // Cosine (every operand type; prec as above, float32 arithmetic for the
 // vector-ALU precision too): the clusters' samples collapsed into one record
@@ -283,16 +304,19 @@ void launch_coh_sep(hipStream_t st, const float* W, int n, int k, const int32_t*
 void launch_rows_draw(hipStream_t st, uint64_t seed, int64_t n, int64_t m, int32_t* rows);
 // mark[rows[i]] = 1 for every valid entry; *bad = 1 if any entry lies outside [0, n)
 void launch_rows_mark(hipStream_t st, const int32_t* rows, int64_t m, int n, int32_t* mark, int* bad);
-// urows[pos[i]] = i for every marked i (ascending, distinct)
-void launch_rows_compact(hipStream_t st, const int32_t* mark, const int32_t* pos, int n, int32_t* urows);
+// flag[i] = mark[perm[i]]: the marked elements in cluster order
+void launch_rows_flag(hipStream_t st, const int32_t* mark, const int32_t* perm, int n, int32_t* flag);
+// urows[pos[i]] = perm[i] for every flagged i (distinct, in cluster order) and
+// slot[perm[i]] = pos[i]
+void launch_rows_compact(hipStream_t st, const int32_t* flag, const int32_t* pos, const int32_t* perm, int n,
+                         int32_t* urows, int32_t* slot);
 // Xs[i] = X[urows[i]], ls[i] = labels[urows[i]]
 void launch_rows_gather(hipStream_t st, const float* X, const int32_t* labels, int d,
                         const int32_t* urows, int mu, float* Xs, int32_t* ls);
-// a/b/s[i] = a/b/s_u[index of rows[i] in urows]; bpart[block] = float64 sum
+// a/b/s[i] = a/b/s_u[slot[rows[i]]]; bpart[block] = float64 sum
 // of the block's s (blocks of kRowsBlock entries)
 constexpr int kRowsBlock = 256;
-void launch_rows_expand(hipStream_t st, const int32_t* rows, int64_t m, const int32_t* urows, int mu,
-                        const float* au, const float* bu, const float* su, float* a, float* b, float* s,
+void launch_rows_expand(hipStream_t st, const int32_t* rows, int64_t m, const int32_t* slot, const float* au, const float* bu, const float* su, float* a, float* b, float* s,
                         double* bpart);
 
 // ---- diagnostics -------------------------------------------------------------

@@ -91,11 +91,13 @@ struct Bufs {
   float* rn = nullptr;
   unsigned char* cstat = nullptr;
   float* cself = nullptr;
+  float* brec = nullptr;
+  uint32_t* bmask = nullptr;
 };
 
 struct Shape {
-  int n, d, k, DM, KP, mprec, p2_rows, seg, units;
-  bool mfma, split, cos;
+  int n, d, k, DM, mprec, p2_rows, seg, units;
+  bool mfma, split, cos, bounds;
   int64_t S_cap;
 };
 
@@ -110,6 +112,7 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
     sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
   }
   if (s.split) sl.add(&b.Wpart, n * k);
+  if (s.bounds) sl.add(&b.brec, k * (int64_t)bound_rec_floats(s.DM)).add(&b.bmask, (int64_t)bound_mask_words(n, s.k));
   if (s.cos) sl.add(&b.rn, n);
   if (s.cos && s.mprec == 2) sl.add(&b.cself, n);
 }
@@ -131,13 +134,20 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   const int path = phase2_path(prm->metric, prm->prec, sh.DM);
   sh.mfma = path == kPathMfma;
   sh.mprec = operand_type(prm->prec);
-  sh.KP = sh.mfma ? mfma_kp(sh.mprec, sh.DM) : 0;
   sh.p2_rows = phase2_rows(path, prm->metric, sh.mprec, sh.DM);
   sh.split = !sh.mfma && phase2_valu_split(prm->metric, sh.DM);
   sh.cos = path == kPathCos;
   sh.seg = sort_seg(sh.n, sh.k);
   sh.units = (int)ceil_div(sh.n, sh.seg);
   sh.S_cap = (int64_t)sh.n + (int64_t)kSamplePad * sh.k;  // every element, each cluster padded
+  // the bounds (the same results) where their buffers fit too
+  sh.bounds = sh.mfma && bounds_pay(sh.n, sh.k, sh.n);
+  if (sh.bounds) {
+    Slices count;
+    Bufs dummy;
+    layout(sh, count, dummy);
+    sh.bounds = count.used <= kScratchBytes;
+  }
   {
     Slices count;
     Bufs dummy;
@@ -216,9 +226,14 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
     if (B.cself) launch_cos_self(st, DM, B.Y32, B.w32, B.gid_pk, B.sp_off, k, (int)sh.S_cap, B.cstat, n, B.cself);
     ok = launch_phase2_cos(st, sh.mprec, DM, A);
   } else if (sh.mfma) {
-    launch_center(st, B.Y32, DM, sh.KP, B.sp_off, B.cnt, k, B.mu);
-    ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym) &&
-         launch_phase2_mfma(st, sh.mprec, DM, A, B.mu, B.Ym, mfma_pb_default(sh.mprec, DM));
+    launch_center(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, B.csize, k, B.mu, sh.bounds ? B.brec : nullptr);
+    A.perm = B.perm;
+    ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym);
+    if (ok && sh.bounds) {
+      launch_bounds(st, DM, X, n, d, labels, B.perm, B.brec, k, B.bmask);
+      A.mask = B.bmask;
+    }
+    ok = ok && launch_phase2_mfma(st, sh.mprec, DM, A, B.mu, B.Ym, mfma_pb_default(sh.mprec, DM));
   } else {
     ok = launch_phase2_valu(st, metric, DM, A);
   }

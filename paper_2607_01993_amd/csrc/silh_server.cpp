@@ -239,7 +239,11 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
   const uint64_t rn = r.metric == SILH_COS
                           ? (r.prec == SILH_FP8 ? 8 : 4) * n + (uint64_t)r.k * silh::cos_stat_bytes(DM)
                           : 0;
-  return 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
+  // Euclidean bounds: a mask per 32 elements, a record per cluster
+  const uint64_t bnd = mfma ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
+                                  4 * (uint64_t)r.k * silh::bound_rec_floats(DM)
+                            : 0;
+  return bnd + 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
 }
 
 silh_params request_params(const Dataset& ds, const silh_request& r, Pool* pool) {
