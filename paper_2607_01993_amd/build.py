@@ -27,6 +27,7 @@ SOURCES = {
     "k_phase1.hip": ["-ffp-contract=off"],
     "k_phase2_valu.hip": [],
     "k_phase2_cos.hip": [],
+    "k_phase2_tab.hip": [],
     "k_phase2_bounds.hip": [],
     "k_rows.hip": [],
     "k_cohsep.hip": [],

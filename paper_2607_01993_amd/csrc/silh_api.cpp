@@ -79,6 +79,7 @@ constexpr int kFp8MinD = 64;
 struct silh_ctx {
   silh_params prm{};
   int64_t t = 0;
+  int64_t t_rows = 0;  // expected sample rows per cluster (exact: all of them)
   hipStream_t st = nullptr;
   const float* X = nullptr;
   const int32_t* labels = nullptr;
@@ -87,6 +88,7 @@ struct silh_ctx {
   bool cos = false;   // Phase 2 by the collapsed cosine sums
   int mprec = 0;      // operand type: 0 float32, 1 bf16, 2 fp8
   int p2_rows = kP2Rows;
+  bool pieces = false;  // long Phase-2 work in pieces (set_pieces)
   int state = 0;  // 0 = indexed, 1 = sampled
 
   std::vector<void*> alloc_init, alloc_sample, alloc_rows, alloc_p2;
@@ -585,6 +587,7 @@ silh_status create(const silh_params* prm, const float* X, const int32_t* labels
   if (!c) return fail(SILH_E_NOMEM, "host allocation failed");
   c->prm = *prm;
   c->t = t;
+  c->t_rows = exact ? prm->n : t;
   c->st = (hipStream_t)stream;
   c->X = X;
   c->labels = labels;
@@ -948,7 +951,21 @@ int pick_pb(silh_ctx* c, P2Args A, uint32_t* mask = nullptr) {
   return choice;
 }
 
-bool launch_p2(silh_ctx* c, const P2Args& A, int pb) {
+// the tables' buffers of a Phase 2 over A's rows, on the given list
+silh_status tab_buffers(silh_ctx* c, const P2Args& A, std::vector<void*>& list, TabPlan& plan, TabBufs& B) {
+  int mr = 1;
+  for (int j = 0; j < c->k; ++j) mr = std::max(mr, c->cnt_h[(size_t)j]);
+  plan = tab_plan(c->prm.metric, A.n, c->d, c->k, c->S_pad, mr, c->pieces);
+  Carve cv;
+  cv.add(&B.chunk, 4 * (size_t)plan.chunks).add(&B.cfirst, (size_t)c->k + 1);
+  cv.add(&B.head, (size_t)plan.group * c->d * tab_head_bytes()).add(&B.Y, plan.knots);
+  cv.add(&B.L, (size_t)plan.group * c->d * tab_cells());
+  cv.add(&B.R, plan.knots * plan.rw).add(&B.XT, (size_t)plan.rows * c->d).add(&B.Wd, (size_t)plan.rows * c->k);
+  return cv.commit(c, list);
+}
+
+bool launch_p2(silh_ctx* c, const P2Args& A, int pb, const TabPlan* plan = nullptr, const TabBufs* tab = nullptr) {
+  if (plan) return launch_phase2_tab(c->st, c->prm.metric, c->DM, A, *plan, *tab);
   if (c->cos) return launch_phase2_cos(c->st, c->mprec, c->DM, A);
   if (!c->mfma) return launch_phase2_valu(c->st, c->prm.metric, c->DM, A);
   return launch_phase2_mfma(c->st, c->mprec, c->DM, A, c->mu, c->Ym, pb);
@@ -977,7 +994,12 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   A.cself = c->cself;
   A.perm = c->perm;
   free_list(c, c->alloc_p2);
-  if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
+  TabPlan plan;
+  TabBufs tab;
+  const bool use_tab = tab_pays(c->prm.metric, A.n, c->k, c->t_rows);
+  if (use_tab) {
+    CHK(tab_buffers(c, A, c->alloc_p2, plan, tab));
+  } else if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
     cv.add(&A.Wpart, (size_t)c->n * c->k);
     CHK(cv.commit(c, c->alloc_p2));
@@ -986,7 +1008,7 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
     const int pb = pick_pb(c, A, c->bmask);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
     mask_clusters(c, A, c->bmask);
-    const bool ok = launch_p2(c, A, pb);
+    const bool ok = launch_p2(c, A, pb, use_tab ? &plan : nullptr, &tab);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
     CHK(L.done());
   }
@@ -1066,7 +1088,12 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   A.cstat = c->cstat;
   A.cself = c->cself;
   A.egid = urows;
-  if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
+  TabPlan plan;
+  TabBufs tab;
+  const bool use_tab = tab_pays(c->prm.metric, mu, c->k, c->t_rows);
+  if (use_tab) {
+    CHK(tab_buffers(c, A, c->alloc_rows, plan, tab));
+  } else if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
     cv.add(&A.Wpart, (size_t)(mu > 0 ? mu : 1) * c->k);
     CHK(cv.commit(c, c->alloc_rows));
@@ -1076,7 +1103,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     const int pb = pick_pb(c, A, mask);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
     mask_clusters(c, A, mask);
-    const bool ok = launch_p2(c, A, pb);
+    const bool ok = launch_p2(c, A, pb, use_tab ? &plan : nullptr, &tab);
     if (!ok) return fail(SILH_E_UNSUPPORTED, "no Phase-2 kernel for metric %d, d=%d", c->prm.metric, c->d);
     CHK(L.done());
   }
@@ -1141,7 +1168,7 @@ int tuned_shape(silh_ctx* c) {
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   if (!c || c->state != 1) return false;
   const bool batch = c->mfma || phase2_valu_jobs_ok(c->prm.metric, c->DM);
-  if (!batch || c->cos) return false;
+  if (!batch || c->cos || tab_pays(c->prm.metric, c->n, c->k, c->t_rows)) return false;
   P2Job J{};
   J.X = c->X;
   J.labels = c->labels;
@@ -1181,6 +1208,10 @@ bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
 bool launch_phase2_class(hipStream_t st, const P2Class& cls, const P2Job* jobs, const int2* items, int nitems) {
   if (cls.mfma) return launch_phase2_mfma_jobs(st, cls.prec, cls.DM, cls.pb, jobs, items, nitems);
   return launch_phase2_valu_jobs(st, cls.metric, cls.DM, jobs, items, nitems);
+}
+
+void set_pieces(silh_ctx* c, bool on) {
+  if (c) c->pieces = on;
 }
 
 silh_status phase2_job_mean(silh_ctx* c, double* mean) {

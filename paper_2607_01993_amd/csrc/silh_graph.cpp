@@ -51,6 +51,7 @@ struct Branch {
   float* brec = nullptr;           // Euclidean bounds: cluster records, group masks
   uint32_t* bmask = nullptr;
   double *bpart = nullptr, *Wpart = nullptr;
+  TabBufs tab;  // Manhattan / Canberra tables
 };
 
 constexpr int kStatusCapacity = kStatusF0 | kStatusPartial | kStatusSample;
@@ -154,7 +155,32 @@ bool alloc_branch(silh_graph* g, Branch& b) {
   }
   if (ok && g->cos) ok = take(g, b.cstat, k * (int64_t)cos_stat_bytes(g->DM));
   if (ok && g->cos && g->mprec == 2) ok = take(g, b.cself, n);
-  if (ok && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
+  // clusterings by tables, and those summed directly at d > 128
+  bool direct = false;
+  TabPlan p;
+  for (size_t i = 0; i < g->ks.size(); ++i) {
+    if (!tab_pays(g->base.metric, n, g->ks[i], g->ts[i])) {
+      direct = true;
+      continue;
+    }
+    const TabPlan q = tab_plan(g->base.metric, n, g->d, g->ks[i], g->S_cap, g->S_cap);
+    p.chunks = std::max(p.chunks, q.chunks);
+    p.group = std::max(p.group, q.group);
+    p.rows = std::max(p.rows, q.rows);
+    p.knots = std::max(p.knots, q.knots);
+    p.rw = q.rw;
+    ok = ok && q.rows > 0;
+  }
+  int64_t wd = 0;
+  for (size_t i = 0; i < g->ks.size(); ++i)
+    if (tab_pays(g->base.metric, n, g->ks[i], g->ts[i]))
+      wd = std::max(wd, tab_plan(g->base.metric, n, g->d, g->ks[i], g->S_cap, g->S_cap).rows * (int64_t)g->ks[i]);
+  if (ok && p.chunks > 0)
+    ok = take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, k + 1) &&
+         take(g, b.tab.head, p.group * g->d * (int64_t)tab_head_bytes()) && take(g, b.tab.Y, (int64_t)p.knots) &&
+         take(g, b.tab.L, p.group * g->d * (int64_t)tab_cells()) &&
+         take(g, b.tab.R, (int64_t)p.knots * p.rw) && take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
+  if (ok && direct && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
   if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
   return ok;
 }
@@ -242,6 +268,9 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
       A.mask = b.bmask;
     }
     if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
+  } else if (tab_pays(metric, n, k, t)) {
+    A.perm = b.perm;
+    if (!launch_phase2_tab(st, metric, DM, A, tab_plan(metric, n, d, k, g->S_cap, g->S_cap), b.tab)) return false;
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
     return false;
   }

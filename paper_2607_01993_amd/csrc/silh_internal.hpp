@@ -112,8 +112,8 @@ struct P2Args {
   const unsigned char* cstat = nullptr;  // cosine: the clusters' records (launch_cos_stats)
   const float* cself = nullptr;    // cosine, fp8: launch_cos_self's values by element id
   const int32_t* egid = nullptr;   // element ids of the rows of X (null: row i is element i)
-  // matrix-core path: the order in which the rows are taken (a permutation of
-  // [0, n), null: as they lie) and the clusters each group of 32 of them
+  // matrix-core path and tables: the order in which the rows are taken (a
+  // permutation of [0, n), null: as they lie); matrix-core path: the clusters each group of 32 of them
   // needs (launch_bounds; null: every cluster)
   const int32_t* perm = nullptr;
   const uint32_t* mask = nullptr;
@@ -211,6 +211,36 @@ void launch_cos_self(hipStream_t st, int DM, const float* Y32, const float* w, c
                      const int32_t* sp_off, int k, int cap, const unsigned char* stat, int n, float* self);
 bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A);
 
+// Manhattan and Canberra by per-coordinate tables (k_phase2_tab.hip): whether
+// they pay for n elements against clusters of about min(t, n / k) sample rows
+bool tab_pays(int metric, int64_t n, int k, int64_t t);
+constexpr int kTabScore = kP2Rows;  // elements per partial of the mean (as the direct kernel)
+struct TabPlan {
+  int64_t chunks = 0, group = 0, rows = 0;  // tables' chunks (at most), chunks and elements taken at once
+  size_t knots = 0;                         // knots of a group's tables (all coordinates)
+  int rw = 0, max_knots = 0;                // floats per record, knots of the longest table
+  bool wait = false;                        // wait for the stream between the pieces
+};
+struct TabBufs {
+  int32_t* chunk = nullptr;   // [4 chunks]
+  int32_t* cfirst = nullptr;  // [k + 1]
+  unsigned char* head = nullptr;  // [group d tab_head_bytes]
+  float* Y = nullptr;         // [knots]
+  float* R = nullptr;         // [knots rw]
+  uint16_t* L = nullptr;      // [group d tab_cells]
+  float* XT = nullptr;        // [rows d]
+  double* Wd = nullptr;       // [k rows]
+};
+// S_pad, max_rows: packed sample rows and the largest cluster's (or bounds);
+// pieces: the elements in pieces of about a millisecond with a wait between
+// them (streams outnumber the hardware queues, so that another stream's short
+// kernels may sit behind a long launch; the results are the same)
+TabPlan tab_plan(int metric, int64_t n, int d, int k, int64_t S_pad, int64_t max_rows, bool pieces = false);
+size_t tab_head_bytes();
+size_t tab_cells();
+size_t tab_bytes(const TabPlan& p, int k, int d);
+bool launch_phase2_tab(hipStream_t st, int metric, int DM, const P2Args& A, const TabPlan& p, const TabBufs& B);
+
 // ---- Phase-2 path of a request ------------------------------------------------
 // cosine: the collapsed sums; Euclidean with matrix-core operands: the MFMA
 // kernel (float32 operands of d > 128 do not fit its registers); else the
@@ -286,6 +316,8 @@ int tuned_shape(silh_ctx* c);
 int64_t sample_rows(const silh_ctx* c);
 // launch work items of requests of one class (workgroup i runs items[i])
 bool launch_phase2_class(hipStream_t st, const P2Class& cls, const P2Job* jobs, const int2* items, int nitems);
+// whether ctx's later Phase-2 launches leave room for other streams' work
+void set_pieces(silh_ctx* c, bool on);
 // after the job's items have all run: the Eq. 9 mean from its block partials
 // (on the context's stream; synchronises it)
 silh_status phase2_job_mean(silh_ctx* c, double* mean);

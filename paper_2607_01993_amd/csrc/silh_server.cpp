@@ -228,7 +228,10 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
   const uint64_t row = (uint64_t)DM * 4 + kp + 24;
   const uint64_t m = r.m > 0 ? (uint64_t)r.m : 0;  // row draws: ids, gathered rows, outputs
   // d > 128 Manhattan / Canberra: float64 partial sums per element and cluster
-  const uint64_t split = (DM > 128 && (r.metric == SILH_MANH || r.metric == SILH_CANB)) ? n * (uint64_t)r.k * 8 : 0;
+  uint64_t split = (DM > 128 && (r.metric == SILH_MANH || r.metric == SILH_CANB)) ? n * (uint64_t)r.k * 8 : 0;
+  // or the tables
+  if (silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
+    split = silh::tab_bytes(silh::tab_plan(r.metric, (int64_t)n, ds.d, r.k, (int64_t)S, (int64_t)S, true), r.k, ds.d);
   // PPS: the W pass keeps its distances for the draw (allocated at their
   // capacity)
   const uint64_t kept = r.sampler == SILH_PPS
@@ -325,6 +328,8 @@ void start_request(silh_server* srv, int w, int64_t ticket, const Dataset& ds, c
     }
     delete a;
   }
+  // this request's own launches: other workers' streams share hardware queues
+  if (s == SILH_OK) silh::set_pieces(ctx, true);
   double mean = 0.0;
   int32_t* rows = nullptr;
   if (s == SILH_OK && r.m > 0) {
