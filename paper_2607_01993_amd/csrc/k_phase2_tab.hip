@@ -25,11 +25,11 @@
 //             is t itself: f can be small next to the sample, and the map's
 //             rounding would not be).
 //
-// Precision: table values from float64 sums of terms good to an ulp of
-// float32, the interpolation in float32 (each result relative to f itself,
-// since every term of the linear part is >= 0 and the knots are exact: rows
-// equal to all of a cluster's values are at distance exactly 0), coordinates
-// added four at a time in float32, then in float64.
+// Precision: table values from float64 sums (Canberra: of float32 terms good
+// to an ulp), kept, interpolated and added up in float64; only the cubic's
+// residual, below a thousandth of f, is float32.  Every term of the linear part
+// is >= 0 and the knots are exact, so results are relative to f itself: rows
+// equal to all of a cluster's values are at distance exactly 0.
 // A table is not used (its rows are summed directly, as in k_p2_valu) where a
 // value is not finite or its magnitude lies outside [2^-30, 2^30] (0 is fine),
 // or the refinement outgrows the table; the elements' values are arbitrary
@@ -72,7 +72,7 @@ struct TabHead {
   int K;        // knots; 0: sum directly
   float Wt;     // sum of the weights
   float Yp, Yn; // Canberra: twice the largest magnitude of the positive / negative values (1 if none)
-  float f0;     // Canberra: f(0)
+  float w0;     // Canberra: the weights of the zeros, f(0) = Wt - w0
   float lo, hi; // Manhattan: first and last knot
   float inv, off;  // cell = z inv + off
   int L;        // steps within a cell
@@ -140,8 +140,8 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
                                                        const int4* __restrict__ chunk,
                                                        const int32_t* __restrict__ cfirst, int k, int q0,
                                                        TabHead* __restrict__ head, float* __restrict__ tabY,
-                                                       float* __restrict__ tabR, uint16_t* __restrict__ tabL) {
-  constexpr int RW = M == kManh ? 2 : 4;  // record width: g, h (, c0, c1)
+                                                       double* __restrict__ tabG, float2* __restrict__ tabC,
+                                                       uint16_t* __restrict__ tabL) {
   __shared__ float ys[kTabRows], ws[kTabRows];
   __shared__ float kn[kTabKnots];
   __shared__ double fk[kTabKnots];
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
   const int r0 = tid * per < m ? tid * per : m, r1 = r0 + per < m ? r0 + per : m;
   const size_t base = tab_base(chunk, q, q0) * (size_t)d + (size_t)c * (size_t)(2 * m + kTabExtra);
   float* oy = tabY + base;
-  float* orec = tabR + base * RW;
+  double2* og = (double2*)tabG + base;
 
   uint16_t* ol = tabL + ((size_t)blockIdx.y * d + c) * kTabCells;
   // the lookup over the K knots kn: cell starts (byte offsets) to ol; the steps to L
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       oy[i] = kn[i];
       if (i + 1 < K) {
         const double ig = 1.0 / ((double)kn[i + 1] - (double)kn[i]);
-        *(float2*)(orec + 2 * (size_t)i) = float2{(float)(fk[i] * ig), (float)(fk[i + 1] * ig)};
+        og[i] = double2{fk[i] * ig, fk[i + 1] * ig};
       }
     }
     const int L = lookup(K);
@@ -420,14 +420,14 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
         const double r2v = f_at(z + 0.75 * gap) - (0.25 * fa + 0.75 * fb);
         const double c1 = (r2v - r1v) * (32.0 / 3.0), c0 = r1v * (16.0 / 3.0) - 0.25 * c1;
         const double ig = 1.0 / gap;
-        *(float4*)(orec + 4 * (size_t)i) = float4{(float)(fa * ig), (float)(fb * ig), (float)(c0 * ig * ig),
-                                                  (float)(c1 * ig * ig * ig)};
+        og[i] = double2{fa * ig, fb * ig};
+        tabC[base + i] = float2{(float)(c0 * ig * ig), (float)(c1 * ig * ig * ig)};
       }
     }
     if (bad) sh_bad = 1;  // two knots fell on one float
     const int L = lookup(K);
     if (tid == 0)
-      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, (float)(wt - wzero), 0.f, 0.f, inv, off, L, {0, 0}};
+      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, (float)wzero, 0.f, 0.f, inv, off, L, {0, 0}};
   }
 }
 
@@ -461,12 +461,13 @@ __global__ __launch_bounds__(256) void k_tab_transpose(const float* __restrict__
 }
 
 // ----------------------------------------------------------------------------
-// n = 1e6, d = 32, k = 16, S = 4,764 Manhattan: Phase 2 5.53 -> 0.70 ms, of
-// which this kernel 0.53 (9.6e11 table evaluations a second); n = 5e5, d = 64,
-// k = 64, S = 9,337 Canberra 39.6 -> 2.98 ms, this kernel 2.51, the tables 0.30.
-// Blocks of 512 threads 0.61 / 2.95 ms, 1024 threads 0.60 / 4.31, 16 elements a
-// thread 0.77 / 3.89, 4 elements 0.53 / 2.68; searching in halves alone 0.85 /
-// 3.59.
+// n = 1e6, d = 32, k = 16, S = 4,764 Manhattan: Phase 2 5.53 -> 0.81 ms, of
+// which this kernel 0.64 (8e11 table evaluations a second); n = 5e5, d = 64,
+// k = 64, S = 9,337 Canberra 39.6 -> 3.4 ms, this kernel 2.91, the tables 0.30.
+// The same with float32 records and sums 0.52 and 2.51 ms, but 1.5 times the
+// direct sums' error at d <= 24, t = 500; so 0.64 and 2.91.  Searching in halves
+// alone 0.85 / 3.59 (float32 records), 512 threads a block 0.61 / 2.95, 1024
+// threads 0.60 / 4.31, 16 elements a thread 0.77 / 3.89.
 //
 // One block per (tile of kEvalT E elements, cluster): for each of the
 // cluster's chunks in the group, and each coordinate, the table into LDS and
@@ -478,20 +479,19 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
                                                      const int4* __restrict__ chunk,
                                                      const int32_t* __restrict__ cfirst, int k, int q0, int q1,
                                                      const TabHead* __restrict__ head,
-                                                     const float* __restrict__ tabY, const float* __restrict__ tabR,
+                                                     const float* __restrict__ tabY, const double* __restrict__ tabG,
+                                                     const float2* __restrict__ tabC,
                                                      const uint16_t* __restrict__ tabL,
                                                      const float* __restrict__ Y32, int DM,
                                                      const float* __restrict__ w, int tiles, int knots,
                                                      double* __restrict__ Wd) {
-  constexpr int RW = M == kManh ? 2 : 4;
-  typedef float rec_t __attribute__((ext_vector_type(RW)));
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   // knots (and kTabPad times +inf, so that steps past the end find nothing),
   // cell starts, records
   float* ly = (float*)lds;
   uint16_t* lc = (uint16_t*)(lds + (size_t)(knots + kTabPad) * 4);
-  unsigned char* lrb = lds + (size_t)(knots + kTabPad) * 4 + kTabCells * 2;
-  rec_t* lr = (rec_t*)lrb;
+  unsigned char* lg = lds + (size_t)(knots + kTabPad) * 4 + kTabCells * 2;  // g, h
+  unsigned char* lp = lg + (size_t)knots * 16;                                // Canberra: c0, c1
   // eight XCDs take the blocks in turn: the blocks of one tile (its k
   // clusters) go to one XCD, whose L2 then holds the tile's columns
   const int b = blockIdx.x, grp = b / (8 * k), in = b - grp * 8 * k;
@@ -513,9 +513,6 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
     const int4 ck = chunk[q];
     const int m = ck.z;
     const size_t base = tab_base(chunk, q, q0) * (size_t)d;
-    float part[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) part[e] = 0.0f;
     for (int c = 0; c < d; ++c) {
       const TabHead hd = head[(size_t)(q - q0) * d + c];
       const int K = hd.K;
@@ -531,7 +528,8 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
         const size_t tb = base + (size_t)c * (size_t)(2 * m + kTabExtra);
         for (int i = threadIdx.x; i < K; i += kEvalT) {
           ly[i] = tabY[tb + i];
-          lr[i] = *(const rec_t*)(tabR + (tb + i) * RW);
+          ((double2*)lg)[i] = ((const double2*)tabG)[tb + i];
+          if (M == kCanb) ((float2*)lp)[i] = tabC[tb + i];
         }
         if (threadIdx.x < kTabPad) ly[K + threadIdx.x] = __builtin_inff();
         if (threadIdx.x < kTabCells / 2)
@@ -599,16 +597,27 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
         for (int e = 0; e < E; ++e) {
           const float* yp = (const float*)((const unsigned char*)ly + at[e]);
           const float ya = yp[0], yb = yp[1];
-          const rec_t r = *(const rec_t*)(lrb + at[e] * RW);
-          const float a = yb - z[e], bb = z[e] - ya;
-          float f = fmaf(a, r.x, bb * r.y);
-          if constexpr (M == kManh) {
-            f = fmaf(hd.Wt, fabsf(x[e] - z[e]), f);
-          } else {
-            f = fmaf(a * bb, fmaf(r.w, bb, r.z), f);
-            f = x[e] == 0.0f ? hd.f0 : f;
+          const double2 g = *(const double2*)(lg + 4 * at[e]);
+          const double zd = (double)z[e];
+          acc[e] = fma((double)yb - zd, g.x, acc[e]);
+          acc[e] = fma(zd - (double)ya, g.y, acc[e]);
+          if constexpr (M == kCanb) {
+            const float2 p = *(const float2*)(lp + 2 * at[e]);
+            const float a = yb - z[e], bb = z[e] - ya;
+            acc[e] += (double)(a * bb * fmaf(p.y, bb, p.x));
           }
-          part[e] += f;
+        }
+        if (M == kManh) {
+          bool out = false;
+#pragma unroll
+          for (int e = 0; e < E; ++e) out = out || x[e] != z[e];
+          if (__any(out)) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = fma((double)hd.Wt, fabs((double)x[e] - (double)z[e]), acc[e]);
+          }
+        } else if (hd.w0 != 0.0f) {  // uniform
+#pragma unroll
+          for (int e = 0; e < E; ++e) acc[e] -= x[e] == 0.0f ? (double)hd.w0 : 0.0;
         }
       } else {
         // directly: 32 rows in float32, then float64
@@ -633,13 +642,6 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
           }
 #pragma unroll
           for (int e = 0; e < E; ++e) acc[e] += (double)s[e];
-        }
-      }
-      if ((c & 3) == 3 || c + 1 == d) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          acc[e] += (double)part[e];
-          part[e] = 0.0f;
         }
       }
     }
@@ -718,7 +720,7 @@ size_t tab_bytes(const TabPlan& p, int k, int d) {
 
 TabPlan tab_plan(int metric, int64_t n, int d, int k, int64_t S_pad, int64_t max_rows, bool pieces) {
   TabPlan p;
-  const int RW = metric == kManh ? 2 : 4;
+  const int RW = metric == kManh ? 4 : 6;  // floats per record: g, h (float64), Canberra c0, c1
   const size_t kb = (size_t)(1 + RW) * sizeof(float);
   p.chunks = ceil_div(S_pad, kTabRows) + k;
   const size_t per = (size_t)kTabKnots * d * kb;  // one chunk's tables at most
@@ -753,7 +755,7 @@ static void launch_eval(hipStream_t st, const TabBufs& B, const TabPlan& p, int 
   const int grid = (int)ceil_div(tiles, 8) * 8 * k;
   const size_t lds = (size_t)p.max_knots * (size_t)(1 + p.rw) * sizeof(float) + 4 * kTabPad + 2 * kTabCells;
   hipLaunchKernelGGL((k_tab_eval<M, E>), dim3((unsigned)grid), dim3(kEvalT), lds, st, B.XT, R, d, (const int4*)B.chunk,
-                     B.cfirst, k, q0, q1, (const TabHead*)B.head, B.Y, B.R, B.L, Y32, DM, w, tiles, p.max_knots, B.Wd);
+                     B.cfirst, k, q0, q1, (const TabHead*)B.head, B.Y, B.G, (const float2*)B.C, B.L, Y32, DM, w, tiles, p.max_knots, B.Wd);
 }
 
 template <int M>
@@ -769,10 +771,10 @@ static void launch_tab(hipStream_t st, int DM, const P2Args& A, const TabPlan& p
       const int64_t nq = p.chunks - q0 < p.group ? p.chunks - q0 : p.group;
       if (i0 == 0 || p.group < p.chunks)
         hipLaunchKernelGGL(k_tab_build<M>, dim3((unsigned)d, (unsigned)nq), dim3(kBuildT), 0, st, A.Y, DM, d, A.w,
-                           (const int4*)B.chunk, B.cfirst, k, (int)q0, (TabHead*)B.head, B.Y, B.R, B.L);
+                           (const int4*)B.chunk, B.cfirst, k, (int)q0, (TabHead*)B.head, B.Y, B.G, (float2*)B.C, B.L);
       // elements per thread: as many as leave eight blocks per CU
       if ((int64_t)R * k >= (int64_t)2048 * kEvalT * 8)
-        launch_eval<M, 8>(st, B, p, R, d, k, (int)q0, (int)(q0 + nq), A.Y, DM, A.w);
+        launch_eval<M, M == kManh ? 4 : 8>(st, B, p, R, d, k, (int)q0, (int)(q0 + nq), A.Y, DM, A.w);
       else if ((int64_t)R * k >= (int64_t)2048 * kEvalT * 2)
         launch_eval<M, 2>(st, B, p, R, d, k, (int)q0, (int)(q0 + nq), A.Y, DM, A.w);
       else

@@ -960,7 +960,7 @@ silh_status tab_buffers(silh_ctx* c, const P2Args& A, std::vector<void*>& list, 
   cv.add(&B.chunk, 4 * (size_t)plan.chunks).add(&B.cfirst, (size_t)c->k + 1);
   cv.add(&B.head, (size_t)plan.group * c->d * tab_head_bytes()).add(&B.Y, plan.knots);
   cv.add(&B.L, (size_t)plan.group * c->d * tab_cells());
-  cv.add(&B.R, plan.knots * plan.rw).add(&B.XT, (size_t)plan.rows * c->d).add(&B.Wd, (size_t)plan.rows * c->k);
+  cv.add(&B.G, 2 * plan.knots).add(&B.C, c->prm.metric == SILH_CANB ? 2 * plan.knots : 0).add(&B.XT, (size_t)plan.rows * c->d).add(&B.Wd, (size_t)plan.rows * c->k);
   return cv.commit(c, list);
 }
 

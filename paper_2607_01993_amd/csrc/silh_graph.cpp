@@ -179,7 +179,8 @@ bool alloc_branch(silh_graph* g, Branch& b) {
     ok = take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, k + 1) &&
          take(g, b.tab.head, p.group * g->d * (int64_t)tab_head_bytes()) && take(g, b.tab.Y, (int64_t)p.knots) &&
          take(g, b.tab.L, p.group * g->d * (int64_t)tab_cells()) &&
-         take(g, b.tab.R, (int64_t)p.knots * p.rw) && take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
+         take(g, b.tab.G, 2 * (int64_t)p.knots) &&
+         take(g, b.tab.C, g->base.metric == SILH_CANB ? 2 * (int64_t)p.knots : 0) && take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
   if (ok && direct && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
   if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
   return ok;

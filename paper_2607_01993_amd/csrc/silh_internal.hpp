@@ -226,7 +226,8 @@ struct TabBufs {
   int32_t* cfirst = nullptr;  // [k + 1]
   unsigned char* head = nullptr;  // [group d tab_head_bytes]
   float* Y = nullptr;         // [knots]
-  float* R = nullptr;         // [knots rw]
+  double* G = nullptr;        // [2 knots]
+  float* C = nullptr;         // [2 knots], Canberra
   uint16_t* L = nullptr;      // [group d tab_cells]
   float* XT = nullptr;        // [rows d]
   double* Wd = nullptr;       // [k rows]
