@@ -17,7 +17,8 @@ namespace silh {
 // not change the value.
 // One coordinate of a float64 distance, in coordinate order with one rounding
 // per operation (the oracle's order), and the final step.
-template <int M>
+// NY: cosine also sums the row's own squared norm (else it is known)
+template <int M, bool NY = true>
 __device__ __forceinline__ void dist64_step(double& acc, double& dot, double& ny2, double xc, double yc) {
   if (M == kEucl) {
     const double df = xc - yc;
@@ -31,7 +32,7 @@ __device__ __forceinline__ void dist64_step(double& acc, double& dot, double& ny
     acc = acc + term;
   } else {
     dot = dot + xc * yc;
-    ny2 = ny2 + yc * yc;
+    if (NY) ny2 = ny2 + yc * yc;
   }
 }
 
@@ -47,23 +48,26 @@ __device__ __forceinline__ double dist64_final(double acc, double dot, double ny
   return acc;
 }
 
-// the element's row in registers
-template <int M, int DM>
-__device__ __forceinline__ double dist64(const float (&x)[DM], double nx2, const double* __restrict__ y) {
-  double acc = 0.0, dot = 0.0, ny2 = 0.0;
-#pragma unroll
-  for (int c = 0; c < DM; ++c) dist64_step<M>(acc, dot, ny2, (double)x[c], y[c]);
-  return dist64_final<M>(acc, dot, ny2, nx2);
+// the final step with both norms known (cosine: sqrt(nx2), sqrt(ny2))
+template <int M>
+__device__ __forceinline__ double dist64_norms(double acc, double dot, double nx, double ny) {
+  if (M == kEucl) return __dsqrt_rn(acc);
+  if (M == kCos) {
+    const double den = nx * ny;
+    const double sim = den > 0.0 ? dot / den : 0.0;
+    const double v = 1.0 - sim;
+    return v < 0.0 ? 0.0 : (v > 2.0 ? 2.0 : v);
+  }
+  return acc;
 }
 
-// the element's row in LDS, one column per lane (x[c * 64])
+// the element's row in registers; cosine: the norms of both rows
 template <int M, int DM>
-__device__ __forceinline__ double dist64_col(const float* __restrict__ x, double nx2,
-                                             const double* __restrict__ y) {
+__device__ __forceinline__ double dist64(const float (&x)[DM], double nx, const double* __restrict__ y, double ny) {
   double acc = 0.0, dot = 0.0, ny2 = 0.0;
-#pragma unroll 16
-  for (int c = 0; c < DM; ++c) dist64_step<M>(acc, dot, ny2, (double)x[c * kWave], y[c]);
-  return dist64_final<M>(acc, dot, ny2, nx2);
+#pragma unroll
+  for (int c = 0; c < DM; ++c) dist64_step<M, false>(acc, dot, ny2, (double)x[c], y[c]);
+  return dist64_norms<M>(acc, dot, nx, ny);
 }
 
 // x row -> registers (vector loads when the row is 16-byte aligned), and its
@@ -96,15 +100,10 @@ __device__ __forceinline__ double load_row(const float* __restrict__ X, int d, i
   return nx2;
 }
 
-// Rows too long for registers (d > 128): each thread streams its row from
-// memory in chunks of kWideC coordinates and evaluates the distances to a
-// group of kWideG rows of the initial sample together (kWideG independent
-// float64 chains, so the wave is not held by one chain's latency); the
-// group's rows sit in LDS, read by every lane at the same address.  Each
-// distance still takes its coordinates in increasing order.
+// Rows too long for registers (d > 128) in the draw: each thread streams its
+// row from memory in chunks of kWideC coordinates.
 constexpr int kWideDM = 256;
 constexpr int kWideC = 32;
-constexpr int kWideG = 8;
 
 // coordinates [c0, c0 + kWideC) of row xr (zero from d on)
 __device__ __forceinline__ void load_chunk_wide(const float* __restrict__ xr, int d, int c0, bool vec,
@@ -143,28 +142,6 @@ __device__ __forceinline__ double row_norm2_wide(const float* __restrict__ xr, i
   return nx2;
 }
 
-// distances from row xr to the kWideG rows ys[e][.] (stride kWideDM)
-template <int M, int DW = kWideDM>
-__device__ __forceinline__ void dist64_group_wide(const float* __restrict__ xr, int d, bool vec, double nx2,
-                                                  const double (*__restrict__ ys)[kWideDM],
-                                                  double (&dv)[kWideG]) {
-  double acc[kWideG], dot[kWideG], ny2[kWideG];
-#pragma unroll
-  for (int e = 0; e < kWideG; ++e) acc[e] = dot[e] = ny2[e] = 0.0;
-  for (int c0 = 0; c0 < DW; c0 += kWideC) {
-    float x[kWideC];
-    load_chunk_wide(xr, d, c0, vec, x);
-#pragma unroll
-    for (int c = 0; c < kWideC; ++c) {
-      const double xc = (double)x[c];
-#pragma unroll
-      for (int e = 0; e < kWideG; ++e) dist64_step<M>(acc[e], dot[e], ny2[e], xc, ys[e][c0 + c]);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < kWideG; ++e) dv[e] = dist64_final<M>(acc[e], dot[e], ny2[e], nx2);
-}
-
 constexpr int kEB = 4;  // initial-sample rows summed together in the W pass
 
 // ----------------------------------------------------------------------------
@@ -196,7 +173,8 @@ __global__ __launch_bounds__(256) void k_f0_pack(const int32_t* __restrict__ per
                                                  const int32_t* __restrict__ pos, int n,
                                                  const float* __restrict__ X, int d, int DM,
                                                  int cap, int64_t* __restrict__ f0_gid,
-                                                 int32_t* __restrict__ f0_cl, double* __restrict__ f0X) {
+                                                 int32_t* __restrict__ f0_cl, double* __restrict__ f0X,
+                                                 double* __restrict__ f0N) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n || !flag[i]) return;
   const int dst = pos[i];
@@ -216,13 +194,18 @@ __global__ __launch_bounds__(256) void k_f0_pack(const int32_t* __restrict__ per
   } else {
     for (int c = 0; c < DM; ++c) yr[c] = c < d ? (double)xr[c] : 0.0;
   }
+  if (f0N != nullptr) {  // cosine: the row's norm, in coordinate order
+    double n2 = 0.0;
+    for (int c = 0; c < d; ++c) n2 = n2 + (double)xr[c] * (double)xr[c];
+    f0N[dst] = __dsqrt_rn(n2);
+  }
 }
 
 void launch_f0_pack(hipStream_t st, const int32_t* perm, const int32_t* slab, const int32_t* flag,
                     const int32_t* pos, int n, const float* X, int d, int DM, int cap, int64_t* f0_gid,
-                    int32_t* f0_cl, double* f0X) {
+                    int32_t* f0_cl, double* f0X, double* f0N) {
   hipLaunchKernelGGL(k_f0_pack, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, perm, slab, flag, pos,
-                     n, X, d, DM, cap, f0_gid, f0_cl, f0X);
+                     n, X, d, DM, cap, f0_gid, f0_cl, f0X, f0N);
 }
 
 // ----------------------------------------------------------------------------
@@ -259,11 +242,17 @@ __global__ __launch_bounds__(256) void k_w_partial(const int32_t* __restrict__ i
                                                    const int32_t* __restrict__ perm,
                                                    const float* __restrict__ X, int d,
                                                    const double* __restrict__ f0X,
+                                                   const double* __restrict__ f0N,
                                                    double* __restrict__ partial, DistStore ds) {
-  static_assert(DM <= 64, "longer rows take k_w_partial_wide");
+  static_assert(DM <= 64, "longer rows take k_w_tile");
   __shared__ double sh[4][kWSlots];  // per wave, per initial element of the current batch
   const int32_t* it = items + (size_t)blockIdx.x * 6;
   const int begin = it[1], end = it[2], f0b = it[3], f0n = it[4], pb = it[5];
+  // the blocks of one item share its initial-sample rows: block y takes rows
+  // [ea, eb), a multiple of kEB rows at a time
+  const int per = ((f0n + (int)gridDim.y - 1) / (int)gridDim.y + kEB - 1) / kEB * kEB;
+  const int ea = (int)blockIdx.y * per, eb = ea + per < f0n ? ea + per : f0n;
+  if (ea >= eb) return;
   // the kept distances of this item's members (cluster it[0]): one column
   // per initial element, members contiguous
   double* keep = nullptr;
@@ -285,16 +274,18 @@ __global__ __launch_bounds__(256) void k_w_partial(const int32_t* __restrict__ i
 #pragma unroll
     for (int c = 0; c < DM; ++c) x[c] = 0.0f;
   }
+  const double nx = M == kCos ? __dsqrt_rn(nx2) : 0.0;
   // per initial element: member distances summed over the wave, then the
   // four wave sums in wave order (one thread per element)
-  for (int s0 = 0; s0 < f0n; s0 += kWSlots) {
-    const int ns = f0n - s0 < kWSlots ? f0n - s0 : kWSlots;
+  for (int s0 = ea; s0 < eb; s0 += kWSlots) {
+    const int ns = eb - s0 < kWSlots ? eb - s0 : kWSlots;
     for (int e0 = 0; e0 < ns; e0 += kEB) {
       double dv[kEB];
 #pragma unroll
       for (int e = 0; e < kEB; ++e) {
         const int ee = e0 + e < ns ? e0 + e : ns - 1;   // repeats a row instead of branching
-        const double v = dist64<M, DM>(x, nx2, f0X + (size_t)(f0b + s0 + ee) * DM);
+        const int row = f0b + s0 + ee;
+        const double v = dist64<M, DM>(x, nx, f0X + (size_t)row * DM, M == kCos ? f0N[row] : 0.0);
         dv[e] = have ? v : 0.0;
         if (keep != nullptr && have && e0 + e < ns) keep[(int64_t)(s0 + e0 + e) * kstride] = v;
       }
@@ -313,49 +304,132 @@ __global__ __launch_bounds__(256) void k_w_partial(const int32_t* __restrict__ i
   }
 }
 
-// d > 64: a 256-thread block per item (one member per thread), each thread
-// streaming its row from memory, the item's initial-sample rows (stride DW)
-// staged kWideG at a time.  At d <= 128 the row would fit the registers, but
-// beside the float64 chains of k_w_partial it leaves one wave per SIMD
+// Wider rows: a 256-thread block per item (one member per thread) takes up to
+// kTE initial-sample rows at a time, one float64 chain each, and goes over the
+// coordinates in chunks of kTC that all its rows share: the members' chunk and
+// the rows' chunk sit in LDS, the former read coalesced, once per kTE rows.
+// At d <= 64 it is no faster than the rows in registers (d = 32 126 against 123
+// us, d = 64 Canberra 570 against 530).  Before, each thread streamed its row
+// from memory for every 8 rows (lines 512 bytes apart, three times over):
+// n = 4e6, d = 128, k = 64 cosine 2.24 -> 1.13 ms (with the initial sample's
+// norms no longer summed anew for every member), n = 5e5, d = 256 Euclidean 438
+// -> 396 us.  What bounds it: float64 operations, 2.15e10 of them for the
+// former (0.74 ms at the 2.9e13 a second measured).  Chunks of 32 coordinates
+// 1.42 ms, 32 rows at a time 1.20.
+constexpr int kTC = 16, kTE = 24, kTLd = kTC + 4;
+
+template <int M>
+__device__ __forceinline__ void step64(double& v, double xc, double yc) {
+  double other = 0.0, ny2 = 0.0;
+  if (M == kCos)
+    dist64_step<M, false>(other, v, ny2, xc, yc);
+  else
+    dist64_step<M, false>(v, other, ny2, xc, yc);
+}
+
 template <int M, int DW>
-__global__ __launch_bounds__(256) void k_w_partial_wide(const int32_t* __restrict__ items,
-                                                        const int32_t* __restrict__ perm,
-                                                        const float* __restrict__ X, int d,
-                                                        const double* __restrict__ f0X,
-                                                        double* __restrict__ partial, DistStore ds) {
-  __shared__ double ys[kWideG][kWideDM];
-  __shared__ double sh[4];
+__global__ __launch_bounds__(256) void k_w_tile(const int32_t* __restrict__ items,
+                                                const int32_t* __restrict__ perm,
+                                                const float* __restrict__ X, int d,
+                                                const double* __restrict__ f0X,
+                                                const double* __restrict__ f0N,
+                                                double* __restrict__ partial, DistStore ds) {
+  static_assert(DW % kTC == 0, "whole chunks");
+  __shared__ __attribute__((aligned(16))) float xt[256 * kTLd];
+  __shared__ __attribute__((aligned(16))) double ys[kTE][kTC];
+  __shared__ double sh[4][kTE];
+  __shared__ int32_t rows[256];
   const int32_t* it = items + (size_t)blockIdx.x * 6;
   const int begin = it[1], end = it[2], f0b = it[3], f0n = it[4], pb = it[5];
+  // block y of the item takes the initial-sample rows [ea, eb)
+  const int per = ((f0n + (int)gridDim.y - 1) / (int)gridDim.y + kEB - 1) / kEB * kEB;
+  const int ea = (int)blockIdx.y * per, eb = ea + per < f0n ? ea + per : f0n;
+  if (ea >= eb) return;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
   double* keep = nullptr;
   int64_t kstride = 0;
-  if (ds.d != nullptr && f0n > 0 && *ds.use) {
+  if (ds.d != nullptr && *ds.use) {
     const int j = it[0];
     kstride = ds.off[j + 1] - ds.off[j];
-    keep = ds.d + ds.base[j] + (begin - ds.off[j]) + threadIdx.x;
+    keep = ds.d + ds.base[j] + (begin - ds.off[j]) + tid;
   }
-  const int r = begin + threadIdx.x;
-  const bool have = r < end;
-  const float* xr = X + (size_t)(have ? perm[r] : 0) * d;
+  const bool have = begin + tid < end;
+  rows[tid] = perm[have ? begin + tid : begin];
   const bool vec = (d & 3) == 0 && ((uintptr_t)X & 15) == 0;
-  const double nx2 = M == kCos ? row_norm2_wide<DW>(xr, d, vec) : 0.0;
-  for (int e0 = 0; e0 < f0n; e0 += kWideG) {
-    const int ne = f0n - e0 < kWideG ? f0n - e0 : kWideG;  // uniform over the block
-    __syncthreads();
-    for (int q = threadIdx.x; q < kWideG * DW; q += 256) {
-      const int e = q / DW, c = q - e * DW;
-      ys[e][c] = f0X[(size_t)(f0b + e0 + (e < ne ? e : ne - 1)) * DW + c];  // past ne: a copy
+  double nx2 = 0.0;  // cosine: summed with the first rows
+  for (int e0 = ea; e0 < eb; e0 += kTE) {
+    const int ne = eb - e0 < kTE ? eb - e0 : kTE;  // uniform over the block
+    double v[kTE];
+#pragma unroll
+    for (int e = 0; e < kTE; ++e) v[e] = 0.0;
+    for (int c0 = 0; c0 < DW; c0 += kTC) {
+      if (c0 >= d) break;  // the rest are exact zeros
+      __syncthreads();
+      if (vec) {
+        for (int q = tid; q < 256 * (kTC / 4); q += 256) {
+          const int r = q / (kTC / 4), c = (q % (kTC / 4)) * 4;
+          float4 x = float4{0.f, 0.f, 0.f, 0.f};
+          if (c0 + c < d) x = *(const float4*)(X + (size_t)rows[r] * d + c0 + c);
+          *(float4*)(xt + r * kTLd + c) = x;
+        }
+      } else {
+        for (int q = tid; q < 256 * kTC; q += 256) {
+          const int r = q / kTC, c = q % kTC;
+          xt[r * kTLd + c] = c0 + c < d ? X[(size_t)rows[r] * d + c0 + c] : 0.0f;
+        }
+      }
+      for (int q = tid; q < kTE * kTC; q += 256) {
+        const int e = q / kTC, c = q % kTC;
+        if (e < ((ne + kEB - 1) & ~(kEB - 1))) ys[e][c] = f0X[(size_t)(f0b + e0 + (e < ne ? e : ne - 1)) * DW + c0 + c];
+      }
+      __syncthreads();
+      for (int c = 0; c < kTC; c += 4) {
+        const float4 x4 = *(const float4*)(xt + tid * kTLd + c);
+        const double x[4] = {(double)x4.x, (double)x4.y, (double)x4.z, (double)x4.w};
+        if (M == kCos && e0 == ea) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) nx2 = nx2 + x[i] * x[i];
+        }
+#pragma unroll
+        for (int g = 0; g < kTE / kEB; ++g) {
+          if (kEB * g < ne) {  // uniform
+#pragma unroll
+            for (int e = kEB * g; e < kEB * (g + 1); ++e) {
+              const double2 ya = *(const double2*)&ys[e][c], yb = *(const double2*)&ys[e][c + 2];
+              step64<M>(v[e], x[0], ya.x);
+              step64<M>(v[e], x[1], ya.y);
+              step64<M>(v[e], x[2], yb.x);
+              step64<M>(v[e], x[3], yb.y);
+            }
+          }
+        }
+      }
+    }
+    const double nx = M == kCos ? __dsqrt_rn(nx2) : 0.0;
+    // distances, kept and summed over the wave four rows at a time, then the
+    // four wave sums in wave order
+#pragma unroll
+    for (int g = 0; g < kTE / kEB; ++g) {
+      if (kEB * g < ne) {  // uniform
+        double dv[kEB];
+#pragma unroll
+        for (int e = 0; e < kEB; ++e) {
+          const int ee = kEB * g + e;
+          const double t = dist64_norms<M>(v[ee], v[ee], nx, M == kCos ? f0N[f0b + e0 + (ee < ne ? ee : ne - 1)] : 0.0);
+          dv[e] = have ? t : 0.0;
+          if (keep != nullptr && have && ee < ne) keep[(int64_t)(e0 + ee) * kstride] = t;
+        }
+        const double w = wave_sum4_f64(dv, lane);
+        const int slot = kEB * g + 2 * ((lane >> 5) & 1) + ((lane >> 4) & 1);
+        if ((lane & 15) == 0) sh[wid][slot] = w;
+      }
     }
     __syncthreads();
-    double dv[kWideG];
-    dist64_group_wide<M, DW>(xr, d, vec, nx2, ys, dv);
+    if (tid < ne) {
+      double t = 0.0;
 #pragma unroll
-    for (int e = 0; e < kWideG; ++e) {
-      if (e < ne) {
-        if (keep != nullptr && have) keep[(int64_t)(e0 + e) * kstride] = dv[e];
-        const double tot = block_sum_f64<256>(have ? dv[e] : 0.0, sh);
-        if (threadIdx.x == 0) partial[pb + e0 + e] = tot;
-      }
+      for (int i = 0; i < 4; ++i) t += sh[i][tid];
+      partial[pb + e0 + tid] = t;
     }
   }
 }
@@ -387,33 +461,40 @@ __global__ __launch_bounds__(256) void k_w_partial_wide(const int32_t* __restric
   } while (0)
 
 void launch_w_partial(hipStream_t st, int metric, int DM, const int32_t* items, int nitems,
-                      const int32_t* perm, const float* X, int d, const double* f0X, double* partial,
-                      DistStore ds) {
+                      const int32_t* perm, const float* X, int d, const double* f0X, const double* f0N,
+                      double* partial, DistStore ds) {
   if (nitems <= 0) return;
-  if (DM == kWideDM || DM == 128) {
-#define SILH_WP(MM)                                                                                       \
-  do {                                                                                                    \
-    if (DM == 128)                                                                                        \
-      hipLaunchKernelGGL((k_w_partial_wide<MM, 128>), dim3(nitems), dim3(256), 0, st, items, perm, X, d, f0X, \
-                         partial, ds);                                                                    \
-    else                                                                                                  \
-      hipLaunchKernelGGL((k_w_partial_wide<MM, kWideDM>), dim3(nitems), dim3(256), 0, st, items, perm, X, d, \
-                         f0X, partial, ds);                                                               \
+  // Few items leave the chip idle (a block per item, 4 waves): the item's
+  // initial-sample rows, about 20, then go to up to 5 blocks, the same sums:
+  // n = 1e5, d = 64 61 -> 39 us, n = 2,000, d = 8 13.0 -> 5.5.  From 2,048 items on
+  // (1,024 where a block holds most of a CU) one block per item fills the chip.
+  const int ny = nitems >= 2048 || (nitems >= 1024 && DM >= 128) ? 1 : (nitems >= 1024 ? 2 : 5);
+  const dim3 grid((unsigned)nitems, (unsigned)ny);
+  if (DM >= 128) {
+#define SILH_WT(MM, DD)                                                                                       \
+  hipLaunchKernelGGL((k_w_tile<MM, DD>), grid, dim3(256), 0, st, items, perm, X, d, f0X, f0N, partial, ds)
+#define SILH_WTM(MM)                   \
+  do {                                 \
+    if (DM == 128)                     \
+      SILH_WT(MM, 128);                \
+    else                               \
+      SILH_WT(MM, kWideDM);            \
   } while (0)
     switch (metric) {
-      case kEucl: SILH_WP(kEucl); break;
-      case kCos: SILH_WP(kCos); break;
-      case kManh: SILH_WP(kManh); break;
-      default: SILH_WP(kCanb); break;
+      case kEucl: SILH_WTM(kEucl); break;
+      case kCos: SILH_WTM(kCos); break;
+      case kManh: SILH_WTM(kManh); break;
+      default: SILH_WTM(kCanb); break;
     }
-#undef SILH_WP
+#undef SILH_WTM
+#undef SILH_WT
     return;
   }
   // DM <= 64 here (the row in registers beside the float64 chains)
   switch (metric * 8 + (DM == 8 ? 0 : DM == 16 ? 1 : DM == 32 ? 2 : 3)) {
 #define SILH_WPS(CASE, MM, DD)                                                                            \
   case CASE:                                                                                              \
-    hipLaunchKernelGGL((k_w_partial<MM, DD>), dim3(nitems), dim3(256), 0, st, items, perm, X, d, f0X, partial, ds); \
+    hipLaunchKernelGGL((k_w_partial<MM, DD>), grid, dim3(256), 0, st, items, perm, X, d, f0X, f0N, partial, ds); \
     break;
     SILH_WPS(0, kEucl, 8) SILH_WPS(1, kEucl, 16) SILH_WPS(2, kEucl, 32) SILH_WPS(3, kEucl, 64)
     SILH_WPS(8, kCos, 8) SILH_WPS(9, kCos, 16) SILH_WPS(10, kCos, 32) SILH_WPS(11, kCos, 64)
@@ -592,8 +673,8 @@ __global__ __launch_bounds__(256) void k_draw(int sampler, const int32_t* __rest
 }
 
 // d > 128: the kept distances where the W pass kept them (as k_draw), else
-// the element's row streamed against its cluster's initial sample, kWideG
-// rows at a time straight from memory
+// the element's row streamed against its cluster's initial sample, row after
+// row, straight from memory
 template <int M>
 __global__ __launch_bounds__(256) void k_draw_wide(int sampler, const int32_t* __restrict__ perm,
                                                    const int32_t* __restrict__ slab, int n,

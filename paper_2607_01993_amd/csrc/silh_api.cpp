@@ -121,7 +121,7 @@ struct silh_ctx {
   int* p1_status = nullptr;  // capacity bits of the device-built W work items
   int p1_status_h = 0;
   int64_t *f0_gid = nullptr, *gid_view = nullptr;
-  double *f0X = nullptr, *W0 = nullptr, *partial = nullptr, *p_gid = nullptr;
+  double *f0N = nullptr, *f0X = nullptr, *W0 = nullptr, *partial = nullptr, *p_gid = nullptr;
   int32_t *s_off = nullptr, *sp_off = nullptr, *cnt = nullptr, *gid_pk = nullptr;
   float *w32 = nullptr, *aux32 = nullptr, *Y32 = nullptr, *mu = nullptr;
   float* brec = nullptr;      // Euclidean on the matrix cores: the clusters' bound records
@@ -706,7 +706,7 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   c->f0_cl = c->items = c->citem_first = c->citem_count = c->gid_pk = c->imeta = nullptr;
   c->ibase = c->dbase = nullptr;
   c->dkeep = nullptr;
-  c->f0X = c->W0 = c->partial = nullptr;
+  c->f0N = c->f0X = c->W0 = c->partial = nullptr;
   c->w32 = c->aux32 = c->Y32 = c->mu = nullptr;
   c->Ym = nullptr;
   c->cstat = nullptr;
@@ -768,6 +768,7 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
       cv.add(&c->W0, (size_t)f0_cap).add(&c->items, (size_t)items_cap * 6).add(&c->citem_first, (size_t)k);
       cv.add(&c->citem_count, (size_t)k).add(&c->partial, (size_t)part_cap).add(&c->ibase, (size_t)k);
       cv.add(&c->imeta, 2);
+      if (c->rn) cv.add(&c->f0N, (size_t)f0_cap);
       if (dist_cap > 0) cv.add(&c->dbase, (size_t)k).add(&c->dkeep, (size_t)dist_cap);
       CHK(cv.commit(c, c->alloc_sample));
     }
@@ -778,7 +779,7 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
     {
       Launch L(c, K_F0_PACK);
       launch_f0_pack(c->st, c->perm, c->slab, c->flag, c->pos, n, c->X, d, c->DM, (int)f0_cap, c->f0_gid,
-                     c->f0_cl, c->f0X);
+                     c->f0_cl, c->f0X, c->f0N);
       CHK(L.done());
     }
     nitems = (int)items_cap;  // the unused item slots are empty
@@ -813,13 +814,14 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
       cv.add(&c->f0_gid, (size_t)c->F0).add(&c->f0_cl, (size_t)c->F0).add(&c->f0X, (size_t)c->F0 * c->DM);
       cv.add(&c->W0, (size_t)c->F0).add(&c->items, c->items_h.size()).add(&c->citem_first, (size_t)k);
       cv.add(&c->citem_count, (size_t)k).add(&c->partial, (size_t)pbase);
+      if (c->rn) cv.add(&c->f0N, (size_t)c->F0);
       CHK(cv.commit(c, c->alloc_sample));
     }
     if (c->F0 > 0) {
       {
         Launch L(c, K_F0_PACK);
         launch_f0_pack(c->st, c->perm, c->slab, c->flag, c->pos, n, c->X, d, c->DM, (int)c->F0, c->f0_gid,
-                       c->f0_cl, c->f0X);
+                       c->f0_cl, c->f0X, c->f0N);
         CHK(L.done());
       }
       CHK(h2d(c, c->items, c->items_h));
@@ -837,8 +839,8 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
   if (pps && nitems > 0 && f0_rows > 0) {
     {
       Launch L(c, K_W_PARTIAL);
-      launch_w_partial(c->st, c->prm.metric, c->DM, c->items, nitems, c->perm, c->X, d, c->f0X, c->partial,
-                       ds);
+      launch_w_partial(c->st, c->prm.metric, c->DM, c->items, nitems, c->perm, c->X, d, c->f0X, c->f0N,
+                       c->partial, ds);
       CHK(L.done());
     }
     {

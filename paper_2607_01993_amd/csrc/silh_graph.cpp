@@ -37,7 +37,7 @@ struct Branch {
   double* p_gid = nullptr;
   int64_t* f0_gid = nullptr;
   int32_t* f0_cl = nullptr;
-  double *f0X = nullptr, *W0 = nullptr, *partial = nullptr;
+  double *f0N = nullptr, *f0X = nullptr, *W0 = nullptr, *partial = nullptr;
   int32_t *items = nullptr, *citem_first = nullptr, *citem_count = nullptr, *meta = nullptr;
   int64_t* ibase = nullptr;
   int64_t* dbase = nullptr;
@@ -142,7 +142,7 @@ bool alloc_branch(silh_graph* g, Branch& b) {
             take(g, b.pos, n + 1) && take(g, b.scan_tmp, ceil_div(n, kScanTile) + 1) &&
             take(g, b.f0_off, k + 1) && take(g, b.s_off, k + 1) && take(g, b.sp_off, k + 1) &&
             take(g, b.cnt, k) && take(g, b.p_gid, n) && take(g, b.f0_gid, F0) && take(g, b.f0_cl, F0) &&
-            take(g, b.f0X, F0 * DM) && take(g, b.W0, F0) && take(g, b.partial, g->part_cap) &&
+            take(g, b.f0X, F0 * DM) && (g->base.metric != SILH_COS || take(g, b.f0N, F0)) && take(g, b.W0, F0) && take(g, b.partial, g->part_cap) &&
             take(g, b.items, g->items_cap * 6) && take(g, b.citem_first, k) && take(g, b.citem_count, k) &&
             take(g, b.meta, 2) && take(g, b.ibase, k) && take(g, b.gid_view, S) && take(g, b.gid_pk, S) &&
             take(g, b.w32, S) && take(g, b.aux32, S) && take(g, b.Y32, S * DM) &&
@@ -220,8 +220,8 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     launch_gather_at(st, b.pos, b.off, k, b.f0_off);
     launch_f0_items(st, b.csize, b.off, b.f0_off, k, t, g->chunk, (int)g->F0_cap, g->part_cap, (int)g->items_cap,
                     b.citem_first, b.citem_count, b.ibase, b.meta, b.items, b.status, b.dbase, g->dist_cap);
-    launch_f0_pack(st, b.perm, b.slab, b.flag, b.pos, n, g->X, d, DM, (int)g->F0_cap, b.f0_gid, b.f0_cl, b.f0X);
-    launch_w_partial(st, metric, DM, b.items, (int)g->items_cap, b.perm, g->X, d, b.f0X, b.partial, ds);
+    launch_f0_pack(st, b.perm, b.slab, b.flag, b.pos, n, g->X, d, DM, (int)g->F0_cap, b.f0_gid, b.f0_cl, b.f0X, b.f0N);
+    launch_w_partial(st, metric, DM, b.items, (int)g->items_cap, b.perm, g->X, d, b.f0X, b.f0N, b.partial, ds);
     launch_w_final(st, b.f0_cl, (int)g->F0_cap, b.f0_off, k, b.citem_first, b.citem_count, b.items, b.partial,
                    b.W0);
   } else {

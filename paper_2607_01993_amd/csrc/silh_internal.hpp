@@ -41,10 +41,11 @@ void launch_gather_at(hipStream_t st, const int32_t* scan, const int32_t* off, i
 // ---- Phase 1 -----------------------------------------------------------------
 void launch_f0_flag(hipStream_t st, const int32_t* perm, const int32_t* slab, int n,
                     const int32_t* csize, const double* q, int64_t t, uint64_t seed, int32_t* flag);
-// rows past `cap` (the capacity of f0_gid / f0_cl / f0X) are not written
+// rows past `cap` (the capacity of f0_gid / f0_cl / f0X / f0N) are not written;
+// f0N (cosine, else null): the rows' norms
 void launch_f0_pack(hipStream_t st, const int32_t* perm, const int32_t* slab, const int32_t* flag,
                     const int32_t* pos, int n, const float* X, int d, int DM, int cap, int64_t* f0_gid,
-                    int32_t* f0_cl, double* f0X);
+                    int32_t* f0_cl, double* f0X, double* f0N = nullptr);
 // float64 distances from the members of each cluster to its initial-sample
 // rows, kept by the W pass for the draw (which then reads them instead of
 // evaluating them again): the distance of the member at sorted position i of
@@ -61,8 +62,8 @@ struct DistStore {
 // first F0 index of the cluster, |F0_j|, base in `partial`)
 // f0X rows have stride DM (zero-padded)
 void launch_w_partial(hipStream_t st, int metric, int DM, const int32_t* items, int nitems,
-                      const int32_t* perm, const float* X, int d, const double* f0X, double* partial,
-                      DistStore ds = {});
+                      const int32_t* perm, const float* X, int d, const double* f0X, const double* f0N,
+                      double* partial, DistStore ds = {});
 // F0 blocks at most; those at or past f0_off[k] return at once
 void launch_w_final(hipStream_t st, const int32_t* f0_cl, int F0, const int32_t* f0_off, int k,
                     const int32_t* citem_first, const int32_t* citem_count, const int32_t* items,
