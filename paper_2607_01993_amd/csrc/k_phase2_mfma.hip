@@ -444,7 +444,10 @@ constexpr int kMinWaves = (PB == 2 || DM < 32 || (TBX == 2 && MCfg<P, DM>::LDS))
 template <int P, int DM>
 constexpr int kTBDefault = (P == 1 && DM >= 64) ? 2 : 1;
 
-template <int P, int DM, int PB, int TBX>
+// SPLIT (register path): the block's four waves hold the same 32 PB elements
+// and take every fourth of the clusters each, so that few elements still fill
+// the chip; the waves' own sums and smallest others meet in LDS.
+template <int P, int DM, int PB, int TBX, bool SPLIT>
 __device__ __forceinline__ void p2_mfma_block(
     const int blk, const float* __restrict__ X, int n, int d, const int32_t* __restrict__ labels,
     const void* __restrict__ Ym, const float* __restrict__ w,
@@ -501,7 +504,9 @@ __device__ __forceinline__ void p2_mfma_block(
   const int h = lane >> 5;
   const int col = lane & 31;
   // PB blocks of 32 elements per wave share every sample tile
-  const int P0 = __builtin_amdgcn_readfirstlane((blk * 4 + (threadIdx.x >> 6)) * 32 * PB);
+  static_assert(!SPLIT || !kLds, "the LDS path's waves share their tiles");
+  const int P0 =
+      __builtin_amdgcn_readfirstlane((SPLIT ? blk : blk * 4 + (int)(threadIdx.x >> 6)) * 32 * PB);
   const uint32_t lane_off = (uint32_t)((col * C::KP + h * C::FOFF) * C::ELEM);  // bytes
   // kT: this lane's rows of a tile's per-row values (weights)
   const int wr = wrow(lane);
@@ -668,8 +673,13 @@ __device__ __forceinline__ void p2_mfma_block(
     }
   }
 
-  for (int j = next_cluster(0), jn; j < k; j = jn) {
-    jn = next_cluster(j + 1);
+  // split: the wave's clusters are the w-th, w + 4-th, ... of them
+  auto skip = [&](int j, int m) {
+    for (; m > 0 && j < k; --m) j = next_cluster(j + 1);
+    return j;
+  };
+  for (int j = SPLIT ? skip(next_cluster(0), wave) : next_cluster(0), jn; j < k; j = jn) {
+    jn = SPLIT ? skip(j, 4) : next_cluster(j + 1);
     // ---- A operands for cluster j: x~ = x - mu_j (mu zero-padded to KP),
     // rounded to the input precision, plus the augmentation; m is this
     // lane's half of mu_j (in memory, or in the LDS slot of the cluster's
@@ -1044,6 +1054,31 @@ __device__ __forceinline__ void p2_mfma_block(
   // the loads issued ahead of the last stages land in LDS before the block
   // may end (its LDS can then go to another block)
   if constexpr (kLds) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (SPLIT) {
+    // own sum (zero in the waves that did not have the cluster) and smallest
+    // other of each wave's clusters, in wave order
+    __shared__ double shw[4][PB][32], shn[4][PB][32], shd[4][PB][32];
+#pragma unroll
+    for (int b = 0; b < PB; ++b)
+      if (h == 0) {
+        shw[wave][b][col] = w_own[b];
+        shn[wave][b][col] = bnum[b];
+        shd[wave][b][col] = bden[b];
+      }
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int b = 0; b < PB; ++b)
+#pragma unroll
+      for (int i = 1; i < 4; ++i) {
+        w_own[b] += shw[i][b][col];
+        const double num = shn[i][b][col], den = shd[i][b][col];
+        if (den > 0.0 && num * bden[b] < bnum[b] * den) {
+          bnum[b] = num;
+          bden[b] = den;
+        }
+      }
+  }
 #pragma unroll
   for (int b = 0; b < PB; ++b) {
     const int szo = csize[own[b]];
@@ -1059,8 +1094,13 @@ __device__ __forceinline__ void p2_mfma_block(
     }
     // a float64 partial per 32 elements (fixed tree over the wave) ...
     const double part = wave_sum_f64(writer ? s : 0.0);
-    if (lane == 0) sh32[(threadIdx.x >> 6) * PB + b] = part;
+    if constexpr (SPLIT) {
+      if (lane == 0 && P0 + 32 * b < n) bpart[blk * PB + b] = part;  // (launch_mean adds four)
+    } else {
+      if (lane == 0) sh32[(threadIdx.x >> 6) * PB + b] = part;
+    }
   }
+  if constexpr (SPLIT) return;
   // ... and per 128 elements the four of them added in element order, so the
   // partials, and the mean, do not depend on the block shape PB
   __syncthreads();
@@ -1072,7 +1112,7 @@ __device__ __forceinline__ void p2_mfma_block(
   }
 }
 
-template <int P, int DM, int PB, int TBX>
+template <int P, int DM, int PB, int TBX, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P, DM, PB, TBX>))) void k_p2_mfma(
     const float* __restrict__ X, int n, int d, const int32_t* __restrict__ labels,
     const void* __restrict__ Ym, const float* __restrict__ w,
@@ -1081,7 +1121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
     float* __restrict__ a_out, float* __restrict__ b_out, float* __restrict__ s_out,
     float* __restrict__ What, double* __restrict__ bpart, const float* __restrict__ Y32,
     const int32_t* __restrict__ perm, const uint32_t* __restrict__ mask) {
-  p2_mfma_block<P, DM, PB, TBX>(blockIdx.x, X, n, d, labels, Ym, w, sp_off, cnt, csize, k, mu, a_out, b_out,
+  p2_mfma_block<P, DM, PB, TBX, SPLIT>(blockIdx.x, X, n, d, labels, Ym, w, sp_off, cnt, csize, k, mu, a_out, b_out,
                               s_out, What, bpart, Y32, perm, mask);
 }
 
@@ -1102,7 +1142,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
   const int jx = ((citem_ptr)items)[2 * blockIdx.x];
   const int blk = ((citem_ptr)items)[2 * blockIdx.x + 1];
   const auto& J = ((cjob_ptr)jobs)[jx];
-  p2_mfma_block<P, DM, PB, TBX>(blk, J.X, J.n, J.d, J.labels, J.Ym, J.w, J.sp_off, J.cnt, J.csize, J.k, J.mu,
+  p2_mfma_block<P, DM, PB, TBX, false>(blk, J.X, J.n, J.d, J.labels, J.Ym, J.w, J.sp_off, J.cnt, J.csize, J.k, J.mu,
                               J.a, J.b, J.s, J.What, J.bpart, J.Y32, J.perm, J.mask);
 }
 
@@ -1116,6 +1156,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
 //     LDS path only).
 // The arithmetic of every element, and the 128-element partials of the
 // mean, are the same in every shape.
+// Split blocks up to this many elements, past which unsplit ones fill the chip:
+// Phase 2 unsplit -> split, exact n = 40,000, d = 16, k = 9 float32 6.72 -> 4.83
+// ms, n = 150,001, d = 16, k = 100 bf16 476 -> 360 us, n = 2,000, d = 8, k = 4
+// float32 14.7 -> 8.7, n = 200,000, d = 32 float32 sums 798 -> 758, n = 101,000
+// rows, d = 32 37.5 -> 36.4; n = 1e6, d = 32, k = 16 195 -> 284.
+constexpr int64_t kSplitN = (int64_t)1 << 18;
 int mfma_pb_default(int prec, int DM) { return (prec == 0 && DM <= 32) ? 2 : 1; }
 int mfma_pb_max(int, int DM) { return DM > 64 ? 1 : 2; }
 int mfma_shapes(int prec, int DM, int* ids) {
@@ -1128,8 +1174,16 @@ int mfma_shapes(int prec, int DM, int* ids) {
 
 template <int P, int DM, int PB, int TBX>
 static void launch_mfma_pb(hipStream_t st, const P2Args& A, const float* mu, const void* Ym) {
+  if constexpr (!MCfg<P, DM>::LDS) {
+    if (A.split) {
+      hipLaunchKernelGGL((k_p2_mfma<P, DM, PB, TBX, true>), dim3((int)ceil_div(A.n, 32 * PB)), dim3(256), 0, st, A.X,
+                         A.n, A.d, A.labels, Ym, A.w, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart,
+                         A.Y, A.perm, A.mask);
+      return;
+    }
+  }
   const int blocks = (int)ceil_div(A.n, 128 * PB);
-  hipLaunchKernelGGL((k_p2_mfma<P, DM, PB, TBX>), dim3(blocks), dim3(256), 0, st, A.X, A.n, A.d, A.labels, Ym,
+  hipLaunchKernelGGL((k_p2_mfma<P, DM, PB, TBX, false>), dim3(blocks), dim3(256), 0, st, A.X, A.n, A.d, A.labels, Ym,
                      A.w, A.sp_off, A.cnt, A.csize, A.k, mu, A.a, A.b, A.s, A.What, A.bpart, A.Y, A.perm,
                      A.mask);
 }
@@ -1213,5 +1267,6 @@ bool launch_phase2_mfma_jobs(hipStream_t st, int prec, int DM, int shape, const 
 }
 
 int phase2_mfma_rows(int, int) { return 128; }
+bool mfma_split(int prec, int DM, int64_t n, int k) { return !mfma_lds_path(prec, DM) && k >= 4 && n <= kSplitN; }
 
 }  // namespace silh

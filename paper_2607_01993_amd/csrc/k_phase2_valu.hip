@@ -349,11 +349,22 @@ __device__ __forceinline__ void neumaier_add(double& s, double& c, double v) {
 }
 
 __global__ __launch_bounds__(256) void k_mean(const double* __restrict__ bpart, int nb, int64_t n,
-                                              double* __restrict__ out) {
+                                              double* __restrict__ out, int nq) {
   __shared__ double ss[256], cc[256];
   double s = 0.0, c = 0.0;
+  if (nq > 0) {
+    // four partials to one, as a block of 128 elements adds its own
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nb; i += 256) {
+      double p[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] = 4 * i + e < nq ? bpart[4 * i + e] : 0.0;
+      neumaier_add(s, c, ((p[0] + p[1]) + p[2]) + p[3]);
+    }
+  } else {
 #pragma unroll 8
-  for (int i = threadIdx.x; i < nb; i += 256) neumaier_add(s, c, bpart[i]);  // loads issued ahead
+    for (int i = threadIdx.x; i < nb; i += 256) neumaier_add(s, c, bpart[i]);  // loads issued ahead
+  }
   ss[threadIdx.x] = s;
   cc[threadIdx.x] = c;
   __syncthreads();
@@ -369,8 +380,8 @@ __global__ __launch_bounds__(256) void k_mean(const double* __restrict__ bpart, 
   if (threadIdx.x == 0) out[0] = (ss[0] + cc[0]) / (double)n;
 }
 
-void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out) {
-  hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, bpart, nb, n, out);
+void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq) {
+  hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, bpart, nb, n, out, nq);
 }
 
 }  // namespace silh

@@ -714,7 +714,7 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   c->brec = nullptr;
   c->bmask = nullptr;
   const int n = c->n, k = c->k;
-  const int nb = (int)ceil_div(n, c->p2_rows);
+  const int nb = (int)ceil_div(n, c->mfma ? 32 : c->p2_rows);  // (32: split blocks)
   Carve cv;
   cv.add(&c->flag, (size_t)n).add(&c->pos, (size_t)n + 1).add(&c->scan_tmp, (size_t)ceil_div(n, kScanTile) + 1);
   // f0_off, s_off and the Phase-1 status are read back together (one copy)
@@ -995,6 +995,7 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   A.cstat = c->cstat;
   A.cself = c->cself;
   A.perm = c->perm;
+  A.split = c->mfma && mfma_split(c->mprec, c->DM, c->n, c->k);
   free_list(c, c->alloc_p2);
   TabPlan plan;
   TabBufs tab;
@@ -1017,7 +1018,8 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   if (mean_host) {
     {
       Launch L(c, K_MEAN);
-      launch_mean(c->st, c->bpart, (int)ceil_div(c->n, c->p2_rows), c->n, c->mean_d);
+      launch_mean(c->st, c->bpart, (int)ceil_div(c->n, c->p2_rows), c->n, c->mean_d,
+                  A.split ? (int)ceil_div(c->n, 32) : 0);
       CHK(L.done());
     }
     CHK(fetch(c, {{&c->mean_h, c->mean_d, sizeof(double)}}));
@@ -1047,7 +1049,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     cv.add(&mark, (size_t)n).add(&flag, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
     cv.add(&urows, (size_t)cap).add(&bad, 1).add(&Xs, (size_t)cap * d).add(&ls, (size_t)cap);
     cv.add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
-    cv.add(&bpu, (size_t)ceil_div(cap, c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
+    cv.add(&bpu, (size_t)ceil_div(cap, c->mfma ? 32 : c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
     if (c->rn) cv.add(&rnu, (size_t)cap);
     if (c->brec) cv.add(&mask, bound_mask_words(cap, c->k));
     CHK(cv.commit(c, c->alloc_rows));
@@ -1090,6 +1092,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   A.cstat = c->cstat;
   A.cself = c->cself;
   A.egid = urows;
+  A.split = c->mfma && mfma_split(c->mprec, c->DM, mu, c->k);
   TabPlan plan;
   TabBufs tab;
   const bool use_tab = tab_pays(c->prm.metric, mu, c->k, c->t_rows);

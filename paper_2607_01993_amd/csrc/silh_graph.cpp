@@ -146,7 +146,7 @@ bool alloc_branch(silh_graph* g, Branch& b) {
             take(g, b.items, g->items_cap * 6) && take(g, b.citem_first, k) && take(g, b.citem_count, k) &&
             take(g, b.meta, 2) && take(g, b.ibase, k) && take(g, b.gid_view, S) && take(g, b.gid_pk, S) &&
             take(g, b.w32, S) && take(g, b.aux32, S) && take(g, b.Y32, S * DM) &&
-            take(g, b.bpart, ceil_div(n, g->p2_rows));
+            take(g, b.bpart, ceil_div(n, g->mfma ? 32 : g->p2_rows));
   if (ok && g->mfma) {
     unsigned char* ym = nullptr;
     ok = take(g, b.mu, mfma_mu_floats(g->mprec, g->DM, k)) && take(g, ym, S * (size_t)mfma_row_bytes(g->mprec, g->DM));
@@ -264,6 +264,7 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     launch_center(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, b.csize, k, b.mu, bounds ? b.brec : nullptr);
     if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym)) return false;
     A.perm = b.perm;
+    A.split = mfma_split(g->mprec, DM, n, k);
     if (bounds) {
       launch_bounds(st, DM, A.X, n, d, lab, b.perm, b.brec, k, b.bmask);
       A.mask = b.bmask;
@@ -275,7 +276,7 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
     return false;
   }
-  launch_mean(st, b.bpart, (int)ceil_div(n, g->p2_rows), n, g->means_d + i);
+  launch_mean(st, b.bpart, (int)ceil_div(n, g->p2_rows), n, g->means_d + i, A.split ? (int)ceil_div(n, 32) : 0);
   launch_put_status(st, b.status, g->status_d + i);
   return hipGetLastError() == hipSuccess;
 }

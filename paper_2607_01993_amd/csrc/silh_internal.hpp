@@ -118,6 +118,9 @@ struct P2Args {
   // needs (launch_bounds; null: every cluster)
   const int32_t* perm = nullptr;
   const uint32_t* mask = nullptr;
+  // matrix-core path: split blocks (mfma_split), whose bpart holds a partial per
+  // 32 elements, for launch_mean's quads
+  bool split = false;
 };
 // One request's Phase-2 launch as a work source of a multi-request launch
 // (the arguments of P2Args and of the matrix-core operands, in device memory).
@@ -180,6 +183,8 @@ int phase2_mfma_rows(int prec, int DM);
 // stage (the LDS-staged shapes only).  The default choice of blocks per wave:
 int mfma_pb_default(int prec, int DM);
 int mfma_pb_max(int prec, int DM);
+// whether a launch over n elements splits the clusters over a block's waves
+bool mfma_split(int prec, int DM, int64_t n, int k);
 bool mfma_lds_path(int prec, int DM);
 // the shape ids valid for (prec, DM) into ids[0..2]; returns their count
 int mfma_shapes(int prec, int DM, int* ids);
@@ -254,7 +259,8 @@ int operand_type(int prec);
 int phase2_rows(int path, int metric, int mprec, int DM);
 
 // ---- global mean -------------------------------------------------------------
-void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out);
+// quads: bpart holds nq partials, of which every four are added first (in order)
+void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq = 0);
 
 // ---- device-side sizes for the capturable pipeline (k_graph.hip) ------------
 // bits of a clustering's status word

@@ -97,7 +97,7 @@ struct Bufs {
 
 struct Shape {
   int n, d, k, DM, mprec, p2_rows, seg, units;
-  bool mfma, split, cos, bounds;
+  bool mfma, split, cos, bounds, split32;
   int64_t S_cap;
 };
 
@@ -107,7 +107,7 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
   sl.add(&b.perm, n).add(&b.slab, n).add(&b.q, k).add(&b.flag, n).add(&b.pos, n + 1);
   sl.add(&b.scan_tmp, ceil_div(n, kScanTile) + 1).add(&b.s_off, k + 1).add(&b.sp_off, k + 1).add(&b.cnt, k);
   sl.add(&b.p_gid, n).add(&b.gid_view, s.S_cap).add(&b.gid_pk, s.S_cap).add(&b.w32, s.S_cap);
-  sl.add(&b.aux32, s.S_cap).add(&b.Y32, s.S_cap * s.DM).add(&b.bpart, ceil_div(n, s.p2_rows));
+  sl.add(&b.aux32, s.S_cap).add(&b.Y32, s.S_cap * s.DM).add(&b.bpart, ceil_div(n, s.split32 ? 32 : s.p2_rows));
   if (s.mfma) {
     sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
   }
@@ -140,6 +140,7 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   sh.seg = sort_seg(sh.n, sh.k);
   sh.units = (int)ceil_div(sh.n, sh.seg);
   sh.S_cap = (int64_t)sh.n + (int64_t)kSamplePad * sh.k;  // every element, each cluster padded
+  sh.split32 = sh.mfma && mfma_split(sh.mprec, sh.DM, sh.n, sh.k);
   // the bounds (the same results) where their buffers fit too
   sh.bounds = sh.mfma && bounds_pay(sh.n, sh.k, sh.n);
   if (sh.bounds) {
@@ -228,6 +229,7 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   } else if (sh.mfma) {
     launch_center(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, B.csize, k, B.mu, sh.bounds ? B.brec : nullptr);
     A.perm = B.perm;
+    A.split = sh.split32;
     ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym);
     if (ok && sh.bounds) {
       launch_bounds(st, DM, X, n, d, labels, B.perm, B.brec, k, B.bmask);
@@ -238,7 +240,7 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
     ok = launch_phase2_valu(st, metric, DM, A);
   }
   if (!ok) return set_error(SILH_E_UNSUPPORTED, "no Phase-2 kernel for this metric and dimension");
-  launch_mean(st, B.bpart, (int)ceil_div(n, sh.p2_rows), n, B.mean);
+  launch_mean(st, B.bpart, (int)ceil_div(n, sh.p2_rows), n, B.mean, sh.split32 ? (int)ceil_div(n, 32) : 0);
   // the status word and the mean come back together: B.status and B.mean are
   // the first two 256-byte slices, so one copy of 264 bytes holds both
   struct {
