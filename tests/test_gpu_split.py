@@ -26,3 +26,14 @@ def test_split_blocks(n, d, k, prec, mode):
     ref = oracle.exact(X, L, k, "eucl")
     compare_scores(res, ref, prec=prec)
     assert abs(res["mean"] - np.asarray(res["s"].cpu().numpy(), dtype=np.float64).mean()) <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("n,d,k", [(700, 16, 3), (1301, 9, 5), (333, 3, 2)])
+def test_clusters_of_several_blobs(n, d, k):
+    """Cells of more blobs than clusters: most near pairs are recomputed."""
+    X, _ = synth.tiny_case(n, d, 4 * k, seed=n)
+    L = synth.voronoi_labels(X, synth.voronoi_centers(n, k, (n, k)))
+    print(f"several blobs n={n} d={d} k={k}", flush=True)
+    Xd, Ld = dev(X, L)
+    res = native.silh_exact(Xd, Ld, k, "eucl", "fp32")
+    compare_scores(res, oracle.exact(X, L, k, "eucl"))
