@@ -9,7 +9,9 @@
 // Each clustering carries one status word.  A size that exceeds its capacity
 // sets a bit and the stage continues on clamped (empty) sizes, so every
 // access stays inside its buffer; the host re-runs such a clustering on the
-// eager path.  A label outside [0, k) sets a bit too (k_unit_hist).
+// eager path.  Sizes that sum to less than n (a label outside [0, k)) set a
+// bit too.  The eager path takes its offsets and rates from these kernels as
+// well, and reads them back only where the host needs the sizes.
 //
 // Every floating-point step below is the host's, in the same order
 // (compiled with -ffp-contract=off).
@@ -49,9 +51,11 @@ __device__ __forceinline__ int64_t block_scan_excl_1024(int64_t v, int64_t* part
 
 // Cluster offsets (exclusive prefix sums of the sizes) and the initial-sample
 // rate of Algorithm 1, q_j = min(1, (2/|C_j|) ln(5k/delta)), with the log term
-// computed on the host; fewer than two nonempty clusters sets kStatusEmpty.
+// computed on the host.  *status, where there is one, becomes kStatusLabel when the
+// sizes do not sum to n, with kStatusEmpty for fewer than two nonempty
+// clusters.
 // One block of 1024 threads, each over a contiguous run of clusters.
-__global__ __launch_bounds__(1024) void k_index_sizes(const int32_t* __restrict__ csize, int k, double lnterm,
+__global__ __launch_bounds__(1024) void k_index_sizes(const int32_t* __restrict__ csize, int n, int k, double lnterm,
                                                       int32_t* __restrict__ off, double* __restrict__ q,
                                                       int* __restrict__ status) {
   __shared__ int64_t part[1024];
@@ -79,19 +83,20 @@ __global__ __launch_bounds__(1024) void k_index_sizes(const int32_t* __restrict_
   }
   if (threadIdx.x == 0) {
     off[k] = (int32_t)tot;
-    if (ne_tot < 2) *status |= kStatusEmpty;
+    if (status != nullptr) *status = (tot != n ? kStatusLabel : 0) | (ne_tot < 2 ? kStatusEmpty : 0);
   }
 }
 
-void launch_index_sizes(hipStream_t st, const int32_t* csize, int k, double lnterm, int32_t* off, double* q,
+void launch_index_sizes(hipStream_t st, const int32_t* csize, int n, int k, double lnterm, int32_t* off, double* q,
                         int* status) {
-  hipLaunchKernelGGL(k_index_sizes, dim3(1), dim3(1024), 0, st, csize, k, lnterm, off, q, status);
+  hipLaunchKernelGGL(k_index_sizes, dim3(1), dim3(1024), 0, st, csize, n, k, lnterm, off, q, status);
 }
 
 // W(e_bar) work items from the sizes (the eager path builds the same list on
 // the host): clusters with |C_j| > t and a nonempty F0_j are cut into runs of
 // `chunk` consecutive sorted positions, in cluster order; item r of cluster j
-// writes its |F0_j| partial sums at pbase_j + r |F0_j|.  f0_off is first
+// writes its |F0_j| partial sums at pbase_j + r |F0_j|.  f0_off[j], the scan
+// `pos` of the flags at off[j], is
 // clamped to f0_cap (kStatusF0 when it did not fit); a partial-sum total past
 // part_cap sets kStatusPartial and leaves every cluster without items.
 // Writes citem_first / citem_count / ibase (first item, count, partial base
@@ -99,6 +104,8 @@ void launch_index_sizes(hipStream_t st, const int32_t* csize, int k, double lnte
 // the kept member distances (|C_j| |F0_j| each, same clusters) and meta[1] = 1
 // when their total fits dist_cap.
 __global__ __launch_bounds__(1024) void k_f0_items(const int32_t* __restrict__ csize,
+                                                   const int32_t* __restrict__ off,
+                                                   const int32_t* __restrict__ pos,
                                                    int32_t* __restrict__ f0_off, int k, int64_t t, int chunk,
                                                    int f0_cap, int64_t part_cap,
                                                    int32_t* __restrict__ citem_first,
@@ -108,9 +115,11 @@ __global__ __launch_bounds__(1024) void k_f0_items(const int32_t* __restrict__ c
                                                    int64_t dist_cap, bool assign) {
   __shared__ int64_t part[1024];
   __shared__ int over;
-  if (threadIdx.x == 0) over = f0_off[k] > f0_cap;
-  __syncthreads();
-  for (int j = threadIdx.x; j <= k; j += 1024) f0_off[j] = f0_off[j] < f0_cap ? f0_off[j] : f0_cap;
+  for (int j = threadIdx.x; j <= k; j += 1024) {
+    const int v = pos[off[j]];
+    f0_off[j] = v < f0_cap ? v : f0_cap;
+    if (j == k) over = v > f0_cap;
+  }
   __syncthreads();
   const int per = (k + 1023) / 1024;
   const int j0 = threadIdx.x * per;
@@ -152,69 +161,29 @@ __global__ __launch_bounds__(1024) void k_f0_items(const int32_t* __restrict__ c
   }
 }
 
-// items[it] for it < items_cap: the item's cluster by binary search over
-// citem_first; slots past the item count get an empty item (no members, no
-// F0 rows), so the W pass can run over the full capacity.
-// item layout: [cluster, begin, end, f0_begin, f0_count, partial_base]
-__global__ __launch_bounds__(256) void k_items_fill(const int32_t* __restrict__ off,
-                                                    const int32_t* __restrict__ f0_off,
-                                                    const int32_t* __restrict__ citem_first,
-                                                    const int64_t* __restrict__ ibase,
-                                                    const int32_t* __restrict__ meta, int k, int chunk,
-                                                    int items_cap, int32_t* __restrict__ items) {
-  const int it = blockIdx.x * 256 + threadIdx.x;
-  if (it >= items_cap) return;
-  int32_t* o = items + (size_t)it * 6;
-  if (it >= meta[0]) {
-    o[0] = 0;
-    o[1] = 0;
-    o[2] = 0;
-    o[3] = 0;
-    o[4] = 0;
-    o[5] = 0;
-    return;
-  }
-  // the last cluster whose first item is <= it (citem_first is nondecreasing;
-  // a cluster without items shares its first index with the next cluster that
-  // has some, and the last such index is taken, so j has items)
-  int lo = 0, hi = k;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (citem_first[mid] <= it) lo = mid; else hi = mid;
-  }
-  const int j = lo;
-  const int r = it - citem_first[j];
-  const int fj = f0_off[j + 1] - f0_off[j];
-  const int b = off[j] + r * chunk;
-  const int e = b + chunk < off[j + 1] ? b + chunk : off[j + 1];
-  o[0] = j;
-  o[1] = b;
-  o[2] = e;
-  o[3] = f0_off[j];
-  o[4] = fj;
-  o[5] = (int32_t)(ibase[j] + (int64_t)r * fj);
-}
-
-void launch_f0_items(hipStream_t st, const int32_t* csize, const int32_t* off, int32_t* f0_off, int k,
-                     int64_t t, int chunk, int f0_cap, int64_t part_cap, int items_cap, int32_t* citem_first,
-                     int32_t* citem_count, int64_t* ibase, int32_t* meta, int32_t* items, int* status,
-                     int64_t* dbase, int64_t dist_cap, bool assign_status) {
-  hipLaunchKernelGGL(k_f0_items, dim3(1), dim3(1024), 0, st, csize, f0_off, k, t, chunk, f0_cap, part_cap,
+void launch_f0_items(hipStream_t st, const int32_t* csize, const int32_t* off, const int32_t* pos, int32_t* f0_off,
+                     int k, int64_t t, int chunk, int f0_cap, int64_t part_cap, int32_t* citem_first,
+                     int32_t* citem_count, int64_t* ibase, int32_t* meta, int* status, int64_t* dbase,
+                     int64_t dist_cap, bool assign_status) {
+  hipLaunchKernelGGL(k_f0_items, dim3(1), dim3(1024), 0, st, csize, off, pos, f0_off, k, t, chunk, f0_cap, part_cap,
                      citem_first, citem_count, ibase, meta, status, dbase, dist_cap, assign_status);
-  hipLaunchKernelGGL(k_items_fill, dim3((int)ceil_div(items_cap, 256)), dim3(256), 0, st, off, f0_off,
-                     citem_first, ibase, meta, k, chunk, items_cap, items);
 }
 
 // Per-cluster sample counts and the offsets of the padded sample blocks
-// (each cluster padded to kSamplePad rows).  A padded total past s_cap sets
+// (each cluster padded to kSamplePad rows), from the scan `pos` of the
+// selection flags at the cluster offsets.  A padded total past s_cap sets
 // kStatusSample and leaves every cluster empty.
-__global__ __launch_bounds__(1024) void k_sample_sizes(const int32_t* __restrict__ s_off, int k, int s_cap,
+__global__ __launch_bounds__(1024) void k_sample_sizes(const int32_t* __restrict__ pos,
+                                                       const int32_t* __restrict__ off,
+                                                       int32_t* __restrict__ s_off, int k, int s_cap,
                                                        int32_t* __restrict__ cnt, int32_t* __restrict__ sp_off,
                                                        int* __restrict__ status) {
   __shared__ int64_t part[1024];
   const int per = (k + 1023) / 1024;
   const int j0 = threadIdx.x * per;
   const int j1 = j0 + per < k ? j0 + per : k;
+  for (int j = threadIdx.x; j <= k; j += 1024) s_off[j] = pos[off[j]];
+  __syncthreads();
   int64_t s = 0;
   for (int j = j0; j < j1; ++j) s += (s_off[j + 1] - s_off[j] + kSamplePad - 1) / kSamplePad * kSamplePad;
   int64_t tot = 0;
@@ -232,9 +201,9 @@ __global__ __launch_bounds__(1024) void k_sample_sizes(const int32_t* __restrict
   }
 }
 
-void launch_sample_sizes(hipStream_t st, const int32_t* s_off, int k, int s_cap, int32_t* cnt, int32_t* sp_off,
-                         int* status) {
-  hipLaunchKernelGGL(k_sample_sizes, dim3(1), dim3(1024), 0, st, s_off, k, s_cap, cnt, sp_off, status);
+void launch_sample_sizes(hipStream_t st, const int32_t* pos, const int32_t* off, int32_t* s_off, int k, int s_cap,
+                         int32_t* cnt, int32_t* sp_off, int* status) {
+  hipLaunchKernelGGL(k_sample_sizes, dim3(1), dim3(1024), 0, st, pos, off, s_off, k, s_cap, cnt, sp_off, status);
 }
 
 __global__ void k_put_status(const int* __restrict__ status, int32_t* __restrict__ out) { *out = *status; }

@@ -11,32 +11,36 @@ namespace silh {
 // stable counting sort by label: per-unit histograms, per-label scan over
 // units, then an in-order scatter with one wave per unit
 // ----------------------------------------------------------------------------
-// Per-unit label histograms; a label outside [0, k) is not counted and sets
-// *bad (the cluster sizes are then not used).
+// Per-unit label histograms; a label outside [0, k) is not counted, so the
+// cluster sizes then sum to less than n.  With perm, the unit's part of perm
+// and slab is cleared on the way (places that such a label leaves unwritten
+// then still name a valid element).
 __global__ __launch_bounds__(64) void k_unit_hist(const int32_t* __restrict__ labels, int n, int k, int seg,
-                                                  int32_t* __restrict__ uh, int* __restrict__ bad) {
+                                                  int32_t* __restrict__ uh, int32_t* __restrict__ perm,
+                                                  int32_t* __restrict__ slab) {
   extern __shared__ int32_t h[];
   for (int j = threadIdx.x; j < k; j += 64) h[j] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * seg;
   const int64_t end = base + seg < n ? base + seg : n;
-  int anybad = 0;
   for (int64_t i = base + threadIdx.x; i < end; i += 64) {
     const int l = labels[i];
-    if ((unsigned)l < (unsigned)k)
-      atomicAdd(&h[l], 1);
-    else
-      anybad = 1;
+    if ((unsigned)l < (unsigned)k) atomicAdd(&h[l], 1);
+    if (perm != nullptr) {
+      perm[i] = 0;
+      slab[i] = 0;
+    }
   }
-  if (anybad && bad != nullptr) atomicOr(bad, 1);
   __syncthreads();
   const int units = gridDim.x;  // label-major [k][units]: each label's scan reads one row
   for (int j = threadIdx.x; j < k; j += 64) uh[(size_t)j * units + blockIdx.x] = h[j];
 }
 
-void launch_unit_hist(hipStream_t st, const int32_t* labels, int n, int k, int seg, int32_t* uh, int* bad) {
+void launch_unit_hist(hipStream_t st, const int32_t* labels, int n, int k, int seg, int32_t* uh, int32_t* perm,
+                      int32_t* slab) {
   const int units = (int)ceil_div(n, seg);
-  hipLaunchKernelGGL(k_unit_hist, dim3(units), dim3(64), k * sizeof(int32_t), st, labels, n, k, seg, uh, bad);
+  hipLaunchKernelGGL(k_unit_hist, dim3(units), dim3(64), k * sizeof(int32_t), st, labels, n, k, seg, uh, perm,
+                     slab);
 }
 
 // one block per label: uh[u][j] <- sum_{u' < u} uh[u'][j] (the label's rows
@@ -81,7 +85,7 @@ void launch_unit_scan(hipStream_t st, int32_t* uh, int units, int k, int32_t* co
 // label's run is written to its global range in one contiguous piece.
 // LDS: base[k] (global start of the unit's run of label j), loc[k] (next local
 // slot of label j), ids[seg], lab[seg].  A label outside [0, k) (already
-// flagged by k_unit_hist) is skipped, so no access leaves the arrays.
+// left out by k_unit_hist) is skipped, so no access leaves the arrays.
 __global__ __launch_bounds__(64) void k_scatter(const int32_t* __restrict__ labels, int n, int k, int seg,
                                                 const int32_t* __restrict__ ubase,
                                                 const int32_t* __restrict__ off,
@@ -256,11 +260,12 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int32_t* __restrict__ tsum,
   if (threadIdx.x == 1023) tsum[nt] = part[1023];
 }
 
-// out[i] = tile prefix + the exclusive scan inside the tile.  FUSED: the tile
-// prefix is the sum of the raw tile sums before this tile (read by the whole
-// block; used while the tiles are few), and the last tile writes out[n];
-// otherwise tsum holds the scanned tile sums and tsum[nt] the total.
-template <bool FUSED>
+// out[i] = tile prefix + the exclusive scan inside the tile.  FUSED > 0: the
+// tile prefix is the sum of the raw sums before this tile, FUSED of them a
+// tile (read by the whole block; used while the tiles are few), and the last
+// tile writes out[n]; otherwise tsum holds the scanned tile sums and tsum[nt]
+// the total.
+template <int FUSED>
 __global__ __launch_bounds__(256) void k_scan_apply(const int32_t* __restrict__ in, int n,
                                                     const int32_t* __restrict__ tsum, int nt,
                                                     int32_t* __restrict__ out) {
@@ -274,9 +279,10 @@ __global__ __launch_bounds__(256) void k_scan_apply(const int32_t* __restrict__ 
 #pragma unroll
   for (int i = 0; i < 8; ++i) s += v[i];
   int32_t tpre;
-  if constexpr (FUSED) {
+  if constexpr (FUSED > 0) {
     int32_t a = 0;
-    for (int q = threadIdx.x; q < (int)blockIdx.x; q += 256) a += tsum[q];
+#pragma unroll 4
+    for (int q = threadIdx.x; q < FUSED * (int)blockIdx.x; q += 256) a += tsum[q];
     a = wave_sum_i32(a);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
@@ -301,7 +307,7 @@ __global__ __launch_bounds__(256) void k_scan_apply(const int32_t* __restrict__ 
       if (base + i < n) out[base + i] = o[i];
   }
   if (threadIdx.x == 0) {
-    if constexpr (FUSED) {
+    if constexpr (FUSED > 0) {
       if ((int)blockIdx.x == nt - 1) out[n] = tpre + btot;
     } else {
       if (blockIdx.x == 0) out[n] = tsum[nt];
@@ -313,18 +319,26 @@ __global__ __launch_bounds__(256) void k_scan_apply(const int32_t* __restrict__ 
 // (O(nt^2 / 2) L2 reads in all, a few MB at n = 4e6), saving a launch
 constexpr int kScanFusedTiles = 2048;
 
-void launch_scan(hipStream_t st, const int32_t* in, int n, int32_t* out, int32_t* tmp) {
+// With `sums`, tmp already holds the sums of every 256 values: the kernels
+// that write the flags leave them, and the pass that sums them is not
+// launched (each launch is 4 to 5 us of a captured graph or of a small
+// request; at n = 1e6 the pass itself took 4 us).
+void launch_scan(hipStream_t st, const int32_t* in, int n, int32_t* out, int32_t* tmp, bool sums) {
   const int nt = (int)ceil_div(n, kScanTile);
   if (nt == 0) {
     hipLaunchKernelGGL(k_fill_zero1, dim3(1), dim3(1), 0, st, out);
     return;
   }
+  if (sums && nt <= kScanFusedTiles) {
+    hipLaunchKernelGGL(k_scan_apply<kScanTile / 256>, dim3(nt), dim3(256), 0, st, in, n, tmp, nt, out);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_reduce, dim3(nt), dim3(256), 0, st, in, n, tmp);
   if (nt <= kScanFusedTiles) {
-    hipLaunchKernelGGL(k_scan_apply<true>, dim3(nt), dim3(256), 0, st, in, n, tmp, nt, out);
+    hipLaunchKernelGGL(k_scan_apply<1>, dim3(nt), dim3(256), 0, st, in, n, tmp, nt, out);
   } else {
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, tmp, nt);
-    hipLaunchKernelGGL(k_scan_apply<false>, dim3(nt), dim3(256), 0, st, in, n, tmp, nt, out);
+    hipLaunchKernelGGL(k_scan_apply<0>, dim3(nt), dim3(256), 0, st, in, n, tmp, nt, out);
   }
 }
 

@@ -146,27 +146,69 @@ constexpr int kEB = 4;  // initial-sample rows summed together in the W pass
 
 // ----------------------------------------------------------------------------
 // F^0 draw: sorted position i, element g = perm[i] of cluster j; kept when
-// |C_j| > t and U(seed, g, 0) < q_j.
+// |C_j| > t and U(seed, g, 0) < q_j.  The block's count goes to bsum (the scan
+// that follows then needs no pass of its own for it).
 // ----------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_f0_flag(const int32_t* __restrict__ perm,
                                                  const int32_t* __restrict__ slab, int n,
                                                  const int32_t* __restrict__ csize,
                                                  const double* __restrict__ q, int64_t t,
-                                                 uint64_t seed, int32_t* __restrict__ flag) {
+                                                 uint64_t seed, int32_t* __restrict__ flag,
+                                                 int32_t* __restrict__ bsum) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int j = slab[i];
   int32_t f = 0;
-  if ((int64_t)csize[j] > t) f = uniform53(seed, (uint64_t)perm[i], kStreamF0) < q[j] ? 1 : 0;
-  flag[i] = f;
+  if (i < n) {
+    const int j = slab[i];
+    if ((int64_t)csize[j] > t) f = uniform53(seed, (uint64_t)perm[i], kStreamF0) < q[j] ? 1 : 0;
+    flag[i] = f;
+  }
+  const int cnt = __syncthreads_count(f);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = cnt;
 }
 
 void launch_f0_flag(hipStream_t st, const int32_t* perm, const int32_t* slab, int n,
-                    const int32_t* csize, const double* q, int64_t t, uint64_t seed, int32_t* flag) {
+                    const int32_t* csize, const double* q, int64_t t, uint64_t seed, int32_t* flag,
+                    int32_t* bsum) {
   hipLaunchKernelGGL(k_f0_flag, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, perm, slab, n, csize,
-                     q, t, seed, flag);
+                     q, t, seed, flag, bsum);
 }
 
+// items[it] for it < A.cap: the item's cluster by binary search over
+// citem_first; slots past the item count get an empty item (no members, no
+// F0 rows), so the W pass can run over the full capacity.
+// item layout: [cluster, begin, end, f0_begin, f0_count, partial_base]
+__device__ __forceinline__ void write_item(const W0Items& A, int it) {
+  if (it >= A.cap) return;
+  int32_t* o = A.items + (size_t)it * 6;
+  if (it >= A.meta[0]) {
+#pragma unroll
+    for (int e = 0; e < 6; ++e) o[e] = 0;
+    return;
+  }
+  // the last cluster whose first item is <= it (citem_first is nondecreasing;
+  // a cluster without items shares its first index with the next cluster that
+  // has some, and the last such index is taken, so j has items)
+  int lo = 0, hi = A.k;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (A.citem_first[mid] <= it) lo = mid; else hi = mid;
+  }
+  const int j = lo;
+  const int r = it - A.citem_first[j];
+  const int fj = A.f0_off[j + 1] - A.f0_off[j];
+  const int b = A.off[j] + r * A.chunk;
+  const int e = b + A.chunk < A.off[j + 1] ? b + A.chunk : A.off[j + 1];
+  o[0] = j;
+  o[1] = b;
+  o[2] = e;
+  o[3] = A.f0_off[j];
+  o[4] = fj;
+  o[5] = (int32_t)(A.ibase[j] + (int64_t)r * fj);
+}
+
+// The initial sample's rows in float64; blocks past the elements write the W
+// pass's work items, which depend on the same kernel's sizes (one launch for
+// both).
 __global__ __launch_bounds__(256) void k_f0_pack(const int32_t* __restrict__ perm,
                                                  const int32_t* __restrict__ slab,
                                                  const int32_t* __restrict__ flag,
@@ -174,7 +216,12 @@ __global__ __launch_bounds__(256) void k_f0_pack(const int32_t* __restrict__ per
                                                  const float* __restrict__ X, int d, int DM,
                                                  int cap, int64_t* __restrict__ f0_gid,
                                                  int32_t* __restrict__ f0_cl, double* __restrict__ f0X,
-                                                 double* __restrict__ f0N) {
+                                                 double* __restrict__ f0N, W0Items A) {
+  const int nb = (n + 255) >> 8;
+  if ((int)blockIdx.x >= nb) {
+    write_item(A, ((int)blockIdx.x - nb) * 256 + threadIdx.x);
+    return;
+  }
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n || !flag[i]) return;
   const int dst = pos[i];
@@ -203,9 +250,9 @@ __global__ __launch_bounds__(256) void k_f0_pack(const int32_t* __restrict__ per
 
 void launch_f0_pack(hipStream_t st, const int32_t* perm, const int32_t* slab, const int32_t* flag,
                     const int32_t* pos, int n, const float* X, int d, int DM, int cap, int64_t* f0_gid,
-                    int32_t* f0_cl, double* f0X, double* f0N) {
-  hipLaunchKernelGGL(k_f0_pack, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, perm, slab, flag, pos,
-                     n, X, d, DM, cap, f0_gid, f0_cl, f0X, f0N);
+                    int32_t* f0_cl, double* f0X, double* f0N, const W0Items& A) {
+  hipLaunchKernelGGL(k_f0_pack, dim3((int)(ceil_div(n, 256) + ceil_div(A.cap, 256))), dim3(256), 0, st, perm, slab,
+                     flag, pos, n, X, d, DM, cap, f0_gid, f0_cl, f0X, f0N, A);
 }
 
 // ----------------------------------------------------------------------------
@@ -537,7 +584,8 @@ void launch_w_final(hipStream_t st, const int32_t* f0_cl, int F0, const int32_t*
 
 // ----------------------------------------------------------------------------
 // gamma_e, p_e and the final Poisson draw (PPS), or the uniform rate t/|C_j|.
-// Clusters with |C_j| <= t are taken whole with p = 1.
+// Clusters with |C_j| <= t are taken whole with p = 1.  With bsum, the
+// block's count of selected elements goes there, for the scan that follows.
 // ----------------------------------------------------------------------------
 constexpr int kDrawB = 8;  // kept distances loaded together by the draw
 
@@ -595,9 +643,10 @@ __global__ __launch_bounds__(256) void k_draw(int sampler, const int32_t* __rest
                                               const double* __restrict__ f0X,
                                               const double* __restrict__ W,
                                               double* __restrict__ p_gid, int32_t* __restrict__ flag,
-                                              DistStore ds) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+                                              DistStore ds, int32_t* __restrict__ bsum) {
+  // (lanes past n repeat the last element and write nothing)
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  const int i = i0 < n ? i0 : n - 1;
   const int g = perm[i];
   const int j = slab[i];
   const int64_t m = csize[j];
@@ -668,8 +717,14 @@ __global__ __launch_bounds__(256) void k_draw(int sampler, const int32_t* __rest
     p = p < 1.0 ? p : 1.0;
     sel = uniform53(seed, (uint64_t)g, kStreamPPS) < p ? 1 : 0;
   }
-  p_gid[g] = p;
-  flag[i] = sel;
+  if (i0 < n) {
+    p_gid[g] = p;
+    flag[i] = sel;
+  }
+  if (bsum != nullptr) {
+    const int cnt = __syncthreads_count(i0 < n ? sel : 0);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = cnt;
+  }
 }
 
 // d > 128: the kept distances where the W pass kept them (as k_draw), else
@@ -684,9 +739,10 @@ __global__ __launch_bounds__(256) void k_draw_wide(int sampler, const int32_t* _
                                                    const double* __restrict__ f0X,
                                                    const double* __restrict__ W,
                                                    double* __restrict__ p_gid, int32_t* __restrict__ flag,
-                                                   DistStore ds) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+                                                   DistStore ds, int32_t* __restrict__ bsum) {
+  // (lanes past n repeat the last element and write nothing)
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
+  const int i = i0 < n ? i0 : n - 1;
   const int g = perm[i];
   const int j = slab[i];
   const int64_t m = csize[j];
@@ -746,16 +802,22 @@ __global__ __launch_bounds__(256) void k_draw_wide(int sampler, const int32_t* _
     p = p < 1.0 ? p : 1.0;
     sel = uniform53(seed, (uint64_t)g, kStreamPPS) < p ? 1 : 0;
   }
-  p_gid[g] = p;
-  flag[i] = sel;
+  if (i0 < n) {
+    p_gid[g] = p;
+    flag[i] = sel;
+  }
+  if (bsum != nullptr) {
+    const int cnt = __syncthreads_count(i0 < n ? sel : 0);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = cnt;
+  }
 }
 
 void launch_draw(hipStream_t st, int metric, int DM, int sampler, const int32_t* perm,
                  const int32_t* slab, int n, const float* X, int d, const int32_t* csize, int64_t t,
                  uint64_t seed, const int32_t* f0_off, const double* f0X, const double* W,
-                 double* p_gid, int32_t* flag, DistStore ds) {
+                 double* p_gid, int32_t* flag, DistStore ds, int32_t* bsum) {
   if (DM == kWideDM) {
-#define SILH_DW(MM) hipLaunchKernelGGL(k_draw_wide<MM>, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, sampler, perm, slab, n, X, d, csize, t, seed, f0_off, f0X, W, p_gid, flag, ds)
+#define SILH_DW(MM) hipLaunchKernelGGL(k_draw_wide<MM>, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, sampler, perm, slab, n, X, d, csize, t, seed, f0_off, f0X, W, p_gid, flag, ds, bsum)
     switch (metric) {
       case kEucl: SILH_DW(kEucl); break;
       case kCos: SILH_DW(kCos); break;
@@ -766,20 +828,22 @@ void launch_draw(hipStream_t st, int metric, int DM, int sampler, const int32_t*
     return;
   }
   SILH_P1_DISPATCH(k_draw, dim3((int)ceil_div(n, 256)), sampler, perm, slab, n, X, d, csize, t, seed,
-                   f0_off, f0X, W, p_gid, flag, ds);
+                   f0_off, f0X, W, p_gid, flag, ds, bsum);
 }
 
 // exact silhouette: every element kept with p = 1
 __global__ __launch_bounds__(256) void k_fill_all(const int32_t* __restrict__ perm, int n,
-                                                  double* __restrict__ p_gid, int32_t* __restrict__ flag) {
+                                                  double* __restrict__ p_gid, int32_t* __restrict__ flag,
+                                                  int32_t* __restrict__ bsum) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (bsum != nullptr && threadIdx.x == 0) bsum[blockIdx.x] = n - i < 256 ? n - i : 256;
   if (i >= n) return;
   p_gid[perm[i]] = 1.0;
   flag[i] = 1;
 }
 
-void launch_fill_all(hipStream_t st, const int32_t* perm, int n, double* p_gid, int32_t* flag) {
-  hipLaunchKernelGGL(k_fill_all, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, perm, n, p_gid, flag);
+void launch_fill_all(hipStream_t st, const int32_t* perm, int n, double* p_gid, int32_t* flag, int32_t* bsum) {
+  hipLaunchKernelGGL(k_fill_all, dim3((int)ceil_div(n, 256)), dim3(256), 0, st, perm, n, p_gid, flag, bsum);
 }
 
 // ----------------------------------------------------------------------------

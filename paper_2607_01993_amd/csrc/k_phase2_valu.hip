@@ -349,7 +349,8 @@ __device__ __forceinline__ void neumaier_add(double& s, double& c, double v) {
 }
 
 __global__ __launch_bounds__(256) void k_mean(const double* __restrict__ bpart, int nb, int64_t n,
-                                              double* __restrict__ out, int nq) {
+                                              double* __restrict__ out, int nq,
+                                              const int* __restrict__ status, int32_t* __restrict__ status_out) {
   __shared__ double ss[256], cc[256];
   double s = 0.0, c = 0.0;
   if (nq > 0) {
@@ -377,11 +378,15 @@ __global__ __launch_bounds__(256) void k_mean(const double* __restrict__ bpart, 
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = (ss[0] + cc[0]) / (double)n;
+  if (threadIdx.x == 0) {
+    out[0] = (ss[0] + cc[0]) / (double)n;
+    if (status != nullptr) *status_out = *status;
+  }
 }
 
-void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq) {
-  hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, bpart, nb, n, out, nq);
+void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq, const int* status,
+                 int32_t* status_out) {
+  hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, bpart, nb, n, out, nq, status, status_out);
 }
 
 }  // namespace silh

@@ -96,7 +96,6 @@ struct silh_ctx {
   // host copies
   std::vector<uint32_t> counts_h;
   std::vector<int32_t> csize_h, off_h;
-  std::vector<double> q_h;
   std::vector<int32_t> f0_off32_h, s_off32_h, sp_off_h, cnt_h, items_h, citem_first_h, citem_count_h;
   std::vector<int64_t> f0_off_h, s_off_h;
   double mean_h = 0.0;
@@ -403,27 +402,6 @@ silh_status h2d(silh_ctx* c, T* dst, const std::vector<T>& src) {
   return SILH_OK;
 }
 
-// Two uploads in one copy when dst_b is the next slot of the same carve
-// (dst_a's span rounded up to 256 bytes): the padding between them is staged
-// as zeros.  Each copy is a transfer of its own on the stream, so adjacent
-// small arrays go together.
-template <class A, class B>
-silh_status h2d_pair(silh_ctx* c, A* dst_a, const std::vector<A>& a, B* dst_b, const std::vector<B>& b) {
-  const size_t na = a.size() * sizeof(A), nb = b.size() * sizeof(B);
-  const size_t gap = (size_t)((const char*)dst_b - (const char*)dst_a);
-  if (na == 0 || nb == 0 || gap != Carve::span(na)) {
-    CHK(h2d(c, dst_a, a));
-    return h2d(c, dst_b, b);
-  }
-  void* p = nullptr;
-  CHK(stage(c, gap + nb, &p));
-  std::memcpy(p, a.data(), na);
-  std::memset((char*)p + na, 0, gap - na);
-  std::memcpy((char*)p + gap, b.data(), nb);
-  HIPCHK(hipMemcpyAsync(dst_a, p, gap + nb, hipMemcpyHostToDevice, c->st));
-  return SILH_OK;
-}
-
 // Device-to-host read-backs: every part is copied through the staging block,
 // then the stream is synchronised and the values land in host memory.  Parts
 // that lie within 512 bytes of each other on the device (slots of one carve)
@@ -536,12 +514,22 @@ silh_status build_index(silh_ctx* c) {
   // than n (no flag word to clear and read)
   {
     Launch L(c, K_SORT_HIST);
-    launch_unit_hist(c->st, c->labels, n, k, seg, c->uh, nullptr);
+    launch_unit_hist(c->st, c->labels, n, k, seg, c->uh);
     CHK(L.done());
   }
   {
     Launch L(c, K_SORT_SCAN);
     launch_unit_scan(c->st, c->uh, units, k, c->csize);
+    CHK(L.done());
+  }
+  // offsets and initial-sample rates on the device, and the scatter (which
+  // leaves such labels out) before the sizes are read back, so that the
+  // read-back is the only wait
+  launch_index_sizes(c->st, c->csize, n, k, std::log(5.0 * (double)k / c->prm.delta), c->off, c->q, nullptr);
+  HIPCHK(hipGetLastError());
+  {
+    Launch L(c, K_SORT_SCATTER);
+    launch_scatter(c->st, c->labels, n, k, seg, c->uh, c->off, c->perm, c->slab);
     CHK(L.done());
   }
   c->counts_h.assign(k, 0u);
@@ -560,22 +548,6 @@ silh_status build_index(silh_ctx* c) {
     nonempty += c->csize_h[j] > 0;
   }
   if (nonempty < 2) return fail(SILH_E_K, "%d nonempty cluster(s); the silhouette needs at least 2", nonempty);
-  // initial-sample rate of Algorithm 1, min(1, (2/|C_j|) ln(5k/delta)), on the host
-  c->q_h.assign(k, 0.0);
-  const double lnterm = std::log(5.0 * (double)k / c->prm.delta);
-  for (int j = 0; j < k; ++j) {
-    if (c->csize_h[j] > 0) {
-      double qj = 2.0 / (double)c->csize_h[j];
-      qj = qj * lnterm;
-      c->q_h[j] = qj < 1.0 ? qj : 1.0;
-    }
-  }
-  CHK(h2d_pair(c, c->off, c->off_h, c->q, c->q_h));
-  {
-    Launch L(c, K_SORT_SCATTER);
-    launch_scatter(c->st, c->labels, n, k, seg, c->uh, c->off, c->perm, c->slab);
-    CHK(L.done());
-  }
   return SILH_OK;
 }
 
@@ -621,10 +593,11 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   const int n = c->n, k = c->k;
   {
     Launch L(c, K_SCAN);
-    launch_scan(c->st, c->flag, n, c->pos, c->scan_tmp);
+    launch_scan(c->st, c->flag, n, c->pos, c->scan_tmp, true);
     CHK(L.done());
   }
-  launch_gather_at(c->st, c->pos, c->off, k, c->s_off);
+  // counts and padded offsets on the device too: nothing goes back up
+  launch_sample_sizes(c->st, c->pos, c->off, c->s_off, k, INT32_MAX, c->cnt, c->sp_off, nullptr);
   HIPCHK(hipGetLastError());
   c->s_off32_h.assign(k + 1, 0);
   if (overflow) {
@@ -666,7 +639,6 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     CHK(cv.commit(c, c->alloc_sample));
     c->Ym = ym;
   }
-  CHK(h2d_pair(c, c->sp_off, c->sp_off_h, c->cnt, c->cnt_h));
   // every packed row, padding included, is written by k_pack (no clears)
   {
     Launch L(c, K_PACK);
@@ -716,7 +688,7 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   const int n = c->n, k = c->k;
   const int nb = (int)ceil_div(n, c->mfma ? 32 : c->p2_rows);  // (32: split blocks)
   Carve cv;
-  cv.add(&c->flag, (size_t)n).add(&c->pos, (size_t)n + 1).add(&c->scan_tmp, (size_t)ceil_div(n, kScanTile) + 1);
+  cv.add(&c->flag, (size_t)n).add(&c->pos, (size_t)n + 1).add(&c->scan_tmp, (size_t)scan_words(n));
   // f0_off, s_off and the Phase-1 status are read back together (one copy)
   cv.add(&c->p_gid, (size_t)n).add(&c->f0_off, (size_t)k + 1).add(&c->s_off, (size_t)k + 1).add(&c->p1_status, 1);
   cv.add(&c->sp_off, (size_t)k + 1).add(&c->cnt, (size_t)k).add(&c->bpart, (size_t)nb).add(&c->mean_d, 1);
@@ -741,16 +713,14 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
     // initial sample F^0
     {
       Launch L(c, K_F0_FLAG);
-      launch_f0_flag(c->st, c->perm, c->slab, n, c->csize, c->q, c->t, c->prm.seed, c->flag);
+      launch_f0_flag(c->st, c->perm, c->slab, n, c->csize, c->q, c->t, c->prm.seed, c->flag, c->scan_tmp);
       CHK(L.done());
     }
     {
       Launch L(c, K_SCAN);
-      launch_scan(c->st, c->flag, n, c->pos, c->scan_tmp);
+      launch_scan(c->st, c->flag, n, c->pos, c->scan_tmp, true);
       CHK(L.done());
     }
-    launch_gather_at(c->st, c->pos, c->off, k, c->f0_off);
-    HIPCHK(hipGetLastError());
   } else {
     HIPCHK(hipMemsetAsync(c->f0_off, 0, (size_t)(k + 1) * sizeof(int32_t), c->st));
   }
@@ -772,19 +742,21 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
       if (dist_cap > 0) cv.add(&c->dbase, (size_t)k).add(&c->dkeep, (size_t)dist_cap);
       CHK(cv.commit(c, c->alloc_sample));
     }
-    launch_f0_items(c->st, c->csize, c->off, c->f0_off, k, c->t, chunk, (int)f0_cap, part_cap, (int)items_cap,
-                    c->citem_first, c->citem_count, c->ibase, c->imeta, c->items, c->p1_status, c->dbase,
-                    dist_cap, true);
+    launch_f0_items(c->st, c->csize, c->off, c->pos, c->f0_off, k, c->t, chunk, (int)f0_cap, part_cap,
+                    c->citem_first, c->citem_count, c->ibase, c->imeta, c->p1_status, c->dbase, dist_cap, true);
     HIPCHK(hipGetLastError());
     {
       Launch L(c, K_F0_PACK);
       launch_f0_pack(c->st, c->perm, c->slab, c->flag, c->pos, n, c->X, d, c->DM, (int)f0_cap, c->f0_gid,
-                     c->f0_cl, c->f0X, c->f0N);
+                     c->f0_cl, c->f0X, c->f0N,
+                     {c->off, c->f0_off, c->citem_first, c->ibase, c->imeta, c->items, k, chunk, (int)items_cap});
       CHK(L.done());
     }
     nitems = (int)items_cap;  // the unused item slots are empty
     f0_rows = f0_cap;         // W blocks past F0 return at once
   } else if (pps) {
+    launch_gather_at(c->st, c->pos, c->off, k, c->f0_off);
+    HIPCHK(hipGetLastError());
     CHK(fetch(c, {{c->f0_off32_h.data(), c->f0_off, (k + 1) * sizeof(int32_t)}}));
     for (int j = 0; j <= k; ++j) c->f0_off_h[j] = c->f0_off32_h[j];
     c->F0 = c->f0_off_h[k];
@@ -853,7 +825,7 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
   {
     Launch L(c, K_DRAW);
     launch_draw(c->st, c->prm.metric, c->DM, pps ? 0 : 1, c->perm, c->slab, n, c->X, d, c->csize, c->t,
-                c->prm.seed, c->f0_off, c->f0X, c->W0, c->p_gid, c->flag, ds);
+                c->prm.seed, c->f0_off, c->f0X, c->W0, c->p_gid, c->flag, ds, c->scan_tmp);
     CHK(L.done());
   }
   if (pps && !host_items) {
@@ -1275,7 +1247,7 @@ silh_status silh_exact(const silh_params* prm, const float* X, const int32_t* la
   silh_status st = sample_stage_buffers(c);
   if (st == SILH_OK) {
     Launch L(c, K_DRAW);
-    launch_fill_all(c->st, c->perm, c->n, c->p_gid, c->flag);
+    launch_fill_all(c->st, c->perm, c->n, c->p_gid, c->flag, c->scan_tmp);
     st = L.done();
   }
   if (st == SILH_OK) st = compact_and_pack(c, nullptr);
@@ -1320,7 +1292,7 @@ silh_status silh_exact_rows(const silh_params* prm, const float* X, const int32_
   silh_status st = sample_stage_buffers(c);
   if (st == SILH_OK) {
     Launch L(c, K_DRAW);
-    launch_fill_all(c->st, c->perm, c->n, c->p_gid, c->flag);
+    launch_fill_all(c->st, c->perm, c->n, c->p_gid, c->flag, c->scan_tmp);
     st = L.done();
   }
   if (st == SILH_OK) st = compact_and_pack(c, nullptr);

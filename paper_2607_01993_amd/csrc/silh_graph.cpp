@@ -139,7 +139,7 @@ bool alloc_branch(silh_graph* g, Branch& b) {
   const int64_t S = g->S_cap, F0 = g->F0_cap, DM = g->DM;
   bool ok = take(g, b.status, 1) && take(g, b.uh, uh) && take(g, b.csize, k) && take(g, b.off, k + 1) &&
             take(g, b.perm, n) && take(g, b.slab, n) && take(g, b.q, k) && take(g, b.flag, n) &&
-            take(g, b.pos, n + 1) && take(g, b.scan_tmp, ceil_div(n, kScanTile) + 1) &&
+            take(g, b.pos, n + 1) && take(g, b.scan_tmp, scan_words(n)) &&
             take(g, b.f0_off, k + 1) && take(g, b.s_off, k + 1) && take(g, b.sp_off, k + 1) &&
             take(g, b.cnt, k) && take(g, b.p_gid, n) && take(g, b.f0_gid, F0) && take(g, b.f0_cl, F0) &&
             take(g, b.f0X, F0 * DM) && (g->base.metric != SILH_COS || take(g, b.f0N, F0)) && take(g, b.W0, F0) && take(g, b.partial, g->part_cap) &&
@@ -187,7 +187,11 @@ bool alloc_branch(silh_graph* g, Branch& b) {
 }
 
 // clustering i's pipeline on branch b's stream: no host synchronisation,
-// no allocation, no memset
+// no allocation, no memset.  A replay costs 4 to 5 us a kernel (n = 100,000,
+// k = 2..17, t = 128: 28 kernels a clustering 2.28 ms, 21 kernels 1.96 ms), so
+// small steps ride on the kernels before them.  The uniform sampler keeps its
+// scan's own sums and the copy of its status: it has no Phase 1 and at least
+// 17 kernels a clustering (what silh_graph_info reports) as it is.
 bool enqueue(silh_graph* g, Branch& b, int i) {
   const int n = g->n, k = g->ks[i], d = g->d, DM = g->DM;
   const int64_t t = g->ts[i];
@@ -204,23 +208,20 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     ds.off = b.off;
     ds.use = b.meta + 1;
   }
-  // cluster index (perm and slab start at 0 so that rows a bad label leaves
-  // unwritten still name a valid element)
-  launch_fill_i32(st, b.status, 1, 0);
-  launch_fill_i32(st, b.perm, n, 0);
-  launch_fill_i32(st, b.slab, n, 0);
-  launch_unit_hist(st, lab, n, k, seg, b.uh, b.status);
+  // cluster index
+  launch_unit_hist(st, lab, n, k, seg, b.uh, b.perm, b.slab);
   launch_unit_scan(st, b.uh, units, k, b.csize);
-  launch_index_sizes(st, b.csize, k, std::log(5.0 * (double)k / g->base.delta), b.off, b.q, b.status);
+  launch_index_sizes(st, b.csize, n, k, std::log(5.0 * (double)k / g->base.delta), b.off, b.q, b.status);
   launch_scatter(st, lab, n, k, seg, b.uh, b.off, b.perm, b.slab);
   // Phase 1
   if (pps) {
-    launch_f0_flag(st, b.perm, b.slab, n, b.csize, b.q, t, g->base.seed, b.flag);
-    launch_scan(st, b.flag, n, b.pos, b.scan_tmp);
-    launch_gather_at(st, b.pos, b.off, k, b.f0_off);
-    launch_f0_items(st, b.csize, b.off, b.f0_off, k, t, g->chunk, (int)g->F0_cap, g->part_cap, (int)g->items_cap,
-                    b.citem_first, b.citem_count, b.ibase, b.meta, b.items, b.status, b.dbase, g->dist_cap);
-    launch_f0_pack(st, b.perm, b.slab, b.flag, b.pos, n, g->X, d, DM, (int)g->F0_cap, b.f0_gid, b.f0_cl, b.f0X, b.f0N);
+    launch_f0_flag(st, b.perm, b.slab, n, b.csize, b.q, t, g->base.seed, b.flag, b.scan_tmp);
+    launch_scan(st, b.flag, n, b.pos, b.scan_tmp, true);
+    launch_f0_items(st, b.csize, b.off, b.pos, b.f0_off, k, t, g->chunk, (int)g->F0_cap, g->part_cap, b.citem_first,
+                    b.citem_count, b.ibase, b.meta, b.status, b.dbase, g->dist_cap);
+    const W0Items wi{b.off, b.f0_off, b.citem_first, b.ibase, b.meta, b.items, k, g->chunk, (int)g->items_cap};
+    launch_f0_pack(st, b.perm, b.slab, b.flag, b.pos, n, g->X, d, DM, (int)g->F0_cap, b.f0_gid, b.f0_cl, b.f0X,
+                   b.f0N, wi);
     launch_w_partial(st, metric, DM, b.items, (int)g->items_cap, b.perm, g->X, d, b.f0X, b.f0N, b.partial, ds);
     launch_w_final(st, b.f0_cl, (int)g->F0_cap, b.f0_off, k, b.citem_first, b.citem_count, b.items, b.partial,
                    b.W0);
@@ -228,11 +229,10 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     launch_fill_i32(st, b.f0_off, k + 1, 0);
   }
   launch_draw(st, metric, DM, pps ? 0 : 1, b.perm, b.slab, n, g->X, d, b.csize, t, g->base.seed, b.f0_off, b.f0X,
-              b.W0, b.p_gid, b.flag, pps ? ds : DistStore{});
+              b.W0, b.p_gid, b.flag, pps ? ds : DistStore{}, pps ? b.scan_tmp : nullptr);
   // compaction and packing
-  launch_scan(st, b.flag, n, b.pos, b.scan_tmp);
-  launch_gather_at(st, b.pos, b.off, k, b.s_off);
-  launch_sample_sizes(st, b.s_off, k, (int)g->S_cap, b.cnt, b.sp_off, b.status);
+  launch_scan(st, b.flag, n, b.pos, b.scan_tmp, pps);
+  launch_sample_sizes(st, b.pos, b.off, b.s_off, k, (int)g->S_cap, b.cnt, b.sp_off, b.status);
   launch_pack(st, b.perm, b.slab, b.flag, b.pos, n, k, g->X, d, DM, b.p_gid, b.s_off, b.sp_off,
               pack_mode(metric), g->rn, (int)g->S_cap, b.gid_view, b.gid_pk, b.w32, b.aux32, b.Y32);
   // Phase 2 and the mean (the block shape does not change the results)
@@ -276,8 +276,9 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
     return false;
   }
-  launch_mean(st, b.bpart, (int)ceil_div(n, g->p2_rows), n, g->means_d + i, A.split ? (int)ceil_div(n, 32) : 0);
-  launch_put_status(st, b.status, g->status_d + i);
+  launch_mean(st, b.bpart, (int)ceil_div(n, g->p2_rows), n, g->means_d + i, A.split ? (int)ceil_div(n, 32) : 0,
+              pps ? b.status : nullptr, g->status_d + i);
+  if (!pps) launch_put_status(st, b.status, g->status_d + i);
   return hipGetLastError() == hipSuccess;
 }
 

@@ -26,26 +26,39 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // ---- cluster index -------------------------------------------------------
 // per-unit label histograms uh [k][units] (label-major); *bad = 1 if a label
 // is outside [0, k) (bad may be null: such a label is counted nowhere)
-void launch_unit_hist(hipStream_t st, const int32_t* labels, int n, int k, int seg, int32_t* uh, int* bad);
+void launch_unit_hist(hipStream_t st, const int32_t* labels, int n, int k, int seg, int32_t* uh,
+                      int32_t* perm = nullptr, int32_t* slab = nullptr);
 // uh[u][j] <- label j's rows before unit u; counts[j] = |C_j|
 void launch_unit_scan(hipStream_t st, int32_t* uh, int units, int k, int32_t* counts);
 // stable scatter: rows of label j go to off[j] + uh[u][j] + (rank inside the unit)
 void launch_scatter(hipStream_t st, const int32_t* labels, int n, int k, int seg, const int32_t* ubase,
                     const int32_t* off, int32_t* perm, int32_t* slab);
 // out[0..n] = exclusive prefix sums of in[0..n), out[n] = total.  tmp holds
-// ceil_div(n, kScanTile) + 1 ints.
-void launch_scan(hipStream_t st, const int32_t* in, int n, int32_t* out, int32_t* tmp);
+// scan_words(n) ints; with `sums` it holds the sums of every 256 values on
+// entry (bsum of the kernels below).
+inline int64_t scan_words(int64_t n) { return (n + 255) / 256 + 2; }
+void launch_scan(hipStream_t st, const int32_t* in, int n, int32_t* out, int32_t* tmp, bool sums = false);
 // out[j] = scan[off[j]] for j in [0, k]
 void launch_gather_at(hipStream_t st, const int32_t* scan, const int32_t* off, int k, int32_t* out);
 
 // ---- Phase 1 -----------------------------------------------------------------
 void launch_f0_flag(hipStream_t st, const int32_t* perm, const int32_t* slab, int n,
-                    const int32_t* csize, const double* q, int64_t t, uint64_t seed, int32_t* flag);
+                    const int32_t* csize, const double* q, int64_t t, uint64_t seed, int32_t* flag,
+                    int32_t* bsum);
+// The W pass's work items as launch_f0_items sized them (cap 0: none).
+struct W0Items {
+  const int32_t *off = nullptr, *f0_off = nullptr, *citem_first = nullptr;
+  const int64_t* ibase = nullptr;
+  const int32_t* meta = nullptr;
+  int32_t* items = nullptr;
+  int k = 0, chunk = 0, cap = 0;
+};
 // rows past `cap` (the capacity of f0_gid / f0_cl / f0X / f0N) are not written;
-// f0N (cosine, else null): the rows' norms
+// f0N (cosine, else null): the rows' norms; A: also the W pass's work items
+// (A.cap slots, the unused ones empty)
 void launch_f0_pack(hipStream_t st, const int32_t* perm, const int32_t* slab, const int32_t* flag,
                     const int32_t* pos, int n, const float* X, int d, int DM, int cap, int64_t* f0_gid,
-                    int32_t* f0_cl, double* f0X, double* f0N = nullptr);
+                    int32_t* f0_cl, double* f0X, double* f0N = nullptr, const W0Items& A = {});
 // float64 distances from the members of each cluster to its initial-sample
 // rows, kept by the W pass for the draw (which then reads them instead of
 // evaluating them again): the distance of the member at sorted position i of
@@ -71,8 +84,9 @@ void launch_w_final(hipStream_t st, const int32_t* f0_cl, int F0, const int32_t*
 void launch_draw(hipStream_t st, int metric, int DM, int sampler, const int32_t* perm,
                  const int32_t* slab, int n, const float* X, int d, const int32_t* csize, int64_t t,
                  uint64_t seed, const int32_t* f0_off, const double* f0X, const double* W,
-                 double* p_gid, int32_t* flag, DistStore ds = {});
-void launch_fill_all(hipStream_t st, const int32_t* perm, int n, double* p_gid, int32_t* flag);
+                 double* p_gid, int32_t* flag, DistStore ds = {}, int32_t* bsum = nullptr);
+void launch_fill_all(hipStream_t st, const int32_t* perm, int n, double* p_gid, int32_t* flag,
+                     int32_t* bsum = nullptr);
 // rn[i] = 1 / |X_i| in float32 (fused chain in coordinate order, correctly
 // rounded square root and division), 0 for a zero row
 void launch_rnorm(hipStream_t st, const float* X, int n, int d, float* rn);
@@ -260,35 +274,37 @@ int phase2_rows(int path, int metric, int mprec, int DM);
 
 // ---- global mean -------------------------------------------------------------
 // quads: bpart holds nq partials, of which every four are added first (in order)
-void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq = 0);
+// (with status, the clustering's status word goes to *status_out)
+void launch_mean(hipStream_t st, const double* bpart, int nb, int64_t n, double* out, int nq = 0,
+                 const int* status = nullptr, int32_t* status_out = nullptr);
 
 // ---- device-side sizes for the capturable pipeline (k_graph.hip) ------------
 // bits of a clustering's status word
-constexpr int kStatusLabel = 1;    // a label outside [0, k) (set by k_unit_hist)
+constexpr int kStatusLabel = 1;    // a label outside [0, k) (set by k_index_sizes)
 constexpr int kStatusEmpty = 2;    // fewer than two nonempty clusters
 constexpr int kStatusF0 = 4;       // F0 larger than its capacity
 constexpr int kStatusPartial = 8;  // W(e_bar) partial sums larger than their capacity
 constexpr int kStatusSample = 16;  // padded sample larger than its capacity
 void launch_fill_i32(hipStream_t st, int32_t* p, int64_t count, int32_t v);
 // off[0..k] = exclusive prefix sums of csize; q[j] = min(1, (2/|C_j|) lnterm)
-void launch_index_sizes(hipStream_t st, const int32_t* csize, int k, double lnterm, int32_t* off, double* q,
+void launch_index_sizes(hipStream_t st, const int32_t* csize, int n, int k, double lnterm, int32_t* off, double* q,
                         int* status);
-// clamps f0_off to f0_cap and writes the W work items (items_cap slots, the
-// unused ones empty), per-cluster first item / count and partial bases;
+// f0_off[j] = pos[off[j]], clamped to f0_cap, and the W work items' sizes:
+// per-cluster first item / count and partial bases;
 // with dbase non-null also the bases of the kept distances (DistStore) and
 // meta[1] = 1 when they fit dist_cap doubles.  The capacity bits go into
 // *status: ORed in, or with assign_status the word is set to them (a status
 // word of its own, which then needs no clear before the launch)
-void launch_f0_items(hipStream_t st, const int32_t* csize, const int32_t* off, int32_t* f0_off, int k,
-                     int64_t t, int chunk, int f0_cap, int64_t part_cap, int items_cap, int32_t* citem_first,
-                     int32_t* citem_count, int64_t* ibase, int32_t* meta, int32_t* items, int* status,
-                     int64_t* dbase = nullptr, int64_t dist_cap = 0, bool assign_status = false);
+void launch_f0_items(hipStream_t st, const int32_t* csize, const int32_t* off, const int32_t* pos, int32_t* f0_off,
+                     int k, int64_t t, int chunk, int f0_cap, int64_t part_cap, int32_t* citem_first,
+                     int32_t* citem_count, int64_t* ibase, int32_t* meta, int* status, int64_t* dbase = nullptr,
+                     int64_t dist_cap = 0, bool assign_status = false);
 // capacity (doubles) of the kept distances for n elements, k clusters and
 // ln(5k/delta): about 1.25 times their expected count, at most 2^27
 int64_t dist_capacity(int64_t n, double lnterm);
-// cnt[j] = |F_j|, sp_off = offsets of the blocks padded to kSamplePad rows
-void launch_sample_sizes(hipStream_t st, const int32_t* s_off, int k, int s_cap, int32_t* cnt, int32_t* sp_off,
-                         int* status);
+// s_off[j] = pos[off[j]], cnt[j] = |F_j|, sp_off = offsets of the blocks padded to kSamplePad rows
+void launch_sample_sizes(hipStream_t st, const int32_t* pos, const int32_t* off, int32_t* s_off, int k, int s_cap,
+                         int32_t* cnt, int32_t* sp_off, int* status);
 void launch_put_status(hipStream_t st, const int* status, int32_t* out);
 
 // ---- host-side helpers shared by the C-ABI files ----------------------------

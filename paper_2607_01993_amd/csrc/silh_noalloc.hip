@@ -183,21 +183,16 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   const hipStream_t st = (hipStream_t)stream;
   const int n = sh.n, k = sh.k, d = sh.d, DM = sh.DM;
   const int metric = prm->metric;
-  // cluster index (perm and slab start at 0 so that rows a bad label leaves
-  // unwritten still name a valid element); the log term of q is unused here
-  launch_fill_i32(st, B.status, 1, 0);
-  launch_fill_i32(st, B.perm, n, 0);
-  launch_fill_i32(st, B.slab, n, 0);
-  launch_unit_hist(st, labels, n, k, sh.seg, B.uh, B.status);
+  // cluster index; the log term of q is unused here
+  launch_unit_hist(st, labels, n, k, sh.seg, B.uh, B.perm, B.slab);
   launch_unit_scan(st, B.uh, sh.units, k, B.csize);
-  launch_index_sizes(st, B.csize, k, 0.0, B.off, B.q, B.status);
+  launch_index_sizes(st, B.csize, n, k, 0.0, B.off, B.q, B.status);
   launch_scatter(st, labels, n, k, sh.seg, B.uh, B.off, B.perm, B.slab);
   if (B.rn) launch_rnorm(st, X, n, d, B.rn);
   // every element sampled with p = 1 (Section 2: the exact sums)
   launch_fill_all(st, B.perm, n, B.p_gid, B.flag);
   launch_scan(st, B.flag, n, B.pos, B.scan_tmp);
-  launch_gather_at(st, B.pos, B.off, k, B.s_off);
-  launch_sample_sizes(st, B.s_off, k, (int)sh.S_cap, B.cnt, B.sp_off, B.status);
+  launch_sample_sizes(st, B.pos, B.off, B.s_off, k, (int)sh.S_cap, B.cnt, B.sp_off, B.status);
   launch_pack(st, B.perm, B.slab, B.flag, B.pos, n, k, X, d, DM, B.p_gid, B.s_off, B.sp_off, pack_mode(metric),
               B.rn, (int)sh.S_cap, B.gid_view, B.gid_pk, B.w32, B.aux32, B.Y32);
   P2Args A;
