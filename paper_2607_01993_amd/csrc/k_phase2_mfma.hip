@@ -28,6 +28,7 @@
 // kT in p2_mfma_block).  The contraction order is free,
 // so each lane feeds the MFMA a contiguous half of the (augmented) row: half
 // h of the row holds logical coordinates [h*HALF, (h+1)*HALF).
+#include <type_traits>
 #include <utility>
 
 #include "device_common.hpp"
@@ -76,16 +77,36 @@ constexpr float kSkipFactor = P == 0 ? 4.0f : 2.25f;
 
 __host__ __device__ constexpr int round_up_c(int a, int b) { return (a + b - 1) / b * b; }
 
-// P = 0: float32 operands (32x32x2), P = 1: bf16 (32x32x16)
+// float32 operands with 16 to 64 coordinates go to the matrix cores as three
+// bf16 pieces each (their sum is the value to 2^-26): six products of pieces
+// cover all terms above 2^-26 of a product, at 6/16 of the float32 steps' cycles
+// (32 for 16 columns against 64 for two), and the norms stay in a float32 step.
+// Errors against 64 bits as before (d = 16 to 64, a and b 4.3e-8 to 5.7e-8 on
+// both sides).  What bounds it now: the vector ALU's square roots and sums, no
+// longer the float32 MFMA rate.  Sums of n = 200,000, k = 16, t = 256, the whole
+// request: d = 32 0.90 -> 0.60 ms, d = 64 1.52 -> 1.01; n = 1e6, d = 16 2.26 ->
+// 1.49, d = 32 3.51 -> 2.21; exact n = 40,000, d = 16 3.01 -> 2.71.  At d = 8 a step
+// would be half empty; at d = 128 the stages of two tiles would pass the LDS.
+__host__ __device__ constexpr bool three_pieces(int P, int DM) { return P == 0 && DM >= 16 && DM <= 64; }
+// contraction columns of a packed row
+__host__ __device__ constexpr int kp_c(int P, int DM) {
+  return three_pieces(P, DM) ? 3 * DM + (DM > 32 ? 16 : 8) : P == 0 ? round_up_c(DM + 2, 4) : round_up_c(DM + 6, 16);
+}
+// long rows go through LDS (the block's waves share each tile)
+__host__ __device__ constexpr bool lds_c(int P, int DM) { return P == 0 ? DM > 32 : kp_c(P, DM) / 2 > 30; }
+
+// P = 0: float32 operands (32x32x2, or SP: three bf16 pieces), P = 1: bf16
+// (32x32x16)
 template <int P, int DM>
 struct MCfg {
-  static constexpr int AUG = P == 0 ? 2 : 6;
-  static constexpr int KP = P == 0 ? round_up_c(DM + AUG, 4) : round_up_c(DM + AUG, 16);
+  static constexpr bool SP = three_pieces(P, DM);
+  static constexpr bool B16 = P == 1 || SP;  // bf16 operands
+  static constexpr int AUG = P == 1 ? 6 : 2;
+  static constexpr int KP = kp_c(P, DM);
   static constexpr int HALF = KP / 2;
-  static constexpr int NSTEP = P == 0 ? HALF : HALF / 8;
-  static constexpr int ELEM = P == 0 ? 4 : 2;  // operand bytes
-  // long rows go through LDS (the block's waves share each tile)
-  static constexpr bool LDS = HALF > 30;
+  static constexpr int NSTEP = SP ? 3 * DM / 16 + 1 : B16 ? HALF / 8 : HALF;
+  static constexpr int ELEM = B16 ? 2 : 4;  // operand bytes
+  static constexpr bool LDS = lds_c(P, DM);
   // bytes per packed row: the operands, and on the LDS path a 16-byte tail
   // with the sample's weight and per-sample value (so that one contiguous
   // copy brings a whole tile into LDS)
@@ -94,25 +115,24 @@ struct MCfg {
   // 16-wide MFMA step s, so both halves hold DM / 2 coordinates and the
   // augmentation sits in step DM / 16 (elements 8 s + e of a lane); float32
   // gives each half a contiguous half row [h HALF, (h+1) HALF)
-  static constexpr bool IL = P == 1;
+  // (SP: DM / 16 such steps of each piece, then a float32 one of the norms)
+  static constexpr bool IL = B16;
   static constexpr int FOFF = IL ? 8 : HALF;   // first element of half h: FOFF h
   static constexpr int FSTEP = IL ? 16 : 8;    // bf16 elements between steps
   // lane elements that can hold coordinates (the rest: augmentation, zeros)
   static constexpr int XR = IL ? 8 * ((DM + 15) / 16) : HALF;
 };
 
-int mfma_kp(int prec, int DM) {
-  return prec == 0 ? round_up_c(DM + 2, 4) : round_up_c(DM + 6, 16);
-}
+int mfma_kp(int prec, int DM) { return kp_c(prec, DM); }
 
-bool mfma_lds_path(int prec, int DM) {
-  return mfma_kp(prec, DM) / 2 > 30;
-}
+bool mfma_lds_path(int prec, int DM) { return lds_c(prec, DM); }
+
+bool mfma_three_pieces(int prec, int DM) { return three_pieces(prec, DM); }
 
 size_t mfma_mu_floats(int prec, int DM, int k) { return (size_t)k * mfma_kp(prec, DM) + k; }
 
 int mfma_row_bytes(int prec, int DM) {
-  return mfma_kp(prec, DM) * (prec == 0 ? 4 : 2) + (mfma_lds_path(prec, DM) ? 16 : 0);
+  return mfma_kp(prec, DM) * (prec == 0 && !three_pieces(prec, DM) ? 4 : 2) + (mfma_lds_path(prec, DM) ? 16 : 0);
 }
 
 __device__ __forceinline__ float q_bf16(float v) { return (float)(__bf16)v; }
@@ -167,30 +187,34 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
       float v = y[c] - m[c];
       if (P == 1) v = q_bf16(v);
       ny = fmaf(v, v, ny);
-      row[c] = -2.0f * v;
+      if constexpr (C::SP)
+        split3(-2.0f * v, row[c], row[DM + c], row[2 * DM + c]);
+      else
+        row[c] = -2.0f * v;
     }
     ny_r = ny;
-    if (P == 0) {
+    if constexpr (!C::B16) {
       row[DM + 1] = ny;
-    } else {
+    } else if constexpr (P == 1) {
       split3(ny, row[DM + 3], row[DM + 4], row[DM + 5]);
     }
   }
-  if (P == 0) {
+  if constexpr (!C::B16) {
     row[DM] = 1.0f;
-  } else {
+  } else if constexpr (P == 1) {
     row[DM] = row[DM + 1] = row[DM + 2] = 1.0f;
   }
   if (valid) {
     unsigned char* rowp = (unsigned char*)Ym + (size_t)s * C::ROWB;
-    if constexpr (P == 0) {
+    if constexpr (!C::B16) {
       float* out = (float*)rowp;
 #pragma unroll
       for (int c = 0; c < C::KP; ++c) out[c] = row[c];
     } else {
       __bf16* out = (__bf16*)rowp;
 #pragma unroll
-      for (int c = 0; c < C::KP; ++c) out[c] = (__bf16)row[c];
+      for (int c = 0; c < (C::SP ? 3 * DM : C::KP); ++c) out[c] = (__bf16)row[c];
+      if constexpr (C::SP) *(float4*)(out + 3 * DM) = float4{1.0f, ny_r, 0.0f, 0.0f};
     }
     if constexpr (C::LDS)
       *(u32x4*)(rowp + C::KP * C::ELEM) =
@@ -321,25 +345,12 @@ __device__ __forceinline__ float transpose_reduce16(float (&v)[16], int lane) {
 }
 
 template <int P, int DM>
-struct AFrag;
-template <int DM>
-struct AFrag<0, DM> {
-  float v[MCfg<0, DM>::NSTEP];
+struct AFrag {
+  std::conditional_t<MCfg<P, DM>::B16, bf16x8, float> v[MCfg<P, DM>::NSTEP];
 };
-template <int DM>
-struct AFrag<1, DM> {
-  bf16x8 v[MCfg<1, DM>::NSTEP];
-};
-
 template <int P, int DM>
-struct BFrag;
-template <int DM>
-struct BFrag<0, DM> {
-  float2 v[MCfg<0, DM>::NSTEP / 2];
-};
-template <int DM>
-struct BFrag<1, DM> {
-  bf16x8 v[MCfg<1, DM>::NSTEP];
+struct BFrag {
+  std::conditional_t<MCfg<P, DM>::B16, bf16x8, float2> v[MCfg<P, DM>::NSTEP / (MCfg<P, DM>::B16 ? 1 : 2)];
 };
 
 // A raw buffer resource over `bytes` bytes at p (gfx9 descriptor: stride 0,
@@ -407,7 +418,7 @@ __device__ __forceinline__ void load_chunk(const float* __restrict__ xp, int c, 
 // wrow(lane) and 16 + wrow(lane)
 template <int P, int DM>
 __device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const float* __restrict__ w, int row0,
-                                          uint32_t lane_off, uint32_t wr, BFrag<P, DM>& b, float (&wv)[2]) {
+                                          uint32_t lane_off, uint32_t aug_off, uint32_t wr, BFrag<P, DM>& b, float (&wv)[2]) {
   using C = MCfg<P, DM>;
   // row0 is wave-uniform: each 32-row tile gets buffer descriptors built on
   // the scalar unit, and a lane reads at a fixed byte offset (no per-tile
@@ -415,14 +426,17 @@ __device__ __forceinline__ void load_tile(const void* __restrict__ Ym, const flo
   const auto rb = rsrc_at((const unsigned char*)Ym + (size_t)row0 * (size_t)(C::KP * C::ELEM),
                           32 * C::KP * C::ELEM);
   const auto rw = rsrc_at(w + row0, 32 * 4);
-  if constexpr (P == 0) {
+  if constexpr (!C::B16) {
 #pragma unroll
     for (int s2 = 0; s2 < C::NSTEP / 2; ++s2)
       b.v[s2] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rb, lane_off + 8u * s2, 0, 0));
   } else {
 #pragma unroll
-    for (int s = 0; s < C::NSTEP; ++s)
+    for (int s = 0; s < C::NSTEP - (C::SP ? 1 : 0); ++s)
       b.v[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, lane_off + 2u * C::FSTEP * s, 0, 0));
+    if constexpr (C::SP)
+      b.v[C::NSTEP - 1] = __builtin_bit_cast(
+          bf16x8, u32x4{__builtin_amdgcn_raw_buffer_load_b32(rb, aug_off, 0, 0), 0u, 0u, 0u});
   }
   wv[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, 4u * wr, 0, 0));
   wv[1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, 4u * (wr + 16u), 0, 0));
@@ -460,7 +474,7 @@ __device__ __forceinline__ void p2_mfma_block(
   // contiguous halves: the augmentation columns always fall in the upper half
   // of the row
   constexpr int AUG0 = DM - C::HALF;
-  static_assert(C::IL || (AUG0 >= 0 && AUG0 + C::AUG <= C::HALF), "augmentation placement");
+  static_assert(C::B16 || (AUG0 >= 0 && AUG0 + C::AUG <= C::HALF), "augmentation placement");
   __shared__ double sh32[4 * PB];  // 32-element partials of the block, in element order
   // Long rows (bf16 / float32 with d >= 64): the block's
   // four waves sweep the same tiles, so each is loaded once per block into
@@ -486,7 +500,7 @@ __device__ __forceinline__ void p2_mfma_block(
   constexpr int kDw = (kTileI + 3) / 4;             // loads per wave per tile
   constexpr int kNIw = kTB * kDw;                   // per wave per stage, without mu
   // LDS path with bf16 operands: one tile's epilogue runs beside the
-  // next tile's MFMAs (float32 operands are bound by the MFMA rate)
+  // next tile's MFMAs (float32 operands from d = 64 on keep the sums between the tiles)
   constexpr bool kPipe = kLds && P != 0 && DM >= 128;
   // Accumulator layout.  kT (every path but the pipelined one): samples are
   // the MFMA rows, a lane's 16 accumulator rows all belong to its element
@@ -508,6 +522,8 @@ __device__ __forceinline__ void p2_mfma_block(
   const int P0 =
       __builtin_amdgcn_readfirstlane((SPLIT ? blk : blk * 4 + (int)(threadIdx.x >> 6)) * 32 * PB);
   const uint32_t lane_off = (uint32_t)((col * C::KP + h * C::FOFF) * C::ELEM);  // bytes
+  // (SP) its half of the float32 norm column: 1 and the norm, past the pieces
+  const uint32_t aug_off = (uint32_t)(col * C::KP * C::ELEM + 6 * DM + 4 * h);
   // kT: this lane's rows of a tile's per-row values (weights)
   const int wr = wrow(lane);
   // element-row layout: the element whose sums this lane ends up holding
@@ -734,6 +750,34 @@ __device__ __forceinline__ void p2_mfma_block(
           for (int e = 0; e < 8; ++e) A[b].v[s][e] = pk[4 * s + e / 2][e % 2];
         continue;
       }
+      if constexpr (C::SP) {
+        // each centred coordinate in three bf16 pieces whose sum it is
+        // to about 2^-26, its square into the norm in float32
+        constexpr int NS = DM / 16;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            f32x2 v = {xget(b, 8 * s + e) - mv[8 * s + e], xget(b, 8 * s + e + 1) - mv[8 * s + e + 1]};
+            part = fmaf(v[1], v[1], fmaf(v[0], v[0], part));
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+              const bf16x2 pc = __builtin_convertvector(v, bf16x2);
+              A[b].v[q * NS + s][e] = pc[0];
+              A[b].v[q * NS + s][e + 1] = pc[1];
+              if (q < 2) {
+                v[0] -= (float)pc[0];
+                v[1] -= (float)pc[1];
+              }
+            }
+          }
+        const float an = part + __shfl_xor(part, 32, kWave);
+        thrx[b] = __float_as_int(kRecomputeThr<P> * an);
+        chk[b] = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(an < kSkipFactor<P> * R2) != 0 ? 1 : 0);
+        A[b].v[3 * NS] = __builtin_bit_cast(bf16x8, u32x4{__float_as_uint(h == 0 ? an : 1.0f), 0u, 0u, 0u});
+        continue;
+      }
+      if constexpr (!C::SP) {
 #pragma unroll
       for (int i = 0; i < C::HALF; ++i) {
         const float v = xget(b, i) - mv[i];
@@ -748,6 +792,7 @@ __device__ __forceinline__ void p2_mfma_block(
       xq[AUG0 + 1] = h ? 1.0f : xq[AUG0 + 1];
 #pragma unroll
       for (int s = 0; s < C::NSTEP; ++s) A[b].v[s] = xq[s];
+      }
     }
     };
     if constexpr (!kLds) buildA(mu + (size_t)j * C::KP + h * C::FOFF);
@@ -780,7 +825,22 @@ __device__ __forceinline__ void p2_mfma_block(
 #pragma unroll
       for (int b = 0; b < PB; ++b) {
         f32x16 c;
-        if constexpr (P == 0) {
+        if constexpr (C::SP) {
+          // the products of pieces down to 2^-18 of the whole, small ones
+          // first, then the norms, in float32 (the bf16 step truncates, which
+          // at the norms' size showed as a bias of 6e-9 in the sums); a step
+          // is 16 coordinates
+          constexpr int NS = DM / 16;
+          constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
+          c = f32x16{};
+#pragma unroll
+          for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+              c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(getB(qb[q] * NS + s), A[b].v[qa[q] * NS + s], c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(__builtin_bit_cast(u32x4, getB(3 * NS))[0]),
+                                                   __uint_as_float(__builtin_bit_cast(u32x4, A[b].v[3 * NS])[0]), c, 0, 0, 0);
+        } else if constexpr (P == 0) {
           const float2 b0 = getB(0);
           c = __builtin_amdgcn_mfma_f32_32x32x2f32(b0.x, A[b].v[0], f32x16{}, 0, 0, 0);
           c = __builtin_amdgcn_mfma_f32_32x32x2f32(b0.y, A[b].v[1], c, 0, 0, 0);
@@ -996,9 +1056,11 @@ __device__ __forceinline__ void p2_mfma_block(
         if (t == 0) buildA((const float*)(sb + kMuOff) + h * C::FOFF);
         auto fromLds = [&](int tt) {
           const unsigned char* tl = sb + tt * kTileCh * 16 + col * kLRow + h * C::FOFF * C::ELEM;
-          return [tl](int q) {
-            if constexpr (P == 0) {
+          return [=](int q) {
+            if constexpr (!C::B16) {
               return *(const float2*)(tl + 8 * q);
+            } else if (C::SP && q == C::NSTEP - 1) {  // its half of the norm column
+              return __builtin_bit_cast(bf16x8, u32x4{*(const unsigned*)(tl + 6 * DM - 12 * h), 0u, 0u, 0u});
             } else {
               return *(const bf16x8*)(tl + 2 * C::FSTEP * q);
             }
@@ -1066,19 +1128,19 @@ __device__ __forceinline__ void p2_mfma_block(
       // each tile covers only that tile's loads; an odd last tile runs after
       // the loop from the buffer already loaded, and its successor is loaded
       // into the same buffer once its MFMAs are issued.
-      if (ntile > 0 && pre != base) load_tile<P, DM>(Ym, w, base, lane_off, wr, b0, w0);
+      if (ntile > 0 && pre != base) load_tile<P, DM>(Ym, w, base, lane_off, aug_off, wr, b0, w0);
       int t = 0;
       for (; t + 2 <= ntile; t += 2) {
-        load_tile<P, DM>(Ym, w, base + (t + 1) * 32, lane_off, wr, b1, w1);
+        load_tile<P, DM>(Ym, w, base + (t + 1) * 32, lane_off, aug_off, wr, b1, w1);
         tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, false);
         pre = clamp_row(t + 2 < ntile ? base + (t + 2) * 32 : next_base);
-        load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
+        load_tile<P, DM>(Ym, w, pre, lane_off, aug_off, wr, b0, w0);
         tile([&](int q) { return b1.v[q]; }, w1, base + (t + 1) * 32, t + 2 == ntile);
       }
       if (t < ntile) {
         tile([&](int q) { return b0.v[q]; }, w0, base + t * 32, true);
         pre = clamp_row(next_base);
-        load_tile<P, DM>(Ym, w, pre, lane_off, wr, b0, w0);
+        load_tile<P, DM>(Ym, w, pre, lane_off, aug_off, wr, b0, w0);
       }
     }
     const int sz = csize[j];
@@ -1192,8 +1254,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
 // Block shapes of the matrix-core kernel (ids used by the autotuner):
 //  1  one 32-element block per wave (on the LDS path with kTBDefault tiles
 //     per stage);
-//  2  two blocks per wave: half the B-operand loads per pair (the float32
-//     path is bound by the MFMA rate and gains) but twice the accumulator
+//  2  two blocks per wave: half the B-operand loads per pair but twice the accumulator
 //     and A-operand registers (fewer waves per SIMD); d <= 64;
 //  3  one block per wave with the other number of tiles per LDS stage (the
 //     LDS path only).

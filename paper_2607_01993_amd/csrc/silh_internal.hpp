@@ -200,6 +200,8 @@ int mfma_pb_max(int prec, int DM);
 // whether a launch over n elements splits the clusters over a block's waves
 bool mfma_split(int prec, int DM, int64_t n, int k);
 bool mfma_lds_path(int prec, int DM);
+// the packed rows hold three bf16 pieces of each float32 coordinate
+bool mfma_three_pieces(int prec, int DM);
 // the shape ids valid for (prec, DM) into ids[0..2]; returns their count
 int mfma_shapes(int prec, int DM, int* ids);
 bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const float* mu, const void* Ym,

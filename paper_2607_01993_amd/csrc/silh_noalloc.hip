@@ -40,25 +40,38 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr size_t kRecordBytes = (size_t)4096 * (64 + 256 * 12);
 static __device__ __align__(256) unsigned char records[kRecordBytes];
 
+// Rows of three bf16 pieces and their centres (float32 Euclidean, d from 9 to
+// 64) are larger than the float32 rows that the capacity counts: they have an
+// array of their own, enough for every request that fits the capacity (the
+// largest share is d > 32: 432 bytes a row where `scratch` holds at least 564).
+constexpr size_t kOperandBytes = (size_t)208 << 20;
+static __device__ __align__(256) unsigned char operands[kOperandBytes];
+
+size_t f32_row_bytes(int DM) { return (size_t)(DM + 4) * 4 + (DM > 32 ? 16 : 0); }
+
 std::mutex g_mu[kMaxDevices];
 void* g_ptr[kMaxDevices] = {};
 void* g_rec[kMaxDevices] = {};
+void* g_ops[kMaxDevices] = {};
 
 // The device address of this device's copy of `scratch`, looked up once per
 // device (with that device current) and kept.
-silh_status scratch_for(int dev, unsigned char** out, unsigned char** rec) {
+silh_status scratch_for(int dev, unsigned char** out, unsigned char** rec, unsigned char** ops) {
   if (!g_ptr[dev]) {
-    void *p = nullptr, *r = nullptr;
+    void *p = nullptr, *r = nullptr, *o = nullptr;
     if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || p == nullptr ||
-        hipGetSymbolAddress(&r, HIP_SYMBOL(records)) != hipSuccess || r == nullptr) {
+        hipGetSymbolAddress(&r, HIP_SYMBOL(records)) != hipSuccess || r == nullptr ||
+        hipGetSymbolAddress(&o, HIP_SYMBOL(operands)) != hipSuccess || o == nullptr) {
       (void)hipGetLastError();
       return set_error(SILH_E_HIP, "hipGetSymbolAddress of the static scratch array failed");
     }
     g_ptr[dev] = p;
     g_rec[dev] = r;
+    g_ops[dev] = o;
   }
   *out = (unsigned char*)g_ptr[dev];
   *rec = (unsigned char*)g_rec[dev];
+  *ops = (unsigned char*)g_ops[dev];
   return SILH_OK;
 }
 
@@ -97,7 +110,7 @@ struct Bufs {
 
 struct Shape {
   int n, d, k, DM, mprec, p2_rows, seg, units;
-  bool mfma, split, cos, bounds, split32;
+  bool mfma, split, cos, bounds, split32, pieces;
   int64_t S_cap;
 };
 
@@ -109,7 +122,10 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
   sl.add(&b.p_gid, n).add(&b.gid_view, s.S_cap).add(&b.gid_pk, s.S_cap).add(&b.w32, s.S_cap);
   sl.add(&b.aux32, s.S_cap).add(&b.Y32, s.S_cap * s.DM).add(&b.bpart, ceil_div(n, s.split32 ? 32 : s.p2_rows));
   if (s.mfma) {
-    sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
+    if (s.pieces)
+      sl.add(&b.mu, k * (int64_t)(s.DM + 4) + k).add(&b.Ym, s.S_cap * (int64_t)f32_row_bytes(s.DM));
+    else
+      sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
   }
   if (s.split) sl.add(&b.Wpart, n * k);
   if (s.bounds) sl.add(&b.brec, k * (int64_t)bound_rec_floats(s.DM)).add(&b.bmask, (int64_t)bound_mask_words(n, s.k));
@@ -135,6 +151,7 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   sh.mfma = path == kPathMfma;
   sh.mprec = operand_type(prm->prec);
   sh.p2_rows = phase2_rows(path, prm->metric, sh.mprec, sh.DM);
+  sh.pieces = sh.mfma && mfma_three_pieces(sh.mprec, sh.DM);
   sh.split = !sh.mfma && phase2_valu_split(prm->metric, sh.DM);
   sh.cos = path == kPathCos;
   sh.seg = sort_seg(sh.n, sh.k);
@@ -167,9 +184,9 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
     return set_error(SILH_E_HIP, "no current HIP device");
   }
   std::lock_guard<std::mutex> lk(g_mu[dev]);
-  unsigned char *base = nullptr, *rec = nullptr;
+  unsigned char *base = nullptr, *rec = nullptr, *ops = nullptr;
   {
-    const silh_status v = scratch_for(dev, &base, &rec);
+    const silh_status v = scratch_for(dev, &base, &rec, &ops);
     if (v != SILH_OK) return v;
   }
   Slices sl;
@@ -179,6 +196,13 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   if (sh.cos) B.cstat = rec;
   if (sh.cos && (size_t)sh.k * cos_stat_bytes(sh.DM) > kRecordBytes)
     return set_error(SILH_E_ARG, "too many clusters for the static record array");
+  if (sh.pieces) {
+    const size_t rows = ((size_t)sh.S_cap * mfma_row_bytes(sh.mprec, sh.DM) + 255) & ~(size_t)255;
+    if (rows + mfma_mu_floats(sh.mprec, sh.DM, sh.k) * sizeof(float) > kOperandBytes)
+      return set_error(SILH_E_ARG, "too many rows for the static operand array");
+    B.Ym = ops;
+    B.mu = (float*)(ops + rows);
+  }
 
   const hipStream_t st = (hipStream_t)stream;
   const int n = sh.n, k = sh.k, d = sh.d, DM = sh.DM;

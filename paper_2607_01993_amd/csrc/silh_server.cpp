@@ -217,20 +217,30 @@ namespace {
 // Device bytes one request needs at most, roughly: the cluster index and the
 // Phase-1 arrays (about 24 bytes per element), the distances kept between the
 // W pass and the draw, plus the packed sample, sized for S = 2 k t + 32 k rows
-// (a few times the expected 1-1.5 k t).
-uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
+// (a few times the expected 1-1.5 k t).  `least`: without what only speeds
+// Phase 2 up (tables, bounds, records, rows in three pieces); a request whose
+// least size fits the budget is accepted, and one whose full size does not
+// then runs alone.
+uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool least) {
   const int DM = silh::dm_for(ds.d);
   const uint64_t n = (uint64_t)ds.n;
   uint64_t S = 2ull * (uint64_t)r.k * (uint64_t)r.t + 32ull * (uint64_t)r.k;
   if (S > n + 32ull * (uint64_t)r.k) S = n + 32ull * (uint64_t)r.k;
   const bool mfma = silh::phase2_path(r.metric, r.prec, DM) == silh::kPathMfma;
-  const uint64_t kp = mfma ? (uint64_t)silh::mfma_row_bytes(silh::operand_type(r.prec), DM) : 0;
+  const int op = silh::operand_type(r.prec);
+  uint64_t kp = mfma ? (uint64_t)silh::mfma_row_bytes(op, DM) : 0;
+  // one operand row per sample (float32, bf16 or fp8) where matrix cores or the
+  // cosine records serve the request
+  if (least && (r.metric == SILH_EUCL || r.metric == SILH_COS) && r.prec != SILH_FP32_VALU)
+    kp = op == 0 ? 4 * (uint64_t)(DM + 4) + (DM > 32 ? 16 : 0)
+                 : op == 1 ? (uint64_t)silh::mfma_row_bytes(1, DM)
+                           : ((uint64_t)DM + 63) / 64 * 64 + 16;
   const uint64_t row = (uint64_t)DM * 4 + kp + 24;
   const uint64_t m = r.m > 0 ? (uint64_t)r.m : 0;  // row draws: ids, gathered rows, outputs
   // d > 128 Manhattan / Canberra: float64 partial sums per element and cluster
   uint64_t split = (DM > 128 && (r.metric == SILH_MANH || r.metric == SILH_CANB)) ? n * (uint64_t)r.k * 8 : 0;
   // or the tables
-  if (silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
+  if (!least && silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
     split = silh::tab_bytes(silh::tab_plan(r.metric, (int64_t)n, ds.d, r.k, (int64_t)S, (int64_t)S, true), r.k, ds.d);
   // PPS: the W pass keeps its distances for the draw (allocated at their
   // capacity)
@@ -240,10 +250,11 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r) {
   // cosine: one float32 reciprocal norm per element (fp8: one more value) and
   // a record per cluster
   const uint64_t rn = r.metric == SILH_COS
-                          ? (r.prec == SILH_FP8 ? 8 : 4) * n + (uint64_t)r.k * silh::cos_stat_bytes(DM)
+                          ? (r.prec == SILH_FP8 && !least ? 8 : 4) * n +
+                                (least ? 0 : (uint64_t)r.k * silh::cos_stat_bytes(DM))
                           : 0;
   // Euclidean bounds: a mask per 32 elements, a record per cluster
-  const uint64_t bnd = mfma ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
+  const uint64_t bnd = mfma && !least ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
                                   4 * (uint64_t)r.k * silh::bound_rec_floats(DM)
                             : 0;
   return bnd + 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
@@ -715,8 +726,8 @@ silh_status silh_server_submit(silh_server* srv, const silh_request* req, int64_
   silh_status s = silh::validate_params(&p, ds.X, req->labels, &t);
   if (s != SILH_OK) return s;
   if (req->t < 1 || req->m < 0 || req->m > ((int64_t)1 << 30)) return SILH_E_ARG;
-  const uint64_t est = estimate_bytes(ds, *req);
-  if (est > srv->budget) return SILH_E_NOMEM;
+  if (estimate_bytes(ds, *req, true) > srv->budget) return SILH_E_NOMEM;
+  const uint64_t est = estimate_bytes(ds, *req, false);
   {
     std::lock_guard<std::mutex> lk(srv->mu);
     const int64_t tk = srv->next_ticket++;
