@@ -63,7 +63,9 @@ def traffic_for(metric, prec):
 
 def phase2_roofline(metric, prec, d, n, S, kern_s):
     """Roofline of the Phase-2 launch: algorithmic work per launch (n*S pairs
-    times the per-pair figure) over the average launch duration."""
+    times the per-pair figure) over the average launch duration.  All n*S
+    pairs count, also those that the Euclidean bounds, the cosine records or
+    the tables save the kernel, so a fraction can exceed 1."""
     pairs = float(n) * S
     if metric == "eucl" and prec == "bf16":
         # two ceilings: the square root per pair (transcendental rate) and

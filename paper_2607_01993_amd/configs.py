@@ -14,7 +14,9 @@ For every (workload, metric, operands) the Phase-2 launch is timed with HIP
 events (median of 5 requests after one warm-up) and reported as pairs/s,
 MFMA TFLOP/s (2d flops per pair) against the operand type's peak, and for
 Euclidean the square-root rate against its 19.66e12/s ceiling; vector-ALU
-metrics against 157.3 TFLOP/s.  Prints one JSON line.
+metrics against 157.3 TFLOP/s.  All n*S pairs count as work, also those that
+the Euclidean bounds, the cosine records and the Manhattan / Canberra tables
+save the kernels, so a fraction can exceed 1.  Prints one JSON line.
 """
 from __future__ import annotations
 
