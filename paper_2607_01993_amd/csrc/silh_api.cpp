@@ -938,6 +938,18 @@ silh_status tab_buffers(silh_ctx* c, const P2Args& A, std::vector<void*>& list, 
   return cv.commit(c, list);
 }
 
+// whether the tables serve a Phase 2 over A's rows: where they pay and their
+// buffers can be had (else the direct sums, which need none)
+silh_status want_tables(silh_ctx* c, const P2Args& A, std::vector<void*>& list, TabPlan& plan, TabBufs& B, bool* use) {
+  *use = tab_pays(c->prm.metric, A.n, c->k, c->t_rows);
+  if (!*use) return SILH_OK;
+  const silh_status s = tab_buffers(c, A, list, plan, B);
+  if (s != SILH_E_NOMEM) return s;
+  *use = false;
+  g_err.clear();
+  return SILH_OK;
+}
+
 bool launch_p2(silh_ctx* c, const P2Args& A, int pb, const TabPlan* plan = nullptr, const TabBufs* tab = nullptr) {
   if (plan) return launch_phase2_tab(c->st, c->prm.metric, c->DM, A, *plan, *tab);
   if (c->cos) return launch_phase2_cos(c->st, c->mprec, c->DM, A);
@@ -971,10 +983,9 @@ silh_status run_phase2(silh_ctx* c, float* a, float* b, float* s, float* What, d
   free_list(c, c->alloc_p2);
   TabPlan plan;
   TabBufs tab;
-  const bool use_tab = tab_pays(c->prm.metric, A.n, c->k, c->t_rows);
-  if (use_tab) {
-    CHK(tab_buffers(c, A, c->alloc_p2, plan, tab));
-  } else if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
+  bool use_tab = false;
+  CHK(want_tables(c, A, c->alloc_p2, plan, tab, &use_tab));
+  if (!use_tab && !c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
     cv.add(&A.Wpart, (size_t)c->n * c->k);
     CHK(cv.commit(c, c->alloc_p2));
@@ -1067,10 +1078,9 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   A.split = c->mfma && mfma_split(c->mprec, c->DM, mu, c->k);
   TabPlan plan;
   TabBufs tab;
-  const bool use_tab = tab_pays(c->prm.metric, mu, c->k, c->t_rows);
-  if (use_tab) {
-    CHK(tab_buffers(c, A, c->alloc_rows, plan, tab));
-  } else if (!c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
+  bool use_tab = false;
+  CHK(want_tables(c, A, c->alloc_rows, plan, tab, &use_tab));
+  if (!use_tab && !c->mfma && phase2_valu_split(c->prm.metric, c->DM)) {
     Carve cv;
     cv.add(&A.Wpart, (size_t)(mu > 0 ? mu : 1) * c->k);
     CHK(cv.commit(c, c->alloc_rows));

@@ -68,6 +68,7 @@ struct silh_graph {
   std::vector<int64_t> probe_S;  // padded sample size of the request the shape was tuned on
   int K = 0, n = 0, d = 0, DM = 0, mprec = 0, p2_rows = 0, chunk = 0, kmax = 0;
   bool mfma = false, cos = false;
+  bool tables = true;  // the tables' buffers could be had (else the direct sums)
   int64_t S_cap = 0, F0_cap = 0, items_cap = 0, part_cap = 0, dist_cap = 0;
   std::vector<Branch> br;
   std::vector<void*> allocs;
@@ -169,19 +170,18 @@ bool alloc_branch(silh_graph* g, Branch& b) {
     p.rows = std::max(p.rows, q.rows);
     p.knots = std::max(p.knots, q.knots);
     p.rw = q.rw;
-    ok = ok && q.rows > 0;
   }
   int64_t wd = 0;
   for (size_t i = 0; i < g->ks.size(); ++i)
     if (tab_pays(g->base.metric, n, g->ks[i], g->ts[i]))
       wd = std::max(wd, tab_plan(g->base.metric, n, g->d, g->ks[i], g->S_cap, g->S_cap).rows * (int64_t)g->ks[i]);
-  if (ok && p.chunks > 0)
-    ok = take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, k + 1) &&
+  if (ok && p.chunks > 0 && g->tables)
+    g->tables = take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, k + 1) &&
          take(g, b.tab.head, p.group * g->d * (int64_t)tab_head_bytes()) && take(g, b.tab.Y, (int64_t)p.knots) &&
          take(g, b.tab.L, p.group * g->d * (int64_t)tab_cells()) &&
          take(g, b.tab.G, 2 * (int64_t)p.knots) &&
          take(g, b.tab.C, g->base.metric == SILH_CANB ? 2 * (int64_t)p.knots : 0) && take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
-  if (ok && direct && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
+  if (ok && (direct || !g->tables) && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
   if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
   return ok;
 }
@@ -270,7 +270,7 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
       A.mask = b.bmask;
     }
     if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
-  } else if (tab_pays(metric, n, k, t)) {
+  } else if (g->tables && tab_pays(metric, n, k, t)) {
     A.perm = b.perm;
     if (!launch_phase2_tab(st, metric, DM, A, tab_plan(metric, n, d, k, g->S_cap, g->S_cap), b.tab)) return false;
   } else if (!launch_phase2_valu(st, metric, DM, A)) {
@@ -353,6 +353,9 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
   bool ok = take(g, g->means_d, K) && take(g, g->status_d, K);
   if (ok && base->metric == SILH_COS) ok = take(g, g->rn, g->n);
   for (Branch& b : g->br) ok = ok && alloc_branch(g, b);
+  for (Branch& b : g->br)
+    if (!g->tables && b.Wpart == nullptr && !g->mfma && phase2_valu_split(base->metric, g->DM))
+      ok = ok && take(g, b.Wpart, (int64_t)g->n * g->kmax);
   if (!ok) {
     release(g);
     return set_error(SILH_E_NOMEM, "device allocation failed");
