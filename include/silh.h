@@ -185,7 +185,10 @@ silh_status silh_exact(const silh_params* prm, const float* X, const int32_t* la
  * results and errors as silh_exact; prm->alloc, free and alloc_user are
  * ignored.  The library's buffers (cluster index, packed rows, partial sums)
  * are slices of one static device array of 256 MiB that each device holds
- * from the first call on it until the process ends; a problem whose buffers
+ * from the first call on it until the process ends (the cosine records and
+ * the float32 Euclidean operand rows have static arrays of their own, 220 MiB
+ * together); Manhattan and Canberra keep the direct sums, which agree with
+ * silh_exact's tables to float32 rounding; a problem whose buffers
  * do not fit it (about 270 bytes per element at d = 32 with bf16 operands,
  * so n up to about 10^6) is rejected with SILH_E_ARG before anything is
  * enqueued.  The caller still passes X, labels and the outputs.  The array
