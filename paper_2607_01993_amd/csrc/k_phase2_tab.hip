@@ -418,8 +418,16 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
         const double fa = fk[i], fb = fk[i + 1];
         const double r1v = f_at(z + 0.25 * gap) - (0.75 * fa + 0.25 * fb);
         const double r2v = f_at(z + 0.75 * gap) - (0.25 * fa + 0.75 * fb);
-        const double c1 = (r2v - r1v) * (32.0 / 3.0), c0 = r1v * (16.0 / 3.0) - 0.25 * c1;
+        double c1 = (r2v - r1v) * (32.0 / 3.0), c0 = r1v * (16.0 / 3.0) - 0.25 * c1;
         const double ig = 1.0 / gap;
+        // Knots next to each other at small magnitudes: c1 ig^3 can pass the
+        // float32 range.  The residual's own c1 is at most about Wt (gap /
+        // 2^-30)^3, which Wt <= 2^30 keeps inside it, so such a c1 is the
+        // rounding of f alone, and the mean of the two residuals serves.
+        if (!(fabs(c1 * ig * ig * ig) <= (double)FLT_MAX)) {
+          c1 = 0.0;
+          c0 = (r1v + r2v) * (8.0 / 3.0);
+        }
         og[i] = double2{fa * ig, fb * ig};
         tabC[base + i] = float2{(float)(c0 * ig * ig), (float)(c1 * ig * ig * ig)};
       }

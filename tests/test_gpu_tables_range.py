@@ -1,0 +1,45 @@
+"""Manhattan and Canberra tables over the values they take: whole datasets of
+small magnitude (neighbouring knots 10^-14 and less apart)."""
+import numpy as np
+import pytest
+
+from oracle.distance import dist_matrix
+from parity_util import dev
+from paper_2607_01993_amd import native
+
+pytestmark = pytest.mark.gpu
+
+
+def sums_and_pairs(X, L, k, metric, t, seed=3):
+    """W_hat of 600 elements, sampled ones among them, and the same from the
+    pairs in float64."""
+    n = X.shape[0]
+    Xd, Ld = dev(X, L)
+    ctx = native.silh_sample_init(Xd, Ld, k, metric, "fp32", t=t, seed=seed)
+    S, _ = native.silh_pps_sample(ctx)
+    view = native.silh_sample_view(ctx)
+    W = native.silh_weighted_sums(ctx).cpu().numpy().astype(np.float64)
+    res = native.silh_scores(ctx)
+    native.silh_destroy(ctx)
+    rows = np.unique(np.concatenate([np.random.default_rng(1).integers(0, n, 300), view["gid"][:: max(1, S // 300)]]))
+    ref = np.zeros((rows.size, k))
+    for j in range(k):
+        F = view["gid"][view["offsets"][j]:view["offsets"][j + 1]]
+        ref[:, j] = (dist_matrix(X[rows], X[F], metric) / view["p"][F][None, :]).sum(axis=1)
+    return W, res, rows, ref
+
+
+@pytest.mark.parametrize("metric", ["manh", "canb"])
+@pytest.mark.parametrize("scale", [1e-6, 1e-7, 1.5e-8, 2e-9])
+def test_small_magnitudes(metric, scale):
+    n, d, k, t = 600_000, 24, 2, 600
+    print(f"tables small {metric} scale={scale}", flush=True)
+    rng = np.random.default_rng(5)
+    X = ((0.6 + rng.exponential(1.0, size=(n, d))) * scale).astype(np.float32)   # all above 2^-30
+    L = rng.integers(0, k, size=n).astype(np.int32)
+    W, res, rows, ref = sums_and_pairs(X, L, k, metric, t)
+    assert np.isfinite(W).all() and np.isfinite(res["mean"])
+    assert np.isfinite(res["a"].cpu().numpy()).all() and np.isfinite(res["s"].cpu().numpy()).all()
+    # a table's value to 2^-22 of itself (an ulp of its ends, the weights'
+    # rounding, the cubic), one rounding of the result
+    assert np.all(np.abs(W[rows] - ref) <= 2.0 ** -20 * ref), np.max(np.abs(W[rows] - ref) / ref)
