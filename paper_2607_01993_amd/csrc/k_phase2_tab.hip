@@ -24,6 +24,9 @@
 //             z = Y (2 - Y / |t|), which maps |t| -> infinity to 2 Y (up to Y z
 //             is t itself: f can be small next to the sample, and the map's
 //             rounding would not be).
+//             At t = 0 f jumps to the weights of the nonzero values
+//             alone: a record of its own (Wt less the zeros' weights would
+//             leave their rounding where the sum is small or 0).
 //
 // Precision: table values from float64 sums (Canberra: of float32 terms good
 // to an ulp), kept, interpolated and added up in float64; only the cubic's
@@ -72,7 +75,7 @@ struct TabHead {
   int K;        // knots; 0: sum directly
   float Wt;     // sum of the weights
   float Yp, Yn; // Canberra: twice the largest magnitude of the positive / negative values (1 if none)
-  float w0;     // Canberra: the weights of the zeros, f(0) = Wt - w0
+  int zeros;    // Canberra: the sample has zeros
   float lo, hi; // Manhattan: first and last knot
   float inv, off;  // cell = z inv + off
   int L;        // steps within a cell
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
   __syncthreads();
   int P = 1;
   while (P < m) P <<= 1;
-  double wt = 0.0, wneg = 0.0, wzero = 0.0;
+  double wt = 0.0, wneg = 0.0, wother = 0.0;
   for (int r = tid; r < P; r += kBuildT) {
     float y = __builtin_inff(), wr = 0.0f;
     if (r < m) {
@@ -169,25 +172,25 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       if (!(y == 0.0f || (ay >= kTabMin && ay <= kTabMax)) || !(wr <= kTabMax)) sh_bad = 1;
       wt += (double)wr;
       if (y < 0.0f) wneg += (double)wr;
-      if (y == 0.0f) wzero += (double)wr;
+      if (y != 0.0f) wother += (double)wr;
     }
     ys[r] = y == 0.0f ? 0.0f : y;  // (-0 to 0)
     ws[r] = wr;
   }
   wt = wave_sum_f64(wt);
   wneg = wave_sum_f64(wneg);
-  wzero = wave_sum_f64(wzero);
+  wother = wave_sum_f64(wother);
   if ((tid & 63) == 0) {
     red[tid >> 6][0] = wt;
     red[tid >> 6][1] = wneg;
-    red[tid >> 6][2] = wzero;
+    red[tid >> 6][2] = wother;
   }
   __syncthreads();
-  wt = wneg = wzero = 0.0;
+  wt = wneg = wother = 0.0;
   for (int i = 0; i < kBuildT / kWave; ++i) {
     wt += red[i][0];
     wneg += red[i][1];
-    wzero += red[i][2];
+    wother += red[i][2];
   }
   if (sh_bad) {  // block-uniform
     if (tid == 0) hd->K = 0;
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       }
     }
     const int L = lookup(K);
-    if (tid == 0) *hd = TabHead{K, (float)wt, 1.f, 1.f, 0.f, kn[0], kn[K - 1], inv, off, L, {0, 0}};
+    if (tid == 0) *hd = TabHead{K, (float)wt, 1.f, 1.f, 0, kn[0], kn[K - 1], inv, off, L, {0, 0}};
   } else {
     // first index of the values >= 0 and > 0
     int nneg = 0, nzero = 0;
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       nzero = lo - nneg;
     }
     const int p0 = nneg + nzero;  // positives: [p0, m)
-    const double wpos = wt - wneg - wzero;
+    const double wpos = wother - wneg;
     const double Yp = p0 < m ? 2.0 * (double)ys[m - 1] : 1.0, Yn = nneg > 0 ? -2.0 * (double)ys[0] : 1.0;
     const double up = p0 < m ? (double)ys[p0] : 1.0, un = nneg > 0 ? -(double)ys[nneg - 1] : 1.0;
     // f at signed table position z
@@ -388,7 +391,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     int pos = block_scan(tot);
     const int K = sh_n + 1;
     const int room = 2 * m + kTabExtra;
-    if (K > room || K > kTabKnots - (kTabRows + 8)) {  // block-uniform
+    if (K >= room || K > kTabKnots - (kTabRows + 8)) {  // block-uniform
       if (tid == 0) hd->K = 0;
       return;
     }
@@ -433,9 +436,18 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       }
     }
     if (bad) sh_bad = 1;  // two knots fell on one float
+    if (tid == 0) {
+      // f jumps at 0 where the sample has zeros: f(0) is the sum of the other
+      // weights.  An element's 0 takes the record past the last interval,
+      // E (f(0) / E), E a power of two above every z (the search stops there).
+      const float E = ldexpf(1.0f, ilogbf((float)(4.0 * Yp)) + 1);
+      oy[K] = E;
+      og[K - 1] = double2{wother / (double)E, 0.0};
+      tabC[base + K - 1] = float2{0.0f, 0.0f};
+    }
     const int L = lookup(K);
     if (tid == 0)
-      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, (float)wzero, 0.f, 0.f, inv, off, L, {0, 0}};
+      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, nzero, 0.f, 0.f, inv, off, L, {0, 0}};
   }
 }
 
@@ -534,12 +546,14 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
       __syncthreads();
       if (K > 0) {
         const size_t tb = base + (size_t)c * (size_t)(2 * m + kTabExtra);
+        // (one more knot than the table's: Canberra's for the element's zeros)
+        if (M == kCanb && threadIdx.x == 0) ly[K] = tabY[tb + K];
         for (int i = threadIdx.x; i < K; i += kEvalT) {
           ly[i] = tabY[tb + i];
           ((double2*)lg)[i] = ((const double2*)tabG)[tb + i];
           if (M == kCanb) ((float2*)lp)[i] = tabC[tb + i];
         }
-        if (threadIdx.x < kTabPad) ly[K + threadIdx.x] = __builtin_inff();
+        if (threadIdx.x < kTabPad) ly[K + (M == kCanb ? 1 : 0) + threadIdx.x] = __builtin_inff();
         if (threadIdx.x < kTabCells / 2)
           ((uint32_t*)lc)[threadIdx.x] = ((const uint32_t*)(tabL + ((size_t)(q - q0) * d + c) * kTabCells))[threadIdx.x];
       }
@@ -601,6 +615,10 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
             len -= half;
           }
         }
+        if (M == kCanb && hd.zeros) {  // uniform
+#pragma unroll
+          for (int e = 0; e < E; ++e) at[e] = x[e] == 0.0f ? 4 * (K - 1) : at[e];
+        }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float* yp = (const float*)((const unsigned char*)ly + at[e]);
@@ -623,9 +641,6 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
 #pragma unroll
             for (int e = 0; e < E; ++e) acc[e] = fma((double)hd.Wt, fabs((double)x[e] - (double)z[e]), acc[e]);
           }
-        } else if (hd.w0 != 0.0f) {  // uniform
-#pragma unroll
-          for (int e = 0; e < E; ++e) acc[e] -= x[e] == 0.0f ? (double)hd.w0 : 0.0;
         }
       } else {
         // directly: 32 rows in float32, then float64

@@ -43,3 +43,23 @@ def test_small_magnitudes(metric, scale):
     # a table's value to 2^-22 of itself (an ulp of its ends, the weights'
     # rounding, the cubic), one rounding of the result
     assert np.all(np.abs(W[rows] - ref) <= 2.0 ** -20 * ref), np.max(np.abs(W[rows] - ref) / ref)
+
+
+@pytest.mark.parametrize("zeros", [0.5, 0.99, 1.0])
+def test_sparse_canberra(zeros):
+    """Columns of zeros: an element's zero meets a sampled zero at distance
+    exactly 0, also where nearly the whole sample is 0."""
+    n, d, k, t = 30_000, 9, 3, 700
+    print(f"tables sparse zeros={zeros}", flush=True)
+    rng = np.random.default_rng(7)
+    X = rng.exponential(1.0, size=(n, d)) * rng.choice([-1.0, 1.0], size=(n, d))
+    L = rng.integers(0, k, size=n).astype(np.int32)
+    X[rng.random((n, d)) < zeros] = 0.0
+    X[L == 0] = 0.0                      # one cluster of zero rows only
+    W, res, rows, ref = sums_and_pairs(X.astype(np.float32), L, k, "canb", t)
+    assert np.all(W[L == 0, 0] == 0.0)
+    assert np.all(res["a"].cpu().numpy()[L == 0] == 0.0)
+    if zeros == 1.0:                     # every distance is 0
+        assert np.all(W == 0.0) and res["mean"] == 0.0 and np.all(res["s"].cpu().numpy() == 0.0)
+    # as above
+    assert np.all(np.abs(W[rows] - ref) <= 2.0 ** -20 * ref), np.max(np.abs(W[rows] - ref) / np.maximum(ref, 1e-300))
