@@ -71,12 +71,13 @@ __global__ __launch_bounds__(1024) void k_center(const float* __restrict__ Y32, 
 #pragma unroll 4
   for (int r = rg; r < m; r += G) {
     const float4 v = *(const float4*)(y + (size_t)r * DM);
-    const double wr = (double)w[base + r], in = r < mc ? 1.0 : 0.0;
+    const double wr = (double)w[base + r];
+    const bool in = r < mc;  // (a product with 0 would bring a later row's Inf or NaN into the centre)
     const double dv[4] = {(double)v.x - (double)y0.x, (double)v.y - (double)y0.y, (double)v.z - (double)y0.z,
                           (double)v.w - (double)y0.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      s1[e] += in * dv[e];
+      s1[e] += in ? dv[e] : 0.0;
       sw[e] += wr * dv[e];
       q += wr * dv[e] * dv[e];
     }
