@@ -348,10 +348,10 @@ __global__ __launch_bounds__((64 * kCosWaves<P, DM>)) void k_p2_cos(
       const int j = j0 + u;
       if (j >= k) break;
       // a sum of distances: the rounding of the last subtraction may leave a
-      // value below 0 (NaN passes)
+      // value below 0; an element that is not finite has sums of 0
       double W = W2[u];
       if (P == 2 && j == own) W += selfv;
-      W = W < 0.0 ? 0.0 : W;
+      W = W > 0.0 ? W : 0.0;
       if (What != nullptr && e < n) What[(size_t)e * k + j] = (float)W;
       const int sz = csize[j];
       const double dsz = (double)sz;

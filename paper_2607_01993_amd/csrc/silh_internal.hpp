@@ -94,7 +94,8 @@ void launch_rnorm(hipStream_t st, const float* X, int n, int d, float* rn);
 // 3 Canberra)
 inline int pack_mode(int metric) { return metric == 1 ? 1 : (metric == 3 ? 2 : 0); }
 // Scatter the selected elements into the cluster-blocked, padded sample.
-// mode 0: raw coordinates; 1: rows times rn (unit L2 norm, cosine); 2: raw
+// mode 0: raw coordinates; 1: rows times rn (unit L2 norm, cosine; weight and
+// coordinates 0 for a row that is not finite); 2: raw
 // coordinates with aux32 = 1 for a row holding a coordinate of magnitude
 // above 2^62 (or not finite), else 0 (Canberra; see k_phase2_valu.hip).  Rows at
 // or past `cap` (the capacity of the packed arrays) are not written.  Every

@@ -45,3 +45,27 @@ def test_euclidean_infinite_row_past_the_centre_rows(n, d):
     mine = ok & (L == 0)
     assert np.all(res["a"][mine] == np.inf) and np.isfinite(res["b"][mine]).all()
     assert np.isfinite(res["s"][ok & (L != 0)]).all()
+
+
+@pytest.mark.parametrize("prec,d,first", [("fp32", 20, 3), ("fp32", 200, 3), ("fp32_valu", 20, 3), ("fp32", 20, 700),
+                                          ("bf16", 20, 700), ("bf16", 130, 700), ("fp8", 70, 700)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_cosine_row_that_is_not_finite(prec, d, first, value):
+    """Such a row's pairs count 0: the other elements' sums are those without
+    it, its own are 0 (first: its place among its cluster's sample rows; bf16
+    and fp8 round around the mean of the first 256)."""
+    n, k = 3000, 3
+    print(f"nonfinite cos {prec} d={d} first={first} value={value}", flush=True)
+    X, L = _blobs(n, d, k, seed=d)
+    bad = int(np.flatnonzero(L == 0)[first])
+    ok = np.arange(n) != bad
+    ref, _ = _whole(np.ascontiguousarray(X[ok]), np.ascontiguousarray(L[ok]), k, "cos", prec)
+    X[bad, 1] = value
+    X[bad, 2] = np.inf
+    W, res = _whole(X, L, k, "cos", prec)
+    # float64 sums over the same rows in another order; float32: a centre moved
+    # in its last bit moves an operand by 2^-24
+    assert np.all(np.abs(W[ok].astype(np.float64) - ref) <= 2.0 ** -20 * ref)
+    assert np.all(W[bad] == 0.0)
+    assert res["a"][bad] == 0.0 and res["b"][bad] == 0.0 and res["s"][bad] == 0.0
+    assert all(np.isfinite(res[x]).all() for x in "abs") and np.isfinite(res["mean"])
