@@ -12,16 +12,21 @@
 // and the mean are those of evaluating every cluster, bit for bit.
 //
 // Widening.  With x~ = x - mu_j, y~ = y - mu_j (mu_j the kernel's centre, g_j =
-// |m_j - mu_j|): bf16 operands move each distance by at most 2^-9 (|x~| +
-// |y~|); the float32 expansion, 272 terms at most, by 2^-15 (15 |x~| + d) more,
-// given that pairs with c < 6 tau |x~|^2 are evaluated directly; together below
-// 2^-9 (1.3 |x~| + 1.05 |y~| + 0.03 d), and with |x~| <= D + g, the mean of
-// |y~| at most sqrt(V) + g, the mean of d at most D + sqrt(V) (D = |x - m_j|):
-//   E = Wt 2^-9 (1.33 D + 1.1 sqrt(V) + 2.4 g).
-// float32 operands: the expansion, 132 terms, 2^-16 (7 |x~| + d), covered by
-// the same expression with 2^-13.  The float32 rounding of m_j, of D (at most
-// 256 steps) and of the sums below is covered by relative slacks of 2^-14 and
-// an absolute one of 2^-22 |m_j|.
+// |m_j - mu_j|, D = |x - m_j|).  bf16 operands have eight significant bits: each
+// coordinate moves by up to 2^-8 of itself (257 -> 256), each distance by at
+// most 2^-8 (|x~| + |y~|).  The float32 expansion, 272 terms at most, each
+// addition 2^-23 of the terms' sum (|x~| + |y~|)^2, errs by 2^-16 (|x~| + |y~|)^2 / d
+// more; pairs with c < 6 tau |x~|^2 (or |y~|^2, by the layout) are evaluated
+// directly, so d is at least 0.153 of that norm r, the other at most r + d, and
+// the error at most 2^-15 (15 r + d).  Together below
+// 2^-8 (1.12 |x~| + 1.12 |y~| + 0.03 d), and with |x~| <= D + g, the mean of |y~| at
+// most sqrt(V) + g, the mean of d at most D + sqrt(V):
+//   E = Wt 2^-8 (1.33 D + 1.2 sqrt(V) + 2.4 g).
+// float32 operands: d is at least 0.43 |x~| there, the expansion's error at most
+// 2^-16 (7 |x~| + d) (132 terms; of three pieces a coordinate, 64 terms of full
+// size), covered by the same expression with 2^-13.  The float32 rounding of
+// m_j, of D (at most 256 steps) and of the sums below is covered by relative
+// slacks of 2^-14 and an absolute one of 2^-22 |m_j|.
 //
 // The groups of 32 elements that a Phase-2 wave holds share a mask, the union
 // over the group, so elements go in cluster order (the index's permutation):
@@ -164,7 +169,7 @@ __global__ __launch_bounds__(1024) void k_center(const float* __restrict__ Y32, 
     out[1] = (float)(V * (1.0 + 0x1p-14));
     out[2] = (float)(sqrt(n2) * 0x1p-22);
     out[3] = 1.33f * eta;
-    out[4] = (float)((double)eta * (1.1 * sqrt(V) + 2.4 * sqrt(g2)));
+    out[4] = (float)((double)eta * (1.2 * sqrt(V) + 2.4 * sqrt(g2)));
     out[5] = out[6] = out[7] = 0.0f;
   }
 }
@@ -172,7 +177,7 @@ __global__ __launch_bounds__(1024) void k_center(const float* __restrict__ Y32, 
 void launch_center(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
                    const int32_t* cnt, const int32_t* csize, int k, float* mu, float* rec) {
   hipLaunchKernelGGL(k_center, dim3(k), dim3(1024), 0, st, Y32, DM, mfma_kp(prec, DM), w, sp_off, cnt, csize,
-                     prec == 1 ? 0x1p-9f : 0x1p-13f, mu, rec);
+                     prec == 1 ? 0x1p-8f : 0x1p-13f, mu, rec);
 }
 
 // A block takes 64 elements (two mask groups), their rows in LDS, one element
