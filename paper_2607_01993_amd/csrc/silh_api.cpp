@@ -92,6 +92,7 @@ struct silh_ctx {
   int state = 0;  // 0 = indexed, 1 = sampled
 
   std::vector<void*> alloc_init, alloc_sample, alloc_rows, alloc_p2;
+  std::vector<void*> alloc_opt;  // the bounds' buffers: given up when memory is short
 
   // host copies
   std::vector<uint32_t> counts_h;
@@ -245,6 +246,30 @@ struct Carve {
 void free_list(silh_ctx* c, std::vector<void*>& list) {
   for (void* p : list) raw_free(c, p);
   list.clear();
+}
+
+// Buffers that only save work: where they cannot be had, *got is false and the
+// caller goes on without them.
+silh_status commit_optional(silh_ctx* c, Carve& cv, std::vector<void*>& list, bool* got) {
+  const silh_status s = cv.commit(c, list);
+  *got = s == SILH_OK;
+  if (s != SILH_E_NOMEM) return s;
+  g_err.clear();
+  return SILH_OK;
+}
+
+// Buffers that the call needs, in place of the last Phase 2's and of the
+// bounds' if memory is short (the scores are the same without the bounds).
+silh_status commit_needed(silh_ctx* c, Carve& cv, std::vector<void*>& list) {
+  const silh_status s = cv.commit(c, list);
+  if (s != SILH_E_NOMEM || (c->alloc_opt.empty() && c->alloc_p2.empty())) return s;
+  HIPCHK(hipStreamSynchronize(c->st));
+  free_list(c, c->alloc_p2);
+  free_list(c, c->alloc_opt);
+  c->brec = nullptr;
+  c->bmask = nullptr;
+  g_err.clear();
+  return cv.commit(c, list);
 }
 
 // Timing events outlive the contexts that used them: a per-device pool
@@ -631,13 +656,17 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     if (mfma_pack) {
       cv.add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k));
       cv.add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
-      if (bounds_pay(n, k, c->S_pad))
-        cv.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
     }
     if (c->cos) cv.add(&c->cstat, (size_t)k * cos_stat_bytes(c->DM));
-    if (c->cos && prec == 2) cv.add(&c->cself, (size_t)n);
+    if (c->cos && prec == 2) c->cself = (float*)c->pos;  // (read last by the packing)
     CHK(cv.commit(c, c->alloc_sample));
     c->Ym = ym;
+  }
+  if (mfma_pack && bounds_pay(n, k, c->S_pad)) {
+    Carve cv;
+    cv.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
+    bool got = false;
+    CHK(commit_optional(c, cv, c->alloc_opt, &got));  // without them every cluster is evaluated
   }
   // every packed row, padding included, is written by k_pack (no clears)
   {
@@ -673,6 +702,7 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
 
 silh_status sample_stage_buffers(silh_ctx* c) {
   free_list(c, c->alloc_sample);
+  free_list(c, c->alloc_opt);
   c->state = 0;
   c->f0_gid = c->gid_view = nullptr;
   c->f0_cl = c->items = c->citem_first = c->citem_count = c->gid_pk = c->imeta = nullptr;
@@ -925,17 +955,15 @@ int pick_pb(silh_ctx* c, P2Args A, uint32_t* mask = nullptr) {
   return choice;
 }
 
-// the tables' buffers of a Phase 2 over A's rows, on the given list
-silh_status tab_buffers(silh_ctx* c, const P2Args& A, std::vector<void*>& list, TabPlan& plan, TabBufs& B) {
+// the tables' buffers of a Phase 2 over A's rows
+void tab_buffers(silh_ctx* c, const P2Args& A, Carve& cv, TabPlan& plan, TabBufs& B) {
   int mr = 1;
   for (int j = 0; j < c->k; ++j) mr = std::max(mr, c->cnt_h[(size_t)j]);
   plan = tab_plan(c->prm.metric, A.n, c->d, c->k, c->S_pad, mr, c->pieces);
-  Carve cv;
   cv.add(&B.chunk, 4 * (size_t)plan.chunks).add(&B.cfirst, (size_t)c->k + 1);
   cv.add(&B.head, (size_t)plan.group * c->d * tab_head_bytes()).add(&B.Y, plan.knots);
   cv.add(&B.L, (size_t)plan.group * c->d * tab_cells());
   cv.add(&B.G, 2 * plan.knots).add(&B.C, c->prm.metric == SILH_CANB ? 2 * plan.knots : 0).add(&B.XT, (size_t)plan.rows * c->d).add(&B.Wd, (size_t)plan.rows * c->k);
-  return cv.commit(c, list);
 }
 
 // whether the tables serve a Phase 2 over A's rows: where they pay and their
@@ -943,11 +971,9 @@ silh_status tab_buffers(silh_ctx* c, const P2Args& A, std::vector<void*>& list, 
 silh_status want_tables(silh_ctx* c, const P2Args& A, std::vector<void*>& list, TabPlan& plan, TabBufs& B, bool* use) {
   *use = tab_pays(c->prm.metric, A.n, c->k, c->t_rows);
   if (!*use) return SILH_OK;
-  const silh_status s = tab_buffers(c, A, list, plan, B);
-  if (s != SILH_E_NOMEM) return s;
-  *use = false;
-  g_err.clear();
-  return SILH_OK;
+  Carve cv;
+  tab_buffers(c, A, cv, plan, B);
+  return commit_optional(c, cv, list, use);
 }
 
 bool launch_p2(silh_ctx* c, const P2Args& A, int pb, const TabPlan* plan = nullptr, const TabBufs* tab = nullptr) {
@@ -1021,7 +1047,8 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   free_list(c, c->alloc_rows);
   const int n = c->n, d = c->d;
   const int64_t cap = m < n ? m : n;  // distinct rows
-  int32_t *mark = nullptr, *flag = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr;
+  int32_t *mark = nullptr, *pos = nullptr, *tmp = nullptr, *urows = nullptr, *ls = nullptr;
+  int32_t* const flag = c->flag;  // (the selection flags: the sample is packed)
   uint32_t* mask = nullptr;
   int* bad = nullptr;
   float *Xs = nullptr, *au = nullptr, *bu = nullptr, *su = nullptr, *rnu = nullptr;
@@ -1029,13 +1056,18 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
   const int64_t nbm = ceil_div(m, kRowsBlock);
   {
     Carve cv;
-    cv.add(&mark, (size_t)n).add(&flag, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
+    cv.add(&mark, (size_t)n).add(&pos, (size_t)n + 1).add(&tmp, (size_t)ceil_div(n, kScanTile) + 1);
     cv.add(&urows, (size_t)cap).add(&bad, 1).add(&Xs, (size_t)cap * d).add(&ls, (size_t)cap);
     cv.add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
     cv.add(&bpu, (size_t)ceil_div(cap, c->mfma ? 32 : c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
     if (c->rn) cv.add(&rnu, (size_t)cap);
-    if (c->brec) cv.add(&mask, bound_mask_words(cap, c->k));
-    CHK(cv.commit(c, c->alloc_rows));
+    CHK(commit_needed(c, cv, c->alloc_rows));
+  }
+  if (c->brec) {
+    Carve cv;
+    cv.add(&mask, bound_mask_words(cap, c->k));
+    bool got = false;
+    CHK(commit_optional(c, cv, c->alloc_rows, &got));
   }
   HIPCHK(hipMemsetAsync(mark, 0, (size_t)n * sizeof(int32_t), c->st));
   HIPCHK(hipMemsetAsync(bad, 0, sizeof(int), c->st));
@@ -1326,7 +1358,7 @@ silh_status silh_coh_sep(silh_ctx* c, const float* W_hat, double* coh_host, doub
     Carve cv;
     if (!W_hat) cv.add(&W, (size_t)n * k);
     cv.add(&cpart, (size_t)nb).add(&spart, (size_t)nb).add(&sums, 2);
-    CHK(cv.commit(c, c->alloc_rows));
+    CHK(commit_needed(c, cv, c->alloc_rows));
   }
   if (!W_hat) {
     CHK(run_phase2(c, nullptr, nullptr, nullptr, W, nullptr));
@@ -1437,6 +1469,7 @@ void silh_destroy(silh_ctx* c) {
   pin_release(c);
   free_list(c, c->alloc_p2);
   free_list(c, c->alloc_rows);
+  free_list(c, c->alloc_opt);
   free_list(c, c->alloc_sample);
   free_list(c, c->alloc_init);
   delete c;

@@ -68,7 +68,7 @@ struct silh_graph {
   std::vector<int64_t> probe_S;  // padded sample size of the request the shape was tuned on
   int K = 0, n = 0, d = 0, DM = 0, mprec = 0, p2_rows = 0, chunk = 0, kmax = 0;
   bool mfma = false, cos = false;
-  bool tables = true;  // the tables' buffers could be had (else the direct sums)
+  bool tables = false;  // the tables' buffers could be had (else the direct sums)
   int64_t S_cap = 0, F0_cap = 0, items_cap = 0, part_cap = 0, dist_cap = 0;
   std::vector<Branch> br;
   std::vector<void*> allocs;
@@ -103,6 +103,14 @@ void* gmalloc(silh_graph* g, size_t bytes) {
   return p;
 }
 
+void gfree(silh_graph* g, void* p) {
+  if (g->base.alloc) {
+    if (g->base.free) g->base.free(p, g->base.alloc_user);
+  } else {
+    (void)hipFree(p);
+  }
+}
+
 template <class T>
 bool take(silh_graph* g, T*& p, int64_t count) {
   p = (T*)gmalloc(g, (size_t)(count > 0 ? count : 1) * sizeof(T));
@@ -118,13 +126,7 @@ void release(silh_graph* g) {
   }
   if (g->fork) (void)hipEventDestroy(g->fork);
   if (g->cap_st) (void)hipStreamDestroy(g->cap_st);
-  for (void* p : g->allocs) {
-    if (g->base.alloc) {
-      g->base.free(p, g->base.alloc_user);
-    } else {
-      (void)hipFree(p);
-    }
-  }
+  for (void* p : g->allocs) gfree(g, p);
   if (g->means_h) (void)hipHostFree(g->means_h);
   if (g->status_h) (void)hipHostFree(g->status_h);
   delete g;
@@ -152,38 +154,66 @@ bool alloc_branch(silh_graph* g, Branch& b) {
     unsigned char* ym = nullptr;
     ok = take(g, b.mu, mfma_mu_floats(g->mprec, g->DM, k)) && take(g, ym, S * (size_t)mfma_row_bytes(g->mprec, g->DM));
     b.Ym = ym;
-    ok = ok && take(g, b.brec, k * (int64_t)bound_rec_floats(g->DM)) && take(g, b.bmask, (int64_t)bound_mask_words(n, (int)k));
   }
   if (ok && g->cos) ok = take(g, b.cstat, k * (int64_t)cos_stat_bytes(g->DM));
-  if (ok && g->cos && g->mprec == 2) ok = take(g, b.cself, n);
-  // clusterings by tables, and those summed directly at d > 128
-  bool direct = false;
+  if (ok && g->cos && g->mprec == 2) b.cself = (float*)b.pos;  // (read last by the packing)
+  if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
+  return ok;
+}
+
+// the tables' buffers of every branch, once each has what it needs; where they
+// cannot be had the clusterings are summed directly
+void alloc_tables(silh_graph* g) {
   TabPlan p;
+  int64_t wd = 0;
   for (size_t i = 0; i < g->ks.size(); ++i) {
-    if (!tab_pays(g->base.metric, n, g->ks[i], g->ts[i])) {
-      direct = true;
-      continue;
-    }
-    const TabPlan q = tab_plan(g->base.metric, n, g->d, g->ks[i], g->S_cap, g->S_cap);
+    if (!tab_pays(g->base.metric, g->n, g->ks[i], g->ts[i])) continue;
+    const TabPlan q = tab_plan(g->base.metric, g->n, g->d, g->ks[i], g->S_cap, g->S_cap);
     p.chunks = std::max(p.chunks, q.chunks);
     p.group = std::max(p.group, q.group);
     p.rows = std::max(p.rows, q.rows);
     p.knots = std::max(p.knots, q.knots);
-    p.rw = q.rw;
+    wd = std::max(wd, q.rows * (int64_t)g->ks[i]);
   }
-  int64_t wd = 0;
+  g->tables = p.chunks > 0;
+  const size_t held = g->allocs.size();
+  const int64_t bytes = g->bytes;
+  for (Branch& b : g->br)
+    g->tables = g->tables && take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, g->kmax + 1) &&
+                take(g, b.tab.head, p.group * g->d * (int64_t)tab_head_bytes()) &&
+                take(g, b.tab.Y, (int64_t)p.knots) && take(g, b.tab.L, p.group * g->d * (int64_t)tab_cells()) &&
+                take(g, b.tab.G, 2 * (int64_t)p.knots) &&
+                take(g, b.tab.C, g->base.metric == SILH_CANB ? 2 * (int64_t)p.knots : 0) &&
+                take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
+  if (g->tables) return;
+  for (; g->allocs.size() > held; g->allocs.pop_back()) gfree(g, g->allocs.back());
+  g->bytes = bytes;
+}
+
+// float64 partial sums of the clusterings summed directly at d > 128
+bool alloc_split(silh_graph* g, Branch& b) {
+  if (g->mfma || !phase2_valu_split(g->base.metric, g->DM)) return true;
   for (size_t i = 0; i < g->ks.size(); ++i)
-    if (tab_pays(g->base.metric, n, g->ks[i], g->ts[i]))
-      wd = std::max(wd, tab_plan(g->base.metric, n, g->d, g->ks[i], g->S_cap, g->S_cap).rows * (int64_t)g->ks[i]);
-  if (ok && p.chunks > 0 && g->tables)
-    g->tables = take(g, b.tab.chunk, 4 * p.chunks) && take(g, b.tab.cfirst, k + 1) &&
-         take(g, b.tab.head, p.group * g->d * (int64_t)tab_head_bytes()) && take(g, b.tab.Y, (int64_t)p.knots) &&
-         take(g, b.tab.L, p.group * g->d * (int64_t)tab_cells()) &&
-         take(g, b.tab.G, 2 * (int64_t)p.knots) &&
-         take(g, b.tab.C, g->base.metric == SILH_CANB ? 2 * (int64_t)p.knots : 0) && take(g, b.tab.XT, p.rows * g->d) && take(g, b.tab.Wd, wd);
-  if (ok && (direct || !g->tables) && !g->mfma && phase2_valu_split(g->base.metric, g->DM)) ok = take(g, b.Wpart, n * k);
-  if (ok && g->dist_cap > 0) ok = take(g, b.dbase, k) && take(g, b.dkeep, g->dist_cap);
-  return ok;
+    if (!g->tables || !tab_pays(g->base.metric, g->n, g->ks[i], g->ts[i]))
+      return take(g, b.Wpart, (int64_t)g->n * g->kmax);
+  return true;
+}
+
+// whether clustering i's scores go through the bounds
+bool wants_bounds(const silh_graph* g, size_t i) {
+  return g->mfma &&
+         bounds_pay(g->n, g->ks[i], (int64_t)std::min((double)g->n, (double)g->ks[i] * (double)g->ts[i]));
+}
+
+// the bounds' buffers, for the largest clustering that wants them, once every
+// branch has what it needs; without them every cluster is evaluated
+void alloc_bounds(silh_graph* g, Branch& b) {
+  int kb = 0;
+  for (size_t i = 0; i < g->ks.size(); ++i)
+    if (wants_bounds(g, i)) kb = std::max(kb, (int)g->ks[i]);
+  if (kb == 0) return;
+  if (!take(g, b.brec, kb * (int64_t)bound_rec_floats(g->DM)) || !take(g, b.bmask, (int64_t)bound_mask_words(g->n, kb)))
+    b.brec = nullptr;
 }
 
 // clustering i's pipeline on branch b's stream: no host synchronisation,
@@ -260,7 +290,7 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     if (b.cself) launch_cos_self(st, DM, b.Y32, b.w32, b.gid_pk, b.sp_off, k, (int)g->S_cap, b.cstat, n, b.cself);
     if (!launch_phase2_cos(st, g->mprec, DM, A)) return false;
   } else if (g->mfma) {
-    const bool bounds = bounds_pay(n, k, (int64_t)std::min((double)n, (double)k * (double)t));
+    const bool bounds = b.brec != nullptr && wants_bounds(g, (size_t)i);
     launch_center(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, b.csize, k, b.mu, bounds ? b.brec : nullptr);
     if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym)) return false;
     A.perm = b.perm;
@@ -353,13 +383,13 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
   bool ok = take(g, g->means_d, K) && take(g, g->status_d, K);
   if (ok && base->metric == SILH_COS) ok = take(g, g->rn, g->n);
   for (Branch& b : g->br) ok = ok && alloc_branch(g, b);
-  for (Branch& b : g->br)
-    if (!g->tables && b.Wpart == nullptr && !g->mfma && phase2_valu_split(base->metric, g->DM))
-      ok = ok && take(g, b.Wpart, (int64_t)g->n * g->kmax);
+  if (ok) alloc_tables(g);
+  for (Branch& b : g->br) ok = ok && alloc_split(g, b);
   if (!ok) {
     release(g);
     return set_error(SILH_E_NOMEM, "device allocation failed");
   }
+  for (Branch& b : g->br) alloc_bounds(g, b);
   bool hip = hipHostMalloc((void**)&g->means_h, sizeof(double) * (size_t)K, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&g->status_h, sizeof(int32_t) * (size_t)K, hipHostMallocDefault) == hipSuccess &&
              hipStreamCreateWithFlags(&g->cap_st, hipStreamNonBlocking) == hipSuccess &&

@@ -130,7 +130,6 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
   if (s.split) sl.add(&b.Wpart, n * k);
   if (s.bounds) sl.add(&b.brec, k * (int64_t)bound_rec_floats(s.DM)).add(&b.bmask, (int64_t)bound_mask_words(n, s.k));
   if (s.cos) sl.add(&b.rn, n);
-  if (s.cos && s.mprec == 2) sl.add(&b.cself, n);
 }
 
 }  // namespace
@@ -194,6 +193,7 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   Bufs B;
   layout(sh, sl, B);
   if (sh.cos) B.cstat = rec;
+  if (sh.cos && sh.mprec == 2) B.cself = (float*)B.pos;  // (read last by the packing)
   if (sh.cos && (size_t)sh.k * cos_stat_bytes(sh.DM) > kRecordBytes)
     return set_error(SILH_E_ARG, "too many clusters for the static record array");
   if (sh.pieces) {
