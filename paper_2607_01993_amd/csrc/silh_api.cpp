@@ -516,6 +516,12 @@ silh_status check_params(const silh_params* prm, const float* X, const int32_t* 
   return SILH_OK;
 }
 
+void set_path(silh_ctx* c, int path) {
+  c->mfma = path == kPathMfma;
+  c->cos = path == kPathCos;
+  c->p2_rows = phase2_rows(path, c->prm.metric, c->mprec, c->DM);
+}
+
 // Cluster sizes, offsets and the stable sort by label.
 silh_status build_index(silh_ctx* c) {
   const int n = c->n, k = c->k;
@@ -592,11 +598,8 @@ silh_status create(const silh_params* prm, const float* X, const int32_t* labels
   c->d = prm->d;
   c->k = prm->k;
   c->DM = phase2_valu_dm(prm->d);
-  const int path = phase2_path(prm->metric, prm->prec, c->DM);
-  c->mfma = path == kPathMfma;
-  c->cos = path == kPathCos;
   c->mprec = operand_type(prm->prec);
-  c->p2_rows = phase2_rows(path, prm->metric, c->mprec, c->DM);
+  set_path(c, phase2_path(prm->metric, prm->prec, c->DM));
   silh_status s = build_index(c);
   if (s != SILH_OK) {
     std::string msg = g_err;
@@ -647,19 +650,25 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   c->S = c->s_off_h[k];
   c->S_pad = c->sp_off_h[k];
   const int prec = c->mprec;
-  const bool mfma_pack = c->mfma && c->S_pad > 0;
+  bool mfma_pack = c->mfma && c->S_pad > 0;
+  const bool pieces = mfma_pack && mfma_three_pieces(prec, c->DM);
   {
     Carve cv;
     cv.add(&c->gid_view, (size_t)c->S).add(&c->gid_pk, (size_t)c->S_pad).add(&c->w32, (size_t)c->S_pad);
     cv.add(&c->aux32, (size_t)c->S_pad).add(&c->Y32, (size_t)c->S_pad * c->DM);
     unsigned char* ym = nullptr;
-    if (mfma_pack) {
-      cv.add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k));
-      cv.add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
-    }
+    Carve op;  // the matrix cores' operands
+    (pieces ? op : cv).add(&c->mu, mfma_pack ? mfma_mu_floats(c->mprec, c->DM, k) : 0);
+    (pieces ? op : cv).add(&ym, mfma_pack ? (size_t)c->S_pad * mfma_row_bytes(prec, c->DM) : 0);
     if (c->cos) cv.add(&c->cstat, (size_t)k * cos_stat_bytes(c->DM));
     if (c->cos && prec == 2) c->cself = (float*)c->pos;  // (read last by the packing)
     CHK(cv.commit(c, c->alloc_sample));
+    if (pieces) {
+      // rows of three pieces are larger than float32 rows (1.3 to 1.5 times):
+      // without memory for them the vector ALUs sum the float32 rows
+      CHK(commit_optional(c, op, c->alloc_sample, &mfma_pack));
+      if (!mfma_pack) set_path(c, kPathValu);
+    }
     c->Ym = ym;
   }
   if (mfma_pack && bounds_pay(n, k, c->S_pad)) {
@@ -715,6 +724,7 @@ silh_status sample_stage_buffers(silh_ctx* c) {
   c->cself = nullptr;
   c->brec = nullptr;
   c->bmask = nullptr;
+  set_path(c, phase2_path(c->prm.metric, c->prm.prec, c->DM));
   const int n = c->n, k = c->k;
   const int nb = (int)ceil_div(n, c->mfma ? 32 : c->p2_rows);  // (32: split blocks)
   Carve cv;

@@ -117,6 +117,12 @@ bool take(silh_graph* g, T*& p, int64_t count) {
   return p != nullptr;
 }
 
+void free_allocs(silh_graph* g) {
+  for (void* p : g->allocs) gfree(g, p);
+  g->allocs.clear();
+  g->bytes = 0;
+}
+
 void release(silh_graph* g) {
   if (g->exec) (void)hipGraphExecDestroy(g->exec);
   if (g->graph) (void)hipGraphDestroy(g->graph);
@@ -126,7 +132,7 @@ void release(silh_graph* g) {
   }
   if (g->fork) (void)hipEventDestroy(g->fork);
   if (g->cap_st) (void)hipStreamDestroy(g->cap_st);
-  for (void* p : g->allocs) gfree(g, p);
+  free_allocs(g);
   if (g->means_h) (void)hipHostFree(g->means_h);
   if (g->status_h) (void)hipHostFree(g->status_h);
   delete g;
@@ -197,6 +203,16 @@ bool alloc_split(silh_graph* g, Branch& b) {
     if (!g->tables || !tab_pays(g->base.metric, g->n, g->ks[i], g->ts[i]))
       return take(g, b.Wpart, (int64_t)g->n * g->kmax);
   return true;
+}
+
+// every buffer that the graph cannot do without (and the tables, where they fit)
+bool alloc_needed(silh_graph* g) {
+  bool ok = take(g, g->means_d, g->K) && take(g, g->status_d, g->K);
+  if (ok && g->base.metric == SILH_COS) ok = take(g, g->rn, g->n);
+  for (Branch& b : g->br) ok = ok && alloc_branch(g, b);
+  if (ok) alloc_tables(g);
+  for (Branch& b : g->br) ok = ok && alloc_split(g, b);
+  return ok;
 }
 
 // whether clustering i's scores go through the bounds
@@ -380,11 +396,16 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
                     ? dist_capacity(g->n, std::log(5.0 * (double)g->kmax / base->delta))
                     : 0;
   g->br.resize((size_t)chains);
-  bool ok = take(g, g->means_d, K) && take(g, g->status_d, K);
-  if (ok && base->metric == SILH_COS) ok = take(g, g->rn, g->n);
-  for (Branch& b : g->br) ok = ok && alloc_branch(g, b);
-  if (ok) alloc_tables(g);
-  for (Branch& b : g->br) ok = ok && alloc_split(g, b);
+  bool ok = alloc_needed(g);
+  if (!ok && g->mfma && mfma_three_pieces(g->mprec, g->DM)) {
+    // rows of three pieces are larger than float32 rows: the vector ALUs need
+    // none (as silh_pps_sample does)
+    free_allocs(g);
+    g->br.assign((size_t)chains, Branch());
+    g->mfma = false;
+    g->p2_rows = phase2_rows(kPathValu, base->metric, g->mprec, g->DM);
+    ok = alloc_needed(g);
+  }
   if (!ok) {
     release(g);
     return set_error(SILH_E_NOMEM, "device allocation failed");

@@ -99,3 +99,46 @@ def test_sweep_without_the_bounds_buffers(monkeypatch):
     for i in at:
         got = alloc(sweep, i)
         assert got is not None and _same(got, ref), i
+
+
+@pytest.mark.parametrize("d", [12, 40])
+def test_float32_without_the_larger_operand_rows(d, monkeypatch):
+    """float32 Euclidean at d = 9 to 64 takes larger operand rows than float32
+    itself: without memory for them the request, and a captured sweep, are
+    served by the direct float32 sums."""
+    n, k = 3000, 5
+    print(f"scarce operands d={d}", flush=True)
+    X, L = synth.tiny_case(n, d, k, seed=d)
+    Xd, Ld = torch.from_numpy(X).cuda(), torch.from_numpy(L).cuda()
+
+    def scores(prec="fp32"):
+        return _plain(native.silh_exact(Xd, Ld, k, "eucl", prec))
+
+    alloc = Refusing(monkeypatch)
+    scores()
+    ref = alloc(scores)
+    calls = alloc.calls
+    direct = scores("fp32_valu")
+    served = [got for i in range(calls) if (got := alloc(scores, i)) is not None]
+    assert len(served) == 1 and _same(served[0], direct)
+    assert abs(served[0]["mean"] - ref["mean"]) <= 2.0 ** -20      # float32 sums both
+
+    _hooked(monkeypatch)
+    Lk = Ld[None].contiguous()
+
+    def sweep(prec="fp32"):
+        g = native.SweepGraph(Xd, Lk, [k], "eucl", prec, t=64, seed=5, chains=1)
+        try:
+            return {"means": g.run()["means"]}
+        finally:
+            g.close()
+
+    sweep()
+    alloc(sweep)
+    # rows of three bf16 pieces and the norms (past d = 32 a tail) at the sweep's
+    # capacity of 4 k t rows and a block of padding per cluster
+    row = {12: 2 * (3 * 16 + 8), 40: 2 * (3 * 64 + 16) + 16}[d]
+    at = alloc.bytes.index((4 * k * 64 + 32 * k) * row)
+    want = sweep("fp32_valu")
+    got = alloc(sweep, at)
+    assert got is not None and _same(got, want)
