@@ -11,7 +11,10 @@
  * Requests are admitted in arrival order while the device memory they are
  * estimated to need fits the configured budget (a request that does not fit
  * lets later ones that do go first, up to 8 times, then holds the queue until
- * it fits).  Worker threads, each with its own HIP stream and its own cache
+ * it fits).  The estimate includes what only saves work (the tables of
+ * Manhattan and Canberra, Euclidean bounds, the larger operand rows of float32
+ * Euclidean); a request that fits the budget only without it runs without it
+ * (the direct float32 sums; the bounds change no bit).  Worker threads, each with its own HIP stream and its own cache
  * of device blocks (trimmed after every request to budget / (2 workers)
  * bytes of free blocks), run the cluster index and Phase 1 of admitted
  * requests.  In mode 0 a batcher thread then runs the Phase 2 of every
@@ -93,8 +96,8 @@ silh_status silh_server_add_dataset(silh_server* srv, const float* X, int64_t n,
 
 /* Queue a request; *ticket receives its id.  Arguments are checked as
  * silh_sample_init checks them (SILH_E_ARG / SILH_E_UNSUPPORTED; also m
- * outside [0, 2^30]) before the request is queued; SILH_E_NOMEM if its
- * estimate alone exceeds the budget. */
+ * outside [0, 2^30]) before the request is queued; SILH_E_NOMEM if it
+ * alone exceeds the budget also without what only saves work. */
 silh_status silh_server_submit(silh_server* srv, const silh_request* req, int64_t* ticket);
 
 /* Block until the request has completed, copy its result to *out and retire

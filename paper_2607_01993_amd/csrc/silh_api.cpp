@@ -89,6 +89,7 @@ struct silh_ctx {
   int mprec = 0;      // operand type: 0 float32, 1 bf16, 2 fp8
   int p2_rows = kP2Rows;
   bool pieces = false;  // long Phase-2 work in pieces (set_pieces)
+  bool lean = false;    // no buffers that only save work (set_lean)
   int state = 0;  // 0 = indexed, 1 = sampled
 
   std::vector<void*> alloc_init, alloc_sample, alloc_rows, alloc_p2;
@@ -251,6 +252,8 @@ void free_list(silh_ctx* c, std::vector<void*>& list) {
 // Buffers that only save work: where they cannot be had, *got is false and the
 // caller goes on without them.
 silh_status commit_optional(silh_ctx* c, Carve& cv, std::vector<void*>& list, bool* got) {
+  *got = false;
+  if (c->lean) return SILH_OK;
   const silh_status s = cv.commit(c, list);
   *got = s == SILH_OK;
   if (s != SILH_E_NOMEM) return s;
@@ -1197,7 +1200,7 @@ int tuned_shape(silh_ctx* c) {
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   if (!c || c->state != 1) return false;
   const bool batch = c->mfma || phase2_valu_jobs_ok(c->prm.metric, c->DM);
-  if (!batch || c->cos || tab_pays(c->prm.metric, c->n, c->k, c->t_rows)) return false;
+  if (!batch || c->cos || (!c->lean && tab_pays(c->prm.metric, c->n, c->k, c->t_rows))) return false;
   P2Job J{};
   J.X = c->X;
   J.labels = c->labels;
@@ -1241,6 +1244,10 @@ bool launch_phase2_class(hipStream_t st, const P2Class& cls, const P2Job* jobs, 
 
 void set_pieces(silh_ctx* c, bool on) {
   if (c) c->pieces = on;
+}
+
+void set_lean(silh_ctx* c, bool on) {
+  if (c) c->lean = on;
 }
 
 silh_status phase2_job_mean(silh_ctx* c, double* mean) {

@@ -345,6 +345,9 @@ int64_t sample_rows(const silh_ctx* c);
 bool launch_phase2_class(hipStream_t st, const P2Class& cls, const P2Job* jobs, const int2* items, int nitems);
 // whether ctx's later Phase-2 launches leave room for other streams' work
 void set_pieces(silh_ctx* c, bool on);
+// whether ctx goes without the buffers that only save work: tables, bounds,
+// operand rows of three pieces (set before silh_pps_sample)
+void set_lean(silh_ctx* c, bool on);
 // after the job's items have all run: the Eq. 9 mean from its block partials
 // (on the context's stream; synchronises it)
 silh_status phase2_job_mean(silh_ctx* c, double* mean);

@@ -107,6 +107,7 @@ struct Job {
   silh_request req{};
   silh_result res{};
   uint64_t est = 0;
+  bool lean = false;
   bool done = false;
   int passed = 0;  // admissions that went past it while it waited at the head
 };
@@ -217,11 +218,10 @@ namespace {
 // Device bytes one request needs at most, roughly: the cluster index and the
 // Phase-1 arrays (about 24 bytes per element), the distances kept between the
 // W pass and the draw, plus the packed sample, sized for S = 2 k t + 32 k rows
-// (a few times the expected 1-1.5 k t).  `least`: without what only speeds
-// Phase 2 up (tables, bounds, records, rows in three pieces); a request whose
-// least size fits the budget is accepted, and one whose full size does not
-// then runs alone.
-uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool least) {
+// (a few times the expected 1-1.5 k t).  `lean`: without what only saves work
+// (tables, bounds, operand rows of three pieces).  A request whose lean size
+// fits the budget is accepted; one whose full size does not runs lean.
+uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool lean) {
   const int DM = silh::dm_for(ds.d);
   const uint64_t n = (uint64_t)ds.n;
   uint64_t S = 2ull * (uint64_t)r.k * (uint64_t)r.t + 32ull * (uint64_t)r.k;
@@ -229,9 +229,9 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool least) {
   const bool mfma = silh::phase2_path(r.metric, r.prec, DM) == silh::kPathMfma;
   const int op = silh::operand_type(r.prec);
   uint64_t kp = mfma ? (uint64_t)silh::mfma_row_bytes(op, DM) : 0;
-  // one operand row per sample (float32, bf16 or fp8) where matrix cores or the
-  // cosine records serve the request
-  if (least && (r.metric == SILH_EUCL || r.metric == SILH_COS) && r.prec != SILH_FP32_VALU)
+  // one operand row per sample (float32, bf16 or fp8): more than the vector
+  // ALUs' float32 rows or the cosine records, which serve a lean request
+  if (lean && (r.metric == SILH_EUCL || r.metric == SILH_COS) && r.prec != SILH_FP32_VALU)
     kp = op == 0 ? 4 * (uint64_t)(DM + 4) + (DM > 32 ? 16 : 0)
                  : op == 1 ? (uint64_t)silh::mfma_row_bytes(1, DM)
                            : ((uint64_t)DM + 63) / 64 * 64 + 16;
@@ -240,21 +240,18 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool least) {
   // d > 128 Manhattan / Canberra: float64 partial sums per element and cluster
   uint64_t split = (DM > 128 && (r.metric == SILH_MANH || r.metric == SILH_CANB)) ? n * (uint64_t)r.k * 8 : 0;
   // or the tables
-  if (!least && silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
+  if (!lean && silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
     split = silh::tab_bytes(silh::tab_plan(r.metric, (int64_t)n, ds.d, r.k, (int64_t)S, (int64_t)S, true), r.k, ds.d);
   // PPS: the W pass keeps its distances for the draw (allocated at their
   // capacity)
   const uint64_t kept = r.sampler == SILH_PPS
                             ? 8 * (uint64_t)silh::dist_capacity((int64_t)n, std::log(5.0 * r.k / r.delta))
                             : 0;
-  // cosine: one float32 reciprocal norm per element (fp8: one more value) and
-  // a record per cluster
-  const uint64_t rn = r.metric == SILH_COS
-                          ? (r.prec == SILH_FP8 && !least ? 8 : 4) * n +
-                                (least ? 0 : (uint64_t)r.k * silh::cos_stat_bytes(DM))
-                          : 0;
+  // cosine: one float32 reciprocal norm per element (and a record per cluster,
+  // less than the operand rows counted above)
+  const uint64_t rn = r.metric == SILH_COS ? 4 * n + (lean ? 0 : (uint64_t)r.k * silh::cos_stat_bytes(DM)) : 0;
   // Euclidean bounds: a mask per 32 elements, a record per cluster
-  const uint64_t bnd = mfma && !least ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
+  const uint64_t bnd = mfma && !lean ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
                                   4 * (uint64_t)r.k * silh::bound_rec_floats(DM)
                             : 0;
   return bnd + 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
@@ -304,14 +301,17 @@ void fail_result(silh_result& res, silh_status s) {
 // Phase 1 of one admitted request on the worker's stream.  Its Phase 2 goes
 // to the batcher when it has a multi-request kernel (mode 0), else it runs
 // here (the request's own launch, or the row draws of Eq. 10).
-void start_request(silh_server* srv, int w, int64_t ticket, const Dataset& ds, const silh_request& r, Pool& pool,
-                   hipStream_t st) {
+void start_request(silh_server* srv, int w, int64_t ticket, const Dataset& ds, const silh_request& r, bool lean,
+                   Pool& pool, hipStream_t st) {
   silh_result res{};
   silh_params p = request_params(ds, r, &pool);
   silh_ctx* ctx = nullptr;
   silh_status s = silh_sample_init(&p, ds.X, r.labels, (silh_stream)st, &ctx);
   int64_t S = 0;
-  if (s == SILH_OK) s = silh_pps_sample(ctx, &S, nullptr);
+  if (s == SILH_OK) {
+    silh::set_lean(ctx, lean);
+    s = silh_pps_sample(ctx, &S, nullptr);
+  }
   if (s == SILH_OK && srv->mode == 0 && r.m == 0) {
     Active* a = new (std::nothrow) Active();
     if (a && silh::phase2_job(ctx, &a->job, &a->cls)) {
@@ -413,6 +413,7 @@ void worker_main(silh_server* srv, int w) {
     Active* fin = nullptr;
     int64_t ticket = 0;
     silh_request req{};
+    bool lean = false;
     Dataset ds{};
     {
       std::unique_lock<std::mutex> lk(srv->mu);
@@ -431,6 +432,7 @@ void worker_main(silh_server* srv, int w) {
       } else if (ticket != 0) {
         Job& job = srv->jobs[ticket];
         req = job.req;
+        lean = job.lean;
         ds = srv->datasets[req.dataset];
         srv->in_flight += job.est;
         srv->running += 1;
@@ -447,7 +449,7 @@ void worker_main(silh_server* srv, int w) {
       std::snprintf(res.message, sizeof(res.message), "worker stream creation failed");
       complete(srv, ticket, res);
     } else {
-      start_request(srv, w, ticket, ds, req, pool, st);
+      start_request(srv, w, ticket, ds, req, lean, pool, st);
     }
     pool.trim(srv->pool_keep);
   }
@@ -726,14 +728,17 @@ silh_status silh_server_submit(silh_server* srv, const silh_request* req, int64_
   silh_status s = silh::validate_params(&p, ds.X, req->labels, &t);
   if (s != SILH_OK) return s;
   if (req->t < 1 || req->m < 0 || req->m > ((int64_t)1 << 30)) return SILH_E_ARG;
-  if (estimate_bytes(ds, *req, true) > srv->budget) return SILH_E_NOMEM;
-  const uint64_t est = estimate_bytes(ds, *req, false);
+  const uint64_t least = estimate_bytes(ds, *req, true), full = estimate_bytes(ds, *req, false);
+  if (least > srv->budget) return SILH_E_NOMEM;
+  const bool lean = full > srv->budget;
+  const uint64_t est = lean ? least : full;
   {
     std::lock_guard<std::mutex> lk(srv->mu);
     const int64_t tk = srv->next_ticket++;
     Job& job = srv->jobs[tk];
     job.req = *req;
     job.est = est;
+    job.lean = lean;
     job.res.submit_ns = now_ns();
     srv->queue.push_back(tk);
     *ticket = tk;
