@@ -275,7 +275,8 @@ silh_status silh_coh_sep(silh_ctx* ctx, const float* W_hat, double* coh_host, do
  *          d <= 32, else one);
  *  mode 1  (default) on the first launch for a key (metric, operand type, d
  *          rounded up as in the kernels, floor(log2) of the padded sample
- *          size) time every valid shape twice, keep the fastest; setting
+ *          size, and the launch's form: split blocks for few elements, the
+ *          clusters that bounds leave for scores or every one) time every valid shape twice, keep the fastest; setting
  *          mode 1 again forgets the measurements;
  *  mode 2 / 3 / 4  always shape 1 / 2 / 3 where valid (else the built-in).
  * Results do not depend on the shape (the partial sums of the mean are per
@@ -284,7 +285,9 @@ silh_status silh_coh_sep(silh_ctx* ctx, const float* W_hat, double* coh_host, do
  */
 silh_status silh_set_tuning(int mode);
 
-/* *pb = the measured shape id for that key (1, 2 or 3), 0 if none yet. */
+/* *pb = the measured shape id for that key (1, 2 or 3), 0 if none yet; of
+ * several forms the first measured of: every cluster unsplit, split, bounded
+ * unsplit, bounded and split. */
 silh_status silh_tuning_choice(int metric, int prec, int d, int64_t S_pad, int* pb);
 
 /* Read-only view of a context's Phase-1 result (for inspection and tests). */

@@ -882,13 +882,15 @@ silh_status phase1(silh_ctx* c, bool host_items = false) {
 
 // ---- autotuning of the MFMA Phase-2 block shape ------------------------------
 // Key: (metric, operand type, padded row width, floor(log2(padded sample
-// size))).  On the first Phase-2 launch of a key every valid shape (blocks
+// size)), form: split blocks 1, masked clusters 2, which change what a shape
+// costs: exact n = 40,000, d = 16 split and masked 2.30 ms with one block a
+// wave, 3.51 with two; n = 1e6 sums, unsplit, the same with both).  On the first Phase-2 launch of a key every valid shape (blocks
 // per wave, tiles per LDS stage: mfma_shapes) runs twice on the context's
 // stream, timed with events, and the fastest is kept for the process.  Every
 // shape writes the same values (each element's arithmetic and the
 // 128-element partials of the mean do not depend on it).
 std::mutex g_tune_mu;
-std::map<std::array<int, 4>, int> g_tune;
+std::map<std::array<int, 5>, int> g_tune;
 std::atomic<int> g_tune_mode{1};
 
 int size_bucket(int64_t S_pad) {
@@ -899,8 +901,11 @@ int size_bucket(int64_t S_pad) {
 
 // The masks of the scores' clusters for the rows of A (part of Phase 2);
 // mask holds bound_mask_words words.
+bool masks(const silh_ctx* c, const P2Args& A, const uint32_t* mask) {
+  return c->brec && mask && A.What == nullptr && A.n > 0;
+}
 void mask_clusters(silh_ctx* c, P2Args& A, uint32_t* mask) {
-  if (!c->brec || !mask || A.What != nullptr || A.n <= 0) return;
+  if (!masks(c, A, mask)) return;
   launch_bounds(c->st, c->DM, A.X, A.n, A.d, A.labels, A.perm, c->brec, A.k, mask);
   A.mask = mask;
 }
@@ -909,7 +914,7 @@ void mask_clusters(silh_ctx* c, P2Args& A, uint32_t* mask) {
 void note_cos_shape(const silh_ctx* c) {
   if (g_tune_mode.load() != 1 || c->prm.prec == SILH_FP32_VALU || (c->mprec == 0 && c->DM > 128)) return;
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune.emplace(std::array<int, 4>{SILH_COS, c->mprec, c->DM, size_bucket(c->S_pad)}, 1);
+  g_tune.emplace(std::array<int, 5>{SILH_COS, c->mprec, c->DM, size_bucket(c->S_pad), 0}, 1);
 }
 
 int pick_pb(silh_ctx* c, P2Args A, uint32_t* mask = nullptr) {
@@ -924,7 +929,8 @@ int pick_pb(silh_ctx* c, P2Args A, uint32_t* mask = nullptr) {
       if (ids[i] == mode - 1) return ids[i];
     return mfma_pb_default(c->mprec, c->DM);
   }
-  const std::array<int, 4> key{c->prm.metric, c->mprec, c->DM, size_bucket(c->S_pad)};
+  const std::array<int, 5> key{c->prm.metric, c->mprec, c->DM, size_bucket(c->S_pad),
+                               (A.split ? 1 : 0) + (masks(c, A, mask) ? 2 : 0)};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(key);
@@ -1174,7 +1180,7 @@ int phase2_rows(int path, int metric, int mprec, int DM) {
 silh_status set_error(silh_status st, const char* msg) { return fail(st, "%s", msg); }
 int64_t sample_rows(const silh_ctx* c) { return c && c->state == 1 ? c->S_pad : 0; }
 
-int tuned_shape(silh_ctx* c) {
+int tuned_shape(silh_ctx* c, bool split) {
   if (!c || c->state != 1) return 1;
   P2Args A;
   A.X = c->X;
@@ -1194,6 +1200,7 @@ int tuned_shape(silh_ctx* c) {
   A.cstat = c->cstat;
   A.cself = c->cself;
   A.perm = c->perm;
+  A.split = split && c->mfma && mfma_split(c->mprec, c->DM, c->n, c->k);
   return pick_pb(c, A, c->bmask);
 }
 
@@ -1229,7 +1236,7 @@ bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   K.metric = c->prm.metric;
   K.prec = c->mfma ? c->mprec : -1;
   K.DM = c->DM;
-  K.pb = c->mfma ? tuned_shape(c) : 1;
+  K.pb = c->mfma ? tuned_shape(c, false) : 1;  // (shared launches have no split blocks)
   K.rows = c->mfma ? phase2_mfma_rows(c->mprec, c->DM) * (K.pb == 2 ? 2 : 1) : c->p2_rows;
   K.blocks = ceil_div(c->n, K.rows);
   K.S_pad = c->S_pad;
@@ -1415,8 +1422,11 @@ silh_status silh_tuning_choice(int metric, int prec, int d, int64_t S_pad, int* 
   const int DM = phase2_valu_dm(d);
   const int mprec = prec == SILH_BF16 ? 1 : (prec == SILH_FP8 ? 2 : 0);
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  auto it = g_tune.find(std::array<int, 4>{metric, mprec, DM, size_bucket(S_pad)});
-  *pb = it == g_tune.end() ? 0 : it->second;
+  *pb = 0;
+  for (int form = 0; form < 4 && *pb == 0; ++form) {
+    auto it = g_tune.find(std::array<int, 5>{metric, mprec, DM, size_bucket(S_pad), form});
+    if (it != g_tune.end()) *pb = it->second;
+  }
   return SILH_OK;
 }
 

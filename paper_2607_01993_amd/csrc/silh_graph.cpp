@@ -424,16 +424,18 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
     return set_error(SILH_E_HIP, "stream, event or pinned allocation failed");
   }
   // Phase-2 block shapes from the autotuner: one eager request per group of
-  // clusterings with the same floor(log2(k t)) (the padded sample size is
-  // the tuner's key), tuned on its real sample; a probe that fails (bad
+  // clusterings with the same floor(log2(k t)) and form (split, masked: the
+  // tuner's key), tuned on its real sample; a probe that fails (bad
   // labels, ...) leaves the built-in shape
   g->shape.assign((size_t)K, 1);
   g->probe_S.assign((size_t)K, 0);
   if (g->mfma || g->cos) {
-    std::map<int, std::pair<int32_t, int64_t>> group;
+    std::map<std::pair<int, int>, std::pair<int32_t, int64_t>> group;
     for (int32_t i = 0; i < K; ++i) {
       const double kt = (double)ks[i] * (double)ts[(size_t)i];
-      const int gk = (int)std::floor(std::log2(kt > 1.0 ? kt : 1.0));
+      const int form = (g->mfma && mfma_split(g->mprec, g->DM, g->n, ks[i]) ? 1 : 0) +
+                       (wants_bounds(g, (size_t)i) ? 2 : 0);
+      const auto gk = std::make_pair((int)std::floor(std::log2(kt > 1.0 ? kt : 1.0)), form);
       auto it = group.find(gk);
       if (it == group.end()) {
         silh_params prm = *base;
@@ -442,7 +444,7 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
         std::pair<int32_t, int64_t> pick{g->mfma ? mfma_pb_default(g->mprec, g->DM) : 1, 0};
         if (silh_sample_init(&prm, X, labels + (size_t)i * (size_t)g->n, stream, &c) == SILH_OK &&
             silh_pps_sample(c, nullptr, nullptr) == SILH_OK) {
-          pick = {tuned_shape(c), sample_rows(c)};
+          pick = {tuned_shape(c, true), sample_rows(c)};
         }
         silh_destroy(c);
         it = group.emplace(gk, pick).first;

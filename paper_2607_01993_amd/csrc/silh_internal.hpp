@@ -337,8 +337,9 @@ struct P2Class {
 // (vector ALU with d > 128): then silh_scores runs it alone.
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls);
 // the autotuner's shape for ctx's Phase 2 (timing the shapes on ctx's data
-// when its key is new; the built-in shape on the vector ALUs or in mode 0)
-int tuned_shape(silh_ctx* c);
+// when its key is new; the built-in shape on the vector ALUs or in mode 0);
+// split: in split blocks where the launch takes them (mfma_split)
+int tuned_shape(silh_ctx* c, bool split);
 // padded sample rows of a sampled context (the tuner's size key), else 0
 int64_t sample_rows(const silh_ctx* c);
 // launch work items of requests of one class (workgroup i runs items[i])
