@@ -227,6 +227,10 @@ struct Carve {
     reqs.push_back({(void**)out, count * sizeof(T)});
     return *this;
   }
+  Carve& add(const Carve& o) {
+    reqs.insert(reqs.end(), o.reqs.begin(), o.reqs.end());
+    return *this;
+  }
   // every request gets an address of its own, also an empty one
   static size_t span(size_t b) { return b == 0 ? 256 : (b + 255) / 256 * 256; }
   silh_status commit(silh_ctx* c, std::vector<void*>& list) {
@@ -655,30 +659,41 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   const int prec = c->mprec;
   bool mfma_pack = c->mfma && c->S_pad > 0;
   const bool pieces = mfma_pack && mfma_three_pieces(prec, c->DM);
+  const bool bounds = mfma_pack && bounds_pay(n, k, c->S_pad);
   {
-    Carve cv;
+    unsigned char* ym = nullptr;
+    Carve cv, op, bnd;  // what the sample needs; rows of three pieces; the bounds
     cv.add(&c->gid_view, (size_t)c->S).add(&c->gid_pk, (size_t)c->S_pad).add(&c->w32, (size_t)c->S_pad);
     cv.add(&c->aux32, (size_t)c->S_pad).add(&c->Y32, (size_t)c->S_pad * c->DM);
-    unsigned char* ym = nullptr;
-    Carve op;  // the matrix cores' operands
-    (pieces ? op : cv).add(&c->mu, mfma_pack ? mfma_mu_floats(c->mprec, c->DM, k) : 0);
-    (pieces ? op : cv).add(&ym, mfma_pack ? (size_t)c->S_pad * mfma_row_bytes(prec, c->DM) : 0);
     if (c->cos) cv.add(&c->cstat, (size_t)k * cos_stat_bytes(c->DM));
     if (c->cos && prec == 2) c->cself = (float*)c->pos;  // (read last by the packing)
-    CHK(cv.commit(c, c->alloc_sample));
-    if (pieces) {
-      // rows of three pieces are larger than float32 rows (1.3 to 1.5 times):
-      // without memory for them the vector ALUs sum the float32 rows
-      CHK(commit_optional(c, op, c->alloc_sample, &mfma_pack));
-      if (!mfma_pack) set_path(c, kPathValu);
-    }
-    c->Ym = ym;
-  }
-  if (mfma_pack && bounds_pay(n, k, c->S_pad)) {
-    Carve cv;
-    cv.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
+    if (mfma_pack)
+      (pieces ? op : cv)
+          .add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k))
+          .add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
+    if (bounds) bnd.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
+    // all in one allocation where the bounds are small (an allocator call
+    // through PyTorch is 7 us); what saves work only is left out where it
+    // cannot be had: rows of three pieces are larger than float32 rows (1.3 to
+    // 1.5 times), and the vector ALUs sum the latter; without the bounds every
+    // cluster is evaluated
+    const bool small = 4 * bound_mask_words(n, k) <= (size_t)n / 2;
     bool got = false;
-    CHK(commit_optional(c, cv, c->alloc_opt, &got));  // without them every cluster is evaluated
+    if (pieces || (bounds && small)) {
+      Carve all = cv;
+      all.add(op);
+      if (small) all.add(bnd);
+      CHK(commit_optional(c, all, c->alloc_sample, &got));
+    }
+    if (!got) {
+      CHK(cv.commit(c, c->alloc_sample));
+      if (pieces) {
+        CHK(commit_optional(c, op, c->alloc_sample, &mfma_pack));
+        if (!mfma_pack) set_path(c, kPathValu);
+      }
+    }
+    if (mfma_pack && bounds && !(got && small)) CHK(commit_optional(c, bnd, c->alloc_opt, &got));
+    c->Ym = ym;
   }
   // every packed row, padding included, is written by k_pack (no clears)
   {
@@ -1080,13 +1095,13 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     cv.add(&au, (size_t)cap).add(&bu, (size_t)cap).add(&su, (size_t)cap);
     cv.add(&bpu, (size_t)ceil_div(cap, c->mfma ? 32 : c->p2_rows)).add(&bpm, (size_t)nbm).add(&mean_d, 1);
     if (c->rn) cv.add(&rnu, (size_t)cap);
-    CHK(commit_needed(c, cv, c->alloc_rows));
-  }
-  if (c->brec) {
-    Carve cv;
-    cv.add(&mask, bound_mask_words(cap, c->k));
     bool got = false;
-    CHK(commit_optional(c, cv, c->alloc_rows, &got));
+    if (c->brec) {
+      Carve all = cv;
+      all.add(&mask, bound_mask_words(cap, c->k));
+      CHK(commit_optional(c, all, c->alloc_rows, &got));
+    }
+    if (!got) CHK(commit_needed(c, cv, c->alloc_rows));
   }
   HIPCHK(hipMemsetAsync(mark, 0, (size_t)n * sizeof(int32_t), c->st));
   HIPCHK(hipMemsetAsync(bad, 0, sizeof(int), c->st));

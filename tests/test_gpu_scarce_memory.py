@@ -10,19 +10,31 @@ pytestmark = pytest.mark.gpu
 
 
 class Refusing:
-    """The binding's allocator, refusing its call number `at` (from 0)."""
+    """The binding's allocator, refusing its call number `at` (from 0), blocks
+    of `most` bytes and more, or what would take it past `limit` bytes in use."""
 
     def __init__(self, monkeypatch):
-        self.at, self.calls, self.bytes = None, 0, []
-        self.cb = native.ALLOC_FN(self._alloc)
-        monkeypatch.setattr(native, "_ALLOC_CB", self.cb)
+        self.at, self.calls, self.bytes, self.most, self.limit = None, 0, [], None, None
+        self.live, self.used, self.peak = {}, 0, 0
+        self.cbs = native.ALLOC_FN(self._alloc), native.FREE_FN(self._free)
+        monkeypatch.setattr(native, "_ALLOC_CB", self.cbs[0])
+        monkeypatch.setattr(native, "_FREE_CB", self.cbs[1])
 
     def _alloc(self, nbytes, user):
         self.calls += 1
-        if self.at is not None and self.calls - 1 == self.at:
+        if (self.at is not None and self.calls - 1 == self.at) or (self.most is not None and nbytes >= self.most) \
+                or (self.limit is not None and self.used + nbytes > self.limit):
             return None
         self.bytes.append(nbytes)
-        return native._py_alloc(nbytes, user)
+        p = native._py_alloc(nbytes, user)
+        self.live[p] = nbytes
+        self.used += nbytes
+        self.peak = max(self.peak, self.used)
+        return p
+
+    def _free(self, p, user):
+        self.used -= self.live.pop(p)
+        native._py_free(p, user)
 
     def __call__(self, f, at=None):
         self.at, self.calls, self.bytes = at, 0, []
@@ -41,10 +53,10 @@ def _same(a, b):
     return all(np.array_equal(a[x], b[x]) for x in a)
 
 
-@pytest.mark.parametrize("d,prec", [(16, "bf16"), (5, "fp32"), (200, "bf16")])
-def test_scores_without_the_bounds_buffers(d, prec, monkeypatch):
-    n, k = 40_000, 12
-    print(f"scarce bounds d={d} {prec}", flush=True)
+@pytest.mark.parametrize("d,prec,k", [(16, "bf16", 12), (5, "fp32", 12), (200, "bf16", 200), (16, "bf16", 200)])
+def test_scores_without_the_bounds_buffers(d, prec, k, monkeypatch):
+    n = 40_000
+    print(f"scarce bounds d={d} {prec} k={k}", flush=True)
     X, L = synth.tiny_case(n, d, k, seed=d)
     Xd, Ld = torch.from_numpy(X).cuda(), torch.from_numpy(L).cuda()
     rows = torch.arange(0, n, 2, dtype=torch.int32, device="cuda")
@@ -63,10 +75,18 @@ def test_scores_without_the_bounds_buffers(d, prec, monkeypatch):
     scores()
     ref = alloc(scores)
     served = [i for i in range(alloc.calls) if (got := alloc(scores, i)) is not None and _same(got, ref)]
-    # the records and masks of the scores, the masks of the rows, the rows'
-    # buffers (had in place of the former)
+    # the records and masks of the scores, the masks of the rows
     print("served without allocation", served, flush=True)
-    assert len(served) == 3
+    assert len(served) == 2
+    # the rows' buffers in place of the masks, and of the scores' where those
+    # have an allocation of their own
+    alloc.peak = 0
+    alloc(scores)
+    for less in (1, -(-(n // 2) // 32) * -(-k // 32) * 4 + 4096)[:2 if k > 128 else 1]:
+        alloc.limit = alloc.peak - less
+        got = alloc(scores)
+        alloc.limit = None
+        assert got is not None and _same(got, ref), less
 
 
 def _hooked(monkeypatch):
@@ -117,11 +137,16 @@ def test_float32_without_the_larger_operand_rows(d, monkeypatch):
     alloc = Refusing(monkeypatch)
     scores()
     ref = alloc(scores)
-    calls = alloc.calls
     direct = scores("fp32_valu")
-    served = [got for i in range(calls) if (got := alloc(scores, i)) is not None]
-    assert len(served) == 1 and _same(served[0], direct)
-    assert abs(served[0]["mean"] - ref["mean"]) <= 2.0 ** -20      # float32 sums both
+    # rows of three bf16 pieces and the norms (past d = 32 a tail): more than
+    # the rest of the sample's buffers together
+    row = {12: 2 * (3 * 16 + 8), 40: 2 * (3 * 64 + 16) + 16}[d]
+    assert max(alloc.bytes) >= row * n
+    alloc.most = row * n
+    got = alloc(scores)
+    alloc.most = None
+    assert got is not None and _same(got, direct)
+    assert abs(got["mean"] - ref["mean"]) <= 2.0 ** -20      # float32 sums both
 
     _hooked(monkeypatch)
     Lk = Ld[None].contiguous()
@@ -135,9 +160,7 @@ def test_float32_without_the_larger_operand_rows(d, monkeypatch):
 
     sweep()
     alloc(sweep)
-    # rows of three bf16 pieces and the norms (past d = 32 a tail) at the sweep's
-    # capacity of 4 k t rows and a block of padding per cluster
-    row = {12: 2 * (3 * 16 + 8), 40: 2 * (3 * 64 + 16) + 16}[d]
+    # the sweep's capacity: 4 k t rows and a block of padding per cluster
     at = alloc.bytes.index((4 * k * 64 + 32 * k) * row)
     want = sweep("fp32_valu")
     got = alloc(sweep, at)
