@@ -33,10 +33,11 @@
 // residual, below a thousandth of f, is float32.  Every term of the linear part
 // is >= 0 and the knots are exact, so results are relative to f itself: rows
 // equal to all of a cluster's values are at distance exactly 0.
-// A table is not used (its rows are summed directly, as in k_p2_valu) where a
-// value is not finite or its magnitude lies outside [2^-30, 2^30] (0 is fine),
-// or the refinement outgrows the table; the elements' values are arbitrary
-// (Canberra: a wave with one past 2^62 or not finite sums directly too).
+// A table is not used (its rows are summed directly, in float32 as by k_p2_valu)
+// where a value is not finite, Canberra's where a magnitude lies outside [2^-30,
+// 2^30] (0 is fine; Manhattan's up to 2^126), or the refinement outgrows the
+// table; the elements' values are arbitrary (Canberra: a wave with one past
+// 2^62 or not finite sums directly too).
 //
 // Clusters of more than kTabRows sample rows take several tables (chunks).
 #include <float.h>
@@ -50,12 +51,15 @@ namespace {
 constexpr int kTabRows = 1024;           // sample rows per table at most
 constexpr int kTabExtra = 512;           // knots beyond twice the rows
 constexpr int kTabKnots = 2 * kTabRows + kTabExtra;
+constexpr int kTabMost = kTabKnots - (kTabRows + 8);  // Canberra (base knots wait behind them)
 constexpr int kBuildT = 256, kEvalT = 256;
 // The lookup: grid cell b = (z - z0) NB / (z1 - z0) starts at the last knot of an
 // earlier cell; L steps of 2^(L-1), .., 1 knots then reach any knot of the cell.
 // Tables with a cell of more than 2^kTabSteps knots are searched in halves.
 constexpr int kTabCells = 512, kTabSteps = 6, kTabPad = 1 << kTabSteps;
 constexpr float kTabMin = 0x1p-30f, kTabMax = 0x1p30f;
+constexpr float kManhMax = 0x1p126f;  // (differences of two stay finite)
+constexpr float kPairMax = 0x1p46f;   // Canberra summed directly in pairs of rows: w n d <= 2^124
 // Canberra: knots in steps of at most kCanbStep (f / Wt)^(1/4) of ln(t + u), u
 // the smallest magnitude of the sign, f the smaller of the segment's ends but
 // no less than kCanbFloor Wt: where f starts from 0 it reaches s Wt / 2 within
@@ -79,7 +83,8 @@ struct TabHead {
   float lo, hi; // Manhattan: first and last knot
   float inv, off;  // cell = z inv + off
   int L;        // steps within a cell
-  int pad[2];
+  int wide;     // summed directly: a value past kPairMax or not finite
+  int pad;
 };
 
 // the grid cell of z (the same instructions when the table is built and read)
@@ -151,14 +156,14 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
   __shared__ double red[kBuildT / kWave][3];
   __shared__ int32_t scan[kBuildT];
   __shared__ uint16_t cell[kTabCells];
-  __shared__ int sh_bad, sh_n, sh_max;
+  __shared__ int sh_bad, sh_wide, sh_n, sh_max;
   const int q = q0 + (int)blockIdx.y, c = blockIdx.x;
   if (q >= cfirst[k]) return;
   const int4 ck = chunk[q];
   const int m = ck.z;
   const int tid = threadIdx.x;
   TabHead* hd = head + (size_t)blockIdx.y * d + c;
-  if (tid == 0) sh_bad = 0;
+  if (tid == 0) sh_bad = sh_wide = 0;
   __syncthreads();
   int P = 1;
   while (P < m) P <<= 1;
@@ -169,7 +174,9 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       y = Y32[(size_t)(ck.y + r) * DM + c];
       wr = w[ck.y + r];
       const float ay = fabsf(y);
-      if (!(y == 0.0f || (ay >= kTabMin && ay <= kTabMax)) || !(wr <= kTabMax)) sh_bad = 1;
+      if (M == kManh ? !(ay <= kManhMax) : !(y == 0.0f || (ay >= kTabMin && ay <= kTabMax))) sh_bad = 1;
+      if (!(wr <= kTabMax)) sh_bad = 1;
+      if (!(ay <= kPairMax)) sh_wide = 1;
       wt += (double)wr;
       if (y < 0.0f) wneg += (double)wr;
       if (y != 0.0f) wother += (double)wr;
@@ -193,7 +200,10 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     wother += red[i][2];
   }
   if (sh_bad) {  // block-uniform
-    if (tid == 0) hd->K = 0;
+    if (tid == 0) {
+      hd->K = 0;
+      hd->wide = sh_wide;
+    }
     return;
   }
   // bitonic sort, ascending (padding +inf at the end)
@@ -291,7 +301,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       }
     }
     const int L = lookup(K);
-    if (tid == 0) *hd = TabHead{K, (float)wt, 1.f, 1.f, 0, kn[0], kn[K - 1], inv, off, L, {0, 0}};
+    if (tid == 0) *hd = TabHead{K, (float)wt, 1.f, 1.f, 0, kn[0], kn[K - 1], inv, off, L, 0, 0};
   } else {
     // first index of the values >= 0 and > 0
     int nneg = 0, nzero = 0;
@@ -347,7 +357,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     int at = block_scan(cntd);
     const int nd = sh_n;
     // of them negative: the distinct values before p0
-    float* bk = kn + kTabKnots - (kTabRows + 8);  // base knots wait at the end of kn
+    float* bk = kn + kTabMost;  // base knots wait at the end of kn
     if (tid == 0) {
       bk[0] = (float)(-2.0 * Yn);
       bk[1] = (float)-Yn;
@@ -391,8 +401,11 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     int pos = block_scan(tot);
     const int K = sh_n + 1;
     const int room = 2 * m + kTabExtra;
-    if (K >= room || K > kTabKnots - (kTabRows + 8)) {  // block-uniform
-      if (tid == 0) hd->K = 0;
+    if (K >= room || K > kTabMost) {  // block-uniform
+      if (tid == 0) {
+        hd->K = 0;
+        hd->wide = 0;
+      }
       return;
     }
     for (int i = s0; i < s1; ++i) {
@@ -447,7 +460,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     }
     const int L = lookup(K);
     if (tid == 0)
-      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, nzero, 0.f, 0.f, inv, off, L, {0, 0}};
+      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, nzero, 0.f, 0.f, inv, off, L, 0, 0};
   }
 }
 
@@ -494,8 +507,13 @@ __global__ __launch_bounds__(256) void k_tab_transpose(const float* __restrict__
 // the tile's elements through it.  Wd [k][R]: assigned by the cluster's first
 // chunk (or where it has none), added to by the others.
 // ----------------------------------------------------------------------------
+// Canberra's eight elements a thread hold 96 registers, five waves per SIMD
+// (the direct sums below would take 99: four waves, 3.92 -> 4.29 ms).
 template <int M, int E>
-__global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ XT, int R, int d,
+constexpr int kEvalWaves = M == kCanb && E == 8 ? 5 : 1;
+
+template <int M, int E>
+__global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWaves<M, E>))) void k_tab_eval(const float* __restrict__ XT, int R, int d,
                                                      const int4* __restrict__ chunk,
                                                      const int32_t* __restrict__ cfirst, int k, int q0, int q1,
                                                      const TabHead* __restrict__ head,
@@ -533,9 +551,14 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
     const int4 ck = chunk[q];
     const int m = ck.z;
     const size_t base = tab_base(chunk, q, q0) * (size_t)d;
+    bool refused = false;
     for (int c = 0; c < d; ++c) {
       const TabHead hd = head[(size_t)(q - q0) * d + c];
       const int K = hd.K;
+      if (K == 0) {  // block-uniform
+        refused = true;
+        continue;
+      }
       float x[E];
       const float* xc = XT + (size_t)c * R;
 #pragma unroll
@@ -544,7 +567,7 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
         x[e] = xc[i < R ? i : R - 1];
       }
       __syncthreads();
-      if (K > 0) {
+      {
         const size_t tb = base + (size_t)c * (size_t)(2 * m + kTabExtra);
         // (one more knot than the table's: Canberra's for the element's zeros)
         if (M == kCanb && threadIdx.x == 0) ly[K] = tabY[tb + K];
@@ -564,7 +587,7 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
         for (int e = 0; e < E; ++e) odd = odd || !(fabsf(x[e]) <= 0x1p62f);
         odd = __any(odd);
       }
-      if (K > 0 && !odd) {
+      if (!odd) {
         float z[E];
         bool far = false;
 #pragma unroll
@@ -643,7 +666,8 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
           }
         }
       } else {
-        // directly: 32 rows in float32, then float64
+        // Canberra, a wave with an element past the table's map: as above, from
+        // memory
         const float* yc = Y32 + (size_t)ck.y * DM + c;
         const float* wc = w + ck.y;
         for (int g0 = 0; g0 < m; g0 += 32) {
@@ -655,17 +679,80 @@ __global__ __launch_bounds__(kEvalT) void k_tab_eval(const float* __restrict__ X
             const float y = yc[(size_t)r * DM], wr = wc[r];
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-              if (M == kManh) {
-                s[e] = fmaf(wr, fabsf(x[e] - y), s[e]);
-              } else {
-                const float den = fmaxf(fabsf(x[e]) + fabsf(y), FLT_MIN);
-                s[e] = fmaf(wr, fabsf(x[e] - y) * __builtin_amdgcn_rcpf(den), s[e]);
-              }
+              const float den = fmaxf(fabsf(x[e]) + fabsf(y), FLT_MIN);
+              s[e] = fmaf(wr, fabsf(x[e] - y) * __builtin_amdgcn_rcpf(den), s[e]);
             }
           }
 #pragma unroll
           for (int e = 0; e < E; ++e) acc[e] += (double)s[e];
         }
+      }
+    }
+    if (!refused) continue;
+    for (int c = 0; c < d; ++c) {
+      const TabHead hd = head[(size_t)(q - q0) * d + c];
+      if (hd.K > 0) continue;
+      // the values and weights in pairs of rows
+      __syncthreads();
+      for (int i = threadIdx.x; i < ((m + 1) & ~1); i += kEvalT)
+        ((float2*)lds)[i] = i < m ? float2{Y32[(size_t)(ck.y + i) * DM + c], w[ck.y + i]} : float2{1.0f, 0.0f};
+      float x[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = e0 + e * kEvalT;
+        x[e] = XT[(size_t)c * R + (i < R ? i : R - 1)];
+      }
+      __syncthreads();
+      // directly, 32 rows in float32, then float64.  Canberra: two rows with
+      // one reciprocal, (w0 n0 d1 + w1 n1 d0) / (d0 d1), where the wave's
+      // elements and the values lie in what two factors allow (k_p2_valu pairs
+      // coordinates the same way).  n = 200,000, d = 32, k = 16, t = 256, every
+      // table refused: Canberra 8.95 -> 4.19 ms (pairs of coordinates by k_p2_valu 5.89)
+      bool pairs = M == kCanb && hd.wide == 0;
+      if (pairs) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) pairs = pairs && fabsf(x[e]) >= 0x1p-62f && fabsf(x[e]) <= kPairMax;
+        pairs = __all(pairs);
+      }
+      for (int g0 = 0; g0 < m; g0 += 32) {
+        const int g1 = g0 + 32 < m ? g0 + 32 : m;
+        float s[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) s[e] = 0.0f;
+        const float4* yw = (const float4*)lds + g0 / 2;
+        const int np = (g1 - g0 + 1) / 2;
+        if (M == kManh) {
+          for (int r = 0; r < np; ++r) {
+            const float4 v = yw[r];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              s[e] = fmaf(v.y, fabsf(x[e] - v.x), s[e]);
+              s[e] = v.w != 0.0f ? fmaf(v.w, fabsf(x[e] - v.z), s[e]) : s[e];
+            }
+          }
+        } else if (pairs) {
+#pragma unroll 1
+          for (int r = 0; r < np; ++r) {
+            const float4 v = yw[r];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const float d0 = fabsf(x[e]) + fabsf(v.x), d1 = fabsf(x[e]) + fabsf(v.z);
+              const float n0 = v.y * fabsf(x[e] - v.x), n1 = v.w * fabsf(x[e] - v.z);
+              s[e] = fmaf(fmaf(n0, d1, n1 * d0), __builtin_amdgcn_rcpf(d0 * d1), s[e]);
+            }
+          }
+        } else {
+          for (int r = g0; r < g1; ++r) {
+            const float2 v = ((const float2*)lds)[r];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const float den = fmaxf(fabsf(x[e]) + fabsf(v.x), FLT_MIN);
+              s[e] = fmaf(v.y, fabsf(x[e] - v.x) * __builtin_amdgcn_rcpf(den), s[e]);
+            }
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += (double)s[e];
       }
     }
   }
