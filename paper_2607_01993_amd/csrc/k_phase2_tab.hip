@@ -853,7 +853,7 @@ TabPlan tab_plan(int metric, int64_t n, int d, int k, int64_t S_pad, int64_t max
   p.rw = RW;
   // the longest table: LDS of the evaluation (Manhattan has no refinement)
   const int64_t mr = max_rows < kTabRows ? max_rows : kTabRows;
-  p.max_knots = (int)(metric == kManh ? mr + 2 : 2 * mr + kTabExtra);
+  p.max_knots = (int)(metric == kManh ? mr + 2 : 2 * mr + kTabExtra < kTabMost + 1 ? 2 * mr + kTabExtra : kTabMost + 1);
   p.max_knots = (p.max_knots + 3) & ~3;  // (the records after it are 16-byte aligned)
   return p;
 }
