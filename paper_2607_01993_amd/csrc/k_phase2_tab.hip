@@ -833,11 +833,14 @@ TabPlan tab_plan(int metric, int64_t n, int d, int k, int64_t S_pad, int64_t max
   const int RW = metric == kManh ? 4 : 6;  // floats per record: g, h (float64), Canberra c0, c1
   const size_t kb = (size_t)(1 + RW) * sizeof(float);
   p.chunks = ceil_div(S_pad, kTabRows) + k;
-  const size_t per = (size_t)kTabKnots * d * kb;  // one chunk's tables at most
+  const int64_t mr = max_rows < kTabRows ? max_rows : kTabRows;
+  // one chunk's tables at most (and a cluster's padding rows between chunks)
+  const size_t chunk_knots = (size_t)(2 * mr + kTabExtra + 2 * kSamplePad);
+  const size_t per = chunk_knots * d * kb;
   int64_t g = (int64_t)(kTabGroupBytes / per);
   g = g < 1 ? 1 : g;
   p.group = g < p.chunks ? g : p.chunks;
-  size_t knots = (size_t)p.group * (kTabKnots + 64);  // (a cluster's padding rows lie between chunks)
+  size_t knots = (size_t)p.group * chunk_knots;
   const size_t all = (size_t)(2 * S_pad + kTabExtra * p.chunks);
   knots = knots < all ? knots : all;
   p.knots = knots * (size_t)d;
@@ -852,7 +855,6 @@ TabPlan tab_plan(int metric, int64_t n, int d, int k, int64_t S_pad, int64_t max
   p.rows = R < n ? R : n;
   p.rw = RW;
   // the longest table: LDS of the evaluation (Manhattan has no refinement)
-  const int64_t mr = max_rows < kTabRows ? max_rows : kTabRows;
   p.max_knots = (int)(metric == kManh ? mr + 2 : 2 * mr + kTabExtra < kTabMost + 1 ? 2 * mr + kTabExtra : kTabMost + 1);
   p.max_knots = (p.max_knots + 3) & ~3;  // (the records after it are 16-byte aligned)
   return p;
