@@ -25,8 +25,10 @@
  * on the device joins the next launch and a small request does not wait for
  * a large one to end.  Each work item computes exactly what that block of
  * the request's own launch computes, so results equal a direct call's.
- * Requests with the row draws of Eq. 10, and vector-ALU shapes with d > 128,
- * run their own Phase-2 launch on their worker.
+ * Cosine requests, Manhattan and Canberra ones that tables serve, requests with
+ * the row draws of Eq. 10 and vector-ALU shapes with d > 128 run their own
+ * Phase 2 on their worker; the first two in launches of about a millisecond
+ * with a wait between them, so that others' short kernels get their turn.
  *
  * All calls are thread-safe.  Timestamps are nanoseconds of one steady clock
  * (silh_server_now_ns), so callers can schedule arrivals on the same clock.

@@ -413,10 +413,41 @@ static bool launch_cos_prec(hipStream_t st, int DM, const P2Args& A) {
 // a second); n = 1e6, d = 100, k = 48, S = 15,000, fp8 4.44 -> 0.80 ms.  The
 // collapsed sums win at every S above a few rows per cluster, so there is no
 // rule and no other path.
-bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A) {
+static bool launch_cos_rows(hipStream_t st, int prec, int DM, const P2Args& A) {
   if (prec == 1) return launch_cos_prec<1>(st, DM, A);
   if (prec == 2) return launch_cos_prec<2>(st, DM, A);
   return launch_cos_prec<0>(st, DM, A);
+}
+
+// pieces: as tab_plan's, about 1 ms of coordinate steps each (a block's rows
+// do not depend on the others': the same results)
+constexpr int64_t kPieceSteps = (int64_t)1 << 33;
+
+bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A, bool pieces) {
+  int64_t rows = A.n;
+  if (pieces) {
+    rows = kPieceSteps / ((int64_t)A.k * DM) / kCosRows * kCosRows;
+    rows = rows < kCosRows ? kCosRows : rows;
+  }
+  for (int64_t i0 = 0; i0 < A.n; i0 += rows) {
+    P2Args B = A;
+    B.n = (int)(A.n - i0 < rows ? A.n - i0 : rows);
+    B.X += i0 * A.d;
+    B.labels += i0;
+    B.rn += i0;
+    if (B.egid)
+      B.egid += i0;
+    else if (B.cself)
+      B.cself += i0;
+    if (B.a) B.a += i0;
+    if (B.b) B.b += i0;
+    if (B.s) B.s += i0;
+    if (B.What) B.What += i0 * A.k;
+    B.bpart += i0 / kCosRows;
+    if (!launch_cos_rows(st, prec, DM, B)) return false;
+    if (i0 + rows < A.n && hipStreamSynchronize(st) != hipSuccess) return true;  // (the next call reports it)
+  }
+  return true;
 }
 
 }  // namespace silh

@@ -1012,7 +1012,7 @@ silh_status want_tables(silh_ctx* c, const P2Args& A, std::vector<void*>& list, 
 
 bool launch_p2(silh_ctx* c, const P2Args& A, int pb, const TabPlan* plan = nullptr, const TabBufs* tab = nullptr) {
   if (plan) return launch_phase2_tab(c->st, c->prm.metric, c->DM, A, *plan, *tab);
-  if (c->cos) return launch_phase2_cos(c->st, c->mprec, c->DM, A);
+  if (c->cos) return launch_phase2_cos(c->st, c->mprec, c->DM, A, c->pieces);
   if (!c->mfma) return launch_phase2_valu(c->st, c->prm.metric, c->DM, A);
   return launch_phase2_mfma(c->st, c->mprec, c->DM, A, c->mu, c->Ym, pb);
 }

@@ -232,7 +232,9 @@ void launch_cos_stats(hipStream_t st, int prec, int DM, const float* Y32, const 
 // past `cap` of the packed sample are not read
 void launch_cos_self(hipStream_t st, int DM, const float* Y32, const float* w, const int32_t* gid_pk,
                      const int32_t* sp_off, int k, int cap, const unsigned char* stat, int n, float* self);
-bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A);
+// pieces: the elements in pieces of about a millisecond with a wait between them
+// (tab_plan)
+bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A, bool pieces = false);
 
 // Manhattan and Canberra by per-coordinate tables (k_phase2_tab.hip): whether
 // they pay for n elements against clusters of about min(t, n / k) sample rows
