@@ -1260,12 +1260,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
 //     LDS path only).
 // The arithmetic of every element, and the 128-element partials of the
 // mean, are the same in every shape.
-// Split blocks up to this many elements, past which unsplit ones fill the chip:
-// Phase 2 unsplit -> split, exact n = 40,000, d = 16, k = 9 float32 6.72 -> 4.83
-// ms, n = 150,001, d = 16, k = 100 bf16 476 -> 360 us, n = 2,000, d = 8, k = 4
-// float32 14.7 -> 8.7, n = 200,000, d = 32 float32 sums 798 -> 758, n = 101,000
-// rows, d = 32 37.5 -> 36.4; n = 1e6, d = 32, k = 16 195 -> 284.
-constexpr int64_t kSplitN = (int64_t)1 << 18;
+// Split blocks while unsplit ones would leave the chip idle.  With few clusters
+// the four waves' shares are uneven (5 clusters: two rounds for 1.25), so the
+// line falls with them; d = 17 to 32 (and float32 from d = 9) holds fewer waves
+// per SIMD and gains longer.
+// Requests unsplit -> split, us: k = 5 bf16 d = 8 n = 30,000 332 -> 254, 60,000 358
+// -> 334, 120,000 413 -> 464, 262,144 699 -> 888; k = 9 float32 d = 16 n = 60,000
+// 514 -> 455, 90,000 421 -> 492, 150,000 1,101 -> 1,006; k = 16 bf16 d = 8 n = 120,000
+// 353 -> 315, 150,000 347 -> 356, float32 d = 8 n = 150,000 757 -> 822; k = 100 bf16
+// d = 16 n = 150,000 520 -> 440, 262,144 688 -> 630, k = 40 float32 d = 8 n = 200,000
+// 514 -> 549.  d = 32: k = 6 bf16 n = 90,000 363 -> 328, 150,000 403 -> 371, 200,000
+// 422 -> 468; k = 40 bf16 n = 200,000 346 -> 328; k = 16 float32 n = 150,000 3,916 ->
+// 3,553, 262,144 6,827 -> 7,003.
+static int64_t split_limit(int prec, int DM, int k) {
+  if (DM == 32) return k >= 32 || (prec == 0 && k >= 16) ? (int64_t)1 << 18 : (int64_t)5 << 15;
+  if (k < 16) return prec == 0 && DM == 16 && k >= 8 ? (int64_t)6 << 15 : (int64_t)1 << 16;
+  return (int64_t)1 << (prec == 1 && k >= 32 ? 18 : 17);
+}
 // Where nothing is timed: float32, one block -> two blocks a wave, d = 32
 // n = 200,000 sums 529 -> 430 us, n = 1e6 scores 434 -> 398; d = 16 exact n = 40,000
 // 2.30 -> 3.51 ms, n = 1e6 sums 1.22-1.38 -> 1.35; d = 8 n = 1e6 sums 1.65 -> 1.75.
@@ -1374,6 +1385,8 @@ bool launch_phase2_mfma_jobs(hipStream_t st, int prec, int DM, int shape, const 
 }
 
 int phase2_mfma_rows(int, int) { return 128; }
-bool mfma_split(int prec, int DM, int64_t n, int k) { return !mfma_lds_path(prec, DM) && k >= 4 && n <= kSplitN; }
+bool mfma_split(int prec, int DM, int64_t n, int k) {
+  return !mfma_lds_path(prec, DM) && k >= 4 && n <= split_limit(prec, DM, k);
+}
 
 }  // namespace silh
