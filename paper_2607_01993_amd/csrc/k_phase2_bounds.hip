@@ -31,18 +31,15 @@
 // The groups of 32 elements that a Phase-2 wave holds share a mask, the union
 // over the group, so elements go in cluster order (the index's permutation):
 // a group then has one own cluster (mostly) and nearby ones.
-#include "device_common.hpp"
-#include "silh_internal.hpp"
+#include "bounds_block.hpp"
 
 namespace silh {
 
-namespace {
-constexpr int kHead = 8;  // floats: Wt/|C| (-1: empty cluster), V, slack, E of D, E const, padding
-}  // namespace
-
-// floats per cluster record: head, m_j [DM]
-size_t bound_rec_floats(int DM) { return (size_t)kHead + DM; }
-size_t bound_mask_words(int64_t n, int k) { return (size_t)ceil_div(n, 32) * (size_t)((k + 31) / 32); }
+// the clusters' records, then the probe's counts
+size_t bound_rec_floats(int DM, int k) { return (size_t)k * (kBoundRec + DM) + kBoundProbe; }
+size_t bound_mask_words(int64_t n, int k) {
+  return kBoundHead + (size_t)ceil_div(n, 32) * (size_t)((k + 31) / 32);
+}
 
 // The clusters' centres mu_j (the mean of the first kCenterRows sample rows;
 // any point of the cluster would do, the mean keeps the centred operands
@@ -135,13 +132,13 @@ __global__ __launch_bounds__(1024) void k_center(const float* __restrict__ Y32, 
       if (rec != nullptr) {
         const double sh = wa > 0.0 ? cw / wa : 0.0;
         const float mean = (float)(yc + sh);
-        rec[(size_t)j * (kHead + DM) + kHead + c] = mean;
+        rec[(size_t)j * (kBoundRec + DM) + kBoundRec + c] = mean;
         sh2 = sh * sh;
         n2 = (double)mean * (double)mean;
         g2 = ((double)mean - (double)mv) * ((double)mean - (double)mv);
       }
     } else if (c < DM && rec != nullptr) {
-      rec[(size_t)j * (kHead + DM) + kHead + c] = 0.0f;
+      rec[(size_t)j * (kBoundRec + DM) + kBoundRec + c] = 0.0f;
     }
     mu[(size_t)j * KP + c] = mv;
   }
@@ -164,7 +161,7 @@ __global__ __launch_bounds__(1024) void k_center(const float* __restrict__ Y32, 
     const double qm = wa > 0.0 ? q_all / wa : 0.0;
     double V = qm - sh2;
     V = (V > 0.0 ? V : 0.0) + 1e-12 * qm;  // (the difference's rounding)
-    float* out = rec + (size_t)j * (kHead + DM);
+    float* out = rec + (size_t)j * (kBoundRec + DM);
     out[0] = sz > 0 ? (float)(wa / (double)sz) : -1.0f;
     out[1] = (float)(V * (1.0 + 0x1p-14));
     out[2] = (float)(sqrt(n2) * 0x1p-22);
@@ -180,141 +177,36 @@ void launch_center(hipStream_t st, int prec, int DM, const float* Y32, const flo
                      prec == 1 ? 0x1p-8f : 0x1p-13f, mu, rec);
 }
 
-// A block takes 64 elements (two mask groups), their rows in LDS, one element
-// per lane of each wave; wave w takes cluster pairs as k_p2_cos does.  Up to
-// kBndKeep clusters the lower bounds wait in LDS for the smallest upper bound;
-// beyond, a first sweep finds that bound and a second one tests against it.
-// Waves and kept bounds per row width: the LDS of a block (rows of 64
-// elements, kept bounds) leaves at least 16 waves per CU at every width.
-// n = 1e6, d = 32, k = 16: 69 us with 4 waves, 77 with 8 and 128 kept; n =
-// 5e5, d = 256, k = 16: 512 us with 4 waves (one block per CU), 183 with 8;
-// n = 150,001, d = 16, k = 100: 42 us in two sweeps, 32 in one.
-template <int DM>
-constexpr int kBndWaves = DM == 32 ? 4 : 8;
-template <int DM>
-constexpr int kBndKeep = DM <= 16 ? 128 : DM == 256 ? 32 : 64;
-
+// The masks.  `counts` (null without a probe: scalar loads): the block returns
+// at once where the probe's counts exceed the limit; the first block says
+// which in head[kBoundFlag].
 template <int DM>
 __global__ __launch_bounds__((64 * kBndWaves<DM>)) void k_bounds(const float* __restrict__ X, int n, int d,
                                                            const int32_t* __restrict__ labels,
                                                            const int32_t* __restrict__ perm,
-                                                           const float* __restrict__ rec, int k,
-                                                           uint32_t* __restrict__ mask) {
-  constexpr int NW = kBndWaves<DM>, NT = 64 * NW, LD = DM + 4;
-  __shared__ __attribute__((aligned(16))) float xs[64 * LD];
-  __shared__ float low[kBndKeep<DM>][64];
-  __shared__ float um[NW][64];
-  __shared__ uint32_t bits[2][128];  // k <= 4096
-  __shared__ int rows[64];
-  const int row0 = blockIdx.x * 64;
-  const int kw = (k + 31) >> 5;
-  if (threadIdx.x < 64) {
-    const int i = row0 + (int)threadIdx.x < n ? row0 + (int)threadIdx.x : n - 1;
-    rows[threadIdx.x] = perm != nullptr ? perm[i] : i;
-  }
-  for (int q = threadIdx.x; q < 256; q += NT) bits[q >> 7][q & 127] = 0u;
-  __syncthreads();
-  const bool vec = (d & 3) == 0 && ((uintptr_t)X & 15) == 0;
-  if (vec) {
-    for (int q = threadIdx.x; q < 64 * (DM / 4); q += NT) {
-      const int r = q / (DM / 4), c = (q - r * (DM / 4)) * 4;
-      float4 v = float4{0.f, 0.f, 0.f, 0.f};
-      if (c < d) v = *(const float4*)(X + (size_t)rows[r] * d + c);
-      *(float4*)(xs + r * LD + c) = v;
-    }
-  } else {
-    for (int q = threadIdx.x; q < 64 * DM; q += NT) {
-      const int r = q / DM, c = q - r * DM;
-      xs[r * LD + c] = c < d ? X[(size_t)rows[r] * d + c] : 0.0f;
-    }
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  int own = labels[rows[lane]];
-  own = (unsigned)own < (unsigned)k ? own : 0;  // labels are checked before; stay in bounds
-  __syncthreads();
-  const float* xl = xs + lane * LD;
-  constexpr size_t RS = (size_t)kHead + DM;
-  // |x - m_j|^2 of two clusters
-  auto dist2 = [&](int j, int j2, float (&out)[2]) {
-    const float* m0 = rec + (size_t)j * RS + kHead;
-    const float* m1 = rec + (size_t)j2 * RS + kHead;
-    float a0 = 0.f, a1 = 0.f, b0 = 0.f, b1 = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < DM; c += 4) {
-      const float4 x = *(const float4*)(xl + c);
-      float t;
-      t = x.x - m0[c]; a0 = fmaf(t, t, a0);
-      t = x.y - m0[c + 1]; a1 = fmaf(t, t, a1);
-      t = x.z - m0[c + 2]; a0 = fmaf(t, t, a0);
-      t = x.w - m0[c + 3]; a1 = fmaf(t, t, a1);
-      t = x.x - m1[c]; b0 = fmaf(t, t, b0);
-      t = x.y - m1[c + 1]; b1 = fmaf(t, t, b1);
-      t = x.z - m1[c + 2]; b0 = fmaf(t, t, b0);
-      t = x.w - m1[c + 3]; b1 = fmaf(t, t, b1);
-    }
-    out[0] = a0 + a1;
-    out[1] = b0 + b1;
-  };
-  float umin = __builtin_inff();
-  // sweep 0: upper bounds (and lower bounds kept); sweep 1: the test
-  const bool kept = k <= kBndKeep<DM>;
-  auto sweep = [&](bool test) {
-    for (int j0 = 2 * wave; j0 < k; j0 += 2 * NW) {
-      float D2[2];
-      dist2(j0, j0 + 1 < k ? j0 + 1 : j0, D2);
+                                                           const float* __restrict__ rec, int k, int limit,
+                                                           const uint32_t* __restrict__ counts,
+                                                           uint32_t* __restrict__ head) {
+  bool skip = false;
+  if (counts != nullptr) {
+    int c = 0;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int j = j0 + u;
-        if (j >= k) break;
-        const float* h = rec + (size_t)j * RS;
-        const float f = h[0];
-        const float D = __builtin_amdgcn_sqrtf(D2[u]);
-        const float E = fmaf(h[3], D, h[4]);
-        float L = f * (fmaf(D, 1.0f - 0x1p-14f, -h[2]) - E);
-        if (f < 0.0f) L = __builtin_inff();  // an empty cluster is never evaluated
-        if (!test) {
-          const float Dp = D * (1.0f + 0x1p-14f) + h[2];
-          const float U = f * (__builtin_amdgcn_sqrtf(fmaf(Dp, Dp, h[1])) * (1.0f + 0x1p-14f) + E);
-          if (f >= 0.0f && j != own) umin = fminf(umin, U);
-          if (kept) low[j][lane] = L;
-        } else if (f >= 0.0f) {
-          const uint64_t b = __ballot(!(L > umin));
-          if (lane == 0 && (uint32_t)b) atomicOr(&bits[0][j >> 5], 1u << (j & 31));
-          if (lane == 32 && (uint32_t)(b >> 32)) atomicOr(&bits[1][j >> 5], 1u << (j & 31));
-        }
-      }
-    }
-  };
-  sweep(false);
-  um[wave][lane] = umin;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NW; ++i) umin = fminf(umin, um[i][lane]);
-  if (kept) {
-    for (int j = wave; j < k; j += NW) {
-      const float f = rec[(size_t)j * RS];
-      const uint64_t b = __ballot(f >= 0.0f && !(low[j][lane] > umin));
-      if (lane == 0 && (uint32_t)b) atomicOr(&bits[0][j >> 5], 1u << (j & 31));
-      if (lane == 32 && (uint32_t)(b >> 32)) atomicOr(&bits[1][j >> 5], 1u << (j & 31));
-    }
-  } else {
-    sweep(true);
+    for (int i = 0; i < kBoundProbe; ++i) c += (int)counts[i];
+    skip = c > limit;
   }
-  if (wave == 0) atomicOr(&bits[lane >> 5][own >> 5], 1u << (own & 31));
-  __syncthreads();
-  for (int q = threadIdx.x; q < 2 * kw; q += NT) {
-    const int g = q / kw, wd = q - g * kw;
-    if (row0 + 32 * g < n) mask[(size_t)(blockIdx.x * 2 + g) * kw + wd] = bits[g][wd];
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) head[kBoundFlag] = skip ? 1u : 0u;
+  if (skip) return;
+  bounds_block<DM, kBndWaves<DM>, false>(X, n, d, labels, perm, rec, k, (int)blockIdx.x * 64, head + kBoundHead);
 }
 
-void launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels, const int32_t* perm,
-                   const float* rec, int k, uint32_t* mask) {
-  if (n <= 0) return;
+const uint32_t* launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels,
+                              const int32_t* perm, const float* rec, int k, int limit, uint32_t* buf) {
+  if (n <= 0) return buf + kBoundHead;
   const dim3 grid((unsigned)ceil_div(n, 64));
-#define SILH_BND(D) \
-  hipLaunchKernelGGL(k_bounds<D>, grid, dim3(64 * kBndWaves<D>), 0, st, X, n, d, labels, perm, rec, k, mask)
+  const uint32_t* counts = limit >= 0 ? (const uint32_t*)(rec + (size_t)k * (kBoundRec + DM)) : nullptr;
+#define SILH_BND(D)                                                                                             \
+  hipLaunchKernelGGL(k_bounds<D>, grid, dim3(64 * kBndWaves<D>), 0, st, X, n, d, labels, perm, rec, k, limit, \
+                     counts, buf)
   switch (DM) {
     case 8: SILH_BND(8); break;
     case 16: SILH_BND(16); break;
@@ -324,6 +216,35 @@ void launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const i
     default: SILH_BND(256); break;
   }
 #undef SILH_BND
+  return buf + kBoundHead;
+}
+
+// What the bounds cost against what they can save, in microseconds at the rates
+// measured for both (bf16 and float32 requests of n = 20,000 to 400,000, k = 3
+// to 64, 32 to 512 sample rows a cluster, d = 16, 64, 256, clusters that touch
+// and labels that have nothing to do with the data).  A pair of Phase 2 takes p,
+// a cluster as much as 64 rows more; the bounds take an element's row again and
+// a share a cluster.  Two of k clusters are needed at least.  From 65,536
+// elements on (below, the chip is not full, and both sides take about as long
+// as there) the probe finds how many are, where its own chain (k / 8 cluster
+// pairs) is hidden by the packing or small next to the bounds; without it 0.6
+// of the most is expected.  Without -> with the bounds: n = 400,000, m = 128,
+// cells, d = 16 k = 5 232 -> 256 us, k = 64 803 -> 462; d = 256 k = 3 512 -> 678,
+// k = 64 3,558 -> 2,980; n = 20,000, m = 512, d = 256 k = 3 253 -> 270, k = 8 492 -> 453;
+// random labels d = 64 k = 16 436 -> 498.
+BoundPlan bound_plan(int prec, int DM, int64_t n, int k, int64_t S) {
+  BoundPlan b;
+  if (k <= 2 || n * S < ((int64_t)1 << 24)) return b;
+  const double nn = n < 65536 ? 65536.0 : (double)n;
+  const double p = prec == 1 ? 1.8e-7 + 2.2e-9 * DM : 3e-7 + 9e-9 * DM;
+  const double sums = nn * ((double)S + 64.0 * (double)k) * p;
+  const double cost = 1.1 * nn * (3e-5 + 1.1e-6 * DM + (double)k * (1e-6 + 4e-8 * DM));
+  const double chain = (double)k / 8.0 * (1.5 + 0.04 * DM);
+  const double most = 1.0 - 2.0 / (double)k;
+  const bool probe = n >= 65536 && (chain <= 8.0 || chain < 0.15 * cost);
+  b.use = (probe ? 1.0 : 0.6) * most * sums > 1.5 * cost + 20.0;
+  if (b.use && probe) b.limit = (int)((1.0 - cost / sums) * (double)k * 2.0 * kBoundProbe);
+  return b;
 }
 
 }  // namespace silh

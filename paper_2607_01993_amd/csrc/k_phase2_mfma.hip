@@ -31,6 +31,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "bounds_block.hpp"
 #include "device_common.hpp"
 #include "silh_internal.hpp"
 
@@ -160,8 +161,18 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
                                                    const int32_t* __restrict__ sp_off,
                                                    const int32_t* __restrict__ cnt, int k,
                                                    float* __restrict__ mu, int S_pad,
-                                                   void* __restrict__ Ym) {
+                                                   void* __restrict__ Ym, ProbeArgs A) {
   using C = MCfg<P, DM>;
+  // blocks past the sample: the bounds' probe (a launch of its own for it was 10
+  // to 25 us of a request)
+  const int nb = (S_pad + 255) >> 8;
+  if ((int)blockIdx.x >= nb) {
+    const int b = (int)blockIdx.x - nb;
+    bounds_block<DM, 4, true>(A.X, A.n, A.d, A.labels, A.perm, A.rec, k,
+                              (int)((int64_t)b * ((A.n + 63) / 64) / kBoundProbe) * 64,
+                              (uint32_t*)(A.rec + (size_t)k * (kBoundRec + DM)) + b);
+    return;
+  }
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   // sp_off[k]: packed rows in use (every lane stays to the end, for the
   // wave-wide radius below)
@@ -611,11 +622,12 @@ __device__ __forceinline__ void p2_mfma_block(
   // of the 32-element groups that share the sample tiles (the wave's PB
   // groups; on the LDS path the block's four waves).  next_cluster(j): the
   // first one from j on, k past the last.
+  const bool masked = mask != nullptr && mask[kBoundFlag - kBoundHead] == 0;  // (by k_bounds)
   const int kw = (k + 31) >> 5;
   const int grp0 = kLds ? blk * 4 * PB : P0 >> 5;
   constexpr int kGrp = kLds ? 4 * PB : PB;
   auto next_cluster = [&](int j) {
-    if (mask == nullptr) return j;
+    if (!masked) return j;
     for (int wd = j >> 5; wd < kw; ++wd) {
       uint32_t bits = 0;
 #pragma unroll
@@ -1274,7 +1286,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMinWaves<P
 // 3,553, 262,144 6,827 -> 7,003.
 static int64_t split_limit(int prec, int DM, int k) {
   if (DM == 32) return k >= 32 || (prec == 0 && k >= 16) ? (int64_t)1 << 18 : (int64_t)5 << 15;
-  if (k < 16) return prec == 0 && DM == 16 && k >= 8 ? (int64_t)6 << 15 : (int64_t)1 << 16;
+  if (k < 16) return prec == 0 && DM == 16 ? (int64_t)6 << 15 : (int64_t)1 << 16;
   return (int64_t)1 << (prec == 1 && k >= 32 ? 18 : 17);
 }
 // Where nothing is timed: float32, one block -> two blocks a wave, d = 32
@@ -1340,9 +1352,9 @@ static void launch_jobs_one(hipStream_t st, const P2Job* jobs, const int2* items
 
 template <int P, int DM>
 static void launch_pack_one(hipStream_t st, const float* Y32, const float* w, const int32_t* sp_off,
-                            const int32_t* cnt, int k, float* mu, int S_pad, void* Ym) {
-  hipLaunchKernelGGL((k_pack_mfma<P, DM>), dim3((int)ceil_div(S_pad, 256)), dim3(256), 0, st, Y32, w, sp_off, cnt, k,
-                     mu, S_pad, Ym);
+                            const int32_t* cnt, int k, float* mu, int S_pad, void* Ym, const ProbeArgs& A) {
+  const int blocks = (int)ceil_div(S_pad, 256) + (A.rec ? kBoundProbe : 0);
+  hipLaunchKernelGGL((k_pack_mfma<P, DM>), dim3(blocks), dim3(256), 0, st, Y32, w, sp_off, cnt, k, mu, S_pad, Ym, A);
 }
 
 #define SILH_MFMA_DISPATCH(FN, ...)                 \
@@ -1369,8 +1381,8 @@ static void launch_pack_one(hipStream_t st, const float* Y32, const float* w, co
   } while (0)
 
 bool launch_pack_mfma(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
-                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym) {
-  SILH_MFMA_DISPATCH(launch_pack_one, st, Y32, w, sp_off, cnt, k, mu, S_pad, Ym);
+                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym, const ProbeArgs& A) {
+  SILH_MFMA_DISPATCH(launch_pack_one, st, Y32, w, sp_off, cnt, k, mu, S_pad, Ym, A);
 }
 
 bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const float* mu, const void* Ym,

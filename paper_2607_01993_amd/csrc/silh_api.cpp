@@ -523,6 +523,13 @@ silh_status check_params(const silh_params* prm, const float* X, const int32_t* 
   return SILH_OK;
 }
 
+// the bounds' plan for n of the context's elements
+BoundPlan bounds_of(const silh_ctx* c, int64_t n) {
+  if (!c->mfma) return {};
+  const double kt = (double)c->k * (double)c->t_rows;
+  return bound_plan(c->mprec, c->DM, n, c->k, kt < (double)c->n ? (int64_t)kt : (int64_t)c->n);
+}
+
 void set_path(silh_ctx* c, int path) {
   c->mfma = path == kPathMfma;
   c->cos = path == kPathCos;
@@ -659,7 +666,7 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
   const int prec = c->mprec;
   bool mfma_pack = c->mfma && c->S_pad > 0;
   const bool pieces = mfma_pack && mfma_three_pieces(prec, c->DM);
-  const bool bounds = mfma_pack && bounds_pay(n, k, c->S_pad);
+  const bool bounds = mfma_pack && bounds_of(c, n).use;
   {
     unsigned char* ym = nullptr;
     Carve cv, op, bnd;  // what the sample needs; rows of three pieces; the bounds
@@ -671,7 +678,7 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
       (pieces ? op : cv)
           .add(&c->mu, mfma_mu_floats(c->mprec, c->DM, k))
           .add(&ym, (size_t)c->S_pad * mfma_row_bytes(prec, c->DM));
-    if (bounds) bnd.add(&c->brec, (size_t)k * bound_rec_floats(c->DM)).add(&c->bmask, bound_mask_words(n, k));
+    if (bounds) bnd.add(&c->brec, bound_rec_floats(c->DM, k)).add(&c->bmask, bound_mask_words(n, k));
     // all in one allocation where the bounds are small (an allocator call
     // through PyTorch is 7 us); what saves work only is left out where it
     // cannot be had: rows of three pieces are larger than float32 rows (1.3 to
@@ -718,7 +725,9 @@ silh_status compact_and_pack(silh_ctx* c, bool* overflow) {
     }
     {
       Launch L(c, K_PACK_MFMA);
-      if (!launch_pack_mfma(c->st, prec, c->DM, c->Y32, c->w32, c->sp_off, c->cnt, k, c->mu, (int)c->S_pad, c->Ym))
+      ProbeArgs P;
+      if (c->brec && bounds_of(c, n).limit >= 0) P = {c->X, c->labels, c->perm, c->brec, n, c->d};
+      if (!launch_pack_mfma(c->st, prec, c->DM, c->Y32, c->w32, c->sp_off, c->cnt, k, c->mu, (int)c->S_pad, c->Ym, P))
         return fail(SILH_E_UNSUPPORTED, "no MFMA packing for metric %d, d=%d", c->prm.metric, c->d);
       CHK(L.done());
     }
@@ -921,8 +930,8 @@ bool masks(const silh_ctx* c, const P2Args& A, const uint32_t* mask) {
 }
 void mask_clusters(silh_ctx* c, P2Args& A, uint32_t* mask) {
   if (!masks(c, A, mask)) return;
-  launch_bounds(c->st, c->DM, A.X, A.n, A.d, A.labels, A.perm, c->brec, A.k, mask);
-  A.mask = mask;
+  const BoundPlan b = bounds_of(c, A.n);
+  A.mask = launch_bounds(c->st, c->DM, A.X, A.n, A.d, A.labels, A.perm, c->brec, A.k, b.limit, mask);
 }
 
 // cosine has one shape: it is recorded under the same key, nothing is timed
@@ -1152,7 +1161,7 @@ silh_status rows_phase2(silh_ctx* c, const int32_t* rows, int64_t m, float* a, f
     CHK(cv.commit(c, c->alloc_rows));
   }
   {
-    if (!bounds_pay(mu, c->k, c->S_pad)) mask = nullptr;
+    if (!bounds_of(c, mu).use) mask = nullptr;
     const int pb = pick_pb(c, A, mask);  // (tuning runs stay outside the timed launch)
     Launch L(c, K_PHASE2);
     mask_clusters(c, A, mask);
@@ -1239,8 +1248,8 @@ bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   J.perm = c->perm;
   J.mask = nullptr;
   if (c->brec) {  // on the context's stream, which the caller synchronises
-    launch_bounds(c->st, c->DM, c->X, c->n, c->d, c->labels, c->perm, c->brec, c->k, c->bmask);
-    J.mask = c->bmask;
+    const BoundPlan b = bounds_of(c, c->n);
+    J.mask = launch_bounds(c->st, c->DM, c->X, c->n, c->d, c->labels, c->perm, c->brec, c->k, b.limit, c->bmask);
   }
   J.n = c->n;
   J.d = c->d;

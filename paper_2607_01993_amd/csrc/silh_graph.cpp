@@ -215,10 +215,11 @@ bool alloc_needed(silh_graph* g) {
   return ok;
 }
 
-// whether clustering i's scores go through the bounds
-bool wants_bounds(const silh_graph* g, size_t i) {
-  return g->mfma &&
-         bounds_pay(g->n, g->ks[i], (int64_t)std::min((double)g->n, (double)g->ks[i] * (double)g->ts[i]));
+// how clustering i's scores go through the bounds
+BoundPlan bounds_of(const silh_graph* g, size_t i) {
+  if (!g->mfma) return {};
+  return bound_plan(g->mprec, g->DM, g->n, g->ks[i],
+                    (int64_t)std::min((double)g->n, (double)g->ks[i] * (double)g->ts[i]));
 }
 
 // the bounds' buffers, for the largest clustering that wants them, once every
@@ -226,9 +227,9 @@ bool wants_bounds(const silh_graph* g, size_t i) {
 void alloc_bounds(silh_graph* g, Branch& b) {
   int kb = 0;
   for (size_t i = 0; i < g->ks.size(); ++i)
-    if (wants_bounds(g, i)) kb = std::max(kb, (int)g->ks[i]);
+    if (bounds_of(g, i).use) kb = std::max(kb, (int)g->ks[i]);
   if (kb == 0) return;
-  if (!take(g, b.brec, kb * (int64_t)bound_rec_floats(g->DM)) || !take(g, b.bmask, (int64_t)bound_mask_words(g->n, kb)))
+  if (!take(g, b.brec, (int64_t)bound_rec_floats(g->DM, kb)) || !take(g, b.bmask, (int64_t)bound_mask_words(g->n, kb)))
     b.brec = nullptr;
 }
 
@@ -315,14 +316,16 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     if (b.cself) launch_cos_self(st, DM, b.Y32, b.w32, b.gid_pk, b.sp_off, k, (int)g->S_cap, b.cstat, n, b.cself);
     if (!launch_phase2_cos(st, g->mprec, DM, A)) return false;
   } else if (g->mfma) {
-    const bool bounds = b.brec != nullptr && wants_bounds(g, (size_t)i);
+    const BoundPlan plan = bounds_of(g, (size_t)i);
+    const bool bounds = b.brec != nullptr && plan.use;
     launch_center(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, b.csize, k, b.mu, bounds ? b.brec : nullptr);
-    if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym)) return false;
+    ProbeArgs P;
+    if (bounds && plan.limit >= 0) P = {g->X, lab, b.perm, b.brec, n, d};
+    if (!launch_pack_mfma(st, g->mprec, DM, b.Y32, b.w32, b.sp_off, b.cnt, k, b.mu, (int)g->S_cap, b.Ym, P)) return false;
     A.perm = b.perm;
     A.split = mfma_split(g->mprec, DM, n, k);
     if (bounds) {
-      launch_bounds(st, DM, A.X, n, d, lab, b.perm, b.brec, k, b.bmask);
-      A.mask = b.bmask;
+      A.mask = launch_bounds(st, DM, A.X, n, d, lab, b.perm, b.brec, k, plan.limit, b.bmask);
     }
     if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
   } else if (tables) {
@@ -443,7 +446,7 @@ silh_status silh_graph_create(const silh_params* base, const float* X, const int
     for (int32_t i = 0; i < K; ++i) {
       const double kt = (double)ks[i] * (double)ts[(size_t)i];
       const int form = (g->mfma && mfma_split(g->mprec, g->DM, g->n, ks[i]) ? 1 : 0) +
-                       (wants_bounds(g, (size_t)i) ? 2 : 0);
+                       (bounds_of(g, (size_t)i).use ? 2 : 0);
       const auto gk = std::make_pair((int)std::floor(std::log2(kt > 1.0 ? kt : 1.0)), form);
       auto it = group.find(gk);
       if (it == group.end()) {

@@ -188,8 +188,15 @@ void launch_center(hipStream_t st, int prec, int DM, const float* Y32, const flo
                    const int32_t* cnt, const int32_t* csize, int k, float* mu, float* rec);
 // packs rows [0, min(S_pad, sp_off[k])) (w: weights of the packed rows,
 // copied into the rows' tails on the LDS path)
+// With A: also the bounds' probe over A's elements and records.
+struct ProbeArgs {
+  const float* X = nullptr;
+  const int32_t *labels = nullptr, *perm = nullptr;
+  float* rec = nullptr;  // null: no probe
+  int n = 0, d = 0;
+};
 bool launch_pack_mfma(hipStream_t st, int prec, int DM, const float* Y32, const float* w, const int32_t* sp_off,
-                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym);
+                      const int32_t* cnt, int k, float* mu, int S_pad, void* Ym, const ProbeArgs& A = {});
 // elements per float64 partial of the sum of s_hat written by the MFMA
 // Phase-2 kernel (independent of its block shape)
 int phase2_mfma_rows(int prec, int DM);
@@ -209,17 +216,28 @@ bool launch_phase2_mfma(hipStream_t st, int prec, int DM, const P2Args& A, const
                         int shape);
 
 // Bounds on the Euclidean sums (k_phase2_bounds.hip): a record per cluster
-// (bound_rec_floats floats each, by launch_center), then for every
+// (bound_rec_floats floats in all, by launch_center), then for every
 // group of 32 elements (in perm order, null: as they lie) a mask of the
 // clusters its scores need, bit j of word [group][j / 32]
-size_t bound_rec_floats(int DM);
+// the probe (kBoundProbe blocks of 64 elements, by launch_pack_mfma) leaves the
+// number of clusters that each of its blocks needs behind the records
+constexpr int kBoundProbe = 32;
+size_t bound_rec_floats(int DM, int k);
+// (a head of kBoundHead words before them: head[kBoundFlag] = 1 if the masks are
+// not to be used)
+constexpr int kBoundHead = 64, kBoundFlag = 0;
 size_t bound_mask_words(int64_t n, int k);
-void launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels, const int32_t* perm,
-                   const float* rec, int k, uint32_t* mask);
-// whether scores of n elements against a sample of S rows (or so) go through
-// the bounds: two clusters are both needed, and below 2^24 pairs the two
-// launches cost more than they save
-inline bool bounds_pay(int64_t n, int k, int64_t S) { return k > 2 && n * S >= ((int64_t)1 << 24); }
+// buf: bound_mask_words words.  Returns the masks in it.
+const uint32_t* launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels,
+                              const int32_t* perm, const float* rec, int k, int limit, uint32_t* buf);
+// How scores of n elements against a sample of about S = min(n, k t) rows go
+// through the bounds: not at all, or with a probe first: whether the clusters it finds
+// needed, of every 128 groups' (limit), leave the rest worth the bounds' cost
+struct BoundPlan {
+  bool use = false;
+  int limit = -1;  // -1: no probe
+};
+BoundPlan bound_plan(int prec, int DM, int64_t n, int k, int64_t S);
 
 // Cosine (every operand type; prec as above, float32 arithmetic for the
 // vector-ALU precision too): the clusters' samples collapsed into one record

@@ -128,7 +128,7 @@ void layout(const Shape& s, Slices& sl, Bufs& b) {
       sl.add(&b.mu, mfma_mu_floats(s.mprec, s.DM, k)).add(&b.Ym, s.S_cap * (size_t)mfma_row_bytes(s.mprec, s.DM));
   }
   if (s.split) sl.add(&b.Wpart, n * k);
-  if (s.bounds) sl.add(&b.brec, k * (int64_t)bound_rec_floats(s.DM)).add(&b.bmask, (int64_t)bound_mask_words(n, s.k));
+  if (s.bounds) sl.add(&b.brec, (int64_t)bound_rec_floats(s.DM, s.k)).add(&b.bmask, (int64_t)bound_mask_words(n, s.k));
   if (s.cos) sl.add(&b.rn, n);
 }
 
@@ -158,7 +158,8 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
   sh.S_cap = (int64_t)sh.n + (int64_t)kSamplePad * sh.k;  // every element, each cluster padded
   sh.split32 = sh.mfma && mfma_split(sh.mprec, sh.DM, sh.n, sh.k);
   // the bounds (the same results) where their buffers fit too
-  sh.bounds = sh.mfma && bounds_pay(sh.n, sh.k, sh.n);
+  const BoundPlan plan = sh.mfma ? bound_plan(sh.mprec, sh.DM, sh.n, sh.k, sh.n) : BoundPlan{};
+  sh.bounds = plan.use;
   if (sh.bounds) {
     Slices count;
     Bufs dummy;
@@ -249,10 +250,11 @@ extern "C" silh_status silh_exact_noalloc(const silh_params* prm, const float* X
     launch_center(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, B.csize, k, B.mu, sh.bounds ? B.brec : nullptr);
     A.perm = B.perm;
     A.split = sh.split32;
-    ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym);
+    ProbeArgs P;
+    if (sh.bounds && plan.limit >= 0) P = {X, labels, B.perm, B.brec, n, d};
+    ok = launch_pack_mfma(st, sh.mprec, DM, B.Y32, B.w32, B.sp_off, B.cnt, k, B.mu, (int)sh.S_cap, B.Ym, P);
     if (ok && sh.bounds) {
-      launch_bounds(st, DM, X, n, d, labels, B.perm, B.brec, k, B.bmask);
-      A.mask = B.bmask;
+      A.mask = launch_bounds(st, DM, X, n, d, labels, B.perm, B.brec, k, plan.limit, B.bmask);
     }
     ok = ok && launch_phase2_mfma(st, sh.mprec, DM, A, B.mu, B.Ym, mfma_pb_default(sh.mprec, DM));
   } else {

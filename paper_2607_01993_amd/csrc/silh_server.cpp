@@ -252,7 +252,7 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool lean) {
   const uint64_t rn = r.metric == SILH_COS ? 4 * n + (lean ? 0 : (uint64_t)r.k * silh::cos_stat_bytes(DM)) : 0;
   // Euclidean bounds: a mask per 32 elements, a record per cluster
   const uint64_t bnd = mfma && !lean ? 4 * (uint64_t)silh::bound_mask_words((int64_t)n, r.k) +
-                                  4 * (uint64_t)r.k * silh::bound_rec_floats(DM)
+                                  4 * (uint64_t)silh::bound_rec_floats(DM, r.k)
                             : 0;
   return bnd + 24 * n + S * row + m * ((uint64_t)ds.d * 4 + 32) + split + kept + rn + ((uint64_t)1 << 20);
 }
