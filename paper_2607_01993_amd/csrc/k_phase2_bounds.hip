@@ -241,7 +241,7 @@ BoundPlan bound_plan(int prec, int DM, int64_t n, int k, int64_t S) {
   const double cost = 1.1 * nn * (3e-5 + 1.1e-6 * DM + (double)k * (1e-6 + 4e-8 * DM));
   const double chain = (double)k / 8.0 * (1.5 + 0.04 * DM);
   const double most = 1.0 - 2.0 / (double)k;
-  const bool probe = n >= 65536 && (chain <= 8.0 || chain < 0.15 * cost);
+  const bool probe = n >= 65536 && (chain <= 8.0 || chain < 0.3 * cost);
   b.use = (probe ? 1.0 : 0.6) * most * sums > 1.5 * cost + 20.0;
   if (b.use && probe) b.limit = (int)((1.0 - cost / sums) * (double)k * 2.0 * kBoundProbe);
   return b;
