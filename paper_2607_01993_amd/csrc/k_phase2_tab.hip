@@ -453,7 +453,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       // f jumps at 0 where the sample has zeros: f(0) is the sum of the other
       // weights.  An element's 0 takes the record past the last interval,
       // E (f(0) / E), E a power of two above every z (the search stops there).
-      const float E = ldexpf(1.0f, ilogbf((float)(4.0 * Yp)) + 1);
+      const float E = __uint_as_float((__float_as_uint((float)(4.0 * Yp)) & 0x7f800000u) + 0x00800000u);
       oy[K] = E;
       og[K - 1] = double2{wother / (double)E, 0.0};
       tabC[base + K - 1] = float2{0.0f, 0.0f};
@@ -507,8 +507,10 @@ __global__ __launch_bounds__(256) void k_tab_transpose(const float* __restrict__
 // the tile's elements through it.  Wd [k][R]: assigned by the cluster's first
 // chunk (or where it has none), added to by the others.
 // ----------------------------------------------------------------------------
-// Canberra's eight elements a thread hold 96 registers, five waves per SIMD
-// (the direct sums below would take 99: four waves, 3.92 -> 4.29 ms).
+// Canberra's eight elements a thread hold 96 registers, five waves per SIMD (the
+// direct sums below would take 99: four waves, 3.92 -> 4.29 ms).  Two elements:
+// seven waves (n = 68,362, d = 135, k = 17, t = 61 414 us; held at eight, the scalar
+// registers spill, 525).
 template <int M, int E>
 constexpr int kEvalWaves = M == kCanb && E == 8 ? 5 : 1;
 
