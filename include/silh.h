@@ -46,14 +46,22 @@ typedef enum {
 
 /* The four distances of the paper's experiments (Section 5.1.2).
  * SILH_COS reads the garbled printed formula as 1 - x.y/(|x||y|) (0 similarity
- * for a zero vector), clamped to [0, 2]; SILH_CANB takes a 0/0 coordinate as 0. */
+ * for a zero vector).  Phase 1 clamps each such distance to [0, 2]; Phase 2 adds
+ * a cluster's up as one sum, which is never below 0, without a clamp per pair: a
+ * pair keeps its operands' rounding either way (SILH_FP8: an element's own pair
+ * is never below 0).  A row that is not finite counts 0 there.
+ * SILH_CANB takes a 0/0 coordinate as 0.  Where the tables that Manhattan and
+ * Canberra use cannot be allocated, the direct sums serve the request; the two
+ * agree to float32 rounding. */
 typedef enum { SILH_EUCL = 0, SILH_COS = 1, SILH_MANH = 2, SILH_CANB = 3 } silh_metric;
 
 /* Arithmetic of the Phase-2 distances.  Accumulation is float32 inside
  * a tile and float64 across tiles; Phase 1 always runs in float64.
- *  SILH_FP32       float32.  Euclidean runs on the matrix cores
- *                  (v_mfma_f32_32x32x2_f32, d <= 128), Manhattan and Canberra on
- *                  the vector ALUs; cosine sums in float64.
+ *  SILH_FP32       float32.  Euclidean runs on the matrix cores up to d = 128
+ *                  (v_mfma_f32_32x32x2_f32; d = 9 to 64 three bf16 pieces of each
+ *                  operand, v_mfma_f32_32x32x16_bf16, at the same error), Manhattan
+ *                  and Canberra on the vector ALUs (tables summed in float64);
+ *                  cosine sums in float64.
  *  SILH_BF16       bf16 operands, float32 accumulation (Euclidean:
  *                  v_mfma_f32_32x32x16_bf16); Euclidean and cosine only.
  *  SILH_FP8        OCP e4m3 operands, float32 accumulation; cosine with
@@ -271,8 +279,8 @@ silh_status silh_coh_sep(silh_ctx* ctx, const float* W_hat, double* coh_host, do
  * 3 one block per wave with the other number of tiles per stage
  * (one or two 32-row sample tiles between block barriers) on the shapes that
  * stage sample tiles in LDS (d >= 64).
- *  mode 0  the built-in choice (two blocks for float32 operands with
- *          d <= 32, else one);
+ *  mode 0  the built-in choice (two blocks for float32 operands with d = 17
+ *          to 32, else one);
  *  mode 1  (default) on the first launch for a key (metric, operand type, d
  *          rounded up as in the kernels, floor(log2) of the padded sample
  *          size, and the launch's form: split blocks for few elements, the
