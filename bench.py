@@ -11,13 +11,14 @@ samples per cluster, Euclidean distance.  The timed precision is bf16 MFMA
 
 Prints one JSON line.  `value` is weighted distance evaluations per second of
 the whole step: (n*S + sum_j |C_j| |F0_j|) / step time, with the inputs
-resident in HBM before the timed region.
+resident in HBM before the timed region.  All n*S pairs count as answered;
+Phase 2 does not evaluate each one (the Euclidean bounds rule clusters out,
+cosine takes one record per cluster, Manhattan and Canberra tables).
 """
 from __future__ import annotations
 
 import argparse
 import json
-import math
 import os
 import sys
 import time
@@ -26,74 +27,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# MI355X figures: published peaks, and unit-count derivations from them
-# (256 CUs at 2.4 GHz).  157.3 TFLOP/s fp32 vector = 128 fp32 lanes / clk / CU
-# doing packed FMAs (64 without packing); transcendental instructions
-# (v_sqrt_f32) run at 32 lanes / clk / CU.
-CU, CLK = 256, 2.4e9
-PEAK = {
-    "hbm_gbs": 8000.0,
-    "fp32_vec_tflops": 157.3,
-    "bf16_mfma_tflops": 2500.0,
-    "fp8_mfma_tflops": 5000.0,
-    "fp32_mfma_tflops": 157.3,
-    "sqrt_tops": CU * 32 * CLK / 1e12,   # 19.66 T square roots / s
-}
 WORKLOAD = dict(n=1_000_000, d=32, k=16, t=256, seed=1)
-
-# HBM bytes per Phase-2 launch on this workload from the two rocprofv3 PMC
-# runs (FETCH_SIZE, WRITE_SIZE; scaled by a 256 MiB copy), valid only for the
-# kernel source they were taken with (sha256 prefix of the source file).
-TRAFFIC = {
-    ("eucl", "bf16"): {"src": "paper_2607_01993_amd/csrc/k_phase2_mfma.hip", "sha256": "9991418b0ee7ddce",
-                       "bytes": (136.7 + 12.3) * 1e6,
-                       "profile": "profiles/hbm_traffic_zipf_n1e6_d32_k16_t256.md"},
-}
-
-
-def traffic_for(metric, prec):
-    import hashlib
-    rec = TRAFFIC.get((metric, prec))
-    if rec is None:
-        return None
-    with open(os.path.join(ROOT, rec["src"]), "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()[:16]
-    return rec["bytes"] if sha == rec["sha256"] else None
-
-
-def phase2_roofline(metric, prec, d, n, S, kern_s):
-    """Roofline of the Phase-2 launch: algorithmic work per launch (n*S pairs
-    times the per-pair figure) over the average launch duration.  All n*S
-    pairs count, also those that the Euclidean bounds, the cosine records or
-    the tables save the kernel, so a fraction can exceed 1."""
-    pairs = float(n) * S
-    if metric == "eucl" and prec == "bf16":
-        # two ceilings: the square root per pair (transcendental rate) and
-        # the MFMA contraction (2d flops per pair); the nearer one governs
-        # (the square root at d = 32, the matrix cores at d = 256), the
-        # other is reported beside it
-        sq = pairs / kern_s / 1e12
-        mf = 2 * d * pairs / kern_s / 1e12
-        sqrt_roof = {"bound": "alu", "achieved": sq, "peak": PEAK["sqrt_tops"], "unit": "TFLOP/s",
-                     "frac": sq / PEAK["sqrt_tops"], "work": "1 square root per pair (counted as 1 flop)"}
-        mfma_roof = {"bound": "mfma", "achieved": mf, "peak": PEAK["bf16_mfma_tflops"], "unit": "TFLOP/s",
-                     "frac": mf / PEAK["bf16_mfma_tflops"], "work": f"2d = {2 * d} MFMA flops per pair"}
-        if sqrt_roof["frac"] >= mfma_roof["frac"]:
-            sqrt_roof["mfma"] = {x: mfma_roof[x] for x in ("achieved", "peak", "unit", "frac")}
-            return sqrt_roof
-        mfma_roof["sqrt"] = {x: sqrt_roof[x] for x in ("achieved", "peak", "unit", "frac")}
-        return mfma_roof
-    if metric in ("eucl", "cos") and prec in ("fp32", "bf16", "fp8"):
-        pk = {"fp32": PEAK["fp32_mfma_tflops"], "bf16": PEAK["bf16_mfma_tflops"], "fp8": PEAK["fp8_mfma_tflops"]}[prec]
-        ach = 2 * d * pairs / kern_s / 1e12
-        return {"bound": "mfma", "achieved": ach, "peak": pk, "unit": "TFLOP/s", "frac": ach / pk,
-                "work": f"2d = {2 * d} MFMA flops per pair"}
-    # vector-ALU metrics: per pair and coordinate sub + add (Manhattan) or
-    # sub, add, max, reciprocal, fma (Canberra); plus the weight fma
-    per = {"manh": 2 * d + 2, "canb": 6 * d + 2, "eucl": 3 * d + 3, "cos": 3 * d + 4}[metric]
-    ach = per * pairs / kern_s / 1e12
-    return {"bound": "alu", "achieved": ach, "peak": PEAK["fp32_vec_tflops"], "unit": "TFLOP/s",
-            "frac": ach / PEAK["fp32_vec_tflops"], "work": f"{per} flops per pair"}
 
 
 def _oracle_rows(args):
@@ -202,7 +136,7 @@ def run_steps(native, Xd, Ld, k, metric, prec, t, seed, steps, warmup, out_a, ou
     t_all0 = time.perf_counter()
     for i in range(steps):
         ts = time.perf_counter()
-        S, mean = step(2)   # timed: events around the Phase-2 launch only
+        S, mean = step(2)   # timed: events around Phase 2 only
         times.append(time.perf_counter() - ts)
         print(f"# {metric}/{prec} step {i}: {times[-1] * 1e3:.3f} ms S={S} mean={mean:.7f}",
               file=sys.stderr, flush=True)
@@ -259,8 +193,10 @@ def run_graph(native, Xd, Ld, k, metric, prec, t, seed, steps, warmup, work, eag
 
 def run_leg(native, Xd, Ld, k, metric, prec, t, seed, steps, a, b, s, work_fn=None, gold=None):
     """A request workload other than the headline: steps requests (one
-    warm-up), step time, Phase-2 launch time, its roofline, |mean - oracle|."""
+    warm-up), step time, Phase-2 time, its least traffic, |mean - oracle|."""
     import numpy as np
+
+    from paper_2607_01993_amd.configs import phase2_floor
     r = run_steps(native, Xd, Ld, k, metric, prec, t, seed, steps, 1, a, b, s)
     c2, m2 = r["stats"].get("phase2", (0, 0.0))
     n, d = Xd.shape
@@ -269,7 +205,7 @@ def run_leg(native, Xd, Ld, k, metric, prec, t, seed, steps, a, b, s, work_fn=No
     work = n * r["S"] + p1
     out = {"value": work / (r["t_all"] / steps), "ms_per_step": r["t_all"] / steps * 1e3,
            "phase2_ms": m2 / max(c2, 1), "S": r["S"], "s_mean": r["mean"],
-           "phase2_roofline": phase2_roofline(metric, prec, d, n, r["S"], m2 / max(c2, 1) / 1e3)}
+           "phase2_roofline": phase2_floor(metric, prec, n, d, 3, m2 / max(c2, 1))}
     if gold is not None:
         out["oracle_mean"] = gold
         out["abs_delta_vs_oracle"] = abs(r["mean"] - gold)
@@ -331,6 +267,7 @@ def main():
     import torch
 
     from paper_2607_01993_amd import native, synth
+    from paper_2607_01993_amd.configs import phase2_floor
 
     n, d, k, t, seed = (WORKLOAD[x] for x in ("n", "d", "k", "t", "seed"))
     X, L = synth.config_zipf_gauss(n=n, d=d, k=k, seed=seed)
@@ -366,9 +303,7 @@ def main():
     stats = main_run["stats"]
     p2_cnt, p2_ms = stats.get("phase2", (0, 0.0))
     p2_s = p2_ms / max(p2_cnt, 1) / 1e3
-    roof = phase2_roofline(args.metric, args.prec, d, n, S, p2_s)
-    roof.update({"traffic": traffic_for(args.metric, args.prec), "kernel": "k_p2_mfma" if args.prec in ("bf16", "fp32") and
-                 args.metric in ("eucl", "cos") else "k_p2_valu", "kernel_ms": p2_s * 1e3})
+    roof = phase2_floor(args.metric, args.prec, n, d, 3, p2_s * 1e3)
 
     compare = {}
     if args.compare_steps > 0 and args.metric == "eucl":
@@ -387,7 +322,7 @@ def main():
         compare["manh_fp32"] = {
             "value": w2 / (r["t_all"] / args.compare_steps), "ms_per_step": r["t_all"] / args.compare_steps * 1e3,
             "phase2_ms": m2 / max(c2, 1),
-            "phase2_roofline": phase2_roofline("manh", "fp32", d, n, r["S"], m2 / max(c2, 1) / 1e3)}
+            "phase2_roofline": phase2_floor("manh", "fp32", n, d, 3, m2 / max(c2, 1))}
 
     if args.compare_steps > 0 and not args.no_large:
         # the directional workload: n = 4e6, d = 128, k = 64 vMF blobs, t = 512, cosine
@@ -443,10 +378,11 @@ def main():
                                "p99": float(np.percentile(times_ms, 99)),
                                "note": "one request = one whole step, issued back to back"},
         "phase2_pairs_per_s": n * S / p2_s,
+        "pairs_note": "n * S pairs answered; not every one is evaluated",
         "kernel_avg_ms": {name: round(ms / max(cnt, 1), 4) for name, (cnt, ms) in sorted(main_run["kstats"].items())
                           if cnt},
-        "kernel_avg_ms_note": "from untimed steps with events around every kernel; phase2 in the roofline is "
-                              "from the timed steps",
+        "kernel_avg_ms_note": "from untimed steps with events around every kernel; kernel_ms in the roofline "
+                              "is from the timed steps",
         "roofline": roof,
         "s_mean": main_run["mean"],
         "oracle_mean": gold,
