@@ -76,15 +76,13 @@ constexpr int64_t kTabWork = (int64_t)1 << 26;        // float64 sums held at on
 
 // one (chunk, coordinate) table's head
 struct TabHead {
-  int K;        // knots; 0: sum directly
-  float Wt;     // sum of the weights
-  float Yp, Yn; // Canberra: twice the largest magnitude of the positive / negative values (1 if none)
-  int zeros;    // Canberra: the sample has zeros
-  float lo, hi; // Manhattan: first and last knot
+  int K;           // knots; 0: sum directly, -1: and a value past kPairMax or not finite
+  int L;           // steps within a cell
   float inv, off;  // cell = z inv + off
-  int L;        // steps within a cell
-  int wide;     // summed directly: a value past kPairMax or not finite
-  int pad;
+  float lo, hi;    // Manhattan: first and last knot; Canberra: minus / plus twice the largest magnitude of
+                   // the negative / positive values (1 if none)
+  float Wt;        // Manhattan: sum of the weights
+  float zero;      // Canberra: the knot past the record for zeros, 0 if the sample has none
 };
 
 // the grid cell of z (the same instructions when the table is built and read)
@@ -200,10 +198,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     wother += red[i][2];
   }
   if (sh_bad) {  // block-uniform
-    if (tid == 0) {
-      hd->K = 0;
-      hd->wide = sh_wide;
-    }
+    if (tid == 0) hd->K = sh_wide ? -1 : 0;
     return;
   }
   // bitonic sort, ascending (padding +inf at the end)
@@ -301,7 +296,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       }
     }
     const int L = lookup(K);
-    if (tid == 0) *hd = TabHead{K, (float)wt, 1.f, 1.f, 0, kn[0], kn[K - 1], inv, off, L, 0, 0};
+    if (tid == 0) *hd = TabHead{K, L, inv, off, kn[0], kn[K - 1], (float)wt, 0.f};
   } else {
     // first index of the values >= 0 and > 0
     int nneg = 0, nzero = 0;
@@ -402,10 +397,7 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
     const int K = sh_n + 1;
     const int room = 2 * m + kTabExtra;
     if (K >= room || K > kTabMost) {  // block-uniform
-      if (tid == 0) {
-        hd->K = 0;
-        hd->wide = 0;
-      }
+      if (tid == 0) hd->K = 0;
       return;
     }
     for (int i = s0; i < s1; ++i) {
@@ -449,18 +441,19 @@ __global__ __launch_bounds__(kBuildT) void k_tab_build(const float* __restrict__
       }
     }
     if (bad) sh_bad = 1;  // two knots fell on one float
+    float zero = 0.0f;
     if (tid == 0) {
       // f jumps at 0 where the sample has zeros: f(0) is the sum of the other
       // weights.  An element's 0 takes the record past the last interval,
       // E (f(0) / E), E a power of two above every z (the search stops there).
       const float E = __uint_as_float((__float_as_uint((float)(4.0 * Yp)) & 0x7f800000u) + 0x00800000u);
-      oy[K] = E;
+      if (nzero > 0) zero = E;
       og[K - 1] = double2{wother / (double)E, 0.0};
       tabC[base + K - 1] = float2{0.0f, 0.0f};
     }
     const int L = lookup(K);
     if (tid == 0)
-      *hd = TabHead{sh_bad ? 0 : K, (float)wt, (float)Yp, (float)Yn, nzero, 0.f, 0.f, inv, off, L, 0, 0};
+      *hd = TabHead{sh_bad ? 0 : K, L, inv, off, -(float)Yn, (float)Yp, 0.f, zero};
   }
 }
 
@@ -507,15 +500,20 @@ __global__ __launch_bounds__(256) void k_tab_transpose(const float* __restrict__
 // the tile's elements through it.  Wd [k][R]: assigned by the cluster's first
 // chunk (or where it has none), added to by the others.
 // ----------------------------------------------------------------------------
-// Canberra's eight elements a thread hold 96 registers, five waves per SIMD (the
-// direct sums below would take 99: four waves, 3.92 -> 4.29 ms).  Two elements:
-// seven waves (n = 68,362, d = 135, k = 17, t = 61 414 us; held at eight, the scalar
-// registers spill, 525).
+// Canberra's eight elements a thread hold 92 vector registers, five waves per
+// SIMD (the direct sums below would take 99: four waves, 3.92 -> 4.29 ms).  One
+// and two elements a thread would fill the SIMD's eight, and there the scalar
+// registers count: a wave holds 16 more than the kernel names, so 96 let seven
+// run (n = 55,822, d = 77, k = 44, t = 84: 106 490 us, 100 444, 96 385; forced to
+// eight waves many spill, n = 68,362, d = 135, k = 17, t = 61 414 -> 525, 96 382).
 template <int M, int E>
 constexpr int kEvalWaves = M == kCanb && E == 8 ? 5 : 1;
+constexpr int kEvalSgprs = 96;
+static_assert(kEvalT == kTabCells / 2, "k_tab_eval: a word of cell starts a thread");
+static_assert(kTabPad == kWave, "k_tab_eval: a wave writes the padding");
 
 template <int M, int E>
-__global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWaves<M, E>))) void k_tab_eval(const float* __restrict__ XT, int R, int d,
+__global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWaves<M, E>), amdgpu_num_sgpr(kEvalSgprs))) void k_tab_eval(const float* __restrict__ XT, int R, int d,
                                                      const int4* __restrict__ chunk,
                                                      const int32_t* __restrict__ cfirst, int k, int q0, int q1,
                                                      const TabHead* __restrict__ head,
@@ -549,18 +547,14 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
   double acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int refused = 0;
   for (int q = ca; q < cb; ++q) {
     const int4 ck = chunk[q];
     const int m = ck.z;
     const size_t base = tab_base(chunk, q, q0) * (size_t)d;
-    bool refused = false;
     for (int c = 0; c < d; ++c) {
       const TabHead hd = head[(size_t)(q - q0) * d + c];
-      const int K = hd.K;
-      if (K == 0) {  // block-uniform
-        refused = true;
-        continue;
-      }
       float x[E];
       const float* xc = XT + (size_t)c * R;
 #pragma unroll
@@ -568,19 +562,24 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
         const int i = e0 + e * kEvalT;
         x[e] = xc[i < R ? i : R - 1];
       }
+      const int K = hd.K;
+      if (K <= 0) {  // block-uniform
+        refused = 1;
+        continue;
+      }
       __syncthreads();
       {
         const size_t tb = base + (size_t)c * (size_t)(2 * m + kTabExtra);
-        // (one more knot than the table's: Canberra's for the element's zeros)
-        if (M == kCanb && threadIdx.x == 0) ly[K] = tabY[tb + K];
         for (int i = threadIdx.x; i < K; i += kEvalT) {
           ly[i] = tabY[tb + i];
           ((double2*)lg)[i] = ((const double2*)tabG)[tb + i];
           if (M == kCanb) ((float2*)lp)[i] = tabC[tb + i];
         }
-        if (threadIdx.x < kTabPad) ly[K + (M == kCanb ? 1 : 0) + threadIdx.x] = __builtin_inff();
-        if (threadIdx.x < kTabCells / 2)
-          ((uint32_t*)lc)[threadIdx.x] = ((const uint32_t*)(tabL + ((size_t)(q - q0) * d + c) * kTabCells))[threadIdx.x];
+        if (wave == 0) {
+          ly[K + threadIdx.x] = __builtin_inff();
+          if (M == kCanb && __float_as_int(hd.zero) != 0) ly[K] = hd.zero;  // (after the wave's own +inf)
+        }
+        ((uint32_t*)lc)[threadIdx.x] = ((const uint32_t*)(tabL + ((size_t)(q - q0) * d + c) * kTabCells))[threadIdx.x];
       }
       __syncthreads();
       bool odd = false;  // Canberra: a value past 2^62 or not finite
@@ -598,13 +597,13 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
             z[e] = __builtin_amdgcn_fmed3f(x[e], hd.lo, hd.hi);
           } else {
             z[e] = x[e];
-            far = far || x[e] > hd.Yp || x[e] < -hd.Yn;
+            far = far || x[e] > hd.hi || x[e] < hd.lo;
           }
         }
         if (M == kCanb && __any(far)) {
 #pragma unroll
           for (int e = 0; e < E; ++e) {
-            const float ax = fabsf(x[e]), Y = x[e] < 0.0f ? hd.Yn : hd.Yp;
+            const float ax = fabsf(x[e]), Y = x[e] < 0.0f ? -hd.lo : hd.hi;
             const float zt = fmaf(-Y, canb_term(Y, ax), 2.0f * Y);  // Y (2 - Y / |x|)
             z[e] = ax > Y ? copysignf(fminf(zt, 2.0f * Y), x[e]) : x[e];
           }
@@ -640,7 +639,7 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
             len -= half;
           }
         }
-        if (M == kCanb && hd.zeros) {  // uniform
+        if (M == kCanb && __float_as_int(hd.zero) != 0) {  // uniform
 #pragma unroll
           for (int e = 0; e < E; ++e) at[e] = x[e] == 0.0f ? 4 * (K - 1) : at[e];
         }
@@ -690,10 +689,15 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
         }
       }
     }
-    if (!refused) continue;
+  }
+  // the refused tables, after all others (a loop of its own holds fewer scalar
+  // registers than one within the chunks' loop)
+  for (int q = refused != 0 ? ca : cb; q < cb; ++q) {
+    const int4 ck = chunk[q];
+    const int m = ck.z;
     for (int c = 0; c < d; ++c) {
-      const TabHead hd = head[(size_t)(q - q0) * d + c];
-      if (hd.K > 0) continue;
+      const int K = head[(size_t)(q - q0) * d + c].K;
+      if (K > 0) continue;
       // the values and weights in pairs of rows
       __syncthreads();
       for (int i = threadIdx.x; i < ((m + 1) & ~1); i += kEvalT)
@@ -710,7 +714,7 @@ __global__ __launch_bounds__(kEvalT) __attribute__((amdgpu_waves_per_eu(kEvalWav
       // elements and the values lie in what two factors allow (k_p2_valu pairs
       // coordinates the same way).  n = 200,000, d = 32, k = 16, t = 256, every
       // table refused: Canberra 8.95 -> 4.19 ms (pairs of coordinates by k_p2_valu 5.89)
-      bool pairs = M == kCanb && hd.wide == 0;
+      bool pairs = M == kCanb && K == 0;
       if (pairs) {
 #pragma unroll
         for (int e = 0; e < E; ++e) pairs = pairs && fabsf(x[e]) >= 0x1p-62f && fabsf(x[e]) <= kPairMax;
