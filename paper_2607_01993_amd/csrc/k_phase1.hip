@@ -901,17 +901,11 @@ __global__ __launch_bounds__(256) void k_pack(const int32_t* __restrict__ perm,
   // or not finite (a failed <= test), which keeps the Phase-2 kernel on its
   // per-coordinate form for this sample
   bool big = false;
-  // Cosine: a row whose unit vector is not finite (an infinity or NaN in the
-  // row) is packed with weight 0: its pairs count 0, and it does not reach
-  // the other rows' sums
-  bool ok = true;
   if (vec) {
     // 16-byte row chunks (DM is a multiple of 8)
     for (int c = 0; c < DM; c += 4) {
       const float4 v = c < d ? *(const float4*)(xr + c) : float4{0.f, 0.f, 0.f, 0.f};
-      const float4 y = float4{v.x * scale, v.y * scale, v.z * scale, v.w * scale};
-      *(float4*)(yr + c) = y;
-      ok = ok && y.x - y.x == 0.0f && y.y - y.y == 0.0f && y.z - y.z == 0.0f && y.w - y.w == 0.0f;
+      *(float4*)(yr + c) = float4{v.x * scale, v.y * scale, v.z * scale, v.w * scale};
       big = big || !(fabsf(v.x) <= 0x1p62f && fabsf(v.y) <= 0x1p62f && fabsf(v.z) <= 0x1p62f &&
                      fabsf(v.w) <= 0x1p62f);
     }
@@ -919,15 +913,23 @@ __global__ __launch_bounds__(256) void k_pack(const int32_t* __restrict__ perm,
     for (int c = 0; c < DM; ++c) {
       const float v = c < d ? xr[c] : 0.0f;
       yr[c] = v * scale;
-      ok = ok && v * scale - v * scale == 0.0f;
       big = big || !(fabsf(v) <= 0x1p62f);
     }
   }
   aux32[dst] = (mode == 1 && !(scale > 0.0f)) ? 0.5f : (mode == 2 && big) ? 1.0f : 0.0f;
-  if (mode == 1 && !ok) {
-    w32[dst] = 0.0f;
-    aux32[dst] = 0.0f;
-    for (int c = 0; c < DM; c += 4) *(float4*)(yr + c) = float4{0.f, 0.f, 0.f, 0.f};
+  // Cosine: a row whose unit vector is not finite (an infinity or NaN in the
+  // row) is packed with weight 0: its pairs count 0, and it does not reach the
+  // other rows' sums.  Its norm is not finite, so a row with a positive
+  // reciprocal norm is not looked at (looking at every row in the loop above, n
+  // = 500,000, d = 256, k = 16, t = 256 Euclidean 33 -> 40 us).
+  if (mode == 1 && !(scale > 0.0f)) {
+    float z = 0.0f;
+    for (int c = 0; c < d; ++c) z = fmaf(xr[c] * scale, 0.0f, z);
+    if (z != 0.0f) {  // (NaN)
+      w32[dst] = 0.0f;
+      aux32[dst] = 0.0f;
+      for (int c = 0; c < DM; c += 4) *(float4*)(yr + c) = float4{0.f, 0.f, 0.f, 0.f};
+    }
   }
 }
 
