@@ -25,11 +25,12 @@ constexpr int kBndKeep = DM <= 16 ? 128 : DM == 256 ? 32 : 64;
 
 // Elements row0 .. row0 + 63 (in perm order), NW waves.  out: the masks of all
 // groups; PROBE: one word, the number of clusters that the block's groups need.
-template <int DM, int NW, bool PROBE>
+// stop() is asked once, beside the first loads.
+template <int DM, int NW, bool PROBE, class F>
 __device__ __forceinline__ void bounds_block(const float* __restrict__ X, int n, int d,
                                              const int32_t* __restrict__ labels, const int32_t* __restrict__ perm,
                                              const float* __restrict__ rec, int k, int row0,
-                                             uint32_t* __restrict__ out) {
+                                             uint32_t* __restrict__ out, F stop) {
   constexpr int NT = 64 * NW, LD = DM + 4;
   __shared__ __attribute__((aligned(16))) float xs[64 * LD];
   __shared__ float low[kBndKeep<DM>][64];
@@ -39,10 +40,10 @@ __device__ __forceinline__ void bounds_block(const float* __restrict__ X, int n,
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int kw = (k + 31) >> 5;
-  if (threadIdx.x < 64) {
-    const int i = row0 + (int)threadIdx.x < n ? row0 + (int)threadIdx.x : n - 1;
-    rows[threadIdx.x] = perm != nullptr ? perm[i] : i;
-  }
+  const int i = row0 + lane < n ? row0 + lane : n - 1;
+  const int row = perm != nullptr ? perm[i] : i;
+  if (stop()) return;
+  if (wave == 0) rows[lane] = row;
   for (int q = threadIdx.x; q < 256; q += NT) bits[q >> 7][q & 127] = 0u;
   __syncthreads();
   const bool vec = (d & 3) == 0 && ((uintptr_t)X & 15) == 0;
@@ -59,7 +60,7 @@ __device__ __forceinline__ void bounds_block(const float* __restrict__ X, int n,
       xs[r * LD + c] = c < d ? X[(size_t)rows[r] * d + c] : 0.0f;
     }
   }
-  int own = labels[rows[lane]];
+  int own = labels[row];
   own = (unsigned)own < (unsigned)k ? own : 0;  // labels are checked before; stay in bounds
   __syncthreads();
   const float* xl = xs + lane * LD;

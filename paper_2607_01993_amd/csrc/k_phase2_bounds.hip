@@ -187,16 +187,17 @@ __global__ __launch_bounds__((64 * kBndWaves<DM>)) void k_bounds(const float* __
                                                            const float* __restrict__ rec, int k, int limit,
                                                            const uint32_t* __restrict__ counts,
                                                            uint32_t* __restrict__ head) {
-  bool skip = false;
-  if (counts != nullptr) {
-    int c = 0;
+  bounds_block<DM, kBndWaves<DM>, false>(X, n, d, labels, perm, rec, k, (int)blockIdx.x * 64, head + kBoundHead, [&] {
+    bool skip = false;
+    if (counts != nullptr) {
+      int c = 0;
 #pragma unroll
-    for (int i = 0; i < kBoundProbe; ++i) c += (int)counts[i];
-    skip = c > limit;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) head[kBoundFlag] = skip ? 1u : 0u;
-  if (skip) return;
-  bounds_block<DM, kBndWaves<DM>, false>(X, n, d, labels, perm, rec, k, (int)blockIdx.x * 64, head + kBoundHead);
+      for (int i = 0; i < kBoundProbe; ++i) c += (int)counts[i];
+      skip = c > limit;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) head[kBoundFlag] = skip ? 1u : 0u;
+    return skip;
+  });
 }
 
 const uint32_t* launch_bounds(hipStream_t st, int DM, const float* X, int n, int d, const int32_t* labels,

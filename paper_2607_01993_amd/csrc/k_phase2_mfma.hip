@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void k_pack_mfma(const float* __restrict__ Y32
     const int b = (int)blockIdx.x - nb;
     bounds_block<DM, 4, true>(A.X, A.n, A.d, A.labels, A.perm, A.rec, k,
                               (int)((int64_t)b * ((A.n + 63) / 64) / kBoundProbe) * 64,
-                              (uint32_t*)(A.rec + (size_t)k * (kBoundRec + DM)) + b);
+                              (uint32_t*)(A.rec + (size_t)k * (kBoundRec + DM)) + b, [] { return false; });
     return;
   }
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
