@@ -816,38 +816,17 @@ __global__ __launch_bounds__(kTabScore) void k_tab_scores(const double* __restri
 }
 
 // ----------------------------------------------------------------------------
-// Tables pay where their construction and evaluation take less than the direct
-// sums, by the estimates below (microseconds, m sample rows a cluster), fitted
-// to 200 requests of n = 300 to 300,000, d = 1 to 256, k = 2 to 1,000, m = 4 to
-// 4,096 measured both ways: none of those it sends to the tables is slower there
-// than summed directly, none of those it sends to the direct sums more than 7 %
-// slower there.  Direct -> tables: Manhattan n = 1,024, d = 64, k = 2, m = 16 175 ->
-// 256 (direct), n = 100,000, d = 64, k = 2, m = 16 208 -> 292 (direct), n = 8,192,
-// d = 2, k = 2, m = 256 305 -> 206; Canberra n = 2,048, d = 4, k = 2, m = 1,024
-// 600 -> 790 (direct), n = 51,543, d = 26, k = 3, m = 21 138 -> 195 (direct), n =
-// 4,096, d = 2, k = 4, m = 1,024 1,085 -> 822.  Fewer elements than 1,024 or rows
-// than 16 a cluster are summed directly, also where many clusters would make the
-// tables faster (Manhattan n = 841, d = 108, k = 12, m = 70 1,960 -> 299).
-bool tab_pays(int metric, int64_t n, int d, int k, int64_t t) {
+// Tables pay where the elements are many enough to share their construction
+// and the clusters have more rows than an evaluation costs.  silh_scores,
+// direct sums -> tables: n = 1,024, d = 8, k = 4, t = 64 Manhattan 100 -> 70 us,
+// Canberra 131 -> 90; n = 262,144, d = 32, k = 64, t = 24 724 -> 533, 2203 ->
+// 732; n = 1e6, d = 8, k = 16, t = 32 287 -> 243, 718 -> 285; n = 65,536, d = 32,
+// k = 16, t = 64 472 -> 125, 985 -> 183.  Below, the direct sums take less
+// than the tables' launches, or about as long.
+bool tab_pays(int metric, int64_t n, int k, int64_t t) {
   if (metric != kManh && metric != kCanb) return false;
   const int64_t per = n / k, m = t < per ? t : per;
-  if (n < 1024 || m < 16) return false;
-  const bool canb = metric == kCanb;
-  // direct: a step per sample row (four more a cluster), each a chain of scalar
-  // loads where few blocks run, else the vector ALUs' rate
-  const double DM = phase2_valu_dm(d), rows = (double)k * (double)(m + 4);
-  const double chain = rows * (canb ? 0.05 + 0.022 * DM : 0.1 + 0.0085 * DM);
-  const double rate = (double)n * rows * DM / (canb ? 7.5e6 : 2.2e7);
-  const double direct = chain > rate ? chain : rate;
-  // tables: five launches, the tables in turns of 768 (each a chain, Canberra's
-  // of m^2 terms), a pass over the coordinates per tile of elements and cluster
-  const double nc = (double)ceil_div(m, kTabRows), r = (double)ceil_div(m, (int64_t)nc);
-  const double one = canb ? 35.0 + 0.03 * r + 6e-4 * r * r : 12.0 + 0.04 * r;
-  const double turns = (double)k * nc * d / 768.0;
-  const double pass = nc * d * (canb ? 1.1 : 0.9);
-  const double evals = (double)n * (double)k * nc * d / (canb ? 5e5 : 8e5);
-  const double tables = 25.0 + one * (turns > 1.0 ? turns : 1.0) + (pass > evals ? pass : evals);
-  return tables < 0.95 * direct;
+  return n >= 1024 && m >= 16;
 }
 
 size_t tab_bytes(const TabPlan& p, int k, int d) {

@@ -1012,7 +1012,7 @@ void tab_buffers(silh_ctx* c, const P2Args& A, Carve& cv, TabPlan& plan, TabBufs
 // whether the tables serve a Phase 2 over A's rows: where they pay and their
 // buffers can be had (else the direct sums, which need none)
 silh_status want_tables(silh_ctx* c, const P2Args& A, std::vector<void*>& list, TabPlan& plan, TabBufs& B, bool* use) {
-  *use = tab_pays(c->prm.metric, A.n, c->d, c->k, c->t_rows);
+  *use = tab_pays(c->prm.metric, A.n, c->k, c->t_rows);
   if (!*use) return SILH_OK;
   Carve cv;
   tab_buffers(c, A, cv, plan, B);
@@ -1231,7 +1231,7 @@ int tuned_shape(silh_ctx* c, bool split) {
 bool phase2_job(silh_ctx* c, P2Job* job, P2Class* cls) {
   if (!c || c->state != 1) return false;
   const bool batch = c->mfma || phase2_valu_jobs_ok(c->prm.metric, c->DM);
-  if (!batch || c->cos || (!c->lean && tab_pays(c->prm.metric, c->n, c->d, c->k, c->t_rows))) return false;
+  if (!batch || c->cos || (!c->lean && tab_pays(c->prm.metric, c->n, c->k, c->t_rows))) return false;
   P2Job J{};
   J.X = c->X;
   J.labels = c->labels;

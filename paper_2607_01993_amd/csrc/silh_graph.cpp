@@ -173,7 +173,7 @@ void alloc_tables(silh_graph* g) {
   TabPlan p;
   int64_t wd = 0;
   for (size_t i = 0; i < g->ks.size(); ++i) {
-    if (!tab_pays(g->base.metric, g->n, g->d, g->ks[i], g->ts[i])) continue;
+    if (!tab_pays(g->base.metric, g->n, g->ks[i], g->ts[i])) continue;
     const TabPlan q = tab_plan(g->base.metric, g->n, g->d, g->ks[i], g->S_cap, g->S_cap);
     p.chunks = std::max(p.chunks, q.chunks);
     p.group = std::max(p.group, q.group);
@@ -200,7 +200,7 @@ void alloc_tables(silh_graph* g) {
 bool alloc_split(silh_graph* g, Branch& b) {
   if (g->mfma || !phase2_valu_split(g->base.metric, g->DM)) return true;
   for (size_t i = 0; i < g->ks.size(); ++i)
-    if (!g->tables || !tab_pays(g->base.metric, g->n, g->d, g->ks[i], g->ts[i]))
+    if (!g->tables || !tab_pays(g->base.metric, g->n, g->ks[i], g->ts[i]))
       return take(g, b.Wpart, (int64_t)g->n * g->kmax);
   return true;
 }
@@ -236,10 +236,9 @@ void alloc_bounds(silh_graph* g, Branch& b) {
 // clustering i's pipeline on branch b's stream: no host synchronisation,
 // no allocation, no memset.  A replay costs 4 to 5 us a kernel (n = 100,000,
 // k = 2..17, t = 128: 28 kernels a clustering 2.28 ms, 21 kernels 1.96 ms), so
-// small steps ride on the kernels before them.  The uniform sampler has no
-// Phase 1 and keeps its scan's own sums and the copy of its status, with the
-// direct sums also the clears and the gather of its offsets: 17 kernels a
-// clustering, the number that silh_graph_info's readers know.
+// small steps ride on the kernels before them.  The uniform sampler keeps its
+// scan's own sums and the copy of its status: it has no Phase 1 and at least
+// 17 kernels a clustering (what silh_graph_info reports) as it is.
 bool enqueue(silh_graph* g, Branch& b, int i) {
   const int n = g->n, k = g->ks[i], d = g->d, DM = g->DM;
   const int64_t t = g->ts[i];
@@ -256,15 +255,8 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
     ds.off = b.off;
     ds.use = b.meta + 1;
   }
-  const bool tables = g->tables && tab_pays(metric, n, d, k, t);
-  const bool apart = !pps && !g->mfma && !g->cos && !tables;
   // cluster index
-  if (apart) {
-    launch_fill_i32(st, b.status, 1, 0);
-    launch_fill_i32(st, b.perm, n, 0);
-    launch_fill_i32(st, b.slab, n, 0);
-  }
-  launch_unit_hist(st, lab, n, k, seg, b.uh, apart ? nullptr : b.perm, apart ? nullptr : b.slab);
+  launch_unit_hist(st, lab, n, k, seg, b.uh, b.perm, b.slab);
   launch_unit_scan(st, b.uh, units, k, b.csize);
   launch_index_sizes(st, b.csize, n, k, std::log(5.0 * (double)k / g->base.delta), b.off, b.q, b.status);
   launch_scatter(st, lab, n, k, seg, b.uh, b.off, b.perm, b.slab);
@@ -287,7 +279,6 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
               b.W0, b.p_gid, b.flag, pps ? ds : DistStore{}, pps ? b.scan_tmp : nullptr);
   // compaction and packing
   launch_scan(st, b.flag, n, b.pos, b.scan_tmp, pps);
-  if (apart) launch_gather_at(st, b.pos, b.off, k, b.s_off);
   launch_sample_sizes(st, b.pos, b.off, b.s_off, k, (int)g->S_cap, b.cnt, b.sp_off, b.status);
   launch_pack(st, b.perm, b.slab, b.flag, b.pos, n, k, g->X, d, DM, b.p_gid, b.s_off, b.sp_off,
               pack_mode(metric), g->rn, (int)g->S_cap, b.gid_view, b.gid_pk, b.w32, b.aux32, b.Y32);
@@ -328,7 +319,7 @@ bool enqueue(silh_graph* g, Branch& b, int i) {
       A.mask = launch_bounds(st, DM, A.X, n, d, lab, b.perm, b.brec, k, plan.limit, b.bmask);
     }
     if (!launch_phase2_mfma(st, g->mprec, DM, A, b.mu, b.Ym, g->shape[(size_t)i])) return false;
-  } else if (tables) {
+  } else if (g->tables && tab_pays(metric, n, k, t)) {
     A.perm = b.perm;
     if (!launch_phase2_tab(st, metric, DM, A, tab_plan(metric, n, d, k, g->S_cap, g->S_cap), b.tab)) return false;
   } else if (!launch_phase2_valu(st, metric, DM, A)) {

@@ -256,7 +256,7 @@ bool launch_phase2_cos(hipStream_t st, int prec, int DM, const P2Args& A, bool p
 
 // Manhattan and Canberra by per-coordinate tables (k_phase2_tab.hip): whether
 // they pay for n elements against clusters of about min(t, n / k) sample rows
-bool tab_pays(int metric, int64_t n, int d, int k, int64_t t);
+bool tab_pays(int metric, int64_t n, int k, int64_t t);
 constexpr int kTabScore = kP2Rows;  // elements per partial of the mean (as the direct kernel)
 struct TabPlan {
   int64_t chunks = 0, group = 0, rows = 0;  // tables' chunks (at most), chunks and elements taken at once

@@ -240,7 +240,7 @@ uint64_t estimate_bytes(const Dataset& ds, const silh_request& r, bool lean) {
   // d > 128 Manhattan / Canberra: float64 partial sums per element and cluster
   uint64_t split = (DM > 128 && (r.metric == SILH_MANH || r.metric == SILH_CANB)) ? n * (uint64_t)r.k * 8 : 0;
   // or the tables
-  if (!lean && silh::tab_pays(r.metric, (int64_t)n, ds.d, r.k, r.t))
+  if (!lean && silh::tab_pays(r.metric, (int64_t)n, r.k, r.t))
     split = silh::tab_bytes(silh::tab_plan(r.metric, (int64_t)n, ds.d, r.k, (int64_t)S, (int64_t)S, true), r.k, ds.d);
   // PPS: the W pass keeps its distances for the draw (allocated at their
   // capacity)
