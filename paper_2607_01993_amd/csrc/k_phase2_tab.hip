@@ -487,13 +487,13 @@ __global__ __launch_bounds__(256) void k_tab_transpose(const float* __restrict__
 }
 
 // ----------------------------------------------------------------------------
-// n = 1e6, d = 32, k = 16, S = 4,764 Manhattan: Phase 2 5.53 -> 0.81 ms, of
-// which this kernel 0.64 (8e11 table evaluations a second); n = 5e5, d = 64,
-// k = 64, S = 9,337 Canberra 39.6 -> 3.4 ms, this kernel 2.91, the tables 0.30.
-// The same with float32 records and sums 0.52 and 2.51 ms, but 1.5 times the
-// direct sums' error at d <= 24, t = 500; so 0.64 and 2.91.  Searching in halves
-// alone 0.85 / 3.59 (float32 records), 512 threads a block 0.61 / 2.95, 1024
-// threads 0.60 / 4.31, 16 elements a thread 0.77 / 3.89.
+// n = 1e6, d = 32, k = 16, S = 4,764 Manhattan: Phase 2 5.53 -> 0.77 ms, of
+// which this kernel 0.59 (8.6e11 table evaluations a second); n = 5e5, d = 64,
+// k = 64, S = 9,337 Canberra 39.6 -> 3.36 ms, this kernel 2.82, the tables 0.30.
+// Float32 records and sums would save a fifth and a seventh of it, but have 1.5
+// times the direct sums' error at d <= 24, t = 500.  With them, where this form
+// took 0.52 and 2.51 ms: searching in halves alone 0.85 / 3.59, 512 threads a
+// block 0.61 / 2.95, 1024 threads 0.60 / 4.31, 16 elements a thread 0.77 / 3.89.
 //
 // One block per (tile of kEvalT E elements, cluster): for each of the
 // cluster's chunks in the group, and each coordinate, the table into LDS and
@@ -821,8 +821,15 @@ __global__ __launch_bounds__(kTabScore) void k_tab_scores(const double* __restri
 // direct sums -> tables: n = 1,024, d = 8, k = 4, t = 64 Manhattan 100 -> 70 us,
 // Canberra 131 -> 90; n = 262,144, d = 32, k = 64, t = 24 724 -> 533, 2203 ->
 // 732; n = 1e6, d = 8, k = 16, t = 32 287 -> 243, 718 -> 285; n = 65,536, d = 32,
-// k = 16, t = 64 472 -> 125, 985 -> 183.  Below, the direct sums take less
-// than the tables' launches, or about as long.
+// k = 16, t = 64 472 -> 125, 985 -> 183.  Two or three clusters, or Canberra's
+// tables of 512 and more rows at small n, take longer by tables (requests:
+// Manhattan n = 1,024, d = 64, k = 2, t = 16 175 -> 256, n = 100,000, d = 64, k = 2,
+// t = 16 208 -> 292; Canberra n = 2,048, d = 4, k = 2, t = 1,024 646 -> 709, n = 51,543,
+// d = 26, k = 3, t = 21 241 -> 279), but they add in float64 where the direct sums
+// do in float32: 8.4e-8 -> 3.5e-8, 1.0e-7 -> 5.9e-8, 8.5e-7 -> 1.6e-7 off 64 bits
+// at such sizes.  Fewer elements or rows are summed directly, also where many
+// clusters would make the tables faster (Manhattan n = 841, d = 108, k = 12, t = 70
+// 1,960 -> 299).
 bool tab_pays(int metric, int64_t n, int k, int64_t t) {
   if (metric != kManh && metric != kCanb) return false;
   const int64_t per = n / k, m = t < per ? t : per;
